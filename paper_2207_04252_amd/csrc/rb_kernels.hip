@@ -41,6 +41,7 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
 
   const Geo& g = a.g;
   const GasC gc = gas_consts(g.gamma, g.newton_max);
+  const RecC recc;
   const int F0 = GAS ? 0 : 5 + 4 * species;
   const int slot = GAS ? 0 : 1 + species;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
@@ -143,7 +144,7 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
     constexpr int D = decltype(dirc)::value;
     if constexpr (PG) gas_face_p32<D>(gc, wA, wB, wC, wD, coB, coC, bf, bB, bC, F, st);
     else if constexpr (GAS) gas_face<D, G75>(gc, wA, wB, wC, wD, coB, coC, bf, bB, bC, F, st);
-    else dust_face<D>(wA, wB, wC, wD, coB, coC, F, st);
+    else dust_face<D>(recc, wA, wB, wC, wD, coB, coC, F, st);
   };
   using DR = std::integral_constant<int, 0>;
   using DT = std::integral_constant<int, 1>;
