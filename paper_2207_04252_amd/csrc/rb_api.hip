@@ -121,6 +121,28 @@ bool validate(const rb_config* c, std::string* why) {
   return true;
 }
 
+// z planes per block of a stage kernel of which `per_cu` workgroups fill a CU (the gas one:
+// at most 256 VGPRs per lane, two waves per SIMD; the dust one: 128, four).  A launch runs in
+// ceil(blocks / (256 per_cu)) rounds on the 256 CUs of an MI355X; a block marches tk planes
+// plus about 1.5 planes of set-up (initial column, first z face).  Takes the chunk length
+// with the fewest plane-times.
+int stage_chunk(const Layout& L, size_t nz, size_t per_cu) {
+  if (nz == 1) return 1;
+  const char* env = std::getenv("RB_TK");
+  if (env && std::atoi(env) > 0)  // at most 4096: the Newton histogram's 16-bit bins
+    return (int)std::min<size_t>(std::min(std::atoi(env), 4096), nz);
+  const size_t tiles = (size_t)L.ntj * L.ntm, conc = 256 * per_cu;
+  size_t tk = 2;
+  double best = 1e300;
+  for (size_t cand : {128, 64, 32, 16, 8, 4, 2}) {
+    const size_t c = std::min(cand, nz);
+    const size_t blocks = tiles * ((nz + c - 1) / c);
+    const double t = (double)((blocks + conc - 1) / conc) * ((double)c + 1.5);
+    if (t < best) { best = t; tk = c; }
+  }
+  return (int)tk;
+}
+
 Layout make_layout(const rb_config& c) {
   Layout L;
   const size_t nr = c.nr, nth = c.ntheta, nz = c.nz, nf = 5 + 4 * c.n_dust;
@@ -128,34 +150,11 @@ Layout make_layout(const rb_config& c) {
   L.ntj = (int)((nth + TJ - 1) / TJ);
   L.nti = (int)((nr + TI - 1) / TI);
   L.ntm = (int)((nr + TM - 1) / TM);
-  if (nz == 1) {
-    L.tk = 1;
-  } else {
-    int tk = 2;
-    const char* env = std::getenv("RB_TK");
-    if (env && std::atoi(env) > 0) {
-      tk = std::min(std::atoi(env), 4096);  // the Newton histogram's 16-bit bins
-    } else {
-      // A stage-kernel workgroup of 64 x TM threads holds at most 256 VGPRs per lane (two
-      // waves per SIMD), so 8 / TM workgroups fill a CU and a launch runs in
-      // ceil(blocks / (256 * 8 / TM)) rounds on the 256 CUs of an MI355X; a block marches
-      // tk planes plus about 1.5 planes of set-up (initial ring, first z face).  Take the
-      // chunk length with the fewest plane-times.
-      const size_t tiles = (size_t)L.ntj * L.ntm;
-      const size_t conc = 256 * (8 / TM);
-      const int cand[7] = {128, 64, 32, 16, 8, 4, 2};
-      double best = 1e300;
-      for (int q = 0; q < 7; ++q) {
-        const size_t c = std::min<size_t>(cand[q], nz);
-        const size_t blocks = tiles * ((nz + c - 1) / c);
-        const double t = (double)((blocks + conc - 1) / conc) * ((double)c + 1.5);
-        if (t < best) { best = t; tk = (int)c; }
-      }
-    }
-    L.tk = (int)std::min<size_t>(tk, nz);
-  }
+  L.tk = stage_chunk(L, nz, 1);
+  L.tk_dust = stage_chunk(L, nz, 2);
   L.nkc = (int)((nz + L.tk - 1) / L.tk);
   L.nblocks = L.ntj * L.ntm * L.nkc;
+  L.nblocks_dust = L.ntj * L.ntm * (int)((nz + L.tk_dust - 1) / L.tk_dust);
   L.nblocks_adj = L.ntj * L.nti * L.nkc;
   L.ncfl = (int)std::min<size_t>((N + 255) / 256, 2048);
   size_t o = 0;
@@ -187,8 +186,9 @@ Layout make_layout(const rb_config& c) {
   L.damp = take(nz * nr);
   L.ozr = take(4 * nr);
   L.dtlog = take(DTLOG + 2);
-  L.cflp = take(std::max((size_t)L.nblocks * 5, (size_t)L.ncfl));
-  L.outp = take((size_t)L.nblocks * 5);
+  const size_t nparts = std::max(L.nblocks, L.nblocks_dust);
+  L.cflp = take(std::max(nparts * 5, (size_t)L.ncfl));
+  L.outp = take(nparts * 5);
   L.tsp = take(std::max((size_t)L.nblocks, (size_t)L.ncfl));
   L.red = take(2048 + 16);
   L.total = o;
@@ -237,6 +237,7 @@ StageArgs base_args(rb_ctx* x) {
   a.c.dtlog = w + L.dtlog; a.c.cflp = w + L.cflp; a.c.outp = w + L.outp; a.c.r0w = w + L.r0;
   a.c.tsp = w + L.tsp;
   a.tk = L.tk; a.ntj = L.ntj; a.nti = L.nti; a.nkc = L.nkc; a.ntm = L.ntm;
+  a.tk_dust = L.tk_dust;
   a.dt_idx = -1;
   return a;
 }
@@ -325,12 +326,12 @@ hipError_t run_stage(rb_ctx* x, const StageArgs& a) {
   if (e != hipSuccess) return e;
   {
     ProfScope ps(x, 0);
-    e = launch_stage_group(a, x->L.nblocks, 0, x->stream);
+    e = launch_stage_group(a, x->L, 0, x->stream);
   }
   if (e != hipSuccess || a.gas_only) return e;
   for (int s = 0; s < x->g.nd; ++s) {
     ProfScope ps(x, 1);
-    e = launch_stage_group(a, x->L.nblocks, 1 + s, x->stream);
+    e = launch_stage_group(a, x->L, 1 + s, x->stream);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -425,7 +426,7 @@ rb_status rb_init_state(const rb_config* cfg, const rb_buffers* bufs, const doub
     a.out = nullptr;
     a.mode = MODE_RESID;
     a.gas_only = 1;
-    if (launch_stage(a, x->L.nblocks, x->stream) != hipSuccess) return bail(RB_EDEVICE);
+    if (launch_stage(a, x->L, x->stream) != hipSuccess) return bail(RB_EDEVICE);
   }
   // initial state: noise (one field per fluid) and amplitude fields staged through the
   // stage buffer, which holds at least (2 + n_dust) N doubles in either storage form
@@ -479,7 +480,7 @@ rb_status rb_step(rb_ctx* x, int n, const rb_dt_policy* policy, double* dt_out) 
     {
       ProfScope ps(x, 2);
       HIPCHK(x, launch_cfl(a, x->state, x->L.ncfl, 0, x->stream), "cfl");
-      HIPCHK(x, launch_reduce(a, x->L.ncfl, 0, cfl ? 1 : 0, 0, x->stream), "reduce");
+      HIPCHK(x, launch_reduce(a, x->L.ncfl, 0, 0, cfl ? 1 : 0, 0, x->stream), "reduce");
     }
     for (int q = 0; q < m; ++q) {
       a.step = (int)(x->step + q);
@@ -499,15 +500,15 @@ rb_status rb_step(rb_ctx* x, int n, const rb_dt_policy* policy, double* dt_out) 
         // boundary ledger of the stages, then the drag alone over dt/2 and the CFL step of
         // the relaxed state (which replaces the one the second stage formed)
         ProfScope ps(x, 2);
-        HIPCHK(x, launch_reduce(a, x->L.nblocks, q + 1, 0, 1, x->stream), "ledger");
+        HIPCHK(x, launch_reduce(a, x->L.nblocks, x->L.nblocks_dust, q + 1, 0, 1, x->stream), "ledger");
         HIPCHK(x, launch_drag(a, x->state, 0.5, x->L.ncfl, x->stream), "drag");
         a.step = (int)(x->step + q + 1);
         HIPCHK(x, launch_cfl(a, x->state, x->L.ncfl, 0, x->stream), "cfl");
-        HIPCHK(x, launch_reduce(a, x->L.ncfl, q + 1, cfl ? 1 : 0, 0, x->stream), "reduce");
+        HIPCHK(x, launch_reduce(a, x->L.ncfl, 0, q + 1, cfl ? 1 : 0, 0, x->stream), "reduce");
         a.step = (int)(x->step + q);
       } else {
         ProfScope ps(x, 2);
-        HIPCHK(x, launch_reduce(a, x->L.nblocks, q + 1, cfl ? 1 : 0, 1, x->stream), "reduce");
+        HIPCHK(x, launch_reduce(a, x->L.nblocks, x->L.nblocks_dust, q + 1, cfl ? 1 : 0, 1, x->stream), "reduce");
       }
     }
     std::vector<double> got(m + 1);
@@ -585,7 +586,7 @@ rb_status rb_eval_operator(rb_ctx* x, double* host_out, size_t n_doubles) {
   StageArgs a = base_args(x);
   a.in = x->state; a.base = x->state; a.out = x->stage; a.mode = MODE_OPER; a.gas_only = 0;
   HIPCHK(x, prep_stage(x, a), "indirect sums");
-  HIPCHK(x, launch_stage(a, x->L.nblocks, x->stream), "operator");
+  HIPCHK(x, launch_stage(a, x->L, x->stream), "operator");
   if (x->g.p32) {
     // FP32 form: the kernels write FP32; widened at the boundary
     std::vector<float> tmp(N * x->g.nf);
@@ -647,7 +648,7 @@ rb_status rb_cfl_dt_static(rb_ctx* x, const void* state, double* dt_dev) {
   a.c.tsp = a.c.cflp + SCRATCH_PARTS;
   HIPCHK(x, launch_ctrl_init(a.c.ctrl, x->stream), "scratch control block");
   HIPCHK(x, launch_cfl(a, state, x->L.ncfl, 0, x->stream), "cfl");
-  HIPCHK(x, launch_reduce(a, x->L.ncfl, 0, 1, 0, x->stream), "reduce");
+  HIPCHK(x, launch_reduce(a, x->L.ncfl, 0, 0, 1, 0, x->stream), "reduce");
   HIPCHK(x, launch_cfl_out(a.c.ctrl, a.c.dtlog, dt_dev, x->stream), "cfl out");
   return RB_OK;
 }
@@ -658,7 +659,7 @@ rb_status rb_cfl_dt(rb_ctx* x, double* dt) {
   StageArgs a = base_args(x);
   a.step = (int)x->step;
   HIPCHK(x, launch_cfl(a, x->state, x->L.ncfl, 0, x->stream), "cfl");
-  HIPCHK(x, launch_reduce(a, x->L.ncfl, DTLOG + 1, 1, 0, x->stream), "reduce");
+  HIPCHK(x, launch_reduce(a, x->L.ncfl, 0, DTLOG + 1, 1, 0, x->stream), "reduce");
   HIPCHK(x, hipMemcpyAsync(dt, x->work + x->L.dtlog + DTLOG + 1, sizeof(double),
                            hipMemcpyDeviceToHost, x->stream), "copy out");
   Ctrl c;

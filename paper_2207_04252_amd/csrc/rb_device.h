@@ -87,10 +87,9 @@ struct RecC {
 // limiters taken apart.  With dust_face's one-way path below, the step of the three-dust
 // disc 512 x 1024 x 128 in the FP32-perturbation form went from 25.0 to 22.1 ms (dust launch
 // 2.40 -> 1.92 ms), the one-dust disc 256 x 512 x 64 in FP64 from 2.34 to 2.24 ms.
-template <int DIR>
+template <int DIR, class Co>
 __device__ __forceinline__ void face_pair(const RecC& rc, double A, double B, double C, double D,
-                                          const double* coB, const double* coC, double& L,
-                                          double& R) {
+                                          Co coB, Co coC, double& L, double& R) {
   const double d1 = B - A, d2 = C - B, d3 = D - C;
   const double s = copysign(1.0, d2), a = fabs(d2);
   const double b1 = s * d1, b3 = s * d3;
@@ -543,14 +542,15 @@ __device__ __forceinline__ void gas_face(const GasC& c, const double* wA, const 
 // such faces (nearly every one: the others hold an emptied cell, a midplane or a turning
 // point) takes that flux behind one scalar test instead of the fallback and the rules of
 // dust_riemann, and without selects if all its lanes stream one way.
-template <int DIR>
-__device__ __forceinline__ void dust_face(const RecC& rc, const double* wA, const double* wB,
-                                          const double* wC, const double* wD, const double* coB,
-                                          const double* coC, double F[4], TStat& st) {
+// cell(c, f): field f of the stencil cell c = 0 .. 3 (A, B | C, D), read again where the
+// fallback needs it (held across the solve the cells would cost 16 registers).
+template <int DIR, class Cell, class Co>
+__device__ __forceinline__ void dust_face(const RecC& rc, Cell cell, Co coB, Co coC, double F[4],
+                                          TStat& st) {
   double qL[4], qR[4];
 #pragma unroll
   for (int f = 0; f < 4; ++f)
-    face_pair<DIR>(rc, wA[f], wB[f], wC[f], wD[f], coB, coC, qL[f], qR[f]);
+    face_pair<DIR>(rc, cell(0, f), cell(1, f), cell(2, f), cell(3, f), coB, coC, qL[f], qR[f]);
   constexpr int N = Dirs<DIR>::n, T1 = Dirs<DIR>::t1, T2 = Dirs<DIR>::t2;
   double fl[4];
   const double uL = qL[N], uR = qR[N];
@@ -569,12 +569,12 @@ __device__ __forceinline__ void dust_face(const RecC& rc, const double* wA, cons
   } else {
     if (qL[3] < 0.0) {
 #pragma unroll
-      for (int f = 0; f < 4; ++f) qL[f] = wB[f];
+      for (int f = 0; f < 4; ++f) qL[f] = cell(1, f);
       st.fall++;
     }
     if (qR[3] < 0.0) {
 #pragma unroll
-      for (int f = 0; f < 4; ++f) qR[f] = wC[f];
+      for (int f = 0; f < 4; ++f) qR[f] = cell(2, f);
       st.fall++;
     }
     dust_riemann(qL[3], qL[N], qL[T1], qL[T2], qR[3], qR[N], qR[T1], qR[T2], fl);
@@ -653,6 +653,28 @@ __device__ __forceinline__ void gas_face_p32(const GasC& c, const float* wA, con
 }
 
 // ------------------------------------------------------------------------------------
+// addressing of a wavefront's row
+
+// Read-only tables by scalar loads: constant address space, for indexes that are the same in
+// every lane of a wavefront.  Only tables that no kernel writes while the reading one runs.
+using ctab = const __attribute__((address_space(4))) double*;
+__device__ __forceinline__ ctab to_ctab(const double* p) { return (ctab)(uintptr_t)p; }
+
+// Element at a lane's index from a pointer that is the same in the whole wavefront.  The
+// pointer passes through a scalar register the optimiser cannot see through: otherwise it
+// keeps one vector address per array across the march (about 30 registers).
+template <class T>
+__device__ __forceinline__ T& at_row(T* p, unsigned lane) {
+  asm("" : "+s"(p));
+  return *(T*)((uintptr_t)p + (size_t)(lane * (unsigned)sizeof(T)));
+}
+template <class T>
+__device__ __forceinline__ T& at_plane(T* p, size_t off) {
+  asm("" : "+s"(p));
+  return p[off];
+}
+
+// ------------------------------------------------------------------------------------
 // state access with ghost cells (Sect. 2.4): r and z ghosts come from tables, theta wraps
 
 // FP32-perturbation storage layout: the gas deviation E' (5 fields) and each dust
@@ -699,22 +721,6 @@ __device__ __forceinline__ void st_cell(const StageArgs& a, void* st, int f, int
   } else {
     ((double*)st)[(size_t)f * g.N + cell] = v;
   }
-}
-
-// A whole dust cell (momenta r, theta, z, density) into the FP32 layout from registers:
-// the density, then the velocity deviations formed with it (the same values st_cell
-// stores field by field, without reading the density back); v0 is the stationary
-// azimuthal velocity of the cell
-__device__ __forceinline__ void st_dust32(const StageArgs& a, void* st, int sp, size_t cell,
-                                          const double v[4], double v0) {
-  const Geo& g = a.g;
-  ((double*)st)[p32_f64_base(g) + (size_t)sp * g.N + cell] = v[3];
-  const double ir = v[3] > 1e-300 ? frcp(v[3]) : 0.0;
-  float* vel = (float*)st + (size_t)(5 + 3 * sp) * g.N + cell;
-  const bool full = v[3] > 1e-300;
-  vel[0] = full ? (float)(v[0] * ir) : 0.0f;
-  vel[g.N] = full ? (float)(v[1] * ir - v0) : 0.0f;
-  vel[2 * g.N] = full ? (float)(v[2] * ir) : 0.0f;
 }
 
 // All NG conservative fields of a group at an interior cell: the gas deviation E', the

@@ -10,22 +10,14 @@
 
 namespace rb {
 
-// Tiles: 64 cells along theta (one wavefront per radial row) x TI rows in r, marching
-// through a chunk of z planes; TM rows for the stage kernel (RB_TM at build time), TI for
-// the in-plane adjoint kernel.
+// Tiles: 64 cells along theta (one wavefront per radial row) x 8 rows in r, marching
+// through a chunk of z planes; TM rows for the stage kernels, TI for the in-plane adjoint
+// kernel.
 constexpr int TJ = 64;
 constexpr int TI = 8;
 constexpr int NT = TJ * TI;
-#ifndef RB_TM
-#define RB_TM 8
-#endif
-constexpr int TM = RB_TM;
-#ifndef RB_WPE
-#define RB_WPE 2
-#endif
-constexpr int WPE = RB_WPE;  // stage-kernel waves per SIMD the register budget is set for
+constexpr int TM = 8;
 constexpr int NTM = TJ * TM;
-static_assert(TM == 4 || TM == 8, "stage-kernel tiles of 4 or 8 rows");
 constexpr int MAXF = 21;
 constexpr int DTLOG = 4096;  // device dt log entries per rb_step chunk
 
@@ -66,8 +58,10 @@ struct Layout {
   size_t ctrl, rt, ar, rco, rcell, rface, zc, bgc, bgr, bgz, wc, wr, wz, r0, grav, ghr, ghrw, ghz, ghzw;
   size_t trig, indw, indab, indp, damp, ozr, dtlog, cflp, outp, tsp, red, total;
   int nind;      // blocks of the indirect-gravity sums
-  int nblocks;   // stage-kernel blocks
+  int nblocks;   // gas stage-kernel blocks
+  int nblocks_dust;  // dust stage-kernel blocks
   int ntj, nti, nkc, tk;
+  int tk_dust;   // z planes per dust stage-kernel block
   int ntm;       // stage-kernel tiles in r (TM rows each)
   int nblocks_adj;  // in-plane adjoint kernel blocks (TI-row tiles)
   int ncfl;      // blocks of the standalone CFL / conversion kernels
@@ -139,6 +133,7 @@ struct StageArgs {
   int step;             // global step index (error reporting)
   int tk, ntj, nti, nkc;
   int ntm;              // stage-kernel tiles in r (rows of TM)
+  int tk_dust;          // z planes per dust stage-kernel block
 };
 
 struct InitArgs {
@@ -168,13 +163,14 @@ struct AdjArgs {
 // launchers (rb_kernels.hip)
 hipError_t launch_tables(const InitArgs& a, hipStream_t s);
 hipError_t launch_init_state(const InitArgs& a, hipStream_t s);
-hipError_t launch_stage(const StageArgs& a, int blocks, hipStream_t s);
+hipError_t launch_stage(const StageArgs& a, const Layout& L, hipStream_t s);
 // one group of a stage: 0 the gas, 1 + s dust species s
-hipError_t launch_stage_group(const StageArgs& a, int blocks, int group, hipStream_t s);
+hipError_t launch_stage_group(const StageArgs& a, const Layout& L, int group, hipStream_t s);
 hipError_t launch_cfl(const StageArgs& a, const void* state, int blocks, int dt_idx, hipStream_t s);
 hipError_t launch_drag(const StageArgs& a, void* state, double frac, int blocks, hipStream_t s);
-hipError_t launch_reduce(const StageArgs& a, int nparts, int dt_idx_next, int want_dt,
-                         int want_ledger, hipStream_t s);
+// partials: of the gas blocks (or of the standalone CFL kernel's) and of each dust group's
+hipError_t launch_reduce(const StageArgs& a, int nparts, int nparts_dust, int dt_idx_next,
+                         int want_dt, int want_ledger, hipStream_t s);
 hipError_t launch_fill(double* p, size_t n, double v, hipStream_t s);
 hipError_t launch_ctrl_init(Ctrl* c, hipStream_t s);
 hipError_t launch_cfl_out(const Ctrl* c, const double* dt, double* out, hipStream_t s);

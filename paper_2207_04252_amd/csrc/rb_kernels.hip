@@ -1,27 +1,24 @@
 // Device kernels of the bi-fluid finite-volume library for gfx950 (MI355X).
 //
-// One RK2 stage is one launch of k_stage: a workgroup owns a 64 (theta) x 8 (r) tile of
-// cells and marches through a chunk of z planes.  Each z plane of the tile, with a
-// two-cell halo, is staged in LDS; every thread solves the Riemann problems at the upper
-// theta and r faces of its own cell (the tile's lower-edge faces are solved by the first
-// 72 threads), exchanges the fluxes through LDS, and keeps the z direction in registers
-// (a three-plane ring of the cell's column and the flux of the face below).  Fluxes,
-// divergence, sources, drag and the update are fused: the state is read once per
-// stage (plus the L2-resident halo) and written once.
+// One RK2 stage is one launch per group of fields (k_gas, and k_dust for each species): a
+// workgroup owns a 64 (theta) x 8 (r) tile of cells and marches through a chunk of z planes.
+// Each z plane of the tile, with a two-cell halo, is staged in LDS; every thread solves the
+// Riemann problems at the upper theta and r faces of its own cell (the tile's lower-edge
+// faces are solved by the first 72 threads), exchanges the fluxes through LDS, and keeps its
+// column of the z direction to itself.  Fluxes, divergence, sources, drag and the update are
+// fused: the state is read once per stage (plus the L2-resident halo) and written once.
 #include "rb_device.h"
 
 namespace rb {
 
 // ------------------------------------------------------------------------------------
-// the stage kernels: one launch per group of fields (the gas; each dust species).  The
-// groups interact only through the cell-local drag, which each kernel evaluates from
-// the other group's centre state of the same stage input.
+// the gas stage kernel.  The groups of fields interact only through the cell-local drag,
+// which each kernel evaluates from the other group's centre state of the same stage input.
 
-template <bool GAS, int ND, bool G75, bool P32, bool EXT>
-__global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
-  constexpr int NG = GAS ? 5 : 4;
-  constexpr bool PG = GAS && P32;  // gas in the FP32 perturbation form
-  using T = typename std::conditional<PG, float, double>::type;
+template <int ND, bool G75, bool P32, bool EXT>
+__global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
+  constexpr int NG = 5;
+  using T = typename std::conditional<P32, float, double>::type;
   // a hard error stops the evolution; the flag is read once and broadcast so that the
   // whole workgroup takes the same branch (other workgroups may set it meanwhile)
   __shared__ int s_stop;
@@ -35,15 +32,12 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
   // FP64 gas: per-thread slots (no sharing) for the column's cell below the current plane
   // and the flux of the z face below, kept in LDS between their uses (without them the
   // face solves spill registers); the other kernels keep both in registers
-  constexpr bool LR = GAS && !P32;
+  constexpr bool LR = !P32;
   __shared__ T s_rm[LR ? NG : 1][LR ? NTM : 1];
   __shared__ T s_fz[LR ? NG : 1][LR ? NTM : 1];
 
   const Geo& g = a.g;
   const GasC gc = gas_consts(g.gamma, g.newton_max);
-  const RecC recc;
-  const int F0 = GAS ? 0 : 5 + 4 * species;
-  const int slot = GAS ? 0 : 1 + species;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int tjb = tile % a.ntj;
   const int tib = (tile / a.ntj) % a.ntm;
@@ -69,27 +63,23 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
   // faces the thread owns (each face of the mesh is owned by one thread of the launch),
   // 16 bits a bin in LDS slots private to the thread; a thread owns at most 4 faces per
   // plane and one more
-  __shared__ unsigned s_nh[GAS ? 4 : 1][GAS ? NTM : 1];
-  if constexpr (GAS) {
+  __shared__ unsigned s_nh[4][NTM];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) s_nh[q][tid] = 0u;
-  }
+  for (int q = 0; q < 4; ++q) s_nh[q][tid] = 0u;
   auto tally = [&](bool own) {
-    if constexpr (GAS) {
-      const int b = min(st.last, 7);
-      if (own) s_nh[b >> 1][tid] += 1u << (16 * (b & 1));
-    }
+    const int b = min(st.last, 7);
+    if (own) s_nh[b >> 1][tid] += 1u << (16 * (b & 1));
   };
 
   // The per-plane tables of the tile's rows, staged in LDS one plane ahead (double
-  // buffered): the stationary flow at the cell centres (wc) and, for the gas, at the r
+  // buffered): the stationary flow at the cell centres (wc), at the r
   // faces i0-1/2 .. i0+TM-1/2 (wr) and the z face above the plane (wz); the cells'
   // stationary conservative state (bgc) and gravity.  Thread t stages entry t: its
   // address is tab_p0 + plane * tab_stride.
   constexpr int T_WC = 0;
   constexpr int T_WR = T_WC + TM * WB_N;
-  constexpr int T_WZ = T_WR + (GAS ? (TM + 1) * WB_N : 0);
-  constexpr int T_BG = T_WZ + (GAS ? TM * WB_N : 0);
+  constexpr int T_WZ = T_WR + (TM + 1) * WB_N;
+  constexpr int T_BG = T_WZ + TM * WB_N;
   constexpr int T_GR = T_BG + TM * 5;
   constexpr int NTAB = T_GR + TM * 2;
   static_assert(NTAB <= NTM, "one table entry per thread");
@@ -122,11 +112,11 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
     }
   }
   double dtmin = 1e300;
-  // the largest signal speed of the thread's new cells (dust: its square).  The thread's
+  // the largest signal speed of the thread's new cells.  The thread's
   // row (so its volume and largest face area) is fixed, and the CFL bound decreases with
   // the speed, so the bound of the largest speed, formed once after the march, is the
   // smallest one
-  double smax = 0.0, vmax2 = 0.0;
+  double smax = 0.0;
   double tsmin = 1e300;  // smallest stopping time of the new state (drag law 1)
   double ledger = 0.0;
 
@@ -142,9 +132,8 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
   auto face = [&](auto dirc, const T* wA, const T* wB, const T* wC, const T* wD, const double* coB,
                   const double* coC, const double* bf, const double* bB, const double* bC, T* F) {
     constexpr int D = decltype(dirc)::value;
-    if constexpr (PG) gas_face_p32<D>(gc, wA, wB, wC, wD, coB, coC, bf, bB, bC, F, st);
-    else if constexpr (GAS) gas_face<D, G75>(gc, wA, wB, wC, wD, coB, coC, bf, bB, bC, F, st);
-    else dust_face<D>(recc, wA, wB, wC, wD, coB, coC, F, st);
+    if constexpr (P32) gas_face_p32<D>(gc, wA, wB, wC, wD, coB, coC, bf, bB, bC, F, st);
+    else gas_face<D, G75>(gc, wA, wB, wC, wD, coB, coC, bf, bB, bC, F, st);
   };
   using DR = std::integral_constant<int, 0>;
   using DT = std::integral_constant<int, 1>;
@@ -156,17 +145,17 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
   const bool twod = g.twod != 0;
   if (!twod) {
     T e2[NG];
-    load_recon<P32, EXT, NG>(a, in, F0, k0 - 2, ig, jw, e2);
-    load_recon<P32, EXT, NG>(a, in, F0, k0 - 1, ig, jw, rm);
-    load_recon<P32, EXT, NG>(a, in, F0, k0, ig, jw, r0);
-    load_recon<P32, EXT, NG>(a, in, F0, k0 + 1, ig, jw, rp);
+    load_recon<P32, EXT, NG>(a, in, 0, k0 - 2, ig, jw, e2);
+    load_recon<P32, EXT, NG>(a, in, 0, k0 - 1, ig, jw, rm);
+    load_recon<P32, EXT, NG>(a, in, 0, k0, ig, jw, r0);
+    load_recon<P32, EXT, NG>(a, in, 0, k0 + 1, ig, jw, rp);
     const double* bf = a.t.wz + ((size_t)k0 * g.nr + igc) * WB_N;
     face(DZ(), e2, rm, r0, rp, nullptr, nullptr, bf, bg_ptr(a, k0 - 1, igc), bg_ptr(a, k0, igc),
          fzlo);
-    if (GAS) tally(act && k0 == 0);
+    tally(act && k0 == 0);
     if (a.second && k0 == 0 && act) {
       double fm = (double)fzlo[NG - 1];
-      if (PG) fm += bf[WB_RHO] * bf[WB_W];  // background normal mass flux rho0 w0
+      if (P32) fm += bf[WB_RHO] * bf[WB_W];  // background normal mass flux rho0 w0
       ledger -= Az * fm;
     }
     if constexpr (LR) {
@@ -174,7 +163,7 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
       for (int f = 0; f < NG; ++f) { s_rm[f][tslot] = rm[f]; s_fz[f][tslot] = fzlo[f]; }
     }
   } else {
-    load_recon<P32, EXT, NG>(a, in, F0, 0, ig, jw, r0);
+    load_recon<P32, EXT, NG>(a, in, 0, 0, ig, jw, r0);
 #pragma unroll
     for (int f = 0; f < NG; ++f) {
       rm[f] = T(0); rp[f] = T(0); rn[f] = T(0); fzlo[f] = T(0); fzhi[f] = T(0);
@@ -182,39 +171,25 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
   }
 
   // the halo ring of the LDS plane: two rows below and above the tile, then two columns
-  // on each side of its rows; slot tid for every thread, and slot tid + NTM for the first
-  // threads when the ring is larger than the workgroup (4-row tiles).  PF: the first slot
-  // of each plane is loaded one plane ahead, so that its latency hides behind the previous
-  // plane's face solves (not in the FP32-perturbation gas kernel, where the held registers
-  // cost more than they hide).
+  // on each side of its rows; slot tid.  PF: the slots of each plane are loaded one plane
+  // ahead, so that their latency hides behind the previous plane's face solves (not in the
+  // FP32-perturbation form, where the held registers cost more than they hide).
   constexpr int HW = TJ + 4, NHALO = 4 * HW + 4 * TM;
-  constexpr int NH2 = NHALO > NTM ? NHALO - NTM : 0;
-  static_assert(NHALO <= 2 * NTM, "two halo cells per thread at most");
-  auto halo_pos = [&](int h, int& rr, int& cc) {
-    if (h < 2 * HW) { rr = h / HW; cc = h % HW; }
-    else if (h < 4 * HW) { rr = TM + 2 + (h - 2 * HW) / HW; cc = (h - 2 * HW) % HW; }
-    else { const int e = h - 4 * HW; rr = 2 + e / 4; cc = (e & 3) < 2 ? (e & 3) : TJ + (e & 3); }
-  };
+  static_assert(NHALO <= NTM, "one halo cell per thread");
   const bool halo_t = tid < NHALO;
   int h_rr = 0, h_cc = 0;
-  if (halo_t) halo_pos(tid, h_rr, h_cc);
+  if (tid < 2 * HW) { h_rr = tid / HW; h_cc = tid % HW; }
+  else if (tid < 4 * HW) { h_rr = TM + 2 + (tid - 2 * HW) / HW; h_cc = (tid - 2 * HW) % HW; }
+  else if (halo_t) { const int e = tid - 4 * HW; h_rr = 2 + e / 4; h_cc = (e & 3) < 2 ? (e & 3) : TJ + (e & 3); }
   const int h_ii = i0 + h_rr - 2;
   const int h_jj = (j0 + h_cc - 2 + g.nth) % g.nth;
-  const bool halo2 = NH2 > 0 && tid < NH2;
-  int h2_rr = 0, h2_cc = 0;
-  if (halo2) halo_pos(tid + NTM, h2_rr, h2_cc);
-  const int h2_ii = i0 + h2_rr - 2;
-  const int h2_jj = (j0 + h2_cc - 2 + g.nth) % g.nth;
-  constexpr bool PF = !PG;
+  constexpr bool PF = !P32;
   T hv[NG];
-  // dust: the next plane's first-slot halo and the column's cell k+2 are fetched raw at
-  // the top of a plane and formed after the faces (the halo after the second barrier, the
-  // column cell before the z face), so that no wait for them precedes the faces
-  DustRaw<P32> hraw, nraw;
-  // FP32 gas (base boundary options): the column's cell k+2 the same way; the next plane's
-  // halo is requested after the second barrier, ahead of the drag's dust loads (one wait
-  // for both), and formed before the update's stores
-  constexpr bool RAWG = PG && !EXT;
+  // FP32 form (base boundary options): the column's cell k+2 is fetched raw at the top of a
+  // plane and formed before the z face, so that no wait for it precedes the faces; the next
+  // plane's halo is requested after the second barrier, ahead of the drag's dust loads (one
+  // wait for both), and formed before the update's stores
+  constexpr bool RAWG = P32 && !EXT;
   const float gm1f = (float)(g.gamma - 1.0);
   GasRaw32 gnraw, ghraw;
   if constexpr (RAWG) {
@@ -222,13 +197,8 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
       gas_fetch32(a, in, k0, h_ii, h_jj, ghraw);
       gas_finish32(ghraw, gm1f, hv);
     }
-  } else if constexpr (GAS) {
-    if (PF && halo_t) load_recon<P32, EXT, NG>(a, in, F0, k0, h_ii, h_jj, hv);
   } else {
-    if (halo_t) {
-      dust_fetch<P32, EXT>(a, in, F0, k0, h_ii, h_jj, hraw);
-      dust_finish<P32>(hraw, hv);
-    }
+    if (PF && halo_t) load_recon<P32, EXT, NG>(a, in, 0, k0, h_ii, h_jj, hv);
   }
 
   if (tab_t) s_tab[k0 & 1][tid] = tab_p0[(size_t)k0 * tab_stride];
@@ -244,74 +214,36 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
   for (int k = k0; k < k1; ++k) {
     if (!twod) {
       if constexpr (RAWG) gas_fetch32(a, in, k + 2, ig, jw, gnraw);
-      else if constexpr (GAS) load_recon<P32, EXT, NG>(a, in, F0, k + 2, ig, jw, rn);
-      else dust_fetch<P32, EXT>(a, in, F0, k + 2, ig, jw, nraw);
+      else load_recon<P32, EXT, NG>(a, in, 0, k + 2, ig, jw, rn);
     }
     const int kb = k & 1;
     double tab_next = 0.0;
     if (tab_t && k + 1 < k1) tab_next = tab_p0[(size_t)(k + 1) * tab_stride];
-    // the update's base values of this plane's cell and (dust) the gas state the drag
-    // needs, requested here so that their latency hides behind the face solves.  Stage 1
-    // of the FP32 dust layout reads its base from r0 (the same cell of the same state).
+    // the update's base values of this plane's cell, requested here so that their latency
+    // hides behind the face solves (raw stored values: any arithmetic on them here would wait
+    // for the loads).  The FP32 form with the base boundary options requests them after the
+    // second barrier instead, with the drag's loads: held across the faces they would spill
     const size_t cell = ((size_t)k * g.nr + ig) * g.nth + jg;
     const size_t cellw = ((size_t)k * g.nr + igc) * g.nth + jw;
     const bool upd = a.mode == MODE_UPDATE && act;
-    const bool base_r0 = P32 && !GAS && a.base == a.in;
-    // (raw stored values: any arithmetic on them here would wait for the loads)
-    using BT = typename std::conditional<PG, float, double>::type;
-    BT pb[NG];
-    float pvel[P32 && !GAS ? 3 : 1];  // FP32 dust layout: stored velocity deviations
-    // (the FP32 gas kernel requests them after the second barrier instead, with the drag's
-    // loads: held across the faces they would spill)
-    auto load_base_pg = [&]() {
+    T pb[NG];
+    auto load_base = [&]() {
       if (upd) {
 #pragma unroll
-        for (int f = 0; f < NG; ++f) pb[f] = ((const float*)a.base)[(size_t)f * g.N + cell];
+        for (int f = 0; f < NG; ++f) pb[f] = ((const T*)a.base)[(size_t)f * g.N + cell];
       }
     };
-    if (upd && !base_r0) {
-      if constexpr (PG) {
-        if constexpr (!RAWG) load_base_pg();
-      } else if constexpr (P32 && !GAS) {
-        const float* vel = (const float*)a.base + (size_t)(5 + 3 * species) * g.N + cell;
-        pb[3] = ((const double*)a.base)[p32_f64_base(g) + (size_t)species * g.N + cell];
-        pvel[0] = vel[0];
-        pvel[1] = vel[g.N];
-        pvel[2] = vel[2 * (size_t)g.N];
-      } else {
-        load_cons<P32, NG>(a, a.base, F0, k, ig, jg, pb);
-      }
-    }
-    using GT = typename std::conditional<P32, float, double>::type;
-    GT pg[GAS ? 1 : 5];
-    if constexpr (!GAS) {
-      if (drag) {
-#pragma unroll
-        for (int f = 0; f < 5; ++f) pg[f] = ((const GT*)in)[(size_t)f * g.N + cellw];
-      }
-    }
+    if constexpr (!RAWG) load_base();
     // ---- stage the plane (with halo) in LDS
 #pragma unroll
     for (int f = 0; f < NG; ++f) s_pl[f][ti + 2][tj + 2] = r0[f];
     if (halo_t) {
-      if constexpr (GAS && !RAWG) {
-        if (!PF) load_recon<P32, EXT, NG>(a, in, F0, k, h_ii, h_jj, hv);
+      if constexpr (!RAWG) {
+        if (!PF) load_recon<P32, EXT, NG>(a, in, 0, k, h_ii, h_jj, hv);
       }
 #pragma unroll
       for (int f = 0; f < NG; ++f) s_pl[f][h_rr][h_cc] = hv[f];
-      if constexpr (GAS) {
-        if (PF && k + 1 < k1) load_recon<P32, EXT, NG>(a, in, F0, k + 1, h_ii, h_jj, hv);
-      } else {
-        if (k + 1 < k1) dust_fetch<P32, EXT>(a, in, F0, k + 1, h_ii, h_jj, hraw);
-      }
-    }
-    if constexpr (NH2 > 0) {
-      if (halo2) {
-        T hv2[NG];
-        load_recon<P32, EXT, NG>(a, in, F0, k, h2_ii, h2_jj, hv2);
-#pragma unroll
-        for (int f = 0; f < NG; ++f) s_pl[f][h2_rr][h2_cc] = hv2[f];
-      }
+      if (PF && k + 1 < k1) load_recon<P32, EXT, NG>(a, in, 0, k + 1, h_ii, h_jj, hv);
     }
     __syncthreads();
     // ---- theta face j+1/2 and r face i+1/2 of this cell
@@ -325,7 +257,7 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
       {
         const double* bf = &s_tab[kb][T_WC + ti * WB_N];
         face(DT(), eA, eB, eC, eD, nullptr, nullptr, bf, bf, bf, F);
-        if (GAS) tally(act);
+        tally(act);
       }
 #pragma unroll
       for (int f = 0; f < NG; ++f) s_ft[f][ti][tj + 1] = F[f];
@@ -335,13 +267,13 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
         eC[f] = s_pl[f][ti + 3][tj + 2]; eD[f] = s_pl[f][ti + 4][tj + 2];
       }
       {
-        const double* bf = GAS ? &s_tab[kb][T_WR + (ti + 1) * WB_N] : nullptr;
+        const double* bf = &s_tab[kb][T_WR + (ti + 1) * WB_N];
         face(DR(), eA, eB, eC, eD, &s_rco[(ti + 1) * RC_N], &s_rco[(ti + 2) * RC_N], bf,
              bg_ptr(a, k, min(ig, g.nr)), bg_ptr(a, k, min(ig + 1, g.nr)), F);
-        if (GAS) tally(act);
+        tally(act);
         if (a.second && act && ig == g.nr - 1) {
           double fm = (double)F[NG - 1];
-          if (PG) fm += bf[WB_RHO] * bf[WB_U];  // background normal mass flux rho0 u0
+          if (P32) fm += bf[WB_RHO] * bf[WB_U];  // background normal mass flux rho0 u0
           ledger += Arhi * fm;
         }
       }
@@ -358,17 +290,17 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
         eA[f] = s_pl[f][0][col + 2]; eB[f] = s_pl[f][1][col + 2];
         eC[f] = s_pl[f][2][col + 2]; eD[f] = s_pl[f][3][col + 2];
       }
-      const double* bf = GAS ? &s_tab[kb][T_WR] : nullptr;
+      const double* bf = &s_tab[kb][T_WR];
       face(DR(), eA, eB, eC, eD, &s_rco[0], &s_rco[RC_N], bf, bg_ptr(a, k, i0 - 1),
            bg_ptr(a, k, i0), F);
       // the tile's lower r face is the upper face of the tile below, except at the inner
       // boundary
-      if (GAS) tally(i0 == 0 && j0 + col < g.nth);
+      tally(i0 == 0 && j0 + col < g.nth);
 #pragma unroll
       for (int f = 0; f < NG; ++f) s_fr[f][0][col] = F[f];
       if (a.second && i0 == 0 && j0 + col < g.nth) {
         double fm = (double)F[NG - 1];
-        if (PG) fm += bf[WB_RHO] * bf[WB_U];
+        if (P32) fm += bf[WB_RHO] * bf[WB_U];
         ledger -= Ar0 * fm;
       }
     } else if (tid < TJ + TM) {
@@ -387,31 +319,27 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
     // ---- z face k+1/2 from the register ring
     if (!twod) {
       if constexpr (RAWG) gas_finish32(gnraw, gm1f, rn);
-      else if constexpr (!GAS) dust_finish<P32>(nraw, rn);
       if constexpr (LR) {
 #pragma unroll
         for (int f = 0; f < NG; ++f) rm[f] = s_rm[f][tslot];
       }
-      const double* bf = GAS ? &s_tab[kb][T_WZ + ti * WB_N] : nullptr;
+      const double* bf = &s_tab[kb][T_WZ + ti * WB_N];
       face(DZ(), rm, r0, rp, rn, nullptr, nullptr, bf, bg_ptr(a, k, igc), bg_ptr(a, k + 1, igc),
            fzhi);
-      if (GAS) tally(act);
+      tally(act);
       if (a.second && act && k == g.nz - 1) {
         double fm = (double)fzhi[NG - 1];
-        if (PG) fm += bf[WB_RHO] * bf[WB_W];
+        if (P32) fm += bf[WB_RHO] * bf[WB_W];
         ledger += Az * fm;
       }
     }
     __syncthreads();
     // ---- the next plane's tables (read after the next plane's first barrier; buffer
-    //      (k + 1) & 1 was last read before this plane's first barrier) and the dust halo;
-    //      both here, before this plane's stores, so that waiting for them waits for no store
+    //      (k + 1) & 1 was last read before this plane's first barrier), before this plane's
+    //      stores, so that waiting for them waits for no store
     if (tab_t && k + 1 < k1) s_tab[(k + 1) & 1][tid] = tab_next;
-    if constexpr (!GAS) {
-      if (halo_t && k + 1 < k1) dust_finish<P32>(hraw, hv);
-    }
     if constexpr (RAWG) {
-      load_base_pg();
+      load_base();
       if (halo_t && k + 1 < k1) gas_fetch32(a, in, k + 1, h_ii, h_jj, ghraw);
     }
     // ---- divergence -sum_s A_s F.n_s (Sect. 2.2), sources (App. B), drag (Sect. 2.9)
@@ -428,7 +356,7 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
     const double* bgc = &s_tab[kb][T_BG + ti * 5];
     const double* bw = &s_tab[kb][T_WC + ti * WB_N];
     T S[NG];
-    if constexpr (PG) {
+    if constexpr (P32) {
       // source change S(E) - S(E0), every term formed from the perturbations W' (the
       // stationary flow has no radial or vertical velocity)
       const float rp = r0[4], up = r0[0], vp = r0[1], wp = r0[2], pp = r0[3];
@@ -477,7 +405,7 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
         S[2] += (float)dzz;
         S[3] += (float)(u * dx + v * dy + w2 * dzz);
       }
-    } else if constexpr (GAS) {
+    } else {
       // the cell's primitives: stationary flow + W'
       const double rho = bw[WB_RHO] + r0[4];
       const double u = bw[WB_U] + r0[0], v = bw[WB_V] + r0[1], w = bw[WB_W] + r0[2];
@@ -515,48 +443,23 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
         S[2] += dzz;
         S[3] += u * dx + v * dy + w * dzz;
       }
-    } else {
-      // the dust cell's primitives (velocity zero where the density is not positive)
-      const double rd = r0[3], ud = r0[0], vd = r0[1], wd = r0[2];
-      double fx = 0.0, fy = 0.0, fz = 0.0;
-      if (drag) {
-        double q[5];
-#pragma unroll
-        for (int f = 0; f < 5; ++f) q[f] = bgc[f] + (double)pg[f];
-        const double inv = 1.0 / q[4];
-        const double u = q[0] * inv, v = q[1] * inv, w = q[2] * inv;
-        const double pq = (EXT && g.drag_law) ? gc.gm1 * (q[3] - 0.5 * (q[0] * u + q[1] * v + q[2] * w)) : 0.0;
-        const double its = inv_tstop<EXT>(g, species, omk, q[4], pq);
-        fx = rd * (ud - u) * its;
-        fy = rd * (vd - v) * its;
-        fz = rd * (wd - w) * its;
-      }
-      S[0] = (rd * vd * vd) * invrc + rd * gr - fx;
-      S[1] = -(rd * ud * vd) * invrc - fy;
-      S[2] = rd * gz - fz;
-      S[3] = 0.0;
     }
     // indirect gravity (Sect. 2.10): minus the star's acceleration by the disc
     if (EXT && g.indirect && a.mode != MODE_RESID) {
       const double A = a.t.indab[0], B = a.t.indab[1];
       const double cs = a.t.trig[jw], sn = a.t.trig[g.nth + jw];
       const double ar = -g.GM * (A * cs + B * sn), at = -g.GM * (B * cs - A * sn);
-      if constexpr (GAS) {
-        const double rho = bw[WB_RHO] + (double)r0[4];
-        const double mr = rho * (bw[WB_U] + (double)r0[0]), mt = rho * (bw[WB_V] + (double)r0[1]);
-        S[0] += (T)(rho * ar);
-        S[1] += (T)(rho * at);
-        S[3] += (T)(mr * ar + mt * at);
-      } else {
-        S[0] += r0[3] * ar;
-        S[1] += r0[3] * at;
-      }
+      const double rho = bw[WB_RHO] + (double)r0[4];
+      const double mr = rho * (bw[WB_U] + (double)r0[0]), mt = rho * (bw[WB_V] + (double)r0[1]);
+      S[0] += (T)(rho * ar);
+      S[1] += (T)(rho * at);
+      S[3] += (T)(mr * ar + mt * at);
     }
     // boundary damping zones (Sect. 2.4): the gas deviation relaxes to the stationary flow
-    if (EXT && GAS && g.damp) {
+    if (EXT && g.damp) {
       const double kd = a.t.damp[(size_t)k * g.nr + igc];
       double e[NG];
-      load_cons<P32, NG>(a, in, F0, k, igc, jw, e);
+      load_cons<P32, NG>(a, in, 0, k, igc, jw, e);
 #pragma unroll
       for (int f = 0; f < NG; ++f) S[f] -= (T)(kd * e[f]);
     }
@@ -566,13 +469,13 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
     T Gt[NG];
 #pragma unroll
     for (int f = 0; f < NG; ++f) Gt[f] = fma(S[f], T(Vc), Gd[f]);
-    if (GAS && !P32 && a.mode != MODE_RESID) {
+    if (!P32 && a.mode != MODE_RESID) {
       const double* R0 = a.t.r0 + ((size_t)k * g.nr + igc) * 5;
 #pragma unroll
       for (int f = 0; f < NG; ++f) Gt[f] -= (T)R0[f];
     }
     if (a.mode == MODE_RESID) {
-      if (GAS && act && jg == 0) {
+      if (act && jg == 0) {
 #pragma unroll
         for (int f = 0; f < NG; ++f) a.c.r0w[((size_t)k * g.nr + ig) * 5 + f] = (double)Gt[f];
       }
@@ -580,8 +483,7 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
       if (act) {
 #pragma unroll
         for (int f = 0; f < NG; ++f) {
-          if (P32) ((float*)a.out)[(size_t)(F0 + f) * g.N + cell] = (float)Gt[f];
-          else ((double*)a.out)[(size_t)(F0 + f) * g.N + cell] = (double)Gt[f];
+          ((T*)a.out)[(size_t)f * g.N + cell] = Gt[f];
         }
       }
     } else if (act) {
@@ -589,59 +491,20 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
       // kernel stores after its positivity and CFL arithmetic, so that a wait there (a
       // register reload) comes before the stores rather than waiting for them; the others
       // store first (their registers prefer it)
-      double nvd[NG];
-      float nv[PG ? NG : 1];
+      T nv[NG];
       auto store_new = [&]() {
-        if constexpr (PG) {
 #pragma unroll
-          for (int f = 0; f < NG; ++f) ((float*)a.out)[(size_t)f * g.N + cell] = nv[f];
-        } else if constexpr (!P32 || GAS) {
-#pragma unroll
-          for (int f = 0; f < NG; ++f) st_cell<P32>(a, a.out, F0 + f, k, ig, cell, nvd[f]);
-        } else {
-          // FP32 dust velocities are formed with the new density
-          st_dust32(a, a.out, species, cell, nvd, bw[WB_V]);
-        }
+        for (int f = 0; f < NG; ++f) ((T*)a.out)[(size_t)f * g.N + cell] = nv[f];
       };
-      if constexpr (PG) {
-        const float cdt = (float)(a.coef * dt * invV);
+      const T cdt = (T)(a.coef * dt * invV);
 #pragma unroll
-        for (int f = 0; f < NG; ++f) {
-          nv[f] = fma(cdt, Gt[f], pb[f]);
-          nvd[f] = (double)nv[f];
-        }
-      } else {
-        const double cdt = a.coef * dt * invV;
-        double bv[NG];
-        if (base_r0) {
-          // load_cons of the FP32 dust layout: density times (stored velocity deviation +
-          // stationary velocity), the stored deviation being zero where the density is not
-          // positive
-          const double rd = (double)r0[3];
-          const double v0 = bw[WB_V];
-          bv[0] = rd * (double)r0[0];
-          bv[1] = rd * (rd > 0.0 ? (double)r0[1] : v0);
-          bv[2] = rd * (double)r0[2];
-          bv[3] = rd;
-        } else if constexpr (P32 && !GAS) {
-          // load_cons of the FP32 dust layout
-          bv[0] = pb[3] * (double)pvel[0];
-          bv[1] = pb[3] * (bw[WB_V] + (double)pvel[1]);
-          bv[2] = pb[3] * (double)pvel[2];
-          bv[3] = pb[3];
-        } else {
-#pragma unroll
-          for (int f = 0; f < NG; ++f) bv[f] = (double)pb[f];
-        }
-#pragma unroll
-        for (int f = 0; f < NG; ++f) nvd[f] = fma(cdt, (double)Gt[f], bv[f]);
-        store_new();
-      }
-      if (GAS) {
+      for (int f = 0; f < NG; ++f) nv[f] = fma(cdt, Gt[f], pb[f]);
+      if constexpr (!P32) store_new();
+      {
         // positivity of the new gas state; CFL of the new state (second stage)
         double qn[5];
 #pragma unroll
-        for (int f = 0; f < 5; ++f) qn[f] = bgc[f] + nvd[f];
+        for (int f = 0; f < 5; ++f) qn[f] = bgc[f] + (double)nv[f];
         const double in2 = 1.0 / qn[4];
         const double un = qn[0] * in2, vn = qn[1] * in2, wn = qn[2] * in2;
         const double pn = gc.gm1 * (qn[3] - 0.5 * (qn[0] * un + qn[1] * vn + qn[2] * wn));
@@ -657,14 +520,8 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
             for (int s2 = 0; s2 < ND; ++s2) tsmin = fmin(tsmin, 1.0 / inv_tstop<EXT>(g, s2, omk, qn[4], pn));
           }
         }
-      } else if (a.second && nvd[3] < 0.0) {
-        st.negd++;
-      } else if (a.second && nvd[3] > 0.0) {
-        double id = 1.0 / nvd[3];
-        double a1 = nvd[0] * id, a2 = nvd[1] * id, a3 = nvd[2] * id;
-        vmax2 = fmax(vmax2, a1 * a1 + a2 * a2 + a3 * a3);
       }
-      if constexpr (PG) store_new();
+      if constexpr (P32) store_new();
     }
     // ---- shift the ring
 #pragma unroll
@@ -679,20 +536,16 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
   }
 
   // ---- block reductions: counters, CFL partial, boundary outflow partial
-  if constexpr (!GAS) smax = sqrt(vmax2);
   if (smax > 0.0) dtmin = g.cfl * Vc / (smax * maxA);
   const int wv = tid / 64, ln = tid & 63;
   int nf_ = wave_isum(st.fall), nv_ = wave_isum(st.vac), mi_ = wave_imax(st.maxit);
-  int nc_ = wave_imax(st.noconv), nr_ = wave_isum(st.resolve), nd_ = GAS ? 0 : wave_isum(st.negd);
-  if constexpr (GAS) {
+  int nc_ = wave_imax(st.noconv), nr_ = wave_isum(st.resolve);
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const int hb = wave_isum((int)((s_nh[b >> 1][tid] >> (16 * (b & 1))) & 0xffffu));
-      if (ln == 0 && hb) atomicAdd(&a.c.ctrl->newton_hist[b], (unsigned long long)hb);
-    }
+  for (int b = 0; b < 8; ++b) {
+    const int hb = wave_isum((int)((s_nh[b >> 1][tid] >> (16 * (b & 1))) & 0xffffu));
+    if (ln == 0 && hb) atomicAdd(&a.c.ctrl->newton_hist[b], (unsigned long long)hb);
   }
   if (ln == 0) {
-    if (nd_) atomicAdd(&a.c.ctrl->nnegd, (unsigned long long)nd_);
     if (nf_) atomicAdd(&a.c.ctrl->nfall, (unsigned long long)nf_);
     if (nv_) { atomicAdd(&a.c.ctrl->nvac, (unsigned long long)nv_); atomicOr(&a.c.ctrl->status, FL_VAC); }
     if (mi_) atomicMax(&a.c.ctrl->maxit, mi_);
@@ -702,7 +555,7 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
   if (a.second && a.mode == MODE_UPDATE) {
     double m = wave_min(dtmin);
     double ls = wave_sum(ledger);
-    double tm = (EXT && GAS && ND > 0) ? wave_min(tsmin) : 1e300;
+    double tm = (EXT && ND > 0) ? wave_min(tsmin) : 1e300;
     if (ln == 0) { s_red[wv][0] = m; s_red[wv][1] = ls; s_red[wv][2] = tm; }
     __syncthreads();
     if (tid == 0) {
@@ -712,9 +565,429 @@ __global__ void __launch_bounds__(NTM, WPE) k_march(StageArgs a, int species) {
         lsum += s_red[w2][1];
         tmm = fmin(tmm, s_red[w2][2]);
       }
+      a.c.cflp[(size_t)blockIdx.x * 5] = mm;
+      a.c.outp[(size_t)blockIdx.x * 5] = lsum;
+      if (EXT && g.drag_law) a.c.tsp[blockIdx.x] = tmm;
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------
+// the dust stage kernel
+
+// One RK2 stage of one dust species; tiles, planes and update as k_gas.  Bound by
+// instruction issue and by the waits between its barriers, so it is written for two
+// workgroups on a CU (four waves per SIMD, 128 VGPRs): while one waits at a barrier or for
+// memory the other computes.  What a plane needs between phases therefore lives in LDS
+// where it can: the cell below (s_rm) and the current cell (the staged plane itself) of the
+// thread's column; registers keep only the cell above, the flux of the z face below and the
+// raw loads in flight, all requested before the faces that hide them.  Three-dust disc
+// 512 x 1024 x 128, FP32-perturbation form: 1.92 -> 1.74 ms per launch (4.7 GB, 2.7 TB/s);
+// one-dust disc 256 x 512 x 64, FP64: 0.30 -> 0.27 ms (1.0 GB, 3.7 TB/s).
+template <bool P32, bool EXT>
+__global__ void __launch_bounds__(NTM, 4) k_dust(StageArgs a, int species) {
+  __shared__ int s_stop;
+  if (threadIdx.x == 0) s_stop = __atomic_load_n(&a.c.ctrl->status, __ATOMIC_RELAXED);
+  __syncthreads();
+  if (s_stop & FL_HARD) return;
+  constexpr int NG = 4, HW = TJ + 4, NHALO = 4 * HW + 4 * TM;
+  static_assert(NHALO <= NTM, "one halo cell per thread");
+  __shared__ double s_pl[NG][TM + 4][HW];
+  __shared__ double s_ft[NG][TM][TJ + 1];
+  __shared__ double s_fr[NG][TM + 1][TJ];
+  __shared__ double s_rm[NG][NTM];
+  __shared__ double s_red[NTM / 64][2];
+  // per-plane tables: the stationary conservative state and gravity of the tile's rows, one
+  // plane ahead; the stationary azimuthal velocity of the rows and their halo, two ahead
+  constexpr int NTAB = TM * 7, NV0 = TM + 4;
+  __shared__ double s_tab[2][NTAB];
+  __shared__ double s_v0[4][NV0];
+
+  const Geo& g = a.g;
+  const RecC recc;
+  const int F0 = 5 + 4 * species, slot = 1 + species;
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int tjb = tile % a.ntj;
+  const int tib = (tile / a.ntj) % a.ntm;
+  const int kcb = tile / (a.ntj * a.ntm);
+  const int tid = threadIdx.x, tj = tid & (TJ - 1);
+  const int ti = __builtin_amdgcn_readfirstlane(tid / TJ);
+  const int j0 = tjb * TJ, i0 = tib * TM;
+  const int k0 = kcb * a.tk_dust, k1 = min(g.nz, k0 + a.tk_dust);
+  const int jg = j0 + tj;
+  const int ig = i0 + ti, igc = min(ig, g.nr - 1);
+  const bool act = jg < g.nth && ig < g.nr;
+  const bool drag = !g.drag_exact;
+  const bool twod = g.twod != 0;
+  const size_t plane = (size_t)g.nr * g.nth;
+  TStat st = {0, 0, 0, 0, 0, 0, 0};
+  // the tile's columns inside the grid; the threads past them repeat the last one, except
+  // that the first two slots past it belong to the halo (the wrapped cells)
+  const int wcols = min(TJ, g.nth - j0);
+  const unsigned jl = min(tj, wcols - 1);
+  const bool centre = (unsigned)(tj - wcols) >= 2u;
+  const size_t row0 = (size_t)igc * g.nth + j0;  // (a wavefront has one row: scalar)
+  // tables of the wavefront's row, by scalar loads
+  const ctab rt = to_ctab(a.t.rt) + (size_t)igc * RT_N, ar = to_ctab(a.t.ar), rco = to_ctab(a.t.rco);
+  // thread t stages table entry t: tab_p + plane * tab_stride
+  const bool tab_t = tid < NTAB, v0_t = P32 && tid >= NTAB && tid < NTAB + NV0;
+  const double* tab_p = nullptr;
+  unsigned tab_stride = 0;
+  if (tid < TM * 5) {
+    tab_p = a.t.bgc + (size_t)min(i0 + tid / 5, g.nr - 1) * 5 + tid % 5;
+    tab_stride = g.nr * 5u;
+  } else if (tab_t) {
+    const int e = tid - TM * 5;
+    tab_p = a.t.grav + (size_t)min(i0 + e / 2, g.nr - 1) * 2 + e % 2;
+    tab_stride = g.nr * 2u;
+  } else if (v0_t) {
+    tab_p = a.t.wc + (size_t)min(max(i0 + tid - NTAB - 2, 0), g.nr - 1) * WB_N + WB_V;
+    tab_stride = g.nr * (unsigned)WB_N;
+  }
+  auto tab_load = [&](int k) {  // (bgc and gravity of plane k, the velocity of plane k + 2)
+    return tab_p[(size_t)min(v0_t ? k + 2 : k, g.nz - 1) * tab_stride];
+  };
+  auto tab_store = [&](int k, double x) {
+    if (tab_t) s_tab[k & 1][tid] = x;
+    if (v0_t) s_v0[(k + 2) & 3][tid - NTAB] = x;
+  };
+
+  // the state's arrays of this species: FP64 layout, momenta and density; FP32 layout,
+  // velocity deviations (FP32) and density
+  using VT = typename std::conditional<P32, float, double>::type;
+  auto vel_of = [&](const void* s) {
+    return (const VT*)s + (size_t)(P32 ? 5 + 3 * species : F0) * g.N;
+  };
+  auto den_of = [&](const void* s) {
+    return (const double*)s + (P32 ? p32_f64_base(g) + (size_t)species * g.N : (size_t)(F0 + 3) * g.N);
+  };
+  const VT* vin = vel_of(a.in);
+  const double* din = den_of(a.in);
+  struct Raw { VT m[3]; double rd; };
+  // reconstructed variables (velocity, zero where the density is not positive; density)
+  // of a stored cell whose stationary azimuthal velocity is v0
+  auto form = [&](const Raw& R, double v0, double* out) {
+    const bool full = R.rd > 0.0;
+    if constexpr (P32) {
+      out[0] = full ? (double)R.m[0] : 0.0;
+      out[1] = full ? v0 + (double)R.m[1] : 0.0;
+      out[2] = full ? (double)R.m[2] : 0.0;
+    } else {
+      const double id = full ? 1.0 / R.rd : 0.0;
+#pragma unroll
+      for (int f = 0; f < 3; ++f) out[f] = R.m[f] * id;
+    }
+    out[3] = R.rd;
+  };
+  // the thread's cell of plane k of its column; rows and planes outside the grid are
+  // clamped into it and replaced when formed
+  auto col_fetch = [&](const VT* v, const double* d, int k, Raw& R) {
+    const size_t r = (size_t)min(max(k, 0), g.nz - 1) * plane + row0;
+#pragma unroll
+    for (int f = 0; f < 3; ++f) R.m[f] = at_row(v + (size_t)f * g.N + r, jl);
+    R.rd = at_row(d + r, jl);
+  };
+  auto col_form = [&](int k, const Raw& R, double v0, double* out) {
+    if ((k < 0 || k >= g.nz) && !(EXT && g.bc_z == 1)) {
+      const int side = k < 0 ? 0 : 1, layer = min(k < 0 ? -1 - k : k - g.nz, 1);
+      const ctab gt = to_ctab(a.t.ghz) + ((size_t)(side * 2 + layer) * g.nr + igc) * g.nf + F0;
+#pragma unroll
+      for (int f = 0; f < NG; ++f) out[f] = gt[f];
+    } else if (k >= 0 && k < g.nz && ig >= g.nr) {
+      const ctab gt = to_ctab(a.t.ghr) + ((size_t)(2 + min(ig - g.nr, 1)) * g.nz + k) * g.nf + F0;
+#pragma unroll
+      for (int f = 0; f < NG; ++f) out[f] = gt[f];
+    } else {
+      form(R, v0, out);  // (outflow: the boundary cell's variables)
+    }
+  };
+  // the thread's cell of the halo ring
+  const bool halo_t = tid < NHALO;
+  int h_rr = 0, h_cc = 0;
+  if (tid < 2 * HW) { h_rr = tid / HW; h_cc = tid % HW; }
+  else if (tid < 4 * HW) { h_rr = TM + 2 + (tid - 2 * HW) / HW; h_cc = (tid - 2 * HW) % HW; }
+  else if (halo_t) { const int e = tid - 4 * HW; h_rr = 2 + e / 4; h_cc = (e & 3) < 2 ? (e & 3) : wcols + (e & 3); }
+  // (a tile that ends inside the wavefront: the last two slots of its rows repeat the halo,
+  // so that the threads past the grid solve defined faces)
+  int h_pad = 0;
+  if (tid >= 4 * HW && wcols < TJ && h_cc > 1 && TJ + (tid & 3) > wcols + 3) h_pad = TJ + (tid & 3);
+  const int h_ii = i0 + h_rr - 2;
+  const bool h_gh = h_ii < 0 || h_ii >= g.nr;
+  const size_t h_off = (size_t)min(max(h_ii, 0), g.nr - 1) * g.nth + (j0 + h_cc - 2 + g.nth) % g.nth;
+  auto halo_fetch = [&](int k, Raw& R) {
+#pragma unroll
+    for (int f = 0; f < 3; ++f) R.m[f] = at_plane(vin + (size_t)f * g.N + (size_t)k * plane, h_off);
+    R.rd = at_plane(din + (size_t)k * plane, h_off);
+  };
+  auto halo_store = [&](int k, const Raw& R) {
+    double w[NG];
+    if (h_gh) {
+      const int side = h_ii < 0 ? 0 : 1, layer = min(h_ii < 0 ? -1 - h_ii : h_ii - g.nr, 1);
+      const double* gt = a.t.ghr + ((size_t)(side * 2 + layer) * g.nz + k) * g.nf + F0;
+#pragma unroll
+      for (int f = 0; f < NG; ++f) w[f] = gt[f];
+    } else {
+      form(R, P32 ? s_v0[k & 3][h_rr] : 0.0, w);
+    }
+#pragma unroll
+    for (int f = 0; f < NG; ++f) s_pl[f][h_rr][h_cc] = w[f];
+    if (h_pad) {
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_pl[f][h_rr][h_pad] = w[f];
+    }
+  };
+
+  using DR = std::integral_constant<int, 0>;
+  using DT = std::integral_constant<int, 1>;
+  using DZ = std::integral_constant<int, 2>;
+  double ledger = 0.0, vmax2 = 0.0;
+
+  // column: the cell above the current plane (rp), the flux of the z face below; the
+  // current cell goes to the staged plane, the one below to its LDS slot
+  double rp[NG], fzlo[NG];
+  if (tab_t) tab_store(k0, tab_load(k0));
+  for (int p = k0; p < k0 + 3; ++p)
+    if (v0_t) tab_store(p - 2, tab_load(p - 2));
+  {
+    Raw R;
+    double r0[NG];
+    const ctab wc = to_ctab(a.t.wc) + (size_t)igc * WB_N + WB_V;
+    auto vc = [&](int k) { return P32 ? wc[(size_t)min(max(k, 0), g.nz - 1) * g.nr * WB_N] : 0.0; };
+    if (!twod) {
+      double e2[NG], rm[NG];
+      col_fetch(vin, din, k0 - 2, R); col_form(k0 - 2, R, vc(k0 - 2), e2);
+      col_fetch(vin, din, k0 - 1, R); col_form(k0 - 1, R, vc(k0 - 1), rm);
+      col_fetch(vin, din, k0, R); col_form(k0, R, vc(k0), r0);
+      col_fetch(vin, din, k0 + 1, R); col_form(k0 + 1, R, vc(k0 + 1), rp);
+      auto get = [&](int c, int f) { return c == 0 ? e2[f] : c == 1 ? rm[f] : c == 2 ? r0[f] : rp[f]; };
+      dust_face<DZ::value>(recc, get, nullptr, nullptr, fzlo, st);
+      if (a.second && k0 == 0 && act) ledger -= rt[RT_AZ] * fzlo[3];
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_rm[f][tid] = rm[f];
+    } else {
+      col_fetch(vin, din, 0, R); col_form(0, R, vc(0), r0);
+#pragma unroll
+      for (int f = 0; f < NG; ++f) { rp[f] = 0.0; fzlo[f] = 0.0; }
+    }
+    if (centre) {
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_pl[f][ti + 2][tj + 2] = r0[f];
+    }
+    if (P32) __syncthreads();  // the velocity tables, with which the halo is formed
+    if (halo_t) {
+      halo_fetch(k0, R);
+      halo_store(k0, R);
+    }
+  }
+  const double dt = a.dt_idx >= 0 ? a.c.dtlog[a.dt_idx] : 0.0;
+  // the parabola weights of the r face above the row (and below it, for the tile's edge)
+  auto weights = [&](int i) { return rco + (size_t)(min(max(i, -1), g.nr) + 1) * RC_N; };
+
+  for (int k = k0; k < k1; ++k) {
+    const bool more = k + 1 < k1;
+    __syncthreads();
+    // the column's cell k+2 and the next plane's halo
+    Raw nraw, hraw;
+    double tab_next = 0.0;
+    if (!twod) col_fetch(vin, din, k + 2, nraw);
+    if (more) {
+      if (halo_t) halo_fetch(k + 1, hraw);
+      if (tab_t || v0_t) tab_next = tab_load(k + 1);
+    }
+    // ---- theta face j+1/2
+    {
+      auto get = [&](int c, int f) { return s_pl[f][ti + 2][tj + 1 + c]; };
+      double F[NG];
+      dust_face<DT::value>(recc, get, nullptr, nullptr, F, st);
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_ft[f][ti][tj + 1] = F[f];
+    }
+    // the update's base of this cell and the gas state its drag needs (raw stored values);
+    // stage 1 of the FP32 layout has its base in the staged plane
+    const bool upd = a.mode == MODE_UPDATE && act;
+    const bool base_r0 = P32 && a.base == a.in;
+    Raw base;
+    VT pg[5];
+    if (upd && !base_r0) col_fetch(vel_of(a.base), den_of(a.base), k, base);
+    if (drag) {
+#pragma unroll
+      for (int f = 0; f < 5; ++f)
+        pg[f] = at_row((const VT*)a.in + (size_t)f * g.N + (size_t)k * plane + row0, jl);
+    }
+    // ---- r face i+1/2
+    {
+      auto get = [&](int c, int f) { return s_pl[f][ti + 1 + c][tj + 2]; };
+      double F[NG];
+      dust_face<DR::value>(recc, get, weights(ig), weights(ig + 1), F, st);
+      if (a.second && act && ig == g.nr - 1) ledger += ar[igc + 1] * F[3];
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_fr[f][ti + 1][tj] = F[f];
+    }
+    // ---- lower-edge faces of the tile: r face i0-1/2 (threads 0..63) and theta face
+    //      j0-1/2 of each row (threads 64..71)
+    if (tid < TJ) {
+      auto get = [&](int c, int f) { return s_pl[f][c][tid + 2]; };
+      double F[NG];
+      dust_face<DR::value>(recc, get, weights(i0 - 1), weights(i0), F, st);
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_fr[f][0][tid] = F[f];
+      if (a.second && i0 == 0 && j0 + tid < g.nth) ledger -= ar[0] * F[3];
+    } else if (tid < TJ + TM) {
+      const int row = tid - TJ;
+      auto get = [&](int c, int f) { return s_pl[f][row + 2][c]; };
+      double F[NG];
+      dust_face<DT::value>(recc, get, nullptr, nullptr, F, st);
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_ft[f][row][0] = F[f];
+    }
+    // ---- z face k+1/2
+    double rn[NG], dz[NG];
+    if (!twod) {
+      double fzhi[NG];
+      col_form(k + 2, nraw, P32 ? s_v0[(k + 2) & 3][ti + 2] : 0.0, rn);
+      auto get = [&](int c, int f) {
+        return c == 0 ? s_rm[f][tid] : c == 1 ? s_pl[f][ti + 2][tj + 2] : c == 2 ? rp[f] : rn[f];
+      };
+      dust_face<DZ::value>(recc, get, nullptr, nullptr, fzhi, st);
+      if (a.second && act && k == g.nz - 1) ledger += rt[RT_AZ] * fzhi[3];
+#pragma unroll
+      for (int f = 0; f < NG; ++f) {
+        dz[f] = rt[RT_AZ] * (fzhi[f] - fzlo[f]);
+        fzlo[f] = fzhi[f];
+      }
+    } else {
+#pragma unroll
+      for (int f = 0; f < NG; ++f) { rn[f] = 0.0; dz[f] = 0.0; }
+    }
+    // (the entries it replaces were last read before this plane's first barrier)
+    if (more) tab_store(k + 1, tab_next);
+    __syncthreads();
+    if (halo_t && more) halo_store(k + 1, hraw);
+    // ---- divergence -sum_s A_s F.n_s (Sect. 2.2), sources (App. B), drag (Sect. 2.9)
+    double r0[NG];
+#pragma unroll
+    for (int f = 0; f < NG; ++f) r0[f] = s_pl[f][ti + 2][tj + 2];
+    const double* bgc = &s_tab[k & 1][ti * 5];
+    const double gr = s_tab[k & 1][TM * 5 + ti * 2], gz = s_tab[k & 1][TM * 5 + ti * 2 + 1];
+    const double v0 = P32 ? s_v0[k & 3][ti + 2] : 0.0;
+    const double invrc = rt[RT_INVRC];
+    const double rd = r0[3], ud = r0[0], vd = r0[1], wd = r0[2];
+    double fx = 0.0, fy = 0.0, fz = 0.0;
+    if (drag) {
+      double q[5];
+#pragma unroll
+      for (int f = 0; f < 5; ++f) q[f] = bgc[f] + (double)pg[f];
+      const double inv = 1.0 / q[4];
+      const double u = q[0] * inv, v = q[1] * inv, w = q[2] * inv;
+      const double pq = (EXT && g.drag_law)
+          ? (g.gamma - 1.0) * (q[3] - 0.5 * (q[0] * u + q[1] * v + q[2] * w)) : 0.0;
+      const double its = inv_tstop<EXT>(g, species, rt[RT_OMK], q[4], pq);
+      fx = rd * (ud - u) * its;
+      fy = rd * (vd - v) * its;
+      fz = rd * (wd - w) * its;
+    }
+    double S[NG];
+    S[0] = (rd * vd * vd) * invrc + rd * gr - fx;
+    S[1] = -(rd * ud * vd) * invrc - fy;
+    S[2] = rd * gz - fz;
+    S[3] = 0.0;
+    // indirect gravity (Sect. 2.10): minus the star's acceleration by the disc
+    if (EXT && g.indirect) {
+      const double A = a.t.indab[0], B = a.t.indab[1];
+      const double cs = a.t.trig[j0 + jl], sn = a.t.trig[g.nth + j0 + jl];
+      S[0] += rd * (-g.GM * (A * cs + B * sn));
+      S[1] += rd * (-g.GM * (B * cs - A * sn));
+    }
+    double Gt[NG];
+#pragma unroll
+    for (int f = 0; f < NG; ++f) {
+      const double dr = ar[igc + 1] * s_fr[f][ti + 1][tj] - ar[igc] * s_fr[f][ti][tj];
+      const double dth = rt[RT_ATH] * (s_ft[f][ti][tj + 1] - s_ft[f][ti][tj]);
+      Gt[f] = fma(S[f], rt[RT_V], -((dr + dth) + dz[f]));
+    }
+    if (a.mode == MODE_OPER) {
+      if (act) {
+#pragma unroll
+        for (int f = 0; f < NG; ++f)
+          at_row((VT*)a.out + (size_t)(F0 + f) * g.N + (size_t)k * plane + row0, jl) = (VT)Gt[f];
+      }
+    } else if (act) {
+      // all loads before any store (the second stage updates in place)
+      double nv[NG];
+      const double cdt = a.coef * dt * rt[RT_INVV];
+      if (base_r0) {
+        // density times (stored velocity deviation + stationary velocity), the stored
+        // deviation being zero where the density is not positive
+        nv[0] = rd * ud;
+        nv[1] = rd * (rd > 0.0 ? vd : v0);
+        nv[2] = rd * wd;
+        nv[3] = rd;
+      } else if constexpr (P32) {
+        nv[0] = base.rd * (double)base.m[0];
+        nv[1] = base.rd * (v0 + (double)base.m[1]);
+        nv[2] = base.rd * (double)base.m[2];
+        nv[3] = base.rd;
+      } else {
+#pragma unroll
+        for (int f = 0; f < 3; ++f) nv[f] = base.m[f];
+        nv[3] = base.rd;
+      }
+#pragma unroll
+      for (int f = 0; f < NG; ++f) nv[f] = fma(cdt, Gt[f], nv[f]);
+      VT* vo = const_cast<VT*>(vel_of(a.out)) + (size_t)k * plane + row0;
+      at_row(const_cast<double*>(den_of(a.out)) + (size_t)k * plane + row0, jl) = nv[3];
+      if constexpr (P32) {
+        // velocity deviations formed with the new density (zero where it vanishes)
+        const bool full = nv[3] > 1e-300;
+        const double ir = full ? frcp(nv[3]) : 0.0;
+        at_row(vo, jl) = full ? (float)(nv[0] * ir) : 0.0f;
+        at_row(vo + g.N, jl) = full ? (float)(nv[1] * ir - v0) : 0.0f;
+        at_row(vo + 2 * g.N, jl) = full ? (float)(nv[2] * ir) : 0.0f;
+      } else {
+#pragma unroll
+        for (int f = 0; f < 3; ++f) at_row(vo + (size_t)f * g.N, jl) = nv[f];
+      }
+      if (a.second && nv[3] < 0.0) {
+        st.negd++;
+      } else if (a.second && nv[3] > 0.0) {
+        const double id = 1.0 / nv[3];
+        const double a1 = nv[0] * id, a2 = nv[1] * id, a3 = nv[2] * id;
+        vmax2 = fmax(vmax2, a1 * a1 + a2 * a2 + a3 * a3);
+      }
+    }
+    // ---- shift the column
+    if (more) {
+#pragma unroll
+      for (int f = 0; f < NG; ++f) {
+        s_rm[f][tid] = r0[f];
+        if (centre) s_pl[f][ti + 2][tj + 2] = rp[f];
+        rp[f] = rn[f];
+      }
+    }
+  }
+
+  // ---- block reductions: counters, CFL partial, boundary outflow partial
+  const int wv = tid / 64, ln = tid & 63;
+  const int nf = wave_isum(st.fall), nd = wave_isum(st.negd);
+  if (ln == 0) {
+    if (nd) atomicAdd(&a.c.ctrl->nnegd, (unsigned long long)nd);
+    if (nf) atomicAdd(&a.c.ctrl->nfall, (unsigned long long)nf);
+  }
+  if (a.second && a.mode == MODE_UPDATE) {
+    // the CFL bound of the thread's row decreases with the speed: the largest one's
+    const double smax = sqrt(vmax2);
+    const double m = wave_min(smax > 0.0 ? g.cfl * rt[RT_V] / (smax * rt[RT_MAXA]) : 1e300);
+    const double ls = wave_sum(ledger);
+    if (ln == 0) { s_red[wv][0] = m; s_red[wv][1] = ls; }
+    __syncthreads();
+    if (tid == 0) {
+      double mm = s_red[0][0], lsum = s_red[0][1];
+      for (int w2 = 1; w2 < NTM / 64; ++w2) {
+        mm = fmin(mm, s_red[w2][0]);
+        lsum += s_red[w2][1];
+      }
       a.c.cflp[(size_t)blockIdx.x * 5 + slot] = mm;
       a.c.outp[(size_t)blockIdx.x * 5 + slot] = lsum;
-      if (EXT && GAS && g.drag_law) a.c.tsp[blockIdx.x] = tmm;
     }
   }
 }
@@ -924,8 +1197,8 @@ __global__ void __launch_bounds__(256) k_drag(StageArgs a, void* state, double f
 }
 
 // final reduction after a step: next dt (CFL), stiffness check, boundary outflow ledger
-__global__ void __launch_bounds__(256) k_reduce(StageArgs a, int nparts, int dt_next, int want_dt,
-                                                int want_ledger) {
+__global__ void __launch_bounds__(256) k_reduce(StageArgs a, int nparts, int nparts_dust, int dt_next,
+                                                int want_dt, int want_ledger) {
   __shared__ double s_m[4];
   __shared__ double s_ts[4];
   __shared__ double s_l[4][5];
@@ -937,16 +1210,21 @@ __global__ void __launch_bounds__(256) k_reduce(StageArgs a, int nparts, int dt_
   double l[5] = {0, 0, 0, 0, 0};
   const bool dyn_ts = a.g.drag_law && a.g.nd > 0;
   // fixed partition and order: deterministic sums
-  // stage partials: [nparts][5] (gas, dust species); standalone CFL: [nparts]
-  const int per = want_ledger ? 1 + a.g.nd : 1;
+  // stage partials: [block][5] (gas, dust species); standalone CFL: [nparts]
+  const int stride = want_ledger ? 5 : 1;
   for (int b = threadIdx.x; b < nparts; b += blockDim.x) {
     if (dyn_ts) tsm = fmin(tsm, a.c.tsp[b]);
-    if (want_dt)
-      for (int s = 0; s < per; ++s) m = fmin(m, a.c.cflp[want_ledger ? (size_t)b * 5 + s : b]);
-    if (want_ledger)
-#pragma unroll
-      for (int s = 0; s < 5; ++s) l[s] += a.c.outp[(size_t)b * 5 + s];
+    if (want_dt) m = fmin(m, a.c.cflp[(size_t)b * stride]);
+    if (want_ledger) l[0] += a.c.outp[(size_t)b * 5];
   }
+  if (want_ledger)
+    for (int b = threadIdx.x; b < nparts_dust; b += blockDim.x)
+#pragma unroll
+      for (int s = 1; s < 5; ++s)
+        if (s <= a.g.nd) {
+          if (want_dt) m = fmin(m, a.c.cflp[(size_t)b * 5 + s]);
+          l[s] += a.c.outp[(size_t)b * 5 + s];
+        }
   m = wave_min(m);
   tsm = wave_min(tsm);
 #pragma unroll
@@ -1513,52 +1791,56 @@ hipError_t launch_init_state(const InitArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int ND, bool P32, bool EXT>
-static void group_nd3(const StageArgs& a, int blocks, int group, hipStream_t s) {
-  if (group == 0) {
-    if (a.g.gamma == 1.4)
-      hipLaunchKernelGGL((k_march<true, ND, true, P32, EXT>), dim3(blocks), dim3(NTM), 0, s, a, 0);
-    else
-      hipLaunchKernelGGL((k_march<true, ND, false, P32, EXT>), dim3(blocks), dim3(NTM), 0, s, a, 0);
-  } else {
-    hipLaunchKernelGGL((k_march<false, ND, true, P32, EXT>), dim3(blocks), dim3(NTM), 0, s, a,
-                       group - 1);
-  }
-}
-
 // the optional physics (indirect gravity, drag law 1) and boundary options (damping zones,
 // outflow ghosts) run in their own instantiation; the base one compiles them out
 static bool uses_ext(const Geo& g) { return g.indirect || g.damp || g.bc_z == 1 || g.drag_law; }
 
-template <int ND, bool P32>
-static void group_nd2(const StageArgs& a, int blocks, int group, hipStream_t s) {
-  if (uses_ext(a.g)) group_nd3<ND, P32, true>(a, blocks, group, s);
-  else group_nd3<ND, P32, false>(a, blocks, group, s);
+template <int ND, bool P32, bool EXT>
+static void gas_ext(const StageArgs& a, int blocks, hipStream_t s) {
+  // (the FP32-perturbation form is specialised to gamma = 7/5)
+  if (P32 || a.g.gamma == 1.4)
+    hipLaunchKernelGGL((k_gas<ND, true, P32, EXT>), dim3(blocks), dim3(NTM), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_gas<ND, P32, P32, EXT>), dim3(blocks), dim3(NTM), 0, s, a);
 }
-
 template <int ND>
-static void group_nd(const StageArgs& a, int blocks, int group, hipStream_t s) {
-  if (a.g.p32) group_nd2<ND, true>(a, blocks, group, s);
-  else group_nd2<ND, false>(a, blocks, group, s);
+static void gas_nd(const StageArgs& a, int blocks, hipStream_t s) {
+  const bool ext = uses_ext(a.g);
+  if (a.g.p32) {
+    if (ext) gas_ext<ND, true, true>(a, blocks, s);
+    else gas_ext<ND, true, false>(a, blocks, s);
+  } else {
+    if (ext) gas_ext<ND, false, true>(a, blocks, s);
+    else gas_ext<ND, false, false>(a, blocks, s);
+  }
 }
 
-hipError_t launch_stage_group(const StageArgs& a, int blocks, int group, hipStream_t s) {
+hipError_t launch_stage_group(const StageArgs& a, const Layout& L, int group, hipStream_t s) {
+  if (group > 0) {
+    const dim3 blocks(L.nblocks_dust), threads(NTM);
+    const bool ext = uses_ext(a.g);
+    if (a.g.p32 && ext) hipLaunchKernelGGL((k_dust<true, true>), blocks, threads, 0, s, a, group - 1);
+    else if (a.g.p32) hipLaunchKernelGGL((k_dust<true, false>), blocks, threads, 0, s, a, group - 1);
+    else if (ext) hipLaunchKernelGGL((k_dust<false, true>), blocks, threads, 0, s, a, group - 1);
+    else hipLaunchKernelGGL((k_dust<false, false>), blocks, threads, 0, s, a, group - 1);
+    return hipGetLastError();
+  }
   switch (a.g.nd) {
-    case 0: group_nd<0>(a, blocks, group, s); break;
-    case 1: group_nd<1>(a, blocks, group, s); break;
-    case 2: group_nd<2>(a, blocks, group, s); break;
-    case 3: group_nd<3>(a, blocks, group, s); break;
-    case 4: group_nd<4>(a, blocks, group, s); break;
+    case 0: gas_nd<0>(a, L.nblocks, s); break;
+    case 1: gas_nd<1>(a, L.nblocks, s); break;
+    case 2: gas_nd<2>(a, L.nblocks, s); break;
+    case 3: gas_nd<3>(a, L.nblocks, s); break;
+    case 4: gas_nd<4>(a, L.nblocks, s); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-hipError_t launch_stage(const StageArgs& a, int blocks, hipStream_t s) {
-  hipError_t e = launch_stage_group(a, blocks, 0, s);
+hipError_t launch_stage(const StageArgs& a, const Layout& L, hipStream_t s) {
+  hipError_t e = launch_stage_group(a, L, 0, s);
   if (e != hipSuccess || a.gas_only) return e;
   for (int sp = 0; sp < a.g.nd; ++sp) {
-    e = launch_stage_group(a, blocks, 1 + sp, s);
+    e = launch_stage_group(a, L, 1 + sp, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -1601,10 +1883,10 @@ hipError_t launch_drag(const StageArgs& a, void* state, double frac, int blocks,
   return hipGetLastError();
 }
 
-hipError_t launch_reduce(const StageArgs& a, int nparts, int dt_idx_next, int want_dt,
-                         int want_ledger, hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce, dim3(1), dim3(256), 0, s, a, nparts, dt_idx_next, want_dt,
-                     want_ledger);
+hipError_t launch_reduce(const StageArgs& a, int nparts, int nparts_dust, int dt_idx_next,
+                         int want_dt, int want_ledger, hipStream_t s) {
+  hipLaunchKernelGGL(k_reduce, dim3(1), dim3(256), 0, s, a, nparts, nparts_dust, dt_idx_next,
+                     want_dt, want_ledger);
   return hipGetLastError();
 }
 
