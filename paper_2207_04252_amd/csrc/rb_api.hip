@@ -121,8 +121,8 @@ bool validate(const rb_config* c, std::string* why) {
   return true;
 }
 
-// z planes per block of a stage kernel of which `per_cu` workgroups fill a CU (the gas one:
-// at most 256 VGPRs per lane, two waves per SIMD; the dust one: 128, four).  A launch runs in
+// z planes per block of a stage kernel of which `per_cu` workgroups fill a CU (the FP64 gas
+// one: at most 256 VGPRs per lane, two waves per SIMD; the others: 128, four).  A launch runs in
 // ceil(blocks / (256 per_cu)) rounds on the 256 CUs of an MI355X; a block marches tk planes
 // plus about 1.5 planes of set-up (initial column, first z face).  Takes the chunk length
 // with the fewest plane-times.
@@ -172,6 +172,11 @@ Layout make_layout(const rb_config& c) {
   L.wc = take(nz * nr * WB_N);
   L.wr = take(nz * (nr + 1) * WB_N);
   L.wz = take((nz + 1) * nr * WB_N);
+  const size_t pf = c.precision == RB_FP32_PERT ? PF_N / 2 : 0;
+  L.pc = take(nz * nr * pf);
+  L.pr = take(nz * (nr + 1) * pf);
+  L.pz = take((nz + 1) * nr * pf);
+  L.rcf = take(pf ? (nr + 2) * RC_N / 2 : 0);
   L.r0 = take(nz * nr * 5);
   L.grav = take(nz * nr * 2);
   L.ghr = take(4 * nz * nf);
@@ -231,6 +236,8 @@ StageArgs base_args(rb_ctx* x) {
   a.t.wc = w + L.wc; a.t.wr = w + L.wr; a.t.wz = w + L.wz;
   a.t.ghr = w + L.ghr; a.t.ghrw = w + L.ghrw; a.t.ghz = w + L.ghz; a.t.ghzw = w + L.ghzw;
   a.t.trig = w + L.trig; a.t.indw = w + L.indw; a.t.indab = w + L.indab;
+  a.t.pc = w + L.pc; a.t.pr = w + L.pr; a.t.pz = w + L.pz;
+  a.t.rcf = (const float*)(w + L.rcf);
   a.t.damp = w + L.damp;
   a.t.ozr = w + L.ozr;
   a.c.ctrl = reinterpret_cast<Ctrl*>(w + L.ctrl);

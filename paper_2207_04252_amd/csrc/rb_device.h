@@ -55,14 +55,14 @@ __device__ __forceinline__ T inc_lo_u(T em, T e0, T ep) {
   return minmod3<T, SEL>(-(fma(T(3), dm, dp) * T(0.125)), -dm, -dp);
 }
 // Non-uniform r: precomputed parabola weights and limiter bounds of the cell.
-template <class T, bool SEL = false>
-__device__ __forceinline__ T inc_up_c(T em, T e0, T ep, const double* co) {
+template <class T, bool SEL = false, class Co = const double*>
+__device__ __forceinline__ T inc_up_c(T em, T e0, T ep, Co co) {
   T dm = e0 - em, dp = ep - e0;
   return minmod3<T, SEL>(fma(T(co[RC_WPP]), dp, T(co[RC_WPM]) * dm), T(co[RC_LPM]) * dm,
                          T(co[RC_LPP]) * dp);
 }
-template <class T, bool SEL = false>
-__device__ __forceinline__ T inc_lo_c(T em, T e0, T ep, const double* co) {
+template <class T, bool SEL = false, class Co = const double*>
+__device__ __forceinline__ T inc_lo_c(T em, T e0, T ep, Co co) {
   T dm = e0 - em, dp = ep - e0;
   return minmod3<T, SEL>(fma(T(co[RC_WMP]), dp, T(co[RC_WMM]) * dm), T(co[RC_LMM]) * dm,
                          T(co[RC_LMP]) * dp);
@@ -591,66 +591,38 @@ __device__ __forceinline__ void dust_face(const RecC& rc, Cell cell, Co coB, Co 
 
 namespace rb {
 
-// FP32-perturbation gas face: reconstructed W' about the face's stationary flow, the
-// perturbation Riemann problem and the flux change dF = F* - F(W0); faces the FP32 form
-// cannot take (strong perturbation, transonic fan, no convergence, non-positive face
-// state) are re-solved in FP64 on the full states.
-template <int DIR>
-__device__ __forceinline__ void gas_face_p32(const GasC& c, const float* wA, const float* wB,
-                                             const float* wC, const float* wD, const double* coB,
-                                             const double* coC, const double* bf,
-                                             const double* bB, const double* bC, float F[5],
-                                             TStat& st) {
-  float qL[5], qR[5];
+// Reconstructed FP32 face states (W' of the gas, field slots) between cells B and C;
+// cell(c, f) as dust_face's.
+template <int DIR, class Cell, class Co>
+__device__ __forceinline__ void recon32(Cell cell, Co coB, Co coC, float qL[5], float qR[5]) {
 #pragma unroll
   for (int f = 0; f < 5; ++f) {
-    float iB, iC;
-    if (DIR == 0) {
-      iB = inc_up_c<float>(wA[f], wB[f], wC[f], coB);
-      iC = inc_lo_c<float>(wB[f], wC[f], wD[f], coC);
+    const float A = cell(0, f), B = cell(1, f), C = cell(2, f), D = cell(3, f);
+    if constexpr (DIR == 0) {
+      qL[f] = B + inc_up_c<float>(A, B, C, coB);
+      qR[f] = C + inc_lo_c<float>(B, C, D, coC);
     } else {
-      iB = inc_up_u<float>(wA[f], wB[f], wC[f]);
-      iC = inc_lo_u<float>(wB[f], wC[f], wD[f]);
+      qL[f] = B + inc_up_u<float>(A, B, C);
+      qR[f] = C + inc_lo_u<float>(B, C, D);
     }
-    qL[f] = wB[f] + iB;
-    qR[f] = wC[f] + iC;
   }
-  constexpr int N = Dirs<DIR>::n, T1 = Dirs<DIR>::t1, T2 = Dirs<DIR>::t2;
-  const BgW b = bg_face<DIR>(bf);
-  const PW L = {qL[4], qL[N], qL[T1], qL[T2], qL[3]};
-  const PW R = {qR[4], qR[N], qR[T1], qR[T2], qR[3]};
-  const bool okL = (b.rho + (double)L.rho > 0.0) && (b.p + (double)L.p > 0.0);
-  const bool okR = (b.rho + (double)R.rho > 0.0) && (b.p + (double)R.p > 0.0);
-  PW W;
-  float fl[5];
-  if (okL && okR && riemann_pert(b, L, R, c, W, st)) {
-    flux_pert(b, W, (float)c.inv_gm1, fl);
-  } else {
-    st.resolve++;
-    double xL[5], xR[5];
-#pragma unroll
-    for (int f = 0; f < 5; ++f) {
-      xL[f] = okL ? bf[f] + (double)qL[f] : bB[f] + (double)wB[f];
-      xR[f] = okR ? bf[f] + (double)qR[f] : bC[f] + (double)wC[f];
-    }
-    if (!okL) st.fall++;
-    if (!okR) st.fall++;
-    double f64[5];
-    gas_riemann<true>(c, xL[4], frcp(xL[4]), xL[N], xL[T1], xL[T2], xL[3], xR[4], frcp(xR[4]),
-                      xR[N], xR[T1], xR[T2], xR[3], f64, st);
-    const double m0 = b.rho * b.un;
-    fl[0] = (float)(f64[0] - m0);
-    fl[1] = (float)(f64[1] - (m0 * b.un + b.p));
-    fl[2] = (float)(f64[2] - m0 * b.t1);
-    fl[3] = (float)(f64[3] - m0 * b.t2);
-    fl[4] = (float)(f64[4] - b.h * b.un);
-  }
-  F[4] = fl[0];
-  F[N] = fl[1];
-  F[T1] = fl[2];
-  F[T2] = fl[3];
-  F[3] = fl[4];
 }
+
+// A face of the FP32-perturbation form that the short form (gas_face32) does not take: the
+// W' of its stencil cells A, B | C, D (field slots).
+struct Face32 {
+  float A[5], B[5], C[5], D[5];
+};
+struct Face32Out {
+  float F[5];                        // flux change, field slots
+  int last, maxit;                   // Newton iterations of the solve kept; the most of any
+  unsigned fall, vac, resolve, noconv;
+};
+// the same counts of a workgroup
+struct Gas32Count {
+  unsigned fall, vac, resolve;
+  int noconv, pad;
+};
 
 // ------------------------------------------------------------------------------------
 // addressing of a wavefront's row
@@ -659,6 +631,9 @@ __device__ __forceinline__ void gas_face_p32(const GasC& c, const float* wA, con
 // every lane of a wavefront.  Only tables that no kernel writes while the reading one runs.
 using ctab = const __attribute__((address_space(4))) double*;
 __device__ __forceinline__ ctab to_ctab(const double* p) { return (ctab)(uintptr_t)p; }
+
+using ctabf = const __attribute__((address_space(4))) float*;
+__device__ __forceinline__ ctabf to_ctabf(const float* p) { return (ctabf)(uintptr_t)p; }
 
 // Element at a lane's index from a pointer that is the same in the whole wavefront.  The
 // pointer passes through a scalar register the optimiser cannot see through: otherwise it
@@ -770,6 +745,19 @@ __device__ __forceinline__ void cell_w(const float* e, const double* b, float gm
   const float u0sq = (float)(b[WB_U] * b[WB_U] + b[WB_V] * b[WB_V] + b[WB_W] * b[WB_W]);
   const float up = (e[0] - u0 * rp) * ir, vp = (e[1] - v0 * rp) * ir, wp = (e[2] - w0 * rp) * ir;
   const float dke = 0.5f * rp * u0sq + rho * (u0 * up + v0 * vp + w0 * wp) +
+                    0.5f * rho * (up * up + vp * vp + wp * wp);
+  w[0] = up; w[1] = vp; w[2] = wp;
+  w[3] = gm1 * (e[3] - dke);
+  w[4] = rp;
+}
+
+// The same in FP32 from the first four PF_N entries of the cell.
+__device__ __forceinline__ void cell_w32(const float* e, const float* c, float gm1, float* w) {
+  const float rp = e[4];
+  const float rho = c[PF_RHO] + (rp + c[PF_RLO]);
+  const float ir = rcp32(rho);
+  const float up = e[0] * ir, vp = (e[1] - c[PF_V] * rp) * ir, wp = e[2] * ir;
+  const float dke = 0.5f * rp * c[PF_VSQ] + rho * (c[PF_V] * vp) +
                     0.5f * rho * (up * up + vp * vp + wp * wp);
   w[0] = up; w[1] = vp; w[2] = wp;
   w[3] = gm1 * (e[3] - dke);
@@ -920,54 +908,6 @@ __device__ __forceinline__ void dust_fetch(const StageArgs& a, const void* st, i
     }
   }
 }
-// The same two steps for a gas cell in the FP32-perturbation layout (base boundary
-// options): the stored deviations e and the cell's stationary density and azimuthal
-// velocity (the form runs on the disc background, whose stationary flow has no radial or
-// vertical velocity).  Ghost cells (tiles at the radial boundaries, the last planes) are
-// formed at once.
-struct GasRaw32 {
-  double rho0, v0;
-  float e[5];
-  bool ghost;
-};
-__device__ __forceinline__ void gas_fetch32(const StageArgs& a, const void* st, int k, int i, int j,
-                                            GasRaw32& R) {
-  const Geo& g = a.g;
-  const double* gt = nullptr;
-  if (k < 0 || k >= g.nz) {
-    const int ii = min(max(i, 0), g.nr - 1);
-    const int side = k < 0 ? 0 : 1;
-    const int layer = min(k < 0 ? -1 - k : k - g.nz, 1);
-    gt = a.t.ghz + ((size_t)(side * 2 + layer) * g.nr + ii) * g.nf;
-  } else if (i < 0 || i >= g.nr) {
-    const int side = i < 0 ? 0 : 1;
-    const int layer = min(i < 0 ? -1 - i : i - g.nr, 1);
-    gt = a.t.ghr + ((size_t)(side * 2 + layer) * g.nz + k) * g.nf;
-  }
-  R.ghost = gt != nullptr;
-  if (gt) {
-#pragma unroll
-    for (int f = 0; f < 5; ++f) R.e[f] = (float)gt[f];
-  } else {
-    const size_t cell = ((size_t)k * g.nr + i) * g.nth + j;
-    const double* bw = a.t.wc + ((size_t)k * g.nr + i) * WB_N;
-#pragma unroll
-    for (int f = 0; f < 5; ++f) R.e[f] = ((const float*)st)[(size_t)f * g.N + cell];
-    R.rho0 = bw[WB_RHO];
-    R.v0 = bw[WB_V];
-  }
-}
-__device__ __forceinline__ void gas_finish32(const GasRaw32& R, float gm1, float* out) {
-  double bw[WB_N];
-  bw[WB_RHO] = R.rho0;
-  bw[WB_U] = 0.0;
-  bw[WB_V] = R.v0;
-  bw[WB_W] = 0.0;
-  float w[5];
-  cell_w(R.e, bw, gm1, w);
-#pragma unroll
-  for (int f = 0; f < 5; ++f) out[f] = R.ghost ? R.e[f] : w[f];
-}
 template <bool P32>
 __device__ __forceinline__ void dust_finish(const DustRaw<P32>& R, double* out) {
   const double rd = R.d[3];
@@ -999,6 +939,64 @@ __device__ __forceinline__ const double* bg_ptr(const StageArgs& a, int k, int i
 __device__ __forceinline__ const double* rco_ptr(const StageArgs& a, int i) {
   int c = min(max(i, -1), a.g.nr);
   return a.t.rco + (size_t)(c + 1) * RC_N;
+}
+
+// The perturbation Riemann problem at the face in direction dir above cell (k, i) (below row
+// 0: i = -1); faces it cannot take (strong perturbation, transonic fan, no convergence,
+// non-positive face state) are re-solved in FP64 on the full states.
+__device__ __forceinline__ Face32Out gas_face32_general(const StageArgs& a, int dir, int k, int i,
+                                                        const Face32& q) {
+  const GasC c = gas_consts(1.4, a.g.newton_max);
+  const int N = dir, T1 = dir == 0 ? 1 : 0, T2 = dir == 2 ? 1 : 2;
+  const double* bB = bg_ptr(a, k, i);
+  const double* bC = dir == 1 ? bB : (dir == 0 ? bg_ptr(a, k, i + 1) : bg_ptr(a, k + 1, i));
+  const double* bf = dir == 1 ? bB
+      : (dir == 0 ? a.t.wr + ((size_t)k * (a.g.nr + 1) + min(i + 1, a.g.nr)) * WB_N
+                  : a.t.wz + ((size_t)(k + 1) * a.g.nr + i) * WB_N);
+  float qL[5], qR[5];
+  auto cell = [&](int s, int f) { return s == 0 ? q.A[f] : s == 1 ? q.B[f] : s == 2 ? q.C[f] : q.D[f]; };
+  if (dir == 0) recon32<0>(cell, rco_ptr(a, i), rco_ptr(a, i + 1), qL, qR);
+  else recon32<1>(cell, nullptr, nullptr, qL, qR);
+  TStat st = {0, 0, 0, 0, 0, 0, 0};
+  const BgW b = {bf[WB_RHO], bf[N], bf[T1], bf[T2], bf[WB_P], bf[WB_C], bf[WB_H]};
+  const PW L = {qL[4], qL[N], qL[T1], qL[T2], qL[3]};
+  const PW R = {qR[4], qR[N], qR[T1], qR[T2], qR[3]};
+  const bool okL = (b.rho + (double)L.rho > 0.0) && (b.p + (double)L.p > 0.0);
+  const bool okR = (b.rho + (double)R.rho > 0.0) && (b.p + (double)R.p > 0.0);
+  PW W;
+  float fl[5];
+  if (okL && okR && riemann_pert(b, L, R, c, W, st)) {
+    flux_pert(b, W, (float)c.inv_gm1, fl);
+  } else {
+    st.resolve++;
+    double xL[5], xR[5];
+#pragma unroll
+    for (int f = 0; f < 5; ++f) {
+      xL[f] = okL ? bf[f] + (double)qL[f] : bB[f] + (double)q.B[f];
+      xR[f] = okR ? bf[f] + (double)qR[f] : bC[f] + (double)q.C[f];
+    }
+    if (!okL) st.fall++;
+    if (!okR) st.fall++;
+    double f64[5];
+    gas_riemann<true>(c, xL[4], frcp(xL[4]), xL[N], xL[T1], xL[T2], xL[3], xR[4], frcp(xR[4]),
+                      xR[N], xR[T1], xR[T2], xR[3], f64, st);
+    const double m0 = b.rho * b.un;
+    fl[0] = (float)(f64[0] - m0);
+    fl[1] = (float)(f64[1] - (m0 * b.un + b.p));
+    fl[2] = (float)(f64[2] - m0 * b.t1);
+    fl[3] = (float)(f64[3] - m0 * b.t2);
+    fl[4] = (float)(f64[4] - b.h * b.un);
+  }
+  Face32Out o;
+  o.F[4] = fl[0];
+  o.F[N] = fl[1];
+  o.F[T1] = fl[2];
+  o.F[T2] = fl[3];
+  o.F[3] = fl[4];
+  o.last = st.last;
+  o.maxit = st.maxit;
+  o.fall = st.fall; o.vac = st.vac; o.resolve = st.resolve; o.noconv = st.noconv;
+  return o;
 }
 
 __device__ __forceinline__ double wave_min(double v) {

@@ -12,13 +12,13 @@
 namespace rb {
 
 // ------------------------------------------------------------------------------------
-// the gas stage kernel.  The groups of fields interact only through the cell-local drag,
+// the gas stage kernel (FP64).  The groups of fields interact only through the cell-local drag,
 // which each kernel evaluates from the other group's centre state of the same stage input.
 
-template <int ND, bool G75, bool P32, bool EXT>
+template <int ND, bool G75, bool EXT>
 __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
   constexpr int NG = 5;
-  using T = typename std::conditional<P32, float, double>::type;
+  using T = double;
   // a hard error stops the evolution; the flag is read once and broadcast so that the
   // whole workgroup takes the same branch (other workgroups may set it meanwhile)
   __shared__ int s_stop;
@@ -32,9 +32,8 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
   // FP64 gas: per-thread slots (no sharing) for the column's cell below the current plane
   // and the flux of the z face below, kept in LDS between their uses (without them the
   // face solves spill registers); the other kernels keep both in registers
-  constexpr bool LR = !P32;
-  __shared__ T s_rm[LR ? NG : 1][LR ? NTM : 1];
-  __shared__ T s_fz[LR ? NG : 1][LR ? NTM : 1];
+  __shared__ T s_rm[NG][NTM];
+  __shared__ T s_fz[NG][NTM];
 
   const Geo& g = a.g;
   const GasC gc = gas_consts(g.gamma, g.newton_max);
@@ -126,14 +125,12 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
   const double Arlo = a.t.ar[igc], Arhi = a.t.ar[igc + 1];
   const double Ar0 = a.t.ar[0];  // inner boundary face (ledger)
 
-  // gas face: FP64 full states, or FP32 perturbations about the face background; the
-  // cells' reconstructed variables, the stationary flow at the face (bf) and at the
+  // gas face: the cells' reconstructed variables, the stationary flow at the face (bf) and at the
   // centres of the two cells next to it (bB, bC: the positivity fallback)
   auto face = [&](auto dirc, const T* wA, const T* wB, const T* wC, const T* wD, const double* coB,
                   const double* coC, const double* bf, const double* bB, const double* bC, T* F) {
     constexpr int D = decltype(dirc)::value;
-    if constexpr (P32) gas_face_p32<D>(gc, wA, wB, wC, wD, coB, coC, bf, bB, bC, F, st);
-    else gas_face<D, G75>(gc, wA, wB, wC, wD, coB, coC, bf, bB, bC, F, st);
+    gas_face<D, G75>(gc, wA, wB, wC, wD, coB, coC, bf, bB, bC, F, st);
   };
   using DR = std::integral_constant<int, 0>;
   using DT = std::integral_constant<int, 1>;
@@ -145,25 +142,24 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
   const bool twod = g.twod != 0;
   if (!twod) {
     T e2[NG];
-    load_recon<P32, EXT, NG>(a, in, 0, k0 - 2, ig, jw, e2);
-    load_recon<P32, EXT, NG>(a, in, 0, k0 - 1, ig, jw, rm);
-    load_recon<P32, EXT, NG>(a, in, 0, k0, ig, jw, r0);
-    load_recon<P32, EXT, NG>(a, in, 0, k0 + 1, ig, jw, rp);
+    load_recon<false, EXT, NG>(a, in, 0, k0 - 2, ig, jw, e2);
+    load_recon<false, EXT, NG>(a, in, 0, k0 - 1, ig, jw, rm);
+    load_recon<false, EXT, NG>(a, in, 0, k0, ig, jw, r0);
+    load_recon<false, EXT, NG>(a, in, 0, k0 + 1, ig, jw, rp);
     const double* bf = a.t.wz + ((size_t)k0 * g.nr + igc) * WB_N;
     face(DZ(), e2, rm, r0, rp, nullptr, nullptr, bf, bg_ptr(a, k0 - 1, igc), bg_ptr(a, k0, igc),
          fzlo);
     tally(act && k0 == 0);
     if (a.second && k0 == 0 && act) {
       double fm = (double)fzlo[NG - 1];
-      if (P32) fm += bf[WB_RHO] * bf[WB_W];  // background normal mass flux rho0 w0
       ledger -= Az * fm;
     }
-    if constexpr (LR) {
+    {
 #pragma unroll
       for (int f = 0; f < NG; ++f) { s_rm[f][tslot] = rm[f]; s_fz[f][tslot] = fzlo[f]; }
     }
   } else {
-    load_recon<P32, EXT, NG>(a, in, 0, 0, ig, jw, r0);
+    load_recon<false, EXT, NG>(a, in, 0, 0, ig, jw, r0);
 #pragma unroll
     for (int f = 0; f < NG; ++f) {
       rm[f] = T(0); rp[f] = T(0); rn[f] = T(0); fzlo[f] = T(0); fzhi[f] = T(0);
@@ -171,9 +167,8 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
   }
 
   // the halo ring of the LDS plane: two rows below and above the tile, then two columns
-  // on each side of its rows; slot tid.  PF: the slots of each plane are loaded one plane
-  // ahead, so that their latency hides behind the previous plane's face solves (not in the
-  // FP32-perturbation form, where the held registers cost more than they hide).
+  // on each side of its rows; slot tid, loaded one plane ahead, so that the latency hides
+  // behind the previous plane's face solves
   constexpr int HW = TJ + 4, NHALO = 4 * HW + 4 * TM;
   static_assert(NHALO <= NTM, "one halo cell per thread");
   const bool halo_t = tid < NHALO;
@@ -183,23 +178,8 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
   else if (halo_t) { const int e = tid - 4 * HW; h_rr = 2 + e / 4; h_cc = (e & 3) < 2 ? (e & 3) : TJ + (e & 3); }
   const int h_ii = i0 + h_rr - 2;
   const int h_jj = (j0 + h_cc - 2 + g.nth) % g.nth;
-  constexpr bool PF = !P32;
   T hv[NG];
-  // FP32 form (base boundary options): the column's cell k+2 is fetched raw at the top of a
-  // plane and formed before the z face, so that no wait for it precedes the faces; the next
-  // plane's halo is requested after the second barrier, ahead of the drag's dust loads (one
-  // wait for both), and formed before the update's stores
-  constexpr bool RAWG = P32 && !EXT;
-  const float gm1f = (float)(g.gamma - 1.0);
-  GasRaw32 gnraw, ghraw;
-  if constexpr (RAWG) {
-    if (halo_t) {
-      gas_fetch32(a, in, k0, h_ii, h_jj, ghraw);
-      gas_finish32(ghraw, gm1f, hv);
-    }
-  } else {
-    if (PF && halo_t) load_recon<P32, EXT, NG>(a, in, 0, k0, h_ii, h_jj, hv);
-  }
+  if (halo_t) load_recon<false, EXT, NG>(a, in, 0, k0, h_ii, h_jj, hv);
 
   if (tab_t) s_tab[k0 & 1][tid] = tab_p0[(size_t)k0 * tab_stride];
   // the radial parabola weights and limiter bounds of rows i0-1 .. i0+TM (plane
@@ -213,16 +193,14 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
   __builtin_amdgcn_s_waitcnt(0);
   for (int k = k0; k < k1; ++k) {
     if (!twod) {
-      if constexpr (RAWG) gas_fetch32(a, in, k + 2, ig, jw, gnraw);
-      else load_recon<P32, EXT, NG>(a, in, 0, k + 2, ig, jw, rn);
+      load_recon<false, EXT, NG>(a, in, 0, k + 2, ig, jw, rn);
     }
     const int kb = k & 1;
     double tab_next = 0.0;
     if (tab_t && k + 1 < k1) tab_next = tab_p0[(size_t)(k + 1) * tab_stride];
     // the update's base values of this plane's cell, requested here so that their latency
     // hides behind the face solves (raw stored values: any arithmetic on them here would wait
-    // for the loads).  The FP32 form with the base boundary options requests them after the
-    // second barrier instead, with the drag's loads: held across the faces they would spill
+    // for the loads)
     const size_t cell = ((size_t)k * g.nr + ig) * g.nth + jg;
     const size_t cellw = ((size_t)k * g.nr + igc) * g.nth + jw;
     const bool upd = a.mode == MODE_UPDATE && act;
@@ -233,17 +211,14 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
         for (int f = 0; f < NG; ++f) pb[f] = ((const T*)a.base)[(size_t)f * g.N + cell];
       }
     };
-    if constexpr (!RAWG) load_base();
+    load_base();
     // ---- stage the plane (with halo) in LDS
 #pragma unroll
     for (int f = 0; f < NG; ++f) s_pl[f][ti + 2][tj + 2] = r0[f];
     if (halo_t) {
-      if constexpr (!RAWG) {
-        if (!PF) load_recon<P32, EXT, NG>(a, in, 0, k, h_ii, h_jj, hv);
-      }
 #pragma unroll
       for (int f = 0; f < NG; ++f) s_pl[f][h_rr][h_cc] = hv[f];
-      if (PF && k + 1 < k1) load_recon<P32, EXT, NG>(a, in, 0, k + 1, h_ii, h_jj, hv);
+      if (k + 1 < k1) load_recon<false, EXT, NG>(a, in, 0, k + 1, h_ii, h_jj, hv);
     }
     __syncthreads();
     // ---- theta face j+1/2 and r face i+1/2 of this cell
@@ -273,7 +248,6 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
         tally(act);
         if (a.second && act && ig == g.nr - 1) {
           double fm = (double)F[NG - 1];
-          if (P32) fm += bf[WB_RHO] * bf[WB_U];  // background normal mass flux rho0 u0
           ledger += Arhi * fm;
         }
       }
@@ -300,7 +274,6 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
       for (int f = 0; f < NG; ++f) s_fr[f][0][col] = F[f];
       if (a.second && i0 == 0 && j0 + col < g.nth) {
         double fm = (double)F[NG - 1];
-        if (P32) fm += bf[WB_RHO] * bf[WB_U];
         ledger -= Ar0 * fm;
       }
     } else if (tid < TJ + TM) {
@@ -318,8 +291,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
     }
     // ---- z face k+1/2 from the register ring
     if (!twod) {
-      if constexpr (RAWG) gas_finish32(gnraw, gm1f, rn);
-      if constexpr (LR) {
+      {
 #pragma unroll
         for (int f = 0; f < NG; ++f) rm[f] = s_rm[f][tslot];
       }
@@ -329,7 +301,6 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
       tally(act);
       if (a.second && act && k == g.nz - 1) {
         double fm = (double)fzhi[NG - 1];
-        if (P32) fm += bf[WB_RHO] * bf[WB_W];
         ledger += Az * fm;
       }
     }
@@ -338,17 +309,13 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
     //      (k + 1) & 1 was last read before this plane's first barrier), before this plane's
     //      stores, so that waiting for them waits for no store
     if (tab_t && k + 1 < k1) s_tab[(k + 1) & 1][tid] = tab_next;
-    if constexpr (RAWG) {
-      load_base();
-      if (halo_t && k + 1 < k1) gas_fetch32(a, in, k + 1, h_ii, h_jj, ghraw);
-    }
     // ---- divergence -sum_s A_s F.n_s (Sect. 2.2), sources (App. B), drag (Sect. 2.9)
     T Gd[NG];
 #pragma unroll
     for (int f = 0; f < NG; ++f) {
       T dr = T(Arhi) * s_fr[f][ti + 1][tj] - T(Arlo) * s_fr[f][ti][tj];
       T dth = T(Ath) * (s_ft[f][ti][tj + 1] - s_ft[f][ti][tj]);
-      T dz = twod ? T(0) : T(Az) * (fzhi[f] - (LR ? s_fz[f][tslot] : fzlo[f]));
+      T dz = twod ? T(0) : T(Az) * (fzhi[f] - s_fz[f][tslot]);
       Gd[f] = -((dr + dth) + dz);
     }
     const double gr = s_tab[kb][T_GR + ti * 2 + 0];
@@ -356,56 +323,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
     const double* bgc = &s_tab[kb][T_BG + ti * 5];
     const double* bw = &s_tab[kb][T_WC + ti * WB_N];
     T S[NG];
-    if constexpr (P32) {
-      // source change S(E) - S(E0), every term formed from the perturbations W' (the
-      // stationary flow has no radial or vertical velocity)
-      const float rp = r0[4], up = r0[0], vp = r0[1], wp = r0[2], pp = r0[3];
-      const float v0 = (float)bw[WB_V];
-      const float rho = (float)(bw[WB_RHO] + (double)rp);
-      const float ir = (float)invrc, fgr = (float)gr, fgz = (float)gz;
-      const float dmv2 = rp * (float)(bw[WB_V] * bw[WB_V]) + rho * vp * (2.0f * v0 + vp);
-      S[0] = (dmv2 + pp) * ir + rp * fgr;
-      S[1] = -(rho * up * (v0 + vp)) * ir;
-      S[2] = rp * fgz;
-      S[3] = rho * (up * fgr + wp * fgz);
-      S[4] = 0.0f;
-      if (drag) {
-        const double rg = bw[WB_RHO] + (double)rp;
-        const double u = (double)up, v = bw[WB_V] + (double)vp, w2 = (double)wp;
-        const double pq = (EXT && g.drag_law) ? bw[WB_P] + (double)pp : 0.0;
-        double dx = 0.0, dy = 0.0, dzz = 0.0;
-        // every species' density and velocities requested together (loads made
-        // conditional on the density would each wait for it)
-        double rds[ND > 0 ? ND : 1];
-        float vds[ND > 0 ? ND : 1][3];
-#pragma unroll
-        for (int s2 = 0; s2 < ND; ++s2) {
-          const float* vel = (const float*)in + (size_t)(5 + 3 * s2) * g.N + cellw;
-          rds[s2] = ld_cell<P32>(a, in, 5 + 4 * s2 + 3, k, igc, cellw);
-          vds[s2][0] = vel[0];
-          vds[s2][1] = vel[g.N];
-          vds[s2][2] = vel[2 * (size_t)g.N];
-        }
-#pragma unroll
-        for (int s2 = 0; s2 < ND; ++s2) {
-          // the FP32 layout stores the dust velocities as deviations from the stationary
-          // flow's, as the gas W' is: the velocity difference is formed from the deviations
-          const double rd = rds[s2];
-          const bool full = rd > 0.0;
-          const double dud = full ? (double)vds[s2][0] - (double)up : -u;
-          const double dvd = full ? (double)vds[s2][1] - (double)vp : -v;
-          const double dwd = full ? (double)vds[s2][2] - (double)wp : -w2;
-          const double its = inv_tstop<EXT>(g, s2, omk, rg, pq);
-          dx += rd * dud * its;
-          dy += rd * dvd * its;
-          dzz += rd * dwd * its;
-        }
-        S[0] += (float)dx;
-        S[1] += (float)dy;
-        S[2] += (float)dzz;
-        S[3] += (float)(u * dx + v * dy + w2 * dzz);
-      }
-    } else {
+    {
       // the cell's primitives: stationary flow + W'
       const double rho = bw[WB_RHO] + r0[4];
       const double u = bw[WB_U] + r0[0], v = bw[WB_V] + r0[1], w = bw[WB_W] + r0[2];
@@ -417,12 +335,13 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
       S[4] = 0.0;
       if (drag) {
         double dx = 0.0, dy = 0.0, dzz = 0.0;
-        // every species' variables requested together (see the FP32 branch)
+        // every species' variables requested together (loads made conditional on the
+        // density would each wait for it)
         double dvar[ND > 0 ? ND : 1][4];
 #pragma unroll
         for (int s2 = 0; s2 < ND; ++s2)
 #pragma unroll
-          for (int c = 0; c < 4; ++c) dvar[s2][c] = ld_cell<P32>(a, in, 5 + 4 * s2 + c, k, igc, cellw);
+          for (int c = 0; c < 4; ++c) dvar[s2][c] = ld_cell<false>(a, in, 5 + 4 * s2 + c, k, igc, cellw);
 #pragma unroll
         for (int s2 = 0; s2 < ND; ++s2) {
           const double rd = dvar[s2][3];
@@ -459,17 +378,14 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
     if (EXT && g.damp) {
       const double kd = a.t.damp[(size_t)k * g.nr + igc];
       double e[NG];
-      load_cons<P32, NG>(a, in, 0, k, igc, jw, e);
+      load_cons<false, NG>(a, in, 0, k, igc, jw, e);
 #pragma unroll
       for (int f = 0; f < NG; ++f) S[f] -= (T)(kd * e[f]);
-    }
-    if constexpr (RAWG) {
-      if (halo_t && k + 1 < k1) gas_finish32(ghraw, gm1f, hv);
     }
     T Gt[NG];
 #pragma unroll
     for (int f = 0; f < NG; ++f) Gt[f] = fma(S[f], T(Vc), Gd[f]);
-    if (!P32 && a.mode != MODE_RESID) {
+    if (a.mode != MODE_RESID) {
       const double* R0 = a.t.r0 + ((size_t)k * g.nr + igc) * 5;
 #pragma unroll
       for (int f = 0; f < NG; ++f) Gt[f] -= (T)R0[f];
@@ -487,10 +403,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
         }
       }
     } else if (act) {
-      // all loads before any store (the second stage updates in place).  The FP32 gas
-      // kernel stores after its positivity and CFL arithmetic, so that a wait there (a
-      // register reload) comes before the stores rather than waiting for them; the others
-      // store first (their registers prefer it)
+      // all loads before any store (the second stage updates in place)
       T nv[NG];
       auto store_new = [&]() {
 #pragma unroll
@@ -499,7 +412,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
       const T cdt = (T)(a.coef * dt * invV);
 #pragma unroll
       for (int f = 0; f < NG; ++f) nv[f] = fma(cdt, Gt[f], pb[f]);
-      if constexpr (!P32) store_new();
+      store_new();
       {
         // positivity of the new gas state; CFL of the new state (second stage)
         double qn[5];
@@ -521,16 +434,11 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
           }
         }
       }
-      if constexpr (P32) store_new();
     }
     // ---- shift the ring
 #pragma unroll
     for (int f = 0; f < NG; ++f) {
-      if constexpr (LR) {
-        s_rm[f][tslot] = r0[f]; s_fz[f][tslot] = fzhi[f];
-      } else {
-        rm[f] = r0[f]; fzlo[f] = fzhi[f];
-      }
+      s_rm[f][tslot] = r0[f]; s_fz[f][tslot] = fzhi[f];
       r0[f] = rp[f]; rp[f] = rn[f];
     }
   }
@@ -993,6 +901,523 @@ __global__ void __launch_bounds__(NTM, 4) k_dust(StageArgs a, int species) {
 }
 
 // ------------------------------------------------------------------------------------
+// the gas stage kernel of the FP32-perturbation form
+
+// One RK2 stage of the gas in the FP32-perturbation form; tiles, planes and update as k_gas,
+// addressing and use of LDS as k_dust.  Bound by instruction issue and the chains of the
+// face solves: what the faces need of the stationary flow comes as FP32 pairs formed once
+// (PF_N entries, staged a plane ahead), so that they convert nothing, azimuthal faces take
+// the upwind state and the others a short Newton (gas_face32); the faces that form does not
+// take are marked and solved together, by one inlined copy of the general form per plane.
+// Lane-instructions per cell 1506 -> 1050 and transcendentals 73 -> 30: three-dust disc
+// 512 x 1024 x 128, 4.97 -> 3.3 ms per launch; gas disc 128 x 256 x 64, 182 -> 142 us.  Two
+// waves per SIMD: at three (12-row tiles, 168 VGPRs, the general form called) the largest
+// disc gains 4% and the others lose more, at four (128) the general form's registers spill
+// into the faces (7.2 ms).
+template <int ND, bool EXT>
+__global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
+  __shared__ int s_stop;
+  if (threadIdx.x == 0) s_stop = __atomic_load_n(&a.c.ctrl->status, __ATOMIC_RELAXED);
+  __syncthreads();
+  if (s_stop & FL_HARD) return;
+  constexpr int NG = 5, HW = TJ + 4, NHALO = 4 * HW + 4 * TM;
+  static_assert(NHALO <= NTM, "one halo cell per thread");
+  __shared__ float s_pl[NG][TM + 4][HW];
+  __shared__ float s_ft[NG][TM][TJ + 1];
+  __shared__ float s_fr[NG][TM + 1][TJ];
+  __shared__ float s_rm[NG][NTM];
+  __shared__ double s_red[NTM / 64][3];
+  // Newton counts of the faces the thread owns (bins 0..7, 7: seven or more), 16 bits each;
+  // a thread owns at most 4 faces per plane and one more
+  __shared__ unsigned s_nh[4][NTM];
+  __shared__ Gas32Count s_cnt;
+  // per-plane tables, in doubles (an FP32 pair each for the first two): the stationary flow
+  // at the rows' centres, r faces and upper z faces; at the centres of the rows and their
+  // halo, two planes ahead; the update's (conservative state, gravity, density, velocity)
+  constexpr int PFD = PF_N / 2, NFACE = (3 * TM + 1) * PFD, NCEN = (TM + 4) * 2, NUPD = TM * 9;
+  constexpr int T_CEN = NFACE, T_UPD = T_CEN + NCEN, NTAB = T_UPD + NUPD;
+  static_assert(NTAB <= NTM, "one table entry per thread");
+  __shared__ __align__(16) double s_face[2][NFACE];
+  __shared__ __align__(16) double s_cen[4][NCEN];
+  __shared__ double s_upd[2][NUPD];
+
+  const Geo& g = a.g;
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int tjb = tile % a.ntj;
+  const int tib = (tile / a.ntj) % a.ntm;
+  const int kcb = tile / (a.ntj * a.ntm);
+  const int tid = threadIdx.x, tj = tid & (TJ - 1);
+  const int ti = __builtin_amdgcn_readfirstlane(tid / TJ);
+  const int j0 = tjb * TJ, i0 = tib * TM;
+  const int k0 = kcb * a.tk, k1 = min(g.nz, k0 + a.tk);
+  const int jg = j0 + tj;
+  const int ig = i0 + ti, igc = min(ig, g.nr - 1);
+  const bool act = jg < g.nth && ig < g.nr;
+  const bool drag = ND > 0 && !g.drag_exact;
+  const bool twod = g.twod != 0;
+  const size_t plane = (size_t)g.nr * g.nth;
+  const float gm1f = (float)(g.gamma - 1.0);
+  // columns past the grid and their slots: as k_dust
+  const int wcols = min(TJ, g.nth - j0);
+  const unsigned jl = min(tj, wcols - 1);
+  const bool centre = (unsigned)(tj - wcols) >= 2u;
+  const size_t row0 = (size_t)igc * g.nth + j0;
+  const ctab rt = to_ctab(a.t.rt) + (size_t)igc * RT_N, ar = to_ctab(a.t.ar);
+  auto weights = [&](int i) { return to_ctabf(a.t.rcf) + (size_t)(min(max(i, -1), g.nr) + 1) * RC_N; };
+#pragma unroll
+  for (int q = 0; q < 4; ++q) s_nh[q][tid] = 0u;
+  if (tid == 0) s_cnt = Gas32Count{0, 0, 0, 0, 0};
+  int maxit = 0;
+  auto tally = [&](bool own, int last) {
+    const int b = min(last, 7);
+    if (own) atomicAdd(&s_nh[b >> 1][tid], 1u << (16 * (b & 1)));
+  };
+
+  // thread t stages table entry t: tab_p + plane * tab_stride
+  const double* tab_p = nullptr;
+  size_t tab_stride = 0;
+  if (tid < NTAB) {
+    const size_t nr = (size_t)g.nr;
+    if (tid < NFACE) {
+      const int r = tid / PFD, e = tid % PFD;
+      if (r < TM) {
+        tab_p = a.t.pc + (size_t)min(i0 + r, g.nr - 1) * PFD + e;
+        tab_stride = nr * PFD;
+      } else if (r < 2 * TM + 1) {
+        tab_p = a.t.pr + (size_t)min(i0 + r - TM, g.nr) * PFD + e;
+        tab_stride = (nr + 1) * PFD;
+      } else {
+        tab_p = a.t.pz + (nr + (size_t)min(i0 + r - 2 * TM - 1, g.nr - 1)) * PFD + e;
+        tab_stride = nr * PFD;
+      }
+    } else if (tid < T_UPD) {
+      const int r = (tid - T_CEN) / 2, e = (tid - T_CEN) % 2;
+      tab_p = a.t.pc + (size_t)min(max(i0 + r - 2, 0), g.nr - 1) * PFD + e;
+      tab_stride = nr * PFD;
+    } else {
+      const int r = (tid - T_UPD) / 9, e = (tid - T_UPD) % 9;
+      const size_t i = min(i0 + r, g.nr - 1);
+      if (e < 5) { tab_p = a.t.bgc + i * 5 + e; tab_stride = nr * 5; }
+      else if (e < 7) { tab_p = a.t.grav + i * 2 + (e - 5); tab_stride = nr * 2; }
+      else { tab_p = a.t.wc + i * WB_N + (e == 7 ? WB_RHO : WB_V); tab_stride = nr * WB_N; }
+    }
+  }
+  const bool cen_t = tid >= T_CEN && tid < T_UPD;
+  auto tab_load = [&](int k) {  // (the centres' entries: of plane k + 2)
+    return tid < NTAB ? tab_p[(size_t)min(cen_t ? k + 2 : k, g.nz - 1) * tab_stride] : 0.0;
+  };
+  auto tab_store = [&](int k, double x) {
+    if (tid < NFACE) s_face[k & 1][tid] = x;
+    else if (tid < T_UPD) s_cen[(k + 2) & 3][tid - T_CEN] = x;
+    else if (tid < NTAB) s_upd[k & 1][tid - T_UPD] = x;
+  };
+
+  const float* vin = (const float*)a.in;
+  struct Raw { float e[NG]; };
+  auto col_fetch = [&](const float* v, int k, Raw& R) {
+    const size_t r = (size_t)min(max(k, 0), g.nz - 1) * plane + row0;
+#pragma unroll
+    for (int f = 0; f < NG; ++f) R.e[f] = at_row(v + (size_t)f * g.N + r, jl);
+  };
+  // W' of the thread's cell of plane k; ghosts hold the stationary flow (W' = 0), except the
+  // outflow condition's: the boundary cell's deviation scaled by the densities' ratio
+  auto col_form = [&](int k, const Raw& R, const float* c, float* out) {
+    if (EXT && g.bc_z == 1 && (k < 0 || k >= g.nz)) {
+      const size_t e = (size_t)((k < 0 ? 0 : 2) + min(k < 0 ? -1 - k : k - g.nz, 1)) * g.nr + igc;
+      float s[NG];
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s[f] = (float)((double)R.e[f] * a.t.ozr[e]);
+      cell_w(s, a.t.ghzw + e * WB_N, gm1f, out);
+    } else if (k < 0 || k >= g.nz || ig >= g.nr) {
+#pragma unroll
+      for (int f = 0; f < NG; ++f) out[f] = 0.0f;
+    } else {
+      cell_w32(R.e, c, gm1f, out);
+    }
+  };
+  auto cen = [&](int k, int row) { return (const float*)&s_cen[k & 3][row * 2]; };
+  const bool halo_t = tid < NHALO;
+  int h_rr = 0, h_cc = 0;
+  if (tid < 2 * HW) { h_rr = tid / HW; h_cc = tid % HW; }
+  else if (tid < 4 * HW) { h_rr = TM + 2 + (tid - 2 * HW) / HW; h_cc = (tid - 2 * HW) % HW; }
+  else if (halo_t) { const int e = tid - 4 * HW; h_rr = 2 + e / 4; h_cc = (e & 3) < 2 ? (e & 3) : wcols + (e & 3); }
+  int h_pad = 0;
+  if (tid >= 4 * HW && wcols < TJ && h_cc > 1 && TJ + (tid & 3) > wcols + 3) h_pad = TJ + (tid & 3);
+  const int h_ii = i0 + h_rr - 2;
+  const size_t h_off = (size_t)min(max(h_ii, 0), g.nr - 1) * g.nth + (j0 + h_cc - 2 + g.nth) % g.nth;
+  auto halo_fetch = [&](int k, Raw& R) {
+#pragma unroll
+    for (int f = 0; f < NG; ++f) R.e[f] = at_plane(vin + (size_t)f * g.N + (size_t)k * plane, h_off);
+  };
+  auto halo_store = [&](int k, const Raw& R) {
+    float w[NG];
+    cell_w32(R.e, cen(k, h_rr), gm1f, w);
+    const bool ghost = h_ii < 0 || h_ii >= g.nr;
+#pragma unroll
+    for (int f = 0; f < NG; ++f) s_pl[f][h_rr][h_cc] = ghost ? 0.0f : w[f];
+    if (h_pad) {
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_pl[f][h_rr][h_pad] = ghost ? 0.0f : w[f];
+    }
+  };
+
+  // a face by the short form (bp: the face's PF_N entry), with its Newton count tallied if
+  // the thread owns it; returns false where the general form has to solve it
+  auto face = [&](auto dirc, auto cell, auto coB, auto coC, const float* bp, bool own, float* F) {
+    constexpr int D = decltype(dirc)::value;
+    float qL[NG], qR[NG];
+    recon32<D>(cell, coB, coC, qL, qR);
+    int last = 0;
+    const bool ok = gas_face32<D>(bp, qL, qR, F, last);
+    if (ok) maxit = max(maxit, last);
+    tally(own && ok, last);
+    return ok;
+  };
+  // the same by the general form: stencil cells q, direction, lower cell (k, i)
+  auto general = [&](int dir, const Face32& q, int k, int i, bool own, float* F) {
+    const Face32Out o = gas_face32_general(a, dir, k, i, q);
+#pragma unroll
+    for (int f = 0; f < NG; ++f) F[f] = o.F[f];
+    maxit = max(maxit, o.maxit);
+    tally(own, o.last);
+    if (o.fall) atomicAdd(&s_cnt.fall, o.fall);
+    if (o.vac) atomicAdd(&s_cnt.vac, o.vac);
+    if (o.resolve) atomicAdd(&s_cnt.resolve, o.resolve);
+    if (o.noconv) atomicMax(&s_cnt.noconv, 1);
+  };
+  using DR = std::integral_constant<int, 0>;
+  using DT = std::integral_constant<int, 1>;
+  using DZ = std::integral_constant<int, 2>;
+  double smax = 0.0, tsmin = 1e300, ledger = 0.0;
+
+  tab_store(k0, tab_load(k0));
+  for (int p = k0 - 2; p < k0; ++p)
+    if (cen_t) tab_store(p, tab_load(p));
+  __syncthreads();
+  float rp[NG], fzlo[NG];
+  {
+    Raw R;
+    float r0[NG];
+    // (planes below k0 are not in the ring of centre entries)
+    auto form_at = [&](int k, float* out) {
+      const ctabf c = to_ctabf((const float*)a.t.pc) + ((size_t)min(max(k, 0), g.nz - 1) * g.nr + igc) * PF_N;
+      const float cf[4] = {c[0], c[1], c[2], c[3]};
+      col_fetch(vin, k, R);
+      col_form(k, R, cf, out);
+    };
+    if (!twod) {
+      float e2[NG], rm[NG];
+      form_at(k0 - 2, e2);
+      form_at(k0 - 1, rm);
+      form_at(k0, r0);
+      form_at(k0 + 1, rp);
+      const ctabf c = to_ctabf((const float*)a.t.pz) + ((size_t)k0 * g.nr + igc) * PF_N;
+      float bp[PF_N];
+#pragma unroll
+      for (int q = 0; q < PF_N; ++q) bp[q] = c[q];
+      auto get = [&](int s, int f) { return s == 0 ? e2[f] : s == 1 ? rm[f] : s == 2 ? r0[f] : rp[f]; };
+      if (!face(DZ(), get, nullptr, nullptr, bp, act && k0 == 0, fzlo)) {
+        Face32 q;
+#pragma unroll
+        for (int f = 0; f < NG; ++f) { q.A[f] = e2[f]; q.B[f] = rm[f]; q.C[f] = r0[f]; q.D[f] = rp[f]; }
+        general(2, q, k0 - 1, igc, act && k0 == 0, fzlo);
+      }
+      if (a.second && k0 == 0 && act) ledger -= rt[RT_AZ] * (double)fzlo[4];
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_rm[f][tid] = rm[f];
+    } else {
+      form_at(0, r0);
+#pragma unroll
+      for (int f = 0; f < NG; ++f) { rp[f] = 0.0f; fzlo[f] = 0.0f; }
+    }
+    if (centre) {
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_pl[f][ti + 2][tj + 2] = r0[f];
+    }
+    if (halo_t) {
+      halo_fetch(k0, R);
+      halo_store(k0, R);
+    }
+  }
+  const double dt = a.dt_idx >= 0 ? a.c.dtlog[a.dt_idx] : 0.0;
+
+  for (int k = k0; k < k1; ++k) {
+    const bool more = k + 1 < k1;
+    const float* face_c = (const float*)&s_face[k & 1][ti * PFD];
+    const float* face_r = (const float*)&s_face[k & 1][(TM + ti + 1) * PFD];
+    const float* face_z = (const float*)&s_face[k & 1][(2 * TM + 1 + ti) * PFD];
+    __syncthreads();
+    // the column's cell k+2 and the next plane's halo and tables
+    Raw nraw, hraw;
+    double tab_next = 0.0;
+    unsigned bad = 0;
+    if (!twod) col_fetch(vin, k + 2, nraw);
+    if (more) {
+      if (halo_t) halo_fetch(k + 1, hraw);
+      tab_next = tab_load(k + 1);
+    }
+    // ---- theta face j+1/2
+    {
+      auto get = [&](int c, int f) { return s_pl[f][ti + 2][tj + 1 + c]; };
+      float F[NG];
+      if (!face(DT(), get, nullptr, nullptr, face_c, act, F)) bad |= 1;
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_ft[f][ti][tj + 1] = F[f];
+    }
+    // ---- r face i+1/2
+    {
+      auto get = [&](int c, int f) { return s_pl[f][ti + 1 + c][tj + 2]; };
+      float F[NG];
+      if (!face(DR(), get, weights(ig), weights(ig + 1), face_r, act, F)) bad |= 2;
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_fr[f][ti + 1][tj] = F[f];
+    }
+    // ---- lower-edge faces of the tile: r face i0-1/2 (threads 0..63) and theta face
+    //      j0-1/2 of each row (threads 64..71)
+    if (tid < TJ) {
+      auto get = [&](int c, int f) { return s_pl[f][c][tid + 2]; };
+      float F[NG];
+      // (the upper face of the tile below, which owns it, except at the inner boundary)
+      if (!face(DR(), get, weights(i0 - 1), weights(i0), (const float*)&s_face[k & 1][TM * PFD],
+                i0 == 0 && jg < g.nth, F))
+        bad |= 4;
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_fr[f][0][tid] = F[f];
+    } else if (tid < TJ + TM) {
+      const int row = tid - TJ;
+      auto get = [&](int c, int f) { return s_pl[f][row + 2][c]; };
+      float F[NG];
+      if (!face(DT(), get, nullptr, nullptr, (const float*)&s_face[k & 1][row * PFD], false, F))
+        bad |= 4;
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_ft[f][row][0] = F[f];
+    }
+    // the update's base of this cell and the dust its drag needs (raw stored values)
+    Raw base;
+    if (a.mode == MODE_UPDATE && act) col_fetch((const float*)a.base, k, base);
+    double rds[ND > 0 ? ND : 1];
+    float vds[ND > 0 ? ND : 1][3];
+    if (drag) {
+      const size_t r = (size_t)k * plane + row0;
+#pragma unroll
+      for (int s2 = 0; s2 < ND; ++s2) {
+        rds[s2] = at_row((const double*)a.in + p32_f64_base(g) + (size_t)s2 * g.N + r, jl);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) vds[s2][c] = at_row(vin + (size_t)(5 + 3 * s2 + c) * g.N + r, jl);
+      }
+    }
+    // ---- z face k+1/2
+    float rn[NG], fzhi[NG];
+    if (!twod) {
+      col_form(k + 2, nraw, cen(k + 2, ti + 2), rn);
+      auto get = [&](int c, int f) {
+        return c == 0 ? s_rm[f][tid] : c == 1 ? s_pl[f][ti + 2][tj + 2] : c == 2 ? rp[f] : rn[f];
+      };
+      if (!face(DZ(), get, nullptr, nullptr, face_z, act, fzhi)) bad |= 8;
+    } else {
+#pragma unroll
+      for (int f = 0; f < NG; ++f) { rn[f] = 0.0f; fzhi[f] = 0.0f; }
+    }
+    // ---- the faces the short form did not take (rare), one call for all kinds: own theta and
+    //      r face, tile edge, z face
+    if (__builtin_expect(!wave_none(bad != 0), 0)) {
+#pragma nounroll
+      for (int kind = 0; kind < 4; ++kind) {
+        if (!(bad >> kind & 1)) continue;
+        const bool edge_r = kind == 2 && tid < TJ, along_th = kind == 0 || (kind == 2 && !edge_r);
+        const int rr = kind == 0 ? ti + 2 : kind == 1 ? ti + 1 : edge_r ? 0 : tid - TJ + 2;
+        const int cc = kind == 0 ? tj + 1 : along_th ? 0 : tj + 2;
+        Face32 q;
+#pragma unroll
+        for (int f = 0; f < NG; ++f) {
+          const float* p = &s_pl[f][rr][cc];
+          const int st = along_th ? 1 : HW;
+          if (kind == 3) {
+            q.A[f] = s_rm[f][tid]; q.B[f] = s_pl[f][ti + 2][tj + 2]; q.C[f] = rp[f]; q.D[f] = rn[f];
+          } else {
+            q.A[f] = p[0]; q.B[f] = p[st]; q.C[f] = p[2 * st]; q.D[f] = p[3 * st];
+          }
+        }
+        const int i = kind == 1 ? min(ig, g.nr) : kind == 2 ? (edge_r ? i0 - 1 : min(i0 + tid - TJ, g.nr - 1)) : igc;
+        float F[NG];
+        general(along_th ? 1 : kind == 3 ? 2 : 0, q, k, i,
+                kind == 2 ? edge_r && i0 == 0 && jg < g.nth : act, F);
+#pragma unroll
+        for (int f = 0; f < NG; ++f) {
+          if (kind == 0) s_ft[f][ti][tj + 1] = F[f];
+          else if (kind == 1) s_fr[f][ti + 1][tj] = F[f];
+          else if (kind == 3) fzhi[f] = F[f];
+          else if (edge_r) s_fr[f][0][tid] = F[f];
+          else s_ft[f][tid - TJ][0] = F[f];
+        }
+      }
+    }
+    float dz[NG];
+#pragma unroll
+    for (int f = 0; f < NG; ++f) {
+      dz[f] = (float)rt[RT_AZ] * (fzhi[f] - fzlo[f]);
+      fzlo[f] = fzhi[f];
+    }
+    // (the entries it replaces were last read before this plane's first barrier)
+    if (more) tab_store(k + 1, tab_next);
+    __syncthreads();
+    if (halo_t && more) halo_store(k + 1, hraw);
+    // boundary outflow ledger (the stationary flow has no mass flux through these faces)
+    if (a.second && act) {
+      if (ig == g.nr - 1) ledger += ar[igc + 1] * (double)s_fr[4][ti + 1][tj];
+      if (ig == 0) ledger -= ar[0] * (double)s_fr[4][0][tj];
+      if (!twod && k == g.nz - 1) ledger += rt[RT_AZ] * (double)fzlo[4];
+    }
+    // ---- divergence -sum_s A_s F.n_s (Sect. 2.2), sources (App. B), drag (Sect. 2.9): the
+    //      source change S(E) - S(E0), every term formed from the perturbations W' (the
+    //      stationary flow has no radial or vertical velocity)
+    float r0[NG];
+#pragma unroll
+    for (int f = 0; f < NG; ++f) r0[f] = s_pl[f][ti + 2][tj + 2];
+    const double* upd = &s_upd[k & 1][ti * 9];
+    const float rhop = r0[4], up = r0[0], vp = r0[1], wp = r0[2], pp = r0[3];
+    const float v0 = face_c[PF_V], rho = face_c[PF_RHO] + (rhop + face_c[PF_RLO]);
+    const float ir = (float)rt[RT_INVRC], fgr = (float)upd[5], fgz = (float)upd[6];
+    const float dmv2 = rhop * face_c[PF_VSQ] + rho * vp * (2.0f * v0 + vp);
+    float S[NG];
+    S[0] = (dmv2 + pp) * ir + rhop * fgr;
+    S[1] = -(rho * up * (v0 + vp)) * ir;
+    S[2] = rhop * fgz;
+    S[3] = rho * (up * fgr + wp * fgz);
+    S[4] = 0.0f;
+    if (drag) {
+      const double rg = upd[7] + (double)rhop;
+      const double u = (double)up, v = upd[8] + (double)vp, w2 = (double)wp;
+      const double pq = (EXT && g.drag_law) ? a.t.wc[((size_t)k * g.nr + igc) * WB_N + WB_P] + (double)pp : 0.0;
+      double dx = 0.0, dy = 0.0, dzz = 0.0;
+#pragma unroll
+      for (int s2 = 0; s2 < ND; ++s2) {
+        // the FP32 layout stores the dust velocities as deviations from the stationary
+        // flow's, as the gas W' is: the velocity difference is formed from the deviations
+        const double rd = rds[s2];
+        const bool full = rd > 0.0;
+        const double dud = full ? (double)vds[s2][0] - (double)up : -u;
+        const double dvd = full ? (double)vds[s2][1] - (double)vp : -v;
+        const double dwd = full ? (double)vds[s2][2] - (double)wp : -w2;
+        const double its = inv_tstop<EXT>(g, s2, rt[RT_OMK], rg, pq);
+        dx += rd * dud * its;
+        dy += rd * dvd * its;
+        dzz += rd * dwd * its;
+      }
+      S[0] += (float)dx;
+      S[1] += (float)dy;
+      S[2] += (float)dzz;
+      S[3] += (float)(u * dx + v * dy + w2 * dzz);
+    }
+    // indirect gravity (Sect. 2.10): minus the star's acceleration by the disc
+    if (EXT && g.indirect) {
+      const double A = a.t.indab[0], B = a.t.indab[1];
+      const double cs = a.t.trig[j0 + jl], sn = a.t.trig[g.nth + j0 + jl];
+      const double acr = -g.GM * (A * cs + B * sn), act_ = -g.GM * (B * cs - A * sn);
+      const double rg = upd[7] + (double)rhop;
+      S[0] += (float)(rg * acr);
+      S[1] += (float)(rg * act_);
+      S[3] += (float)(rg * (double)up * acr + rg * (upd[8] + (double)vp) * act_);
+    }
+    // boundary damping zones (Sect. 2.4): the gas deviation relaxes to the stationary flow
+    if (EXT && g.damp) {
+      const double kd = a.t.damp[(size_t)k * g.nr + igc];
+      Raw e;
+      col_fetch(vin, k, e);
+#pragma unroll
+      for (int f = 0; f < NG; ++f) S[f] -= (float)(kd * (double)e.e[f]);
+    }
+    float Gt[NG];
+#pragma unroll
+    for (int f = 0; f < NG; ++f) {
+      const float dr = (float)ar[igc + 1] * s_fr[f][ti + 1][tj] - (float)ar[igc] * s_fr[f][ti][tj];
+      const float dth = (float)rt[RT_ATH] * (s_ft[f][ti][tj + 1] - s_ft[f][ti][tj]);
+      Gt[f] = fma(S[f], (float)rt[RT_V], -((dr + dth) + dz[f]));
+    }
+    if (a.mode == MODE_OPER) {
+      if (act) {
+#pragma unroll
+        for (int f = 0; f < NG; ++f)
+          at_row((float*)a.out + (size_t)f * g.N + (size_t)k * plane + row0, jl) = Gt[f];
+      }
+    } else if (act) {
+      // all loads before any store (the second stage updates in place)
+      const float cdt = (float)(a.coef * dt * rt[RT_INVV]);
+      float nv[NG];
+      double qn[NG];
+#pragma unroll
+      for (int f = 0; f < NG; ++f) {
+        nv[f] = fma(cdt, Gt[f], base.e[f]);
+        qn[f] = upd[f] + (double)nv[f];
+        at_row((float*)a.out + (size_t)f * g.N + (size_t)k * plane + row0, jl) = nv[f];
+      }
+      // positivity of the new gas state; CFL of the new state (second stage)
+      const double in2 = 1.0 / qn[4];
+      const double un = qn[0] * in2, vn = qn[1] * in2, wn = qn[2] * in2;
+      const double pn = (g.gamma - 1.0) * (qn[3] - 0.5 * (qn[0] * un + qn[1] * vn + qn[2] * wn));
+      if (!(qn[4] > 0.0 && pn > 0.0)) {
+        atomicOr(&a.c.ctrl->status, FL_NEG);
+        atomicMin(&a.c.ctrl->first_bad, (unsigned long long)((size_t)k * plane + (size_t)ig * g.nth + jg));
+        atomicCAS(&a.c.ctrl->bad_step, -1, a.step);
+      } else if (a.second) {
+        const double spd = sqrt(un * un + vn * vn + wn * wn) + sqrt(g.gamma * pn * in2);
+        smax = fmax(smax, spd);
+        if (EXT && g.drag_law) {
+#pragma unroll
+          for (int s2 = 0; s2 < ND; ++s2)
+            tsmin = fmin(tsmin, 1.0 / inv_tstop<EXT>(g, s2, rt[RT_OMK], qn[4], pn));
+        }
+      }
+    }
+    // ---- shift the column
+    if (more) {
+#pragma unroll
+      for (int f = 0; f < NG; ++f) {
+        s_rm[f][tid] = r0[f];
+        if (centre) s_pl[f][ti + 2][tj + 2] = rp[f];
+        rp[f] = rn[f];
+      }
+    }
+  }
+
+  // ---- block reductions: counters, CFL partial, boundary outflow partial
+  __syncthreads();
+  const int wv = tid / 64, ln = tid & 63;
+  const int mi = wave_imax(maxit);
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    const int hb = wave_isum((int)((s_nh[b >> 1][tid] >> (16 * (b & 1))) & 0xffffu));
+    if (ln == 0 && hb) atomicAdd(&a.c.ctrl->newton_hist[b], (unsigned long long)hb);
+  }
+  if (ln == 0 && mi) atomicMax(&a.c.ctrl->maxit, mi);
+  if (tid == 0) {
+    if (s_cnt.fall) atomicAdd(&a.c.ctrl->nfall, (unsigned long long)s_cnt.fall);
+    if (s_cnt.vac) { atomicAdd(&a.c.ctrl->nvac, (unsigned long long)s_cnt.vac); atomicOr(&a.c.ctrl->status, FL_VAC); }
+    if (s_cnt.resolve) atomicAdd(&a.c.ctrl->nresolve, (unsigned long long)s_cnt.resolve);
+    if (s_cnt.noconv) { atomicOr(&a.c.ctrl->status, FL_NOCONV); atomicCAS(&a.c.ctrl->bad_step, -1, a.step); }
+  }
+  if (a.second && a.mode == MODE_UPDATE) {
+    // the CFL bound of the thread's row decreases with the speed: the largest one's
+    const double m = wave_min(smax > 0.0 ? g.cfl * rt[RT_V] / (smax * rt[RT_MAXA]) : 1e300);
+    const double ls = wave_sum(ledger);
+    const double tm = (EXT && ND > 0) ? wave_min(tsmin) : 1e300;
+    if (ln == 0) { s_red[wv][0] = m; s_red[wv][1] = ls; s_red[wv][2] = tm; }
+    __syncthreads();
+    if (tid == 0) {
+      double mm = s_red[0][0], lsum = s_red[0][1], tmm = s_red[0][2];
+      for (int w2 = 1; w2 < NTM / 64; ++w2) {
+        mm = fmin(mm, s_red[w2][0]);
+        lsum += s_red[w2][1];
+        tmm = fmin(tmm, s_red[w2][2]);
+      }
+      a.c.cflp[(size_t)blockIdx.x * 5] = mm;
+      a.c.outp[(size_t)blockIdx.x * 5] = lsum;
+      if (EXT && g.drag_law) a.c.tsp[blockIdx.x] = tmm;
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------
 // standalone CFL of a state (start of a call) with the positivity check
 
 template <int ND, bool P32>
@@ -1307,6 +1732,21 @@ __device__ void prim_entry(const rb_config& c, const double* q, double* o) {
   o[WB_IRHO] = 1.0 / rho;
 }
 
+// PF_N entry of the FP32-perturbation form from a WB_N entry.
+__device__ void pert_entry(const double* b, double* out) {
+  float* o = (float*)out;
+  o[PF_RHO] = (float)b[WB_RHO];
+  o[PF_RLO] = (float)(b[WB_RHO] - (double)o[PF_RHO]);
+  o[PF_V] = (float)b[WB_V];
+  o[PF_VSQ] = (float)(b[WB_V] * b[WB_V]);
+  o[PF_P] = (float)b[WB_P];
+  o[PF_PLO] = (float)(b[WB_P] - (double)o[PF_P]);
+  o[PF_C] = (float)b[WB_C];
+  o[PF_H] = (float)b[WB_H];
+  o[PF_RHOV] = (float)(b[WB_RHO] * b[WB_V]);
+  o[PF_PAD] = 0.0f;
+}
+
 // Reconstructed variables of a ghost cell whose full state is q (nf fields): the gas
 // deviation W(q) - W0 (zero on a disc, whose ghosts hold the stationary flow; the
 // state's own primitives for the Sod annulus), and each dust fluid's velocity (zero
@@ -1416,6 +1856,8 @@ __global__ void __launch_bounds__(256) k_tables_r(InitArgs a) {
     co[RC_WMM] = (hp * d - d * d) / (hm * sum);
     co[RC_LMM] = 2.0 * d / hm;
     co[RC_LMP] = 2.0 * d / hp;
+    if (a.g.p32)
+      for (int q = 0; q < RC_N; ++q) ((float*)(w + L.rcf))[(size_t)cI * RC_N + q] = (float)co[q];
   }
   if (threadIdx.x == 0) {
     Ctrl* ct = reinterpret_cast<Ctrl*>(w + L.ctrl);
@@ -1477,7 +1919,9 @@ __global__ void __launch_bounds__(256) k_tables_2d(InitArgs a) {
       background_full(a, r, zc, q);
       for (int f = 0; f < 5; ++f) w[L.bgc + ((size_t)kk * nr + ii) * 5 + f] =
           c.init_kind == RB_INIT_DISC ? q[f] : 0.0;
-      prim_entry(c, q, w + L.wc + ((size_t)kk * nr + ii) * WB_N);
+      double* o = w + L.wc + ((size_t)kk * nr + ii) * WB_N;
+      prim_entry(c, q, o);
+      if (a.g.p32) pert_entry(o, w + L.pc + ((size_t)kk * nr + ii) * (PF_N / 2));
       double s3 = pow(r * r + zc * zc, 1.5);
       w[L.grav + ((size_t)kk * nr + ii) * 2 + 0] = -c.GM * r / s3;
       w[L.grav + ((size_t)kk * nr + ii) * 2 + 1] = -c.GM * zc / s3;
@@ -1486,13 +1930,17 @@ __global__ void __launch_bounds__(256) k_tables_2d(InitArgs a) {
       background_full(a, face_r(c, ii), zc, q);
       for (int f = 0; f < 5; ++f) w[L.bgr + ((size_t)kk * (nr + 1) + ii) * 5 + f] =
           c.init_kind == RB_INIT_DISC ? q[f] : 0.0;
-      prim_entry(c, q, w + L.wr + ((size_t)kk * (nr + 1) + ii) * WB_N);
+      double* o = w + L.wr + ((size_t)kk * (nr + 1) + ii) * WB_N;
+      prim_entry(c, q, o);
+      if (a.g.p32) pert_entry(o, w + L.pr + ((size_t)kk * (nr + 1) + ii) * (PF_N / 2));
     }
     if (!twod && iin && kk >= 0 && kk <= nz) {
       background_full(a, cell_r(c, ii), (kk - 0.5 * nz) * dz, q);
       for (int f = 0; f < 5; ++f) w[L.bgz + ((size_t)kk * nr + ii) * 5 + f] =
           c.init_kind == RB_INIT_DISC ? q[f] : 0.0;
-      prim_entry(c, q, w + L.wz + ((size_t)kk * nr + ii) * WB_N);
+      double* o = w + L.wz + ((size_t)kk * nr + ii) * WB_N;
+      prim_entry(c, q, o);
+      if (a.g.p32) pert_entry(o, w + L.pz + ((size_t)kk * nr + ii) * (PF_N / 2));
     }
     // ghost cells: reconstructed variables (gas W', dust primitives) and the stationary
     // flow's primitives
@@ -1795,24 +2243,19 @@ hipError_t launch_init_state(const InitArgs& a, hipStream_t s) {
 // outflow ghosts) run in their own instantiation; the base one compiles them out
 static bool uses_ext(const Geo& g) { return g.indirect || g.damp || g.bc_z == 1 || g.drag_law; }
 
-template <int ND, bool P32, bool EXT>
+template <int ND, bool EXT>
 static void gas_ext(const StageArgs& a, int blocks, hipStream_t s) {
-  // (the FP32-perturbation form is specialised to gamma = 7/5)
-  if (P32 || a.g.gamma == 1.4)
-    hipLaunchKernelGGL((k_gas<ND, true, P32, EXT>), dim3(blocks), dim3(NTM), 0, s, a);
+  if (a.g.p32)
+    hipLaunchKernelGGL((k_gas32<ND, EXT>), dim3(blocks), dim3(NTM), 0, s, a);
+  else if (a.g.gamma == 1.4)
+    hipLaunchKernelGGL((k_gas<ND, true, EXT>), dim3(blocks), dim3(NTM), 0, s, a);
   else
-    hipLaunchKernelGGL((k_gas<ND, P32, P32, EXT>), dim3(blocks), dim3(NTM), 0, s, a);
+    hipLaunchKernelGGL((k_gas<ND, false, EXT>), dim3(blocks), dim3(NTM), 0, s, a);
 }
 template <int ND>
 static void gas_nd(const StageArgs& a, int blocks, hipStream_t s) {
-  const bool ext = uses_ext(a.g);
-  if (a.g.p32) {
-    if (ext) gas_ext<ND, true, true>(a, blocks, s);
-    else gas_ext<ND, true, false>(a, blocks, s);
-  } else {
-    if (ext) gas_ext<ND, false, true>(a, blocks, s);
-    else gas_ext<ND, false, false>(a, blocks, s);
-  }
+  if (uses_ext(a.g)) gas_ext<ND, true>(a, blocks, s);
+  else gas_ext<ND, false>(a, blocks, s);
 }
 
 hipError_t launch_stage_group(const StageArgs& a, const Layout& L, int group, hipStream_t s) {
