@@ -14,6 +14,14 @@ namespace rb {
 // ------------------------------------------------------------------------------------
 // small helpers
 
+// Read-only tables by scalar loads: constant address space, for indexes that are the same in
+// every lane of a wavefront.  Only tables that no kernel writes while the reading one runs.
+using ctab = const __attribute__((address_space(4))) double*;
+__device__ __forceinline__ ctab to_ctab(const double* p) { return (ctab)(uintptr_t)p; }
+
+using ctabf = const __attribute__((address_space(4))) float*;
+__device__ __forceinline__ ctabf to_ctabf(const float* p) { return (ctabf)(uintptr_t)p; }
+
 // minmod of three: when all three share a sign, the one of smallest magnitude, else zero.
 // Three branch-free forms giving the same value (only the sign of a zero result can
 // differ):
@@ -492,48 +500,141 @@ template <int DIR> struct Dirs {
 // whole.  A gas face state is W0(face) + W'(cell) + limited increment; only the flux of
 // the Riemann solution, F* = F(E*), is formed from the face states (Sect. 2.6).
 
-// Reconstructed gas face states, positivity fallback to the cell-centre state
-// W0(cell) + W'(cell), exact Riemann problem, F* in field order.  Cells A, B | C, D along
-// DIR (the face lies between B and C), given by their W' in field slots (u, v, w, P, rho);
-// bf: the stationary flow at the face, bB / bC: at the centres of B and C (WB_N entries).
-template <int DIR, bool G75>
-__device__ __forceinline__ void gas_face(const GasC& c, const double* wA, const double* wB,
-                                         const double* wC, const double* wD, const double* coB,
-                                         const double* coC, const double* bf, const double* bB,
-                                         const double* bC, double F[5], TStat& st) {
-  double qL[5], qR[5];
+// The short form of an FP64 gas face (gamma = 7/5; qL, qR full face states in field slots).
+// Returns false where it does not apply (the general form solves those): a non-positive
+// state, a perturbation p*/p_K - 1 above 1/16, normal velocities above 0.9 c, no convergence,
+// or a supersonic face on which the left state is not proved to be the solution.
+//
+// Supersonic to the right: gas_riemann's proof that the left state is the solution.
+// Otherwise, with x = p / p_K - 1 small both branches of a side's pressure function are
+// polynomials (f = 5/7 c x g(x), f' = D(x) / (rho c)), and so are both densities
+// (rho* = rho_K (1 + x R(x))); with x and the velocities so bounded the state at x/t = 0 is
+// the star state.  The polynomials interpolate at the Chebyshev nodes of [-X, 0] or [0, X]:
+// relative error below 2.5e-17 with degree 4 for X = 1/512 and degree 8 for X = 1/16 (D:
+// 5e-8 with degree 2 and 3e-11 with degree 5, enough that Newton takes the same steps).  f's
+// error is then 1e-16 f, where the general form's difference of a root from 1 leaves 1e-16 c.
+// A Newton step costs some 50 instructions (x below 1/512) instead of 150: the general form
+// runs both branches of both sides wherever a wavefront's lanes differ.
+// Their coefficients, highest degree first, rarefaction and shock in turn (D of the narrow
+// range: one for both): g, D, R for X = 1/512, then for X = 1/16; the constant terms are 1, 1
+// and 5/7.  Read by scalar loads where they are used: as literals they would be kept in
+// registers across the march, and spilled.
+enum : int { WK_G = 0, WK_D = 8, WK_R = 10, WKW_G = 18, WKW_D = 34, WKW_R = 44 };
+static __constant__ double weak_coef[60] = {
+    0.1467684060227819, 0.14703985203134992, -0.1895033823370895, -0.19679205462062704,
+    0.26530612314052177, 0.2755102034197363, -0.42857142857125957, -0.42857142857126684,
+    0.811186511, -0.8571412, 0.016479224249694835, 0.0002970904304251677,
+    -0.024989489144093765, -0.00208246450518904, 0.04373177849459193, 0.014577259474031863,
+    -0.10204081632651371, -0.10204081632653021, 0.09561162951996895, 0.04576086710171662,
+    -0.08223027042671534, -0.06991785492880287, 0.09919333961673185, 0.0893809409570641,
+    -0.11833715584013775, -0.11385591256242655, 0.14618922734393267, 0.14759468994287225,
+    -0.1895043714738181, -0.19679300216171694, 0.2653061224593831, 0.27551020407704946,
+    -0.4285714285714042, -0.42857142857141783, -0.8564544483957558, -0.5772585738467768,
+    0.7202612672781041, 0.7307797030308907, -0.7583698246835111, -0.7869426057675021,
+    0.7959131589272986, 0.8265272800629793, -0.8571428851683863, -0.8571428393645633,
+    0.007149950940208943, -2.8236600908745726e-06, -0.006773265234381003,
+    -1.4623212301073427e-07, 0.008869215307677137, 5.999868831947352e-06,
+    -0.011729358301387537, -4.249561665451796e-05, 0.016421738814645315,
+    0.00029749498580051704, -0.024989587552392552, -0.0020824656376448895, 0.04373177842638611,
+    0.014577259475204975, -0.1020408163265289, -0.10204081632653056,};
+__device__ __forceinline__ ctab weak_table(int at) {
+  ctab t = to_ctab(weak_coef) + at;
+  asm volatile("" : "+s"(t));
+  return t;
+}
+// the polynomial of degree DEG with constant term c0 at x (x > 0: the shock's)
+template <int DEG>
+__device__ __forceinline__ double weak_poly(ctab t, double x, double c0) {
+  double r = t[0], s = t[1];
 #pragma unroll
-  for (int f = 0; f < 5; ++f) {
-    double iB, iC;
-    if (DIR == 0) {
-      iB = inc_up_c(wA[f], wB[f], wC[f], coB);
-      iC = inc_lo_c(wB[f], wC[f], wD[f], coC);
-    } else {
-      iB = inc_up_u(wA[f], wB[f], wC[f]);
-      iC = inc_lo_u(wB[f], wC[f], wD[f]);
-    }
-    qL[f] = bf[f] + (wB[f] + iB);
-    qR[f] = bf[f] + (wC[f] + iC);
+  for (int n = 1; n < DEG; ++n) {
+    r = fma(r, x, t[2 * n]);
+    s = fma(s, x, t[2 * n + 1]);
   }
-  if (!(qL[4] > 0.0 && qL[3] > 0.0)) {
-#pragma unroll
-    for (int f = 0; f < 5; ++f) qL[f] = bB[f] + wB[f];
-    st.fall++;
-  }
-  if (!(qR[4] > 0.0 && qR[3] > 0.0)) {
-#pragma unroll
-    for (int f = 0; f < 5; ++f) qR[f] = bC[f] + wC[f];
-    st.fall++;
-  }
+  return fma(x > 0.0 ? s : r, x, c0);
+}
+
+template <int DIR>
+__device__ __forceinline__ bool gas_face64(const GasC& c, const double* qL, const double* qR,
+                                           double* F, int& last) {
   constexpr int N = Dirs<DIR>::n, T1 = Dirs<DIR>::t1, T2 = Dirs<DIR>::t2;
-  double fl[5];
-  gas_riemann<G75>(c, qL[4], frcp(qL[4]), qL[N], qL[T1], qL[T2], qL[3], qR[4], frcp(qR[4]), qR[N],
-                   qR[T1], qR[T2], qR[3], fl, st);
-  F[4] = fl[0];
-  F[N] = fl[1];
-  F[T1] = fl[2];
-  F[T2] = fl[3];
-  F[3] = fl[4];
+  const double rL = qL[4], rR = qR[4], pL = qL[3], pR = qR[3], uL = qL[N], uR = qR[N];
+  bool ok = rL > 0.0 && pL > 0.0 && rR > 0.0 && pR > 0.0;
+  const double irL = frcp(rL), irR = frcp(rR);
+  const double c2L = c.g * pL * irL, c2R = c.g * pR * irR;
+  const double du = uR - uL;
+  double rho = rL, un = uL, p = pL, t1 = qL[T1], t2 = qL[T2];
+  last = 0;
+  // gas_riemann's test of a face supersonic to the right
+  bool sup = uL > 0.0 && uL * uL >= c2L;
+  if (!wave_none(sup)) {
+    const double u2 = uL * uL;
+    const double phi = (rL * u2 * c.inv_g - c.gm1_2g * pL) * c.inv_gp1_2g;
+    const double d = phi - pL, d2A = d * d * (c.a2 * irL), pb = phi + c.kshock * pL;
+    sup = sup && (du <= 0.0 || du * du < c.g2m1 * c.g2m1 * c2L) && phi >= pR &&
+          (du >= 0.0 || d2A >= du * du * pb) && u2 * pb >= d2A;
+  }
+  if (!wave_none(ok && !sup)) {
+    bool weak = uL * uL < 0.81 * c2L && uR * uR < 0.81 * c2R;
+    const double rsL = frsq(c2L), rsR = frsq(c2R);
+    const double cL = c2L * rsL, cR = c2R * rsR, zL = irL * rsL, zR = irR * rsR;
+    const double ipL = frcp(pL), ipR = frcp(pR);
+    const double gL = (5.0 / 7.0) * cL, gR = (5.0 / 7.0) * cR;
+    double ps = 0.5 * (pL + pR) - 0.125 * du * (rL + rR) * (cL + cR);
+    double fL, fR, dL, dR, dp = 0.0, xm = 0.0;
+    int it = 0;
+    bool going = weak && ok && !sup, conv = false;
+    while (going && it < c.max_iter) {
+      ++it;
+      const double xL = (ps - pL) * ipL, xR = (ps - pR) * ipR;
+      xm = fmax(xm, fmax(fabs(xL), fabs(xR)));
+      if (wave_none(xm > 1.0 / 512.0)) {
+        const ctab t = weak_table(WK_G);
+        fL = gL * xL * weak_poly<4>(t, xL, 1.0);
+        fR = gR * xR * weak_poly<4>(t, xR, 1.0);
+        dL = zL * fma(fma(t[WK_D], xL, t[WK_D + 1]), xL, 1.0);
+        dR = zR * fma(fma(t[WK_D], xR, t[WK_D + 1]), xR, 1.0);
+      } else {
+        const ctab t = weak_table(WKW_G);
+        fL = gL * xL * weak_poly<8>(t, xL, 1.0);
+        fR = gR * xR * weak_poly<8>(t, xR, 1.0);
+        const ctab d = weak_table(WKW_D);
+        dL = zL * weak_poly<5>(d, xL, 1.0);
+        dR = zR * weak_poly<5>(d, xR, 1.0);
+      }
+      const double pn = ps - (fL + fR + du) * frcp(dL + dR);
+      dp = pn - ps;
+      // relative change 2|dp|/(p_new + p_old) <= 1e-12, written without a division
+      conv = 2.0 * fabs(dp) <= 1e-12 * (pn + ps);
+      ps = pn;
+      going = !conv && xm <= 0.0625;
+    }
+    weak = weak && conv && xm <= 0.0625;
+    // star velocity at the converged p* (as gas_riemann)
+    const double us = 0.5 * (uL + uR) + 0.5 * ((fR + dR * dp) - (fL + dL * dp));
+    weak = weak && us * us < 0.81 * fmin(c2L, c2R);
+    const bool left = us >= 0.0;
+    const double pK = left ? pL : pR, ipK = left ? ipL : ipR, rK = left ? rL : rR;
+    const double x = (ps - pK) * ipK;
+    const double R = wave_none(xm > 1.0 / 512.0) ? weak_poly<4>(weak_table(WK_R), x, 5.0 / 7.0)
+                                                 : weak_poly<8>(weak_table(WKW_R), x, 5.0 / 7.0);
+    const double rs = fma(rK * x, R, rK);
+    if (!sup) {
+      ok = ok && weak;
+      last = it;
+      rho = rs; un = us; p = ps;
+      t1 = left ? qL[T1] : qR[T1];
+      t2 = left ? qL[T2] : qR[T2];
+    }
+  }
+  const double en = p * c.inv_gm1 + 0.5 * rho * (un * un + t1 * t1 + t2 * t2);
+  const double m = rho * un;
+  F[4] = m;
+  F[N] = m * un + p;
+  F[T1] = m * t1;
+  F[T2] = m * t2;
+  F[3] = (en + p) * un;
+  return ok;
 }
 
 // Dust face: velocity and density reconstructed whole (no stationary reference); a face
@@ -618,35 +719,33 @@ struct Face32Out {
   int last, maxit;                   // Newton iterations of the solve kept; the most of any
   unsigned fall, vac, resolve, noconv;
 };
-// the same counts of a workgroup
-struct Gas32Count {
+// counts of a workgroup's faces that the general form solved
+struct GasCount {
   unsigned fall, vac, resolve;
-  int noconv, pad;
+  int noconv;
 };
 
 // ------------------------------------------------------------------------------------
 // addressing of a wavefront's row
 
-// Read-only tables by scalar loads: constant address space, for indexes that are the same in
-// every lane of a wavefront.  Only tables that no kernel writes while the reading one runs.
-using ctab = const __attribute__((address_space(4))) double*;
-__device__ __forceinline__ ctab to_ctab(const double* p) { return (ctab)(uintptr_t)p; }
-
-using ctabf = const __attribute__((address_space(4))) float*;
-__device__ __forceinline__ ctabf to_ctabf(const float* p) { return (ctabf)(uintptr_t)p; }
-
 // Element at a lane's index from a pointer that is the same in the whole wavefront.  The
 // pointer passes through a scalar register the optimiser cannot see through: otherwise it
-// keeps one vector address per array across the march (about 30 registers).
+// keeps one vector address per array across the march (about 30 registers).  It stays a
+// pointer to global memory on the way: through a generic one each load would also count as an
+// LDS access, and every wait for an LDS read would wait for the loads from memory with it.
 template <class T>
-__device__ __forceinline__ T& at_row(T* p, unsigned lane) {
-  asm("" : "+s"(p));
-  return *(T*)((uintptr_t)p + (size_t)(lane * (unsigned)sizeof(T)));
+using Global = __attribute__((address_space(1))) T;
+template <class T>
+__device__ __forceinline__ Global<T>& at_row(T* p, unsigned lane) {
+  Global<T>* q = (Global<T>*)(uintptr_t)p;
+  asm("" : "+s"(q));
+  return *(Global<T>*)((uintptr_t)q + (size_t)(lane * (unsigned)sizeof(T)));
 }
 template <class T>
-__device__ __forceinline__ T& at_plane(T* p, size_t off) {
-  asm("" : "+s"(p));
-  return p[off];
+__device__ __forceinline__ Global<T>& at_plane(T* p, size_t off) {
+  Global<T>* q = (Global<T>*)(uintptr_t)p;
+  asm("" : "+s"(q));
+  return q[off];
 }
 
 // ------------------------------------------------------------------------------------
@@ -941,13 +1040,63 @@ __device__ __forceinline__ const double* rco_ptr(const StageArgs& a, int i) {
   return a.t.rco + (size_t)(c + 1) * RC_N;
 }
 
+// Any gas face in FP64: reconstructed states, positivity fallback to the cell-centre state
+// W0(cell) + W'(cell), exact Riemann problem, F* in field order.  Direction dir, stencil
+// cells as dust_face's, the lower one (k, i) (below row 0: i = -1).
+template <bool G75, class Cell>
+__device__ __forceinline__ void gas_face64_general(const StageArgs& a, const GasC& c,
+                                                   const RecC& rc, int dir, int k, int i, Cell cell,
+                                                   double* F, TStat& st) {
+  const double* bB = bg_ptr(a, k, i);
+  const double* bC = dir == 1 ? bB : (dir == 0 ? bg_ptr(a, k, i + 1) : bg_ptr(a, k + 1, i));
+  const double* bf = dir == 1 ? bB
+      : (dir == 0 ? a.t.wr + ((size_t)k * (a.g.nr + 1) + min(i + 1, a.g.nr)) * WB_N
+                  : a.t.wz + ((size_t)(k + 1) * a.g.nr + i) * WB_N);
+  double qL[5], qR[5];
+#pragma unroll
+  for (int f = 0; f < 5; ++f) {
+    if (dir == 0)
+      face_pair<0>(rc, cell(0, f), cell(1, f), cell(2, f), cell(3, f), rco_ptr(a, i),
+                   rco_ptr(a, i + 1), qL[f], qR[f]);
+    else
+      face_pair<1>(rc, cell(0, f), cell(1, f), cell(2, f), cell(3, f), nullptr, nullptr, qL[f], qR[f]);
+    qL[f] = bf[f] + qL[f];
+    qR[f] = bf[f] + qR[f];
+  }
+  if (!(qL[4] > 0.0 && qL[3] > 0.0)) {
+#pragma unroll
+    for (int f = 0; f < 5; ++f) qL[f] = bB[f] + cell(1, f);
+    st.fall++;
+  }
+  if (!(qR[4] > 0.0 && qR[3] > 0.0)) {
+#pragma unroll
+    for (int f = 0; f < 5; ++f) qR[f] = bC[f] + cell(2, f);
+    st.fall++;
+  }
+  // (selects, not indexes: a direction in an index would put the states in memory)
+  auto un = [&](const double* q) { return dir == 0 ? q[0] : dir == 1 ? q[1] : q[2]; };
+  auto t1 = [&](const double* q) { return dir == 0 ? q[1] : q[0]; };
+  auto t2 = [&](const double* q) { return dir == 2 ? q[1] : q[2]; };
+  double fl[5];
+  gas_riemann<G75>(c, qL[4], frcp(qL[4]), un(qL), t1(qL), t2(qL), qL[3], qR[4], frcp(qR[4]), un(qR),
+                   t1(qR), t2(qR), qR[3], fl, st);
+  F[4] = fl[0];
+  F[0] = dir == 0 ? fl[1] : fl[2];
+  F[1] = dir == 1 ? fl[1] : (dir == 0 ? fl[2] : fl[3]);
+  F[2] = dir == 2 ? fl[1] : fl[3];
+  F[3] = fl[4];
+}
+
 // The perturbation Riemann problem at the face in direction dir above cell (k, i) (below row
 // 0: i = -1); faces it cannot take (strong perturbation, transonic fan, no convergence,
 // non-positive face state) are re-solved in FP64 on the full states.
 __device__ __forceinline__ Face32Out gas_face32_general(const StageArgs& a, int dir, int k, int i,
                                                         const Face32& q) {
   const GasC c = gas_consts(1.4, a.g.newton_max);
-  const int N = dir, T1 = dir == 0 ? 1 : 0, T2 = dir == 2 ? 1 : 2;
+  // (selects, as in gas_face64_general)
+  auto un = [&](const auto* v) { return dir == 0 ? v[0] : dir == 1 ? v[1] : v[2]; };
+  auto t1 = [&](const auto* v) { return dir == 0 ? v[1] : v[0]; };
+  auto t2 = [&](const auto* v) { return dir == 2 ? v[1] : v[2]; };
   const double* bB = bg_ptr(a, k, i);
   const double* bC = dir == 1 ? bB : (dir == 0 ? bg_ptr(a, k, i + 1) : bg_ptr(a, k + 1, i));
   const double* bf = dir == 1 ? bB
@@ -958,9 +1107,9 @@ __device__ __forceinline__ Face32Out gas_face32_general(const StageArgs& a, int 
   if (dir == 0) recon32<0>(cell, rco_ptr(a, i), rco_ptr(a, i + 1), qL, qR);
   else recon32<1>(cell, nullptr, nullptr, qL, qR);
   TStat st = {0, 0, 0, 0, 0, 0, 0};
-  const BgW b = {bf[WB_RHO], bf[N], bf[T1], bf[T2], bf[WB_P], bf[WB_C], bf[WB_H]};
-  const PW L = {qL[4], qL[N], qL[T1], qL[T2], qL[3]};
-  const PW R = {qR[4], qR[N], qR[T1], qR[T2], qR[3]};
+  const BgW b = {bf[WB_RHO], un(bf), t1(bf), t2(bf), bf[WB_P], bf[WB_C], bf[WB_H]};
+  const PW L = {qL[4], un(qL), t1(qL), t2(qL), qL[3]};
+  const PW R = {qR[4], un(qR), t1(qR), t2(qR), qR[3]};
   const bool okL = (b.rho + (double)L.rho > 0.0) && (b.p + (double)L.p > 0.0);
   const bool okR = (b.rho + (double)R.rho > 0.0) && (b.p + (double)R.p > 0.0);
   PW W;
@@ -978,8 +1127,8 @@ __device__ __forceinline__ Face32Out gas_face32_general(const StageArgs& a, int 
     if (!okL) st.fall++;
     if (!okR) st.fall++;
     double f64[5];
-    gas_riemann<true>(c, xL[4], frcp(xL[4]), xL[N], xL[T1], xL[T2], xL[3], xR[4], frcp(xR[4]),
-                      xR[N], xR[T1], xR[T2], xR[3], f64, st);
+    gas_riemann<true>(c, xL[4], frcp(xL[4]), un(xL), t1(xL), t2(xL), xL[3], xR[4], frcp(xR[4]),
+                      un(xR), t1(xR), t2(xR), xR[3], f64, st);
     const double m0 = b.rho * b.un;
     fl[0] = (float)(f64[0] - m0);
     fl[1] = (float)(f64[1] - (m0 * b.un + b.p));
@@ -989,9 +1138,9 @@ __device__ __forceinline__ Face32Out gas_face32_general(const StageArgs& a, int 
   }
   Face32Out o;
   o.F[4] = fl[0];
-  o.F[N] = fl[1];
-  o.F[T1] = fl[2];
-  o.F[T2] = fl[3];
+  o.F[0] = dir == 0 ? fl[1] : fl[2];
+  o.F[1] = dir == 1 ? fl[1] : (dir == 0 ? fl[2] : fl[3]);
+  o.F[2] = dir == 2 ? fl[1] : fl[3];
   o.F[3] = fl[4];
   o.last = st.last;
   o.maxit = st.maxit;

@@ -14,320 +14,339 @@ namespace rb {
 // ------------------------------------------------------------------------------------
 // the gas stage kernel (FP64).  The groups of fields interact only through the cell-local drag,
 // which each kernel evaluates from the other group's centre state of the same stage input.
+//
+// Bound by the issue of FP64 instructions (four cycles each) and the latency of the face
+// solves, at two waves per SIMD (256 VGPRs); 1690 -> 1290 lane-instructions per cell by the
+// faces' short form (gas_face64) with the general form behind one inlined copy per plane.
+// LDS holds two planes (161 KB of the CU's 160 KiB = 164 KB, which two waves per SIMD leave
+// free): one barrier per plane, so that a wavefront that ends its faces early goes on with
+// the update, and what the update needs per row is read there in batches (as scalar loads
+// each value waited for its own).  The older wave of a SIMD is served first, so the younger
+// ones end a plane: the first two wavefronts, which solve the tile's edge faces, and the
+// first one's partner take no halo cells.  Gas disc 128 x 256 x 64: 235 -> 150 us per
+// launch (two barriers and scalar loads 194, one barrier 160); bi-fluid disc 256 x 512 x 64,
+// 800 -> 595; 50 steps of the 2D disc 3.32 -> 2.23 ms.
 
 template <int ND, bool G75, bool EXT>
 __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
-  constexpr int NG = 5;
-  using T = double;
-  // a hard error stops the evolution; the flag is read once and broadcast so that the
-  // whole workgroup takes the same branch (other workgroups may set it meanwhile)
   __shared__ int s_stop;
   if (threadIdx.x == 0) s_stop = __atomic_load_n(&a.c.ctrl->status, __ATOMIC_RELAXED);
   __syncthreads();
   if (s_stop & FL_HARD) return;
-  __shared__ T s_pl[NG][TM + 4][TJ + 4];
-  __shared__ T s_ft[NG][TM][TJ + 1];
-  __shared__ T s_fr[NG][TM + 1][TJ];
+  constexpr int NG = 5, HW = TJ + 4, NHALO = 4 * HW + 4 * TM;
+  static_assert(NHALO <= NTM - 3 * 64, "one halo cell per thread");
+  // plane k's W' in the half k & 1; its r faces and the theta faces at the tile's lower edge
+  // likewise (read by the update behind the next barrier); the own theta faces
+  __shared__ double s_pl[2][NG][TM + 4][HW];
+  __shared__ double s_fr[2][NG][TM + 1][TJ];
+  __shared__ double s_fe[2][NG][TM];
+  __shared__ double s_ft[NG][NTM];
+  __shared__ double s_rm[NG][NTM];
   __shared__ double s_red[NTM / 64][3];
-  // FP64 gas: per-thread slots (no sharing) for the column's cell below the current plane
-  // and the flux of the z face below, kept in LDS between their uses (without them the
-  // face solves spill registers); the other kernels keep both in registers
-  __shared__ T s_rm[NG][NTM];
-  __shared__ T s_fz[NG][NTM];
+  // Newton counts of the faces the wavefront owns (bins 0..7, 7: seven or more)
+  __shared__ int s_nh[NTM / 64][8];
+  __shared__ GasCount s_cnt;
+  // per-plane tables: the stationary velocity, pressure and density (NF) at the rows'
+  // centres, r faces and upper z faces; density and velocity at the centres of the rows and
+  // their halo, two planes ahead; the update's conservative state, gravity and residual
+  constexpr int NF = 3, NFACE = (3 * TM + 1) * NF, NCEN = (TM + 4) * 2, NU = 12, NUPD = TM * NU;
+  constexpr int T_CEN = NFACE, T_UPD = T_CEN + NCEN, NTAB = T_UPD + NUPD;
+  static_assert(NTAB <= NTM, "one table entry per thread");
+  __shared__ double s_face[4][NFACE];
+  __shared__ double s_cen[4][NCEN];
+  __shared__ double s_upd[4][NUPD];
+  // per row, the same in every plane: parabola weights of the cells on both sides of the r
+  // face below it (first entry: of the tile's lower edge), geometry of the update
+  __shared__ double s_wt[TM + 1][8];
+  enum { RW_AR0 = 0, RW_AR1, RW_ATH, RW_AZ, RW_V, RW_INVV, RW_INVRC, RW_OMK, RW_N };
+  __shared__ double s_row[TM][RW_N];
 
   const Geo& g = a.g;
-  const GasC gc = gas_consts(g.gamma, g.newton_max);
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int tjb = tile % a.ntj;
   const int tib = (tile / a.ntj) % a.ntm;
   const int kcb = tile / (a.ntj * a.ntm);
-  // one wavefront per radial row (TJ = 64 lanes of a 1D workgroup): the row index is
-  // wavefront-uniform, and saying so puts the per-row tables in scalar registers and
-  // scalar loads (without it the FP64 gas kernel spills)
   const int tid = threadIdx.x, tj = tid & (TJ - 1);
   const int ti = __builtin_amdgcn_readfirstlane(tid / TJ);
   const int j0 = tjb * TJ, i0 = tib * TM;
   const int k0 = kcb * a.tk, k1 = min(g.nz, k0 + a.tk);
   const int jg = j0 + tj;
-  const int jw = jg % g.nth;
-  const int ig = i0 + ti;
+  const int ig = i0 + ti, igc = min(ig, g.nr - 1);
   const bool act = jg < g.nth && ig < g.nr;
-  const int igc = min(ig, g.nr - 1);
   const bool drag = !a.gas_only && ND > 0 && !g.drag_exact;
-  const void* in = a.in;
-  const double dt = a.dt_idx >= 0 ? a.c.dtlog[a.dt_idx] : 0.0;
-
-  TStat st = {0, 0, 0, 0, 0, 0, 0};
-  // histogram of the Newton iteration counts (bins 0..7, 7: seven or more) over the
-  // faces the thread owns (each face of the mesh is owned by one thread of the launch),
-  // 16 bits a bin in LDS slots private to the thread; a thread owns at most 4 faces per
-  // plane and one more
-  __shared__ unsigned s_nh[4][NTM];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) s_nh[q][tid] = 0u;
-  auto tally = [&](bool own) {
-    const int b = min(st.last, 7);
-    if (own) s_nh[b >> 1][tid] += 1u << (16 * (b & 1));
+  const bool twod = g.twod != 0;
+  const size_t plane = (size_t)g.nr * g.nth;
+  const GasC gc = gas_consts(g.gamma, g.newton_max);
+  const RecC recc;
+  // columns past the grid and their slots: as k_dust
+  const int wcols = min(TJ, g.nth - j0);
+  const unsigned jl = min(tj, wcols - 1);
+  const bool centre = (unsigned)(tj - wcols) >= 2u;
+  const size_t row0 = (size_t)igc * g.nth + j0;
+  const ctab rt = to_ctab(a.t.rt) + (size_t)igc * RT_N, ar = to_ctab(a.t.ar);
+  if (tid < (TM + 1) * 8) {
+    const int r = tid / 8, e = tid % 8, i = min(i0 + r - 1 + (e < 4 ? 0 : 1), g.nr);
+    // (RC_WPM .. RC_LPP of the lower cell, RC_WMM .. RC_LMP of the upper)
+    s_wt[r][e] = a.t.rco[(size_t)(i + 1) * RC_N + e];
+  } else if (tid >= 128 && tid < 128 + TM * RW_N) {
+    const int r = (tid - 128) / RW_N, e = (tid - 128) % RW_N, i = min(i0 + r, g.nr - 1);
+    const double* q = a.t.rt + (size_t)i * RT_N;
+    s_row[r][e] = e == RW_AR0   ? a.t.ar[i]
+                  : e == RW_AR1 ? a.t.ar[i + 1]
+                  : e == RW_ATH ? q[RT_ATH]
+                  : e == RW_AZ  ? q[RT_AZ]
+                  : e == RW_V   ? q[RT_V]
+                  : e == RW_INVV ? q[RT_INVV]
+                  : e == RW_INVRC ? q[RT_INVRC]
+                                  : q[RT_OMK];
+  } else if (tid >= 256 && tid < 256 + NTM / 64 * 8) {
+    s_nh[(tid - 256) / 8][tid & 7] = 0;
+  }
+  if (tid == 0) s_cnt = GasCount{0, 0, 0, 0};
+  int maxit = 0;
+  auto tally = [&](bool own, int last) {
+    const int b = min(last, 7);
+    unsigned long long left = __ballot(own);
+    while (left) {
+      const int at = __builtin_ctzll(left), v = __builtin_amdgcn_readlane(b, at);
+      const unsigned long long mk = __ballot(own && b == v);
+      if (tj == at) atomicAdd(&s_nh[ti][v], __popcll(mk));
+      left &= ~mk;
+    }
   };
 
-  // The per-plane tables of the tile's rows, staged in LDS one plane ahead (double
-  // buffered): the stationary flow at the cell centres (wc), at the r
-  // faces i0-1/2 .. i0+TM-1/2 (wr) and the z face above the plane (wz); the cells'
-  // stationary conservative state (bgc) and gravity.  Thread t stages entry t: its
-  // address is tab_p0 + plane * tab_stride.
-  constexpr int T_WC = 0;
-  constexpr int T_WR = T_WC + TM * WB_N;
-  constexpr int T_WZ = T_WR + (TM + 1) * WB_N;
-  constexpr int T_BG = T_WZ + TM * WB_N;
-  constexpr int T_GR = T_BG + TM * 5;
-  constexpr int NTAB = T_GR + TM * 2;
-  static_assert(NTAB <= NTM, "one table entry per thread");
-  __shared__ double s_tab[2][NTAB];
-  const bool tab_t = tid < NTAB;
-  const double* tab_p0 = nullptr;
+  // thread NTM - 1 - t stages table entry t: tab_p + plane * tab_stride (the tile's edge faces
+  // are the first wavefronts')
+  const int tt = NTM - 1 - tid;
+  const double* tab_p = nullptr;
   size_t tab_stride = 0;
-  if (tab_t) {
+  if (tt < NTAB) {
     const size_t nr = (size_t)g.nr;
-    if (tid < T_WR) {
-      const int r = tid / WB_N, e = tid % WB_N;
-      tab_p0 = a.t.wc + (size_t)min(i0 + r, g.nr - 1) * WB_N + e;
+    // (entry e of a face: velocity, pressure, density)
+    if (tt < NFACE) {
+      const int r = tt / NF, e = tt % NF == 0 ? WB_V : WB_W + tt % NF;
+      if (r < TM) {
+        tab_p = a.t.wc + (size_t)min(i0 + r, g.nr - 1) * WB_N + e;
+        tab_stride = nr * WB_N;
+      } else if (r < 2 * TM + 1) {
+        tab_p = a.t.wr + (size_t)min(i0 + r - TM, g.nr) * WB_N + e;
+        tab_stride = (nr + 1) * WB_N;
+      } else {
+        tab_p = a.t.wz + (nr + (size_t)min(i0 + r - 2 * TM - 1, g.nr - 1)) * WB_N + e;
+        tab_stride = nr * WB_N;
+      }
+    } else if (tt < T_UPD) {
+      const int r = (tt - T_CEN) / 2, e = (tt - T_CEN) % 2 ? WB_V : WB_RHO;
+      tab_p = a.t.wc + (size_t)min(max(i0 + r - 2, 0), g.nr - 1) * WB_N + e;
       tab_stride = nr * WB_N;
-    } else if (tid < T_WZ) {
-      const int f = (tid - T_WR) / WB_N, e = (tid - T_WR) % WB_N;
-      tab_p0 = a.t.wr + (size_t)min(i0 + f, g.nr) * WB_N + e;
-      tab_stride = (nr + 1) * WB_N;
-    } else if (tid < T_BG) {
-      const int r = (tid - T_WZ) / WB_N, e = (tid - T_WZ) % WB_N;
-      tab_p0 = a.t.wz + (nr + (size_t)min(i0 + r, g.nr - 1)) * WB_N + e;
-      tab_stride = nr * WB_N;
-    } else if (tid < T_GR) {
-      const int r = (tid - T_BG) / 5, e = (tid - T_BG) % 5;
-      tab_p0 = a.t.bgc + (size_t)min(i0 + r, g.nr - 1) * 5 + e;
-      tab_stride = nr * 5;
     } else {
-      const int r = (tid - T_GR) / 2, e = (tid - T_GR) % 2;
-      tab_p0 = a.t.grav + (size_t)min(i0 + r, g.nr - 1) * 2 + e;
-      tab_stride = nr * 2;
+      const int r = (tt - T_UPD) / NU, e = (tt - T_UPD) % NU;
+      const size_t i = min(i0 + r, g.nr - 1);
+      if (e < 5) { tab_p = a.t.bgc + i * 5 + e; tab_stride = nr * 5; }
+      else if (e < 7) { tab_p = a.t.grav + i * 2 + (e - 5); tab_stride = nr * 2; }
+      else { tab_p = a.t.r0 + i * 5 + (e - 7); tab_stride = nr * 5; }
     }
   }
-  double dtmin = 1e300;
-  // the largest signal speed of the thread's new cells.  The thread's
-  // row (so its volume and largest face area) is fixed, and the CFL bound decreases with
-  // the speed, so the bound of the largest speed, formed once after the march, is the
-  // smallest one
-  double smax = 0.0;
-  double tsmin = 1e300;  // smallest stopping time of the new state (drag law 1)
-  double ledger = 0.0;
+  const bool cen_t = tt >= T_CEN && tt < T_UPD;
+  auto tab_load = [&](int k) {  // (the centres' entries: of plane k + 2)
+    return tt < NTAB ? tab_p[(size_t)min(cen_t ? k + 2 : k, g.nz - 1) * tab_stride] : 0.0;
+  };
+  auto tab_store = [&](int k, double x) {
+    if (tt < NFACE) s_face[k & 3][tt] = x;
+    else if (tt < T_UPD) s_cen[(k + 2) & 3][tt - T_CEN] = x;
+    else if (tt < NTAB) s_upd[k & 3][tt - T_UPD] = x;
+  };
 
-  const double* rt = a.t.rt + (size_t)igc * RT_N;
-  const double Vc = rt[RT_V], invV = rt[RT_INVV], Ath = rt[RT_ATH], Az = rt[RT_AZ];
-  const double invrc = rt[RT_INVRC], omk = rt[RT_OMK], maxA = rt[RT_MAXA];
-  const double Arlo = a.t.ar[igc], Arhi = a.t.ar[igc + 1];
-  const double Ar0 = a.t.ar[0];  // inner boundary face (ledger)
+  const double* vin = (const double*)a.in;
+  struct Raw { double e[NG]; };
+  auto col_fetch = [&](const double* v, int k, Raw& R) {
+    const size_t r = (size_t)min(max(k, 0), g.nz - 1) * plane + row0;
+#pragma unroll
+    for (int f = 0; f < NG; ++f) R.e[f] = at_row(v + (size_t)f * g.N + r, jl);
+  };
+  // W' of a cell with stationary density and azimuthal velocity c (no other velocity)
+  const double gm1 = g.gamma - 1.0;
+  auto form = [&](const double* e, const double* c, double* out) {
+    const double b[WB_N] = {0.0, c[1], 0.0, 0.0, c[0], 0.0, 0.0, 0.0};
+    cell_w(e, b, gm1, out);
+  };
+  // W' of the thread's cell of plane k, or of the ghost in its place
+  auto col_form = [&](int k, const Raw& R, const double* c, double* out) {
+    if (EXT && g.bc_z == 1 && (k < 0 || k >= g.nz)) {
+      const size_t e = (size_t)((k < 0 ? 0 : 2) + min(k < 0 ? -1 - k : k - g.nz, 1)) * g.nr + igc;
+      double s[NG];
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s[f] = R.e[f] * a.t.ozr[e];
+      cell_w(s, a.t.ghzw + e * WB_N, gm1, out);
+    } else if (k < 0 || k >= g.nz) {
+      const size_t l = (k < 0 ? 0 : 2) + min(k < 0 ? -1 - k : k - g.nz, 1);
+      const ctab gt = to_ctab(a.t.ghz) + (l * g.nr + igc) * g.nf;
+#pragma unroll
+      for (int f = 0; f < NG; ++f) out[f] = gt[f];
+    } else if (ig >= g.nr) {
+      const ctab gt = to_ctab(a.t.ghr) + ((size_t)(2 + min(ig - g.nr, 1)) * g.nz + k) * g.nf;
+#pragma unroll
+      for (int f = 0; f < NG; ++f) out[f] = gt[f];
+    } else {
+      form(R.e, c, out);
+    }
+  };
+  auto cen = [&](int k, int row) { return &s_cen[k & 3][row * 2]; };
+  // (not by the first two wavefronts, which solve the tile's edge faces, nor by the fifth, on
+  // the first one's SIMD)
+  const int th = ti < 2 || ti == 4 ? -1 : tid - (ti < 4 ? 2 : 3) * 64;
+  const bool halo_t = th >= 0 && th < NHALO;
+  int h_rr = 0, h_cc = 0;
+  if (!halo_t) {}
+  else if (th < 2 * HW) { h_rr = th / HW; h_cc = th % HW; }
+  else if (th < 4 * HW) { h_rr = TM + 2 + (th - 2 * HW) / HW; h_cc = (th - 2 * HW) % HW; }
+  else if (halo_t) { const int e = th - 4 * HW; h_rr = 2 + e / 4; h_cc = (e & 3) < 2 ? (e & 3) : wcols + (e & 3); }
+  int h_pad = 0;
+  if (th >= 4 * HW && wcols < TJ && h_cc > 1 && TJ + (th & 3) > wcols + 3) h_pad = TJ + (th & 3);
+  const int h_ii = i0 + h_rr - 2;
+  const size_t h_off = (size_t)min(max(h_ii, 0), g.nr - 1) * g.nth + (j0 + h_cc - 2 + g.nth) % g.nth;
+  auto halo_fetch = [&](int k, Raw& R) {
+#pragma unroll
+    for (int f = 0; f < NG; ++f) R.e[f] = at_plane(vin + (size_t)f * g.N + (size_t)k * plane, h_off);
+  };
+  auto halo_store = [&](int k, const Raw& R) {
+    double w[NG];
+    if (h_ii < 0 || h_ii >= g.nr) {
+      const int side = h_ii < 0 ? 0 : 1, layer = min(h_ii < 0 ? -1 - h_ii : h_ii - g.nr, 1);
+      const double* gt = a.t.ghr + ((size_t)(side * 2 + layer) * g.nz + k) * g.nf;
+#pragma unroll
+      for (int f = 0; f < NG; ++f) w[f] = gt[f];
+    } else {
+      form(R.e, cen(k, h_rr), w);
+    }
+#pragma unroll
+    for (int f = 0; f < NG; ++f) s_pl[k & 1][f][h_rr][h_cc] = w[f];
+    if (h_pad) {
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_pl[k & 1][f][h_rr][h_pad] = w[f];
+    }
+  };
 
-  // gas face: the cells' reconstructed variables, the stationary flow at the face (bf) and at the
-  // centres of the two cells next to it (bB, bC: the positivity fallback)
-  auto face = [&](auto dirc, const T* wA, const T* wB, const T* wC, const T* wD, const double* coB,
-                  const double* coC, const double* bf, const double* bB, const double* bC, T* F) {
+  // a face by the short form (bp: the stationary velocity, pressure and density there), with
+  // its Newton count tallied if the thread owns it; returns false where the general form has
+  // to solve it.  (k, i): the lower cell.  Without gamma = 7/5 the general form at once
+  auto general = [&](int dir, auto cell, int k, int i, bool own, double* F) {
+    TStat st = {0, 0, 0, 0, 0, 0, 0};
+    gas_face64_general<G75>(a, gc, recc, dir, k, i, cell, F, st);
+    maxit = max(maxit, st.maxit);
+    tally(own, st.last);
+    if (st.fall) atomicAdd(&s_cnt.fall, (unsigned)st.fall);
+    if (st.vac) atomicAdd(&s_cnt.vac, (unsigned)st.vac);
+    if (st.noconv) atomicMax(&s_cnt.noconv, 1);
+  };
+  // (co: the weights of the cells on both sides)
+  auto face = [&](auto dirc, auto cell, const double* co, const double* bp, int k, int i, bool own,
+                  double* F) {
     constexpr int D = decltype(dirc)::value;
-    gas_face<D, G75>(gc, wA, wB, wC, wD, coB, coC, bf, bB, bC, F, st);
+    if constexpr (!G75) {
+      general(D, cell, k, i, own, F);
+      return true;
+    } else {
+      double qL[NG], qR[NG];
+#pragma unroll
+      for (int f = 0; f < NG; ++f) {
+        face_pair<D>(recc, cell(0, f), cell(1, f), cell(2, f), cell(3, f), co, co, qL[f], qR[f]);
+        if (f == 1 || f > 2) {
+          qL[f] = bp[f == 1 ? 0 : f - 2] + qL[f];
+          qR[f] = bp[f == 1 ? 0 : f - 2] + qR[f];
+        }
+      }
+      int last = 0;
+      const bool ok = gas_face64<D>(gc, qL, qR, F, last);
+      if (ok) maxit = max(maxit, last);
+      tally(own && ok, last);
+      return ok;
+    }
   };
   using DR = std::integral_constant<int, 0>;
   using DT = std::integral_constant<int, 1>;
   using DZ = std::integral_constant<int, 2>;
+  double smax = 0.0, tsmin = 1e300, ledger = 0.0;
 
-  // z ring of the thread's column: e_{k-1}, e_k, e_{k+1}, e_{k+2}; fluxes below/above k
-  T rm[NG], r0[NG], rp[NG], rn[NG], fzlo[NG], fzhi[NG];
-  const int tslot = threadIdx.x;
-  const bool twod = g.twod != 0;
-  if (!twod) {
-    T e2[NG];
-    load_recon<false, EXT, NG>(a, in, 0, k0 - 2, ig, jw, e2);
-    load_recon<false, EXT, NG>(a, in, 0, k0 - 1, ig, jw, rm);
-    load_recon<false, EXT, NG>(a, in, 0, k0, ig, jw, r0);
-    load_recon<false, EXT, NG>(a, in, 0, k0 + 1, ig, jw, rp);
-    const double* bf = a.t.wz + ((size_t)k0 * g.nr + igc) * WB_N;
-    face(DZ(), e2, rm, r0, rp, nullptr, nullptr, bf, bg_ptr(a, k0 - 1, igc), bg_ptr(a, k0, igc),
-         fzlo);
-    tally(act && k0 == 0);
-    if (a.second && k0 == 0 && act) {
-      double fm = (double)fzlo[NG - 1];
-      ledger -= Az * fm;
-    }
-    {
+  tab_store(k0, tab_load(k0));
+  for (int p = k0 - 2; p < k0; ++p)
+    if (cen_t) tab_store(p, tab_load(p));
+  __syncthreads();
+  double rp[NG], fzlo[NG];
+  {
+    Raw R;
+    double r0[NG];
+    // (planes below k0 are not in the ring of centre entries)
+    auto form_at = [&](int k, double* out) {
+      const ctab c = to_ctab(a.t.wc) + ((size_t)min(max(k, 0), g.nz - 1) * g.nr + igc) * WB_N;
+      const double cf[2] = {c[WB_RHO], c[WB_V]};
+      col_fetch(vin, k, R);
+      col_form(k, R, cf, out);
+    };
+    if (!twod) {
+      double e2[NG], rm[NG];
+      form_at(k0 - 2, e2);
+      form_at(k0 - 1, rm);
+      form_at(k0, r0);
+      form_at(k0 + 1, rp);
+      const ctab c = to_ctab(a.t.wz) + ((size_t)k0 * g.nr + igc) * WB_N;
+      const double bp[NF] = {c[WB_V], c[WB_P], c[WB_RHO]};
+      auto get = [&](int s, int f) { return s == 0 ? e2[f] : s == 1 ? rm[f] : s == 2 ? r0[f] : rp[f]; };
+      if (!face(DZ(), get, nullptr, bp, k0 - 1, igc, act && k0 == 0, fzlo))
+        general(2, get, k0 - 1, igc, act && k0 == 0, fzlo);
+      if (a.second && k0 == 0 && act) ledger -= rt[RT_AZ] * fzlo[4];
 #pragma unroll
-      for (int f = 0; f < NG; ++f) { s_rm[f][tslot] = rm[f]; s_fz[f][tslot] = fzlo[f]; }
-    }
-  } else {
-    load_recon<false, EXT, NG>(a, in, 0, 0, ig, jw, r0);
+      for (int f = 0; f < NG; ++f) s_rm[f][tid] = rm[f];
+    } else {
+      form_at(0, r0);
 #pragma unroll
-    for (int f = 0; f < NG; ++f) {
-      rm[f] = T(0); rp[f] = T(0); rn[f] = T(0); fzlo[f] = T(0); fzhi[f] = T(0);
+      for (int f = 0; f < NG; ++f) { rp[f] = 0.0; fzlo[f] = 0.0; }
+    }
+    if (centre) {
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_pl[k0 & 1][f][ti + 2][tj + 2] = r0[f];
+    }
+    if (halo_t) {
+      halo_fetch(k0, R);
+      halo_store(k0, R);
     }
   }
+  const double dt = a.dt_idx >= 0 ? a.c.dtlog[a.dt_idx] : 0.0;
 
-  // the halo ring of the LDS plane: two rows below and above the tile, then two columns
-  // on each side of its rows; slot tid, loaded one plane ahead, so that the latency hides
-  // behind the previous plane's face solves
-  constexpr int HW = TJ + 4, NHALO = 4 * HW + 4 * TM;
-  static_assert(NHALO <= NTM, "one halo cell per thread");
-  const bool halo_t = tid < NHALO;
-  int h_rr = 0, h_cc = 0;
-  if (tid < 2 * HW) { h_rr = tid / HW; h_cc = tid % HW; }
-  else if (tid < 4 * HW) { h_rr = TM + 2 + (tid - 2 * HW) / HW; h_cc = (tid - 2 * HW) % HW; }
-  else if (halo_t) { const int e = tid - 4 * HW; h_rr = 2 + e / 4; h_cc = (e & 3) < 2 ? (e & 3) : TJ + (e & 3); }
-  const int h_ii = i0 + h_rr - 2;
-  const int h_jj = (j0 + h_cc - 2 + g.nth) % g.nth;
-  T hv[NG];
-  if (halo_t) load_recon<false, EXT, NG>(a, in, 0, k0, h_ii, h_jj, hv);
-
-  if (tab_t) s_tab[k0 & 1][tid] = tab_p0[(size_t)k0 * tab_stride];
-  // the radial parabola weights and limiter bounds of rows i0-1 .. i0+TM (plane
-  // invariant), read by the r faces
-  __shared__ double s_rco[(TM + 2) * RC_N];
-  if (tid < (TM + 2) * RC_N) s_rco[tid] = rco_ptr(a, i0 - 1 + tid / RC_N)[tid % RC_N];
-
-  // every load of the set-up done before the march: a load still in flight at the loop's
-  // entry makes the compiler wait for all memory operations at the top of every plane,
-  // the previous plane's stores included
-  __builtin_amdgcn_s_waitcnt(0);
-  for (int k = k0; k < k1; ++k) {
-    if (!twod) {
-      load_recon<false, EXT, NG>(a, in, 0, k + 2, ig, jw, rn);
-    }
-    const int kb = k & 1;
+  // One barrier per plane: behind the one that ends plane k the update of plane k - 1 and, in
+  // the other half of the LDS arrays, the faces of plane k.
+  const double* row = s_row[ti];
+  Raw base;
+  double dvar[ND > 0 ? ND : 1][4], dz[NG];
+  for (int kk = k0;; ++kk) {
+    __syncthreads();
+    // the column's cell kk+2 and the next plane's halo and tables
+    const bool more = kk + 1 < k1;
+    Raw nraw, hraw;
     double tab_next = 0.0;
-    if (tab_t && k + 1 < k1) tab_next = tab_p0[(size_t)(k + 1) * tab_stride];
-    // the update's base values of this plane's cell, requested here so that their latency
-    // hides behind the face solves (raw stored values: any arithmetic on them here would wait
-    // for the loads)
-    const size_t cell = ((size_t)k * g.nr + ig) * g.nth + jg;
-    const size_t cellw = ((size_t)k * g.nr + igc) * g.nth + jw;
-    const bool upd = a.mode == MODE_UPDATE && act;
-    T pb[NG];
-    auto load_base = [&]() {
-      if (upd) {
-#pragma unroll
-        for (int f = 0; f < NG; ++f) pb[f] = ((const T*)a.base)[(size_t)f * g.N + cell];
-      }
-    };
-    load_base();
-    // ---- stage the plane (with halo) in LDS
-#pragma unroll
-    for (int f = 0; f < NG; ++f) s_pl[f][ti + 2][tj + 2] = r0[f];
-    if (halo_t) {
-#pragma unroll
-      for (int f = 0; f < NG; ++f) s_pl[f][h_rr][h_cc] = hv[f];
-      if (k + 1 < k1) load_recon<false, EXT, NG>(a, in, 0, k + 1, h_ii, h_jj, hv);
+    col_fetch(vin, kk + 2, nraw);
+    if (more) {
+      if (halo_t) halo_fetch(kk + 1, hraw);
+      tab_next = tab_load(kk + 1);
     }
-    __syncthreads();
-    // ---- theta face j+1/2 and r face i+1/2 of this cell
-    {
-      T eA[NG], eB[NG], eC[NG], eD[NG], F[NG];
-#pragma unroll
-      for (int f = 0; f < NG; ++f) {
-        eA[f] = s_pl[f][ti + 2][tj + 1]; eB[f] = s_pl[f][ti + 2][tj + 2];
-        eC[f] = s_pl[f][ti + 2][tj + 3]; eD[f] = s_pl[f][ti + 2][tj + 4];
+    if (kk > k0) {
+      const int k = kk - 1;
+      // boundary outflow ledger
+      if (a.second && act) {
+        if (ig == g.nr - 1) ledger += row[RW_AR1] * s_fr[k & 1][4][ti + 1][tj];
+        if (ig == 0) ledger -= row[RW_AR0] * s_fr[k & 1][4][0][tj];
+        if (!twod && k == g.nz - 1) ledger += row[RW_AZ] * fzlo[4];
       }
-      {
-        const double* bf = &s_tab[kb][T_WC + ti * WB_N];
-        face(DT(), eA, eB, eC, eD, nullptr, nullptr, bf, bf, bf, F);
-        tally(act);
-      }
+      // ---- divergence -sum_s A_s F.n_s (Sect. 2.2), sources (App. B), drag (Sect. 2.9)
+      double r0[NG];
 #pragma unroll
-      for (int f = 0; f < NG; ++f) s_ft[f][ti][tj + 1] = F[f];
-#pragma unroll
-      for (int f = 0; f < NG; ++f) {
-        eA[f] = s_pl[f][ti + 1][tj + 2]; eB[f] = s_pl[f][ti + 2][tj + 2];
-        eC[f] = s_pl[f][ti + 3][tj + 2]; eD[f] = s_pl[f][ti + 4][tj + 2];
-      }
-      {
-        const double* bf = &s_tab[kb][T_WR + (ti + 1) * WB_N];
-        face(DR(), eA, eB, eC, eD, &s_rco[(ti + 1) * RC_N], &s_rco[(ti + 2) * RC_N], bf,
-             bg_ptr(a, k, min(ig, g.nr)), bg_ptr(a, k, min(ig + 1, g.nr)), F);
-        tally(act);
-        if (a.second && act && ig == g.nr - 1) {
-          double fm = (double)F[NG - 1];
-          ledger += Arhi * fm;
-        }
-      }
-#pragma unroll
-      for (int f = 0; f < NG; ++f) s_fr[f][ti + 1][tj] = F[f];
-    }
-    // ---- lower-edge faces of the tile: r face i0-1/2 (threads 0..63) and theta face
-    //      j0-1/2 of each row (threads 64..71)
-    if (tid < TJ) {
-      T eA[NG], eB[NG], eC[NG], eD[NG], F[NG];
-      const int col = tid;
-#pragma unroll
-      for (int f = 0; f < NG; ++f) {
-        eA[f] = s_pl[f][0][col + 2]; eB[f] = s_pl[f][1][col + 2];
-        eC[f] = s_pl[f][2][col + 2]; eD[f] = s_pl[f][3][col + 2];
-      }
-      const double* bf = &s_tab[kb][T_WR];
-      face(DR(), eA, eB, eC, eD, &s_rco[0], &s_rco[RC_N], bf, bg_ptr(a, k, i0 - 1),
-           bg_ptr(a, k, i0), F);
-      // the tile's lower r face is the upper face of the tile below, except at the inner
-      // boundary
-      tally(i0 == 0 && j0 + col < g.nth);
-#pragma unroll
-      for (int f = 0; f < NG; ++f) s_fr[f][0][col] = F[f];
-      if (a.second && i0 == 0 && j0 + col < g.nth) {
-        double fm = (double)F[NG - 1];
-        ledger -= Ar0 * fm;
-      }
-    } else if (tid < TJ + TM) {
-      T eA[NG], eB[NG], eC[NG], eD[NG], F[NG];
-      const int row = tid - TJ;
-#pragma unroll
-      for (int f = 0; f < NG; ++f) {
-        eA[f] = s_pl[f][row + 2][0]; eB[f] = s_pl[f][row + 2][1];
-        eC[f] = s_pl[f][row + 2][2]; eD[f] = s_pl[f][row + 2][3];
-      }
-      const double* bf = &s_tab[kb][T_WC + row * WB_N];
-      face(DT(), eA, eB, eC, eD, nullptr, nullptr, bf, bf, bf, F);
-#pragma unroll
-      for (int f = 0; f < NG; ++f) s_ft[f][row][0] = F[f];
-    }
-    // ---- z face k+1/2 from the register ring
-    if (!twod) {
-      {
-#pragma unroll
-        for (int f = 0; f < NG; ++f) rm[f] = s_rm[f][tslot];
-      }
-      const double* bf = &s_tab[kb][T_WZ + ti * WB_N];
-      face(DZ(), rm, r0, rp, rn, nullptr, nullptr, bf, bg_ptr(a, k, igc), bg_ptr(a, k + 1, igc),
-           fzhi);
-      tally(act);
-      if (a.second && act && k == g.nz - 1) {
-        double fm = (double)fzhi[NG - 1];
-        ledger += Az * fm;
-      }
-    }
-    __syncthreads();
-    // ---- the next plane's tables (read after the next plane's first barrier; buffer
-    //      (k + 1) & 1 was last read before this plane's first barrier), before this plane's
-    //      stores, so that waiting for them waits for no store
-    if (tab_t && k + 1 < k1) s_tab[(k + 1) & 1][tid] = tab_next;
-    // ---- divergence -sum_s A_s F.n_s (Sect. 2.2), sources (App. B), drag (Sect. 2.9)
-    T Gd[NG];
-#pragma unroll
-    for (int f = 0; f < NG; ++f) {
-      T dr = T(Arhi) * s_fr[f][ti + 1][tj] - T(Arlo) * s_fr[f][ti][tj];
-      T dth = T(Ath) * (s_ft[f][ti][tj + 1] - s_ft[f][ti][tj]);
-      T dz = twod ? T(0) : T(Az) * (fzhi[f] - s_fz[f][tslot]);
-      Gd[f] = -((dr + dth) + dz);
-    }
-    const double gr = s_tab[kb][T_GR + ti * 2 + 0];
-    const double gz = s_tab[kb][T_GR + ti * 2 + 1];
-    const double* bgc = &s_tab[kb][T_BG + ti * 5];
-    const double* bw = &s_tab[kb][T_WC + ti * WB_N];
-    T S[NG];
-    {
+      for (int f = 0; f < NG; ++f) r0[f] = s_pl[k & 1][f][ti + 2][tj + 2];
+      const double *upd = &s_upd[k & 3][ti * NU], *fc = &s_face[k & 3][ti * NF];
       // the cell's primitives: stationary flow + W'
-      const double rho = bw[WB_RHO] + r0[4];
-      const double u = bw[WB_U] + r0[0], v = bw[WB_V] + r0[1], w = bw[WB_W] + r0[2];
-      const double p = bw[WB_P] + r0[3];
+      const double rho = fc[2] + r0[4], p = fc[1] + r0[3];
+      const double u = r0[0], v = fc[0] + r0[1], w = r0[2];
+      const double invrc = row[RW_INVRC], gr = upd[5], gz = upd[6];
+      double S[NG];
       S[0] = (rho * v * v + p) * invrc + rho * gr;
       S[1] = -(rho * u * v) * invrc;
       S[2] = rho * gz;
@@ -335,24 +354,17 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
       S[4] = 0.0;
       if (drag) {
         double dx = 0.0, dy = 0.0, dzz = 0.0;
-        // every species' variables requested together (loads made conditional on the
-        // density would each wait for it)
-        double dvar[ND > 0 ? ND : 1][4];
-#pragma unroll
-        for (int s2 = 0; s2 < ND; ++s2)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) dvar[s2][c] = ld_cell<false>(a, in, 5 + 4 * s2 + c, k, igc, cellw);
 #pragma unroll
         for (int s2 = 0; s2 < ND; ++s2) {
           const double rd = dvar[s2][3];
           double ud = 0.0, vd = 0.0, wd = 0.0;
           if (rd > 0.0) {
-            double id = 1.0 / rd;
+            const double id = 1.0 / rd;
             ud = dvar[s2][0] * id;
             vd = dvar[s2][1] * id;
             wd = dvar[s2][2] * id;
           }
-          const double its = inv_tstop<EXT>(g, s2, omk, rho, p);
+          const double its = inv_tstop<EXT>(g, s2, row[RW_OMK], rho, p);
           dx += rd * (ud - u) * its;
           dy += rd * (vd - v) * its;
           dzz += rd * (wd - w) * its;
@@ -362,108 +374,210 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
         S[2] += dzz;
         S[3] += u * dx + v * dy + w * dzz;
       }
-    }
-    // indirect gravity (Sect. 2.10): minus the star's acceleration by the disc
-    if (EXT && g.indirect && a.mode != MODE_RESID) {
-      const double A = a.t.indab[0], B = a.t.indab[1];
-      const double cs = a.t.trig[jw], sn = a.t.trig[g.nth + jw];
-      const double ar = -g.GM * (A * cs + B * sn), at = -g.GM * (B * cs - A * sn);
-      const double rho = bw[WB_RHO] + (double)r0[4];
-      const double mr = rho * (bw[WB_U] + (double)r0[0]), mt = rho * (bw[WB_V] + (double)r0[1]);
-      S[0] += (T)(rho * ar);
-      S[1] += (T)(rho * at);
-      S[3] += (T)(mr * ar + mt * at);
-    }
-    // boundary damping zones (Sect. 2.4): the gas deviation relaxes to the stationary flow
-    if (EXT && g.damp) {
-      const double kd = a.t.damp[(size_t)k * g.nr + igc];
-      double e[NG];
-      load_cons<false, NG>(a, in, 0, k, igc, jw, e);
-#pragma unroll
-      for (int f = 0; f < NG; ++f) S[f] -= (T)(kd * e[f]);
-    }
-    T Gt[NG];
-#pragma unroll
-    for (int f = 0; f < NG; ++f) Gt[f] = fma(S[f], T(Vc), Gd[f]);
-    if (a.mode != MODE_RESID) {
-      const double* R0 = a.t.r0 + ((size_t)k * g.nr + igc) * 5;
-#pragma unroll
-      for (int f = 0; f < NG; ++f) Gt[f] -= (T)R0[f];
-    }
-    if (a.mode == MODE_RESID) {
-      if (act && jg == 0) {
-#pragma unroll
-        for (int f = 0; f < NG; ++f) a.c.r0w[((size_t)k * g.nr + ig) * 5 + f] = (double)Gt[f];
+      // indirect gravity (Sect. 2.10): minus the star's acceleration by the disc
+      if (EXT && g.indirect && a.mode != MODE_RESID) {
+        const double A = a.t.indab[0], B = a.t.indab[1];
+        const double cs = a.t.trig[j0 + jl], sn = a.t.trig[g.nth + j0 + jl];
+        const double acr = -g.GM * (A * cs + B * sn), act_ = -g.GM * (B * cs - A * sn);
+        S[0] += rho * acr;
+        S[1] += rho * act_;
+        S[3] += rho * u * acr + rho * v * act_;
       }
-    } else if (a.mode == MODE_OPER) {
-      if (act) {
+      // boundary damping zones (Sect. 2.4): the gas deviation relaxes to the stationary flow
+      if (EXT && g.damp) {
+        const double kd = a.t.damp[(size_t)k * g.nr + igc];
+        Raw e;
+        col_fetch(vin, k, e);
+#pragma unroll
+        for (int f = 0; f < NG; ++f) S[f] -= kd * e.e[f];
+      }
+      // (every face and the residual read first, in one batch)
+      const double *r_hi = &s_fr[k & 1][0][ti + 1][tj], *r_lo = &s_fr[k & 1][0][ti][tj];
+      const double *t_lo = tj ? &s_ft[0][tid - 1] : &s_fe[k & 1][0][ti];
+      const int t_st = tj ? NTM : TM;
+      double Gt[NG], res[NG];
+#pragma unroll
+      for (int f = 0; f < NG; ++f) res[f] = upd[7 + f];
+      const double ar0 = row[RW_AR0], ar1 = row[RW_AR1], ath = row[RW_ATH], vol = row[RW_V];
+#pragma unroll
+      for (int f = 0; f < NG; ++f) {
+        const double dr = ar1 * r_hi[f * (TM + 1) * TJ] - ar0 * r_lo[f * (TM + 1) * TJ];
+        const double dth = ath * (s_ft[f][tid] - t_lo[f * t_st]);
+        Gt[f] = fma(S[f], vol, -((dr + dth) + dz[f]));
+        Gt[f] -= a.mode != MODE_RESID ? res[f] : 0.0;
+      }
+      if (a.mode == MODE_RESID) {
+        if (act && jg == 0) {
+#pragma unroll
+          for (int f = 0; f < NG; ++f) a.c.r0w[((size_t)k * g.nr + ig) * 5 + f] = Gt[f];
+        }
+      } else if (a.mode == MODE_OPER) {
+        if (act) {
+#pragma unroll
+          for (int f = 0; f < NG; ++f)
+            at_row((double*)a.out + (size_t)f * g.N + (size_t)k * plane + row0, jl) = Gt[f];
+        }
+      } else if (act) {
+        // all loads before any store (the second stage updates in place)
+        const double cdt = a.coef * dt * row[RW_INVV];
+        double qn[NG];
+#pragma unroll
+        for (int f = 0; f < NG; ++f) qn[f] = upd[f];
 #pragma unroll
         for (int f = 0; f < NG; ++f) {
-          ((T*)a.out)[(size_t)f * g.N + cell] = Gt[f];
+          const double nv = fma(cdt, Gt[f], base.e[f]);
+          qn[f] += nv;
+          at_row((double*)a.out + (size_t)f * g.N + (size_t)k * plane + row0, jl) = nv;
         }
-      }
-    } else if (act) {
-      // all loads before any store (the second stage updates in place)
-      T nv[NG];
-      auto store_new = [&]() {
-#pragma unroll
-        for (int f = 0; f < NG; ++f) ((T*)a.out)[(size_t)f * g.N + cell] = nv[f];
-      };
-      const T cdt = (T)(a.coef * dt * invV);
-#pragma unroll
-      for (int f = 0; f < NG; ++f) nv[f] = fma(cdt, Gt[f], pb[f]);
-      store_new();
-      {
         // positivity of the new gas state; CFL of the new state (second stage)
-        double qn[5];
-#pragma unroll
-        for (int f = 0; f < 5; ++f) qn[f] = bgc[f] + (double)nv[f];
         const double in2 = 1.0 / qn[4];
         const double un = qn[0] * in2, vn = qn[1] * in2, wn = qn[2] * in2;
-        const double pn = gc.gm1 * (qn[3] - 0.5 * (qn[0] * un + qn[1] * vn + qn[2] * wn));
+        const double pn = (g.gamma - 1.0) * (qn[3] - 0.5 * (qn[0] * un + qn[1] * vn + qn[2] * wn));
         if (!(qn[4] > 0.0 && pn > 0.0)) {
           atomicOr(&a.c.ctrl->status, FL_NEG);
-          atomicMin(&a.c.ctrl->first_bad, (unsigned long long)cell);
+          atomicMin(&a.c.ctrl->first_bad, (unsigned long long)((size_t)k * plane + (size_t)ig * g.nth + jg));
           atomicCAS(&a.c.ctrl->bad_step, -1, a.step);
         } else if (a.second) {
-          double spd = sqrt(un * un + vn * vn + wn * wn) + sqrt(gc.g * pn * in2);
+          const double spd = sqrt(un * un + vn * vn + wn * wn) + sqrt(g.gamma * pn * in2);
           smax = fmax(smax, spd);
           if (EXT && g.drag_law) {
 #pragma unroll
-            for (int s2 = 0; s2 < ND; ++s2) tsmin = fmin(tsmin, 1.0 / inv_tstop<EXT>(g, s2, omk, qn[4], pn));
+            for (int s2 = 0; s2 < ND; ++s2)
+              tsmin = fmin(tsmin, 1.0 / inv_tstop<EXT>(g, s2, row[RW_OMK], qn[4], pn));
           }
         }
       }
+      if (kk < k1) {
+#pragma unroll
+        for (int f = 0; f < NG; ++f) s_rm[f][tid] = r0[f];
+      }
     }
-    // ---- shift the ring
+    if (kk == k1) break;
+    const int k = kk;
+    double (*pl)[TM + 4][HW] = s_pl[k & 1];
+    const double* face_c = &s_face[k & 3][ti * NF];
+    const double* face_r = &s_face[k & 3][(TM + ti + 1) * NF];
+    const double* face_z = &s_face[k & 3][(2 * TM + 1 + ti) * NF];
+    unsigned bad = 0;
+    // ---- theta face j+1/2
+    {
+      auto get = [&](int c, int f) { return pl[f][ti + 2][tj + 1 + c]; };
+      double F[NG];
+      if (!face(DT(), get, nullptr, face_c, k, igc, act, F)) bad |= 1;
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_ft[f][tid] = F[f];
+    }
+    // ---- r face i+1/2
+    {
+      auto get = [&](int c, int f) { return pl[f][ti + 1 + c][tj + 2]; };
+      double F[NG];
+      if (!face(DR(), get, s_wt[ti + 1], face_r, k, min(ig, g.nr), act, F)) bad |= 2;
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_fr[k & 1][f][ti + 1][tj] = F[f];
+    }
+    // ---- lower-edge faces of the tile: r face i0-1/2 (threads 0..63) and theta face
+    //      j0-1/2 of each row (threads 64..71)
+    if (tid < TJ) {
+      auto get = [&](int c, int f) { return pl[f][c][tid + 2]; };
+      double F[NG];
+      // (the upper face of the tile below, which owns it, except at the inner boundary)
+      if (!face(DR(), get, s_wt[0], &s_face[k & 3][TM * NF], k, i0 - 1,
+                i0 == 0 && jg < g.nth, F))
+        bad |= 4;
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_fr[k & 1][f][0][tid] = F[f];
+    } else if (tid < TJ + TM) {
+      const int row = tid - TJ;
+      auto get = [&](int c, int f) { return pl[f][row + 2][c]; };
+      double F[NG];
+      if (!face(DT(), get, nullptr, &s_face[k & 3][row * NF], k,
+                min(i0 + row, g.nr - 1), false, F))
+        bad |= 4;
+#pragma unroll
+      for (int f = 0; f < NG; ++f) s_fe[k & 1][f][row] = F[f];
+    }
+    // the next plane's halo and tables
+    if (more) {
+      if (halo_t) halo_store(k + 1, hraw);
+      tab_store(k + 1, tab_next);
+    }
+    // the update's base of this cell and the dust its drag needs (raw stored values)
+    if (a.mode == MODE_UPDATE && act) col_fetch((const double*)a.base, k, base);
+    if (drag) {
+      const size_t r = (size_t)k * plane + row0;
+#pragma unroll
+      for (int s2 = 0; s2 < ND; ++s2)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) dvar[s2][c] = at_row(vin + (size_t)(5 + 4 * s2 + c) * g.N + r, jl);
+    }
+    // ---- z face k+1/2
+    double rn[NG], fzhi[NG];
+    if (!twod) {
+      col_form(k + 2, nraw, cen(k + 2, ti + 2), rn);
+      auto get = [&](int c, int f) {
+        return c == 0 ? s_rm[f][tid] : c == 1 ? pl[f][ti + 2][tj + 2] : c == 2 ? rp[f] : rn[f];
+      };
+      if (!face(DZ(), get, nullptr, face_z, k, igc, act, fzhi)) bad |= 8;
+    } else {
+#pragma unroll
+      for (int f = 0; f < NG; ++f) { rn[f] = 0.0; fzhi[f] = 0.0; }
+    }
+    // ---- the faces the short form did not take (rare), one call for all kinds: own theta and
+    //      r face, tile edge, z face
+    if (G75 && __builtin_expect(!wave_none(bad != 0), 0)) {
+#pragma nounroll
+      for (int kind = 0; kind < 4; ++kind) {
+        if (!(bad >> kind & 1)) continue;
+        const bool edge_r = kind == 2 && tid < TJ, along_th = kind == 0 || (kind == 2 && !edge_r);
+        const int rr = kind == 0 ? ti + 2 : kind == 1 ? ti + 1 : edge_r ? 0 : tid - TJ + 2;
+        const int cc = kind == 0 ? tj + 1 : along_th ? 0 : tj + 2;
+        const double* p = &pl[0][rr][cc];
+        const int st = along_th ? 1 : HW;
+        auto cell = [&](int c, int f) {
+          if (kind == 3)
+            return c == 0 ? s_rm[f][tid] : c == 1 ? pl[f][ti + 2][tj + 2] : c == 2 ? rp[f] : rn[f];
+          return p[f * (TM + 4) * HW + c * st];
+        };
+        const int i = kind == 1 ? min(ig, g.nr) : kind == 2 ? (edge_r ? i0 - 1 : min(i0 + tid - TJ, g.nr - 1)) : igc;
+        double F[NG];
+        general(along_th ? 1 : kind == 3 ? 2 : 0, cell, k, i,
+                kind == 2 ? edge_r && i0 == 0 && jg < g.nth : act, F);
+#pragma unroll
+        for (int f = 0; f < NG; ++f) {
+          if (kind == 0) s_ft[f][tid] = F[f];
+          else if (kind == 1) s_fr[k & 1][f][ti + 1][tj] = F[f];
+          else if (kind == 3) fzhi[f] = F[f];
+          else if (edge_r) s_fr[k & 1][f][0][tid] = F[f];
+          else s_fe[k & 1][f][tid - TJ] = F[f];
+        }
+      }
+    }
 #pragma unroll
     for (int f = 0; f < NG; ++f) {
-      s_rm[f][tslot] = r0[f]; s_fz[f][tslot] = fzhi[f];
-      r0[f] = rp[f]; rp[f] = rn[f];
+      dz[f] = row[RW_AZ] * (fzhi[f] - fzlo[f]);
+      fzlo[f] = fzhi[f];
+      if (more && centre) s_pl[(k + 1) & 1][f][ti + 2][tj + 2] = rp[f];
+      rp[f] = rn[f];
     }
   }
 
   // ---- block reductions: counters, CFL partial, boundary outflow partial
-  if (smax > 0.0) dtmin = g.cfl * Vc / (smax * maxA);
+  __syncthreads();
   const int wv = tid / 64, ln = tid & 63;
-  int nf_ = wave_isum(st.fall), nv_ = wave_isum(st.vac), mi_ = wave_imax(st.maxit);
-  int nc_ = wave_imax(st.noconv), nr_ = wave_isum(st.resolve);
-#pragma unroll
-  for (int b = 0; b < 8; ++b) {
-    const int hb = wave_isum((int)((s_nh[b >> 1][tid] >> (16 * (b & 1))) & 0xffffu));
-    if (ln == 0 && hb) atomicAdd(&a.c.ctrl->newton_hist[b], (unsigned long long)hb);
-  }
-  if (ln == 0) {
-    if (nf_) atomicAdd(&a.c.ctrl->nfall, (unsigned long long)nf_);
-    if (nv_) { atomicAdd(&a.c.ctrl->nvac, (unsigned long long)nv_); atomicOr(&a.c.ctrl->status, FL_VAC); }
-    if (mi_) atomicMax(&a.c.ctrl->maxit, mi_);
-    if (nr_) atomicAdd(&a.c.ctrl->nresolve, (unsigned long long)nr_);
-    if (nc_) { atomicOr(&a.c.ctrl->status, FL_NOCONV); atomicCAS(&a.c.ctrl->bad_step, -1, a.step); }
+  const int mi = wave_imax(maxit);
+  if (ln < 8 && s_nh[wv][ln])
+    atomicAdd(&a.c.ctrl->newton_hist[ln], (unsigned long long)s_nh[wv][ln]);
+  if (ln == 0 && mi) atomicMax(&a.c.ctrl->maxit, mi);
+  if (tid == 0) {
+    if (s_cnt.fall) atomicAdd(&a.c.ctrl->nfall, (unsigned long long)s_cnt.fall);
+    if (s_cnt.vac) { atomicAdd(&a.c.ctrl->nvac, (unsigned long long)s_cnt.vac); atomicOr(&a.c.ctrl->status, FL_VAC); }
+    if (s_cnt.noconv) { atomicOr(&a.c.ctrl->status, FL_NOCONV); atomicCAS(&a.c.ctrl->bad_step, -1, a.step); }
   }
   if (a.second && a.mode == MODE_UPDATE) {
-    double m = wave_min(dtmin);
-    double ls = wave_sum(ledger);
-    double tm = (EXT && ND > 0) ? wave_min(tsmin) : 1e300;
+    // the CFL bound of the thread's row decreases with the speed: the largest one's
+    const double m = wave_min(smax > 0.0 ? g.cfl * rt[RT_V] / (smax * rt[RT_MAXA]) : 1e300);
+    const double ls = wave_sum(ledger);
+    const double tm = (EXT && ND > 0) ? wave_min(tsmin) : 1e300;
     if (ln == 0) { s_red[wv][0] = m; s_red[wv][1] = ls; s_red[wv][2] = tm; }
     __syncthreads();
     if (tid == 0) {
@@ -930,7 +1044,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
   // Newton counts of the faces the thread owns (bins 0..7, 7: seven or more), 16 bits each;
   // a thread owns at most 4 faces per plane and one more
   __shared__ unsigned s_nh[4][NTM];
-  __shared__ Gas32Count s_cnt;
+  __shared__ GasCount s_cnt;
   // per-plane tables, in doubles (an FP32 pair each for the first two): the stationary flow
   // at the rows' centres, r faces and upper z faces; at the centres of the rows and their
   // halo, two planes ahead; the update's (conservative state, gravity, density, velocity)
@@ -966,7 +1080,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
   auto weights = [&](int i) { return to_ctabf(a.t.rcf) + (size_t)(min(max(i, -1), g.nr) + 1) * RC_N; };
 #pragma unroll
   for (int q = 0; q < 4; ++q) s_nh[q][tid] = 0u;
-  if (tid == 0) s_cnt = Gas32Count{0, 0, 0, 0, 0};
+  if (tid == 0) s_cnt = GasCount{0, 0, 0, 0};
   int maxit = 0;
   auto tally = [&](bool own, int last) {
     const int b = min(last, 7);
