@@ -18,8 +18,8 @@ namespace rb {
 // Bound by the issue of FP64 instructions (four cycles each) and the latency of the face
 // solves, at two waves per SIMD (256 VGPRs); 1690 -> 1290 lane-instructions per cell by the
 // faces' short form (gas_face64) with the general form behind one inlined copy per plane.
-// LDS holds two planes (161 KB of the CU's 160 KiB = 164 KB, which two waves per SIMD leave
-// free): one barrier per plane, so that a wavefront that ends its faces early goes on with
+// LDS holds two planes (160760 of the CU's 163840 bytes, which two waves per SIMD leave free):
+// one barrier per plane, so that a wavefront that ends its faces early goes on with
 // the update, and what the update needs per row is read there in batches (as scalar loads
 // each value waited for its own).  The older wave of a SIMD is served first, so the younger
 // ones end a plane: the first two wavefronts, which solve the tile's edge faces, and the
@@ -1018,14 +1018,14 @@ __global__ void __launch_bounds__(NTM, 4) k_dust(StageArgs a, int species) {
 // the gas stage kernel of the FP32-perturbation form
 
 // One RK2 stage of the gas in the FP32-perturbation form; tiles, planes and update as k_gas,
-// addressing and use of LDS as k_dust.  Bound by instruction issue and the chains of the
+// addressing as k_dust.  Bound by instruction issue and the chains of the
 // face solves: what the faces need of the stationary flow comes as FP32 pairs formed once
 // (PF_N entries, staged a plane ahead), so that they convert nothing, azimuthal faces take
 // the upwind state and the others a short Newton (gas_face32); the faces that form does not
 // take are marked and solved together, by one inlined copy of the general form per plane.
 // Lane-instructions per cell 1506 -> 1050 and transcendentals 73 -> 30: three-dust disc
-// 512 x 1024 x 128, 4.97 -> 3.3 ms per launch; gas disc 128 x 256 x 64, 182 -> 142 us.  Two
-// waves per SIMD: at three (12-row tiles, 168 VGPRs, the general form called) the largest
+// 512 x 1024 x 128, 4.97 -> 3.3 ms per launch; gas disc 128 x 256 x 64, 182 -> 142 us, and
+// with one barrier per plane and batched reads (as k_gas) 113 us.  Two waves per SIMD: at three (12-row tiles, 168 VGPRs, the general form called) the largest
 // disc gains 4% and the others lose more, at four (128) the general form's registers spill
 // into the faces (7.2 ms).
 template <int ND, bool EXT>
@@ -1035,15 +1035,16 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
   __syncthreads();
   if (s_stop & FL_HARD) return;
   constexpr int NG = 5, HW = TJ + 4, NHALO = 4 * HW + 4 * TM;
-  static_assert(NHALO <= NTM, "one halo cell per thread");
-  __shared__ float s_pl[NG][TM + 4][HW];
-  __shared__ float s_ft[NG][TM][TJ + 1];
-  __shared__ float s_fr[NG][TM + 1][TJ];
+  static_assert(NHALO <= NTM - 3 * 64, "one halo cell per thread");
+  // (planes, faces and tables in halves and rings: as k_gas)
+  __shared__ float s_pl[2][NG][TM + 4][HW];
+  __shared__ float s_fr[2][NG][TM + 1][TJ];
+  __shared__ float s_fe[2][NG][TM];
+  __shared__ float s_ft[NG][NTM];
   __shared__ float s_rm[NG][NTM];
   __shared__ double s_red[NTM / 64][3];
-  // Newton counts of the faces the thread owns (bins 0..7, 7: seven or more), 16 bits each;
-  // a thread owns at most 4 faces per plane and one more
-  __shared__ unsigned s_nh[4][NTM];
+  // Newton counts of the faces the wavefront owns (bins 0..7, 7: seven or more)
+  __shared__ int s_nh[NTM / 64][8];
   __shared__ GasCount s_cnt;
   // per-plane tables, in doubles (an FP32 pair each for the first two): the stationary flow
   // at the rows' centres, r faces and upper z faces; at the centres of the rows and their
@@ -1051,9 +1052,12 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
   constexpr int PFD = PF_N / 2, NFACE = (3 * TM + 1) * PFD, NCEN = (TM + 4) * 2, NUPD = TM * 9;
   constexpr int T_CEN = NFACE, T_UPD = T_CEN + NCEN, NTAB = T_UPD + NUPD;
   static_assert(NTAB <= NTM, "one table entry per thread");
-  __shared__ __align__(16) double s_face[2][NFACE];
+  __shared__ __align__(16) double s_face[4][NFACE];
   __shared__ __align__(16) double s_cen[4][NCEN];
-  __shared__ double s_upd[2][NUPD];
+  __shared__ double s_upd[4][NUPD];
+  __shared__ __align__(16) float s_wt[TM + 1][8];
+  enum { RW_AR0 = 0, RW_AR1, RW_ATH, RW_AZ, RW_V, RW_INVV, RW_INVRC, RW_OMK, RW_N };
+  __shared__ double s_row[TM][RW_N];
 
   const Geo& g = a.g;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
@@ -1077,23 +1081,44 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
   const bool centre = (unsigned)(tj - wcols) >= 2u;
   const size_t row0 = (size_t)igc * g.nth + j0;
   const ctab rt = to_ctab(a.t.rt) + (size_t)igc * RT_N, ar = to_ctab(a.t.ar);
-  auto weights = [&](int i) { return to_ctabf(a.t.rcf) + (size_t)(min(max(i, -1), g.nr) + 1) * RC_N; };
-#pragma unroll
-  for (int q = 0; q < 4; ++q) s_nh[q][tid] = 0u;
+  if (tid < (TM + 1) * 8) {
+    const int r = tid / 8, e = tid % 8, i = min(i0 + r - 1 + (e < 4 ? 0 : 1), g.nr);
+    s_wt[r][e] = a.t.rcf[(size_t)(i + 1) * RC_N + e];
+  } else if (tid >= 128 && tid < 128 + TM * RW_N) {
+    const int r = (tid - 128) / RW_N, e = (tid - 128) % RW_N, i = min(i0 + r, g.nr - 1);
+    const double* q = a.t.rt + (size_t)i * RT_N;
+    s_row[r][e] = e == RW_AR0   ? a.t.ar[i]
+                  : e == RW_AR1 ? a.t.ar[i + 1]
+                  : e == RW_ATH ? q[RT_ATH]
+                  : e == RW_AZ  ? q[RT_AZ]
+                  : e == RW_V   ? q[RT_V]
+                  : e == RW_INVV ? q[RT_INVV]
+                  : e == RW_INVRC ? q[RT_INVRC]
+                                  : q[RT_OMK];
+  } else if (tid >= 256 && tid < 256 + NTM / 64 * 8) {
+    s_nh[(tid - 256) / 8][tid & 7] = 0;
+  }
   if (tid == 0) s_cnt = GasCount{0, 0, 0, 0};
   int maxit = 0;
   auto tally = [&](bool own, int last) {
     const int b = min(last, 7);
-    if (own) atomicAdd(&s_nh[b >> 1][tid], 1u << (16 * (b & 1)));
+    unsigned long long left = __ballot(own);
+    while (left) {
+      const int at = __builtin_ctzll(left), v = __builtin_amdgcn_readlane(b, at);
+      const unsigned long long mk = __ballot(own && b == v);
+      if (tj == at) atomicAdd(&s_nh[ti][v], __popcll(mk));
+      left &= ~mk;
+    }
   };
 
-  // thread t stages table entry t: tab_p + plane * tab_stride
+  // thread NTM - 1 - t stages table entry t: as k_gas
+  const int tt = NTM - 1 - tid;
   const double* tab_p = nullptr;
   size_t tab_stride = 0;
-  if (tid < NTAB) {
+  if (tt < NTAB) {
     const size_t nr = (size_t)g.nr;
-    if (tid < NFACE) {
-      const int r = tid / PFD, e = tid % PFD;
+    if (tt < NFACE) {
+      const int r = tt / PFD, e = tt % PFD;
       if (r < TM) {
         tab_p = a.t.pc + (size_t)min(i0 + r, g.nr - 1) * PFD + e;
         tab_stride = nr * PFD;
@@ -1104,26 +1129,26 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
         tab_p = a.t.pz + (nr + (size_t)min(i0 + r - 2 * TM - 1, g.nr - 1)) * PFD + e;
         tab_stride = nr * PFD;
       }
-    } else if (tid < T_UPD) {
-      const int r = (tid - T_CEN) / 2, e = (tid - T_CEN) % 2;
+    } else if (tt < T_UPD) {
+      const int r = (tt - T_CEN) / 2, e = (tt - T_CEN) % 2;
       tab_p = a.t.pc + (size_t)min(max(i0 + r - 2, 0), g.nr - 1) * PFD + e;
       tab_stride = nr * PFD;
     } else {
-      const int r = (tid - T_UPD) / 9, e = (tid - T_UPD) % 9;
+      const int r = (tt - T_UPD) / 9, e = (tt - T_UPD) % 9;
       const size_t i = min(i0 + r, g.nr - 1);
       if (e < 5) { tab_p = a.t.bgc + i * 5 + e; tab_stride = nr * 5; }
       else if (e < 7) { tab_p = a.t.grav + i * 2 + (e - 5); tab_stride = nr * 2; }
       else { tab_p = a.t.wc + i * WB_N + (e == 7 ? WB_RHO : WB_V); tab_stride = nr * WB_N; }
     }
   }
-  const bool cen_t = tid >= T_CEN && tid < T_UPD;
+  const bool cen_t = tt >= T_CEN && tt < T_UPD;
   auto tab_load = [&](int k) {  // (the centres' entries: of plane k + 2)
-    return tid < NTAB ? tab_p[(size_t)min(cen_t ? k + 2 : k, g.nz - 1) * tab_stride] : 0.0;
+    return tt < NTAB ? tab_p[(size_t)min(cen_t ? k + 2 : k, g.nz - 1) * tab_stride] : 0.0;
   };
   auto tab_store = [&](int k, double x) {
-    if (tid < NFACE) s_face[k & 1][tid] = x;
-    else if (tid < T_UPD) s_cen[(k + 2) & 3][tid - T_CEN] = x;
-    else if (tid < NTAB) s_upd[k & 1][tid - T_UPD] = x;
+    if (tt < NFACE) s_face[k & 3][tt] = x;
+    else if (tt < T_UPD) s_cen[(k + 2) & 3][tt - T_CEN] = x;
+    else if (tt < NTAB) s_upd[k & 3][tt - T_UPD] = x;
   };
 
   const float* vin = (const float*)a.in;
@@ -1150,13 +1175,16 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
     }
   };
   auto cen = [&](int k, int row) { return (const float*)&s_cen[k & 3][row * 2]; };
-  const bool halo_t = tid < NHALO;
+  // (by the wavefronts that k_gas takes)
+  const int th = ti < 2 || ti == 4 ? -1 : tid - (ti < 4 ? 2 : 3) * 64;
+  const bool halo_t = th >= 0 && th < NHALO;
   int h_rr = 0, h_cc = 0;
-  if (tid < 2 * HW) { h_rr = tid / HW; h_cc = tid % HW; }
-  else if (tid < 4 * HW) { h_rr = TM + 2 + (tid - 2 * HW) / HW; h_cc = (tid - 2 * HW) % HW; }
-  else if (halo_t) { const int e = tid - 4 * HW; h_rr = 2 + e / 4; h_cc = (e & 3) < 2 ? (e & 3) : wcols + (e & 3); }
+  if (!halo_t) {}
+  else if (th < 2 * HW) { h_rr = th / HW; h_cc = th % HW; }
+  else if (th < 4 * HW) { h_rr = TM + 2 + (th - 2 * HW) / HW; h_cc = (th - 2 * HW) % HW; }
+  else if (halo_t) { const int e = th - 4 * HW; h_rr = 2 + e / 4; h_cc = (e & 3) < 2 ? (e & 3) : wcols + (e & 3); }
   int h_pad = 0;
-  if (tid >= 4 * HW && wcols < TJ && h_cc > 1 && TJ + (tid & 3) > wcols + 3) h_pad = TJ + (tid & 3);
+  if (th >= 4 * HW && wcols < TJ && h_cc > 1 && TJ + (th & 3) > wcols + 3) h_pad = TJ + (th & 3);
   const int h_ii = i0 + h_rr - 2;
   const size_t h_off = (size_t)min(max(h_ii, 0), g.nr - 1) * g.nth + (j0 + h_cc - 2 + g.nth) % g.nth;
   auto halo_fetch = [&](int k, Raw& R) {
@@ -1168,19 +1196,19 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
     cell_w32(R.e, cen(k, h_rr), gm1f, w);
     const bool ghost = h_ii < 0 || h_ii >= g.nr;
 #pragma unroll
-    for (int f = 0; f < NG; ++f) s_pl[f][h_rr][h_cc] = ghost ? 0.0f : w[f];
+    for (int f = 0; f < NG; ++f) s_pl[k & 1][f][h_rr][h_cc] = ghost ? 0.0f : w[f];
     if (h_pad) {
 #pragma unroll
-      for (int f = 0; f < NG; ++f) s_pl[f][h_rr][h_pad] = ghost ? 0.0f : w[f];
+      for (int f = 0; f < NG; ++f) s_pl[k & 1][f][h_rr][h_pad] = ghost ? 0.0f : w[f];
     }
   };
 
   // a face by the short form (bp: the face's PF_N entry), with its Newton count tallied if
   // the thread owns it; returns false where the general form has to solve it
-  auto face = [&](auto dirc, auto cell, auto coB, auto coC, const float* bp, bool own, float* F) {
+  auto face = [&](auto dirc, auto cell, const float* co, const float* bp, bool own, float* F) {
     constexpr int D = decltype(dirc)::value;
     float qL[NG], qR[NG];
-    recon32<D>(cell, coB, coC, qL, qR);
+    recon32<D>(cell, co, co, qL, qR);
     int last = 0;
     const bool ok = gas_face32<D>(bp, qL, qR, F, last);
     if (ok) maxit = max(maxit, last);
@@ -1230,7 +1258,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
 #pragma unroll
       for (int q = 0; q < PF_N; ++q) bp[q] = c[q];
       auto get = [&](int s, int f) { return s == 0 ? e2[f] : s == 1 ? rm[f] : s == 2 ? r0[f] : rp[f]; };
-      if (!face(DZ(), get, nullptr, nullptr, bp, act && k0 == 0, fzlo)) {
+      if (!face(DZ(), get, nullptr, bp, act && k0 == 0, fzlo)) {
         Face32 q;
 #pragma unroll
         for (int f = 0; f < NG; ++f) { q.A[f] = e2[f]; q.B[f] = rm[f]; q.C[f] = r0[f]; q.D[f] = rp[f]; }
@@ -1246,7 +1274,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
     }
     if (centre) {
 #pragma unroll
-      for (int f = 0; f < NG; ++f) s_pl[f][ti + 2][tj + 2] = r0[f];
+      for (int f = 0; f < NG; ++f) s_pl[k0 & 1][f][ti + 2][tj + 2] = r0[f];
     }
     if (halo_t) {
       halo_fetch(k0, R);
@@ -1255,62 +1283,195 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
   }
   const double dt = a.dt_idx >= 0 ? a.c.dtlog[a.dt_idx] : 0.0;
 
-  for (int k = k0; k < k1; ++k) {
-    const bool more = k + 1 < k1;
-    const float* face_c = (const float*)&s_face[k & 1][ti * PFD];
-    const float* face_r = (const float*)&s_face[k & 1][(TM + ti + 1) * PFD];
-    const float* face_z = (const float*)&s_face[k & 1][(2 * TM + 1 + ti) * PFD];
+  // One barrier per plane: behind the one that ends plane k the update of plane k - 1 and, in
+  // the other half of the LDS arrays, the faces of plane k.
+  const double* row = s_row[ti];
+  Raw base;
+  double rds[ND > 0 ? ND : 1];
+  float vds[ND > 0 ? ND : 1][3], dz[NG];
+  for (int kk = k0;; ++kk) {
     __syncthreads();
-    // the column's cell k+2 and the next plane's halo and tables
+    // the column's cell kk+2 and the next plane's halo and tables
+    const bool more = kk + 1 < k1;
     Raw nraw, hraw;
     double tab_next = 0.0;
-    unsigned bad = 0;
-    if (!twod) col_fetch(vin, k + 2, nraw);
+    col_fetch(vin, kk + 2, nraw);
     if (more) {
-      if (halo_t) halo_fetch(k + 1, hraw);
-      tab_next = tab_load(k + 1);
+      if (halo_t) halo_fetch(kk + 1, hraw);
+      tab_next = tab_load(kk + 1);
     }
+    if (kk > k0) {
+      const int k = kk - 1;
+      // boundary outflow ledger (the stationary flow has no mass flux through these faces)
+      if (a.second && act) {
+        if (ig == g.nr - 1) ledger += row[RW_AR1] * (double)s_fr[k & 1][4][ti + 1][tj];
+        if (ig == 0) ledger -= row[RW_AR0] * (double)s_fr[k & 1][4][0][tj];
+        if (!twod && k == g.nz - 1) ledger += row[RW_AZ] * (double)fzlo[4];
+      }
+      // ---- divergence -sum_s A_s F.n_s (Sect. 2.2), sources (App. B), drag (Sect. 2.9): the
+      //      source change S(E) - S(E0), every term formed from the perturbations W' (the
+      //      stationary flow has no radial or vertical velocity)
+      float r0[NG];
+#pragma unroll
+      for (int f = 0; f < NG; ++f) r0[f] = s_pl[k & 1][f][ti + 2][tj + 2];
+      const double* upd = &s_upd[k & 3][ti * 9];
+      const float* fc = (const float*)&s_face[k & 3][ti * PFD];
+      const float rhop = r0[4], up = r0[0], vp = r0[1], wp = r0[2], pp = r0[3];
+      const float v0 = fc[PF_V], rho = fc[PF_RHO] + (rhop + fc[PF_RLO]);
+      const float ir = (float)row[RW_INVRC], fgr = (float)upd[5], fgz = (float)upd[6];
+      const float dmv2 = rhop * fc[PF_VSQ] + rho * vp * (2.0f * v0 + vp);
+      float S[NG];
+      S[0] = (dmv2 + pp) * ir + rhop * fgr;
+      S[1] = -(rho * up * (v0 + vp)) * ir;
+      S[2] = rhop * fgz;
+      S[3] = rho * (up * fgr + wp * fgz);
+      S[4] = 0.0f;
+      if (drag) {
+        const double rg = upd[7] + (double)rhop;
+        const double u = (double)up, v = upd[8] + (double)vp, w2 = (double)wp;
+        const double pq = (EXT && g.drag_law) ? a.t.wc[((size_t)k * g.nr + igc) * WB_N + WB_P] + (double)pp : 0.0;
+        double dx = 0.0, dy = 0.0, dzz = 0.0;
+#pragma unroll
+        for (int s2 = 0; s2 < ND; ++s2) {
+          // the FP32 layout stores the dust velocities as deviations from the stationary
+          // flow's, as the gas W' is: the velocity difference is formed from the deviations
+          const double rd = rds[s2];
+          const bool full = rd > 0.0;
+          const double dud = full ? (double)vds[s2][0] - (double)up : -u;
+          const double dvd = full ? (double)vds[s2][1] - (double)vp : -v;
+          const double dwd = full ? (double)vds[s2][2] - (double)wp : -w2;
+          const double its = inv_tstop<EXT>(g, s2, row[RW_OMK], rg, pq);
+          dx += rd * dud * its;
+          dy += rd * dvd * its;
+          dzz += rd * dwd * its;
+        }
+        S[0] += (float)dx;
+        S[1] += (float)dy;
+        S[2] += (float)dzz;
+        S[3] += (float)(u * dx + v * dy + w2 * dzz);
+      }
+      // indirect gravity (Sect. 2.10): minus the star's acceleration by the disc
+      if (EXT && g.indirect) {
+        const double A = a.t.indab[0], B = a.t.indab[1];
+        const double cs = a.t.trig[j0 + jl], sn = a.t.trig[g.nth + j0 + jl];
+        const double acr = -g.GM * (A * cs + B * sn), act_ = -g.GM * (B * cs - A * sn);
+        const double rg = upd[7] + (double)rhop;
+        S[0] += (float)(rg * acr);
+        S[1] += (float)(rg * act_);
+        S[3] += (float)(rg * (double)up * acr + rg * (upd[8] + (double)vp) * act_);
+      }
+      // boundary damping zones (Sect. 2.4): the gas deviation relaxes to the stationary flow
+      if (EXT && g.damp) {
+        const double kd = a.t.damp[(size_t)k * g.nr + igc];
+        Raw e;
+        col_fetch(vin, k, e);
+#pragma unroll
+        for (int f = 0; f < NG; ++f) S[f] -= (float)(kd * (double)e.e[f]);
+      }
+      // (every face read first, in one batch)
+      const float *r_hi = &s_fr[k & 1][0][ti + 1][tj], *r_lo = &s_fr[k & 1][0][ti][tj];
+      const float* t_lo = tj ? &s_ft[0][tid - 1] : &s_fe[k & 1][0][ti];
+      const int t_st = tj ? NTM : TM;
+      const float ar0 = (float)row[RW_AR0], ar1 = (float)row[RW_AR1], ath = (float)row[RW_ATH], vol = (float)row[RW_V];
+      float Gt[NG];
+#pragma unroll
+      for (int f = 0; f < NG; ++f) {
+        const float dr = ar1 * r_hi[f * (TM + 1) * TJ] - ar0 * r_lo[f * (TM + 1) * TJ];
+        const float dth = ath * (s_ft[f][tid] - t_lo[f * t_st]);
+        Gt[f] = fma(S[f], vol, -((dr + dth) + dz[f]));
+      }
+      if (a.mode == MODE_OPER) {
+        if (act) {
+#pragma unroll
+          for (int f = 0; f < NG; ++f)
+            at_row((float*)a.out + (size_t)f * g.N + (size_t)k * plane + row0, jl) = Gt[f];
+        }
+      } else if (act) {
+        // all loads before any store (the second stage updates in place)
+        const float cdt = (float)(a.coef * dt * row[RW_INVV]);
+        float nv[NG];
+        double qn[NG];
+#pragma unroll
+        for (int f = 0; f < NG; ++f) qn[f] = upd[f];
+#pragma unroll
+        for (int f = 0; f < NG; ++f) {
+          nv[f] = fma(cdt, Gt[f], base.e[f]);
+          qn[f] += (double)nv[f];
+          at_row((float*)a.out + (size_t)f * g.N + (size_t)k * plane + row0, jl) = nv[f];
+        }
+        // positivity of the new gas state; CFL of the new state (second stage)
+        const double in2 = 1.0 / qn[4];
+        const double un = qn[0] * in2, vn = qn[1] * in2, wn = qn[2] * in2;
+        const double pn = (g.gamma - 1.0) * (qn[3] - 0.5 * (qn[0] * un + qn[1] * vn + qn[2] * wn));
+        if (!(qn[4] > 0.0 && pn > 0.0)) {
+          atomicOr(&a.c.ctrl->status, FL_NEG);
+          atomicMin(&a.c.ctrl->first_bad, (unsigned long long)((size_t)k * plane + (size_t)ig * g.nth + jg));
+          atomicCAS(&a.c.ctrl->bad_step, -1, a.step);
+        } else if (a.second) {
+          const double spd = sqrt(un * un + vn * vn + wn * wn) + sqrt(g.gamma * pn * in2);
+          smax = fmax(smax, spd);
+          if (EXT && g.drag_law) {
+#pragma unroll
+            for (int s2 = 0; s2 < ND; ++s2)
+              tsmin = fmin(tsmin, 1.0 / inv_tstop<EXT>(g, s2, row[RW_OMK], qn[4], pn));
+          }
+        }
+      }
+      if (kk < k1) {
+#pragma unroll
+        for (int f = 0; f < NG; ++f) s_rm[f][tid] = r0[f];
+      }
+    }
+    if (kk == k1) break;
+    const int k = kk;
+    float (*pl)[TM + 4][HW] = s_pl[k & 1];
+    const float* face_c = (const float*)&s_face[k & 3][ti * PFD];
+    const float* face_r = (const float*)&s_face[k & 3][(TM + ti + 1) * PFD];
+    const float* face_z = (const float*)&s_face[k & 3][(2 * TM + 1 + ti) * PFD];
+    unsigned bad = 0;
     // ---- theta face j+1/2
     {
-      auto get = [&](int c, int f) { return s_pl[f][ti + 2][tj + 1 + c]; };
+      auto get = [&](int c, int f) { return pl[f][ti + 2][tj + 1 + c]; };
       float F[NG];
-      if (!face(DT(), get, nullptr, nullptr, face_c, act, F)) bad |= 1;
+      if (!face(DT(), get, nullptr, face_c, act, F)) bad |= 1;
 #pragma unroll
-      for (int f = 0; f < NG; ++f) s_ft[f][ti][tj + 1] = F[f];
+      for (int f = 0; f < NG; ++f) s_ft[f][tid] = F[f];
     }
     // ---- r face i+1/2
     {
-      auto get = [&](int c, int f) { return s_pl[f][ti + 1 + c][tj + 2]; };
+      auto get = [&](int c, int f) { return pl[f][ti + 1 + c][tj + 2]; };
       float F[NG];
-      if (!face(DR(), get, weights(ig), weights(ig + 1), face_r, act, F)) bad |= 2;
+      if (!face(DR(), get, s_wt[ti + 1], face_r, act, F)) bad |= 2;
 #pragma unroll
-      for (int f = 0; f < NG; ++f) s_fr[f][ti + 1][tj] = F[f];
+      for (int f = 0; f < NG; ++f) s_fr[k & 1][f][ti + 1][tj] = F[f];
     }
     // ---- lower-edge faces of the tile: r face i0-1/2 (threads 0..63) and theta face
     //      j0-1/2 of each row (threads 64..71)
     if (tid < TJ) {
-      auto get = [&](int c, int f) { return s_pl[f][c][tid + 2]; };
+      auto get = [&](int c, int f) { return pl[f][c][tid + 2]; };
       float F[NG];
       // (the upper face of the tile below, which owns it, except at the inner boundary)
-      if (!face(DR(), get, weights(i0 - 1), weights(i0), (const float*)&s_face[k & 1][TM * PFD],
+      if (!face(DR(), get, s_wt[0], (const float*)&s_face[k & 3][TM * PFD],
                 i0 == 0 && jg < g.nth, F))
         bad |= 4;
 #pragma unroll
-      for (int f = 0; f < NG; ++f) s_fr[f][0][tid] = F[f];
+      for (int f = 0; f < NG; ++f) s_fr[k & 1][f][0][tid] = F[f];
     } else if (tid < TJ + TM) {
       const int row = tid - TJ;
-      auto get = [&](int c, int f) { return s_pl[f][row + 2][c]; };
+      auto get = [&](int c, int f) { return pl[f][row + 2][c]; };
       float F[NG];
-      if (!face(DT(), get, nullptr, nullptr, (const float*)&s_face[k & 1][row * PFD], false, F))
+      if (!face(DT(), get, nullptr, (const float*)&s_face[k & 3][row * PFD], false, F))
         bad |= 4;
 #pragma unroll
-      for (int f = 0; f < NG; ++f) s_ft[f][row][0] = F[f];
+      for (int f = 0; f < NG; ++f) s_fe[k & 1][f][row] = F[f];
+    }
+    // the next plane's halo and tables
+    if (more) {
+      if (halo_t) halo_store(k + 1, hraw);
+      tab_store(k + 1, tab_next);
     }
     // the update's base of this cell and the dust its drag needs (raw stored values)
-    Raw base;
     if (a.mode == MODE_UPDATE && act) col_fetch((const float*)a.base, k, base);
-    double rds[ND > 0 ? ND : 1];
-    float vds[ND > 0 ? ND : 1][3];
     if (drag) {
       const size_t r = (size_t)k * plane + row0;
 #pragma unroll
@@ -1325,9 +1486,9 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
     if (!twod) {
       col_form(k + 2, nraw, cen(k + 2, ti + 2), rn);
       auto get = [&](int c, int f) {
-        return c == 0 ? s_rm[f][tid] : c == 1 ? s_pl[f][ti + 2][tj + 2] : c == 2 ? rp[f] : rn[f];
+        return c == 0 ? s_rm[f][tid] : c == 1 ? pl[f][ti + 2][tj + 2] : c == 2 ? rp[f] : rn[f];
       };
-      if (!face(DZ(), get, nullptr, nullptr, face_z, act, fzhi)) bad |= 8;
+      if (!face(DZ(), get, nullptr, face_z, act, fzhi)) bad |= 8;
     } else {
 #pragma unroll
       for (int f = 0; f < NG; ++f) { rn[f] = 0.0f; fzhi[f] = 0.0f; }
@@ -1344,10 +1505,10 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
         Face32 q;
 #pragma unroll
         for (int f = 0; f < NG; ++f) {
-          const float* p = &s_pl[f][rr][cc];
+          const float* p = &pl[f][rr][cc];
           const int st = along_th ? 1 : HW;
           if (kind == 3) {
-            q.A[f] = s_rm[f][tid]; q.B[f] = s_pl[f][ti + 2][tj + 2]; q.C[f] = rp[f]; q.D[f] = rn[f];
+            q.A[f] = s_rm[f][tid]; q.B[f] = pl[f][ti + 2][tj + 2]; q.C[f] = rp[f]; q.D[f] = rn[f];
           } else {
             q.A[f] = p[0]; q.B[f] = p[st]; q.C[f] = p[2 * st]; q.D[f] = p[3 * st];
           }
@@ -1358,139 +1519,20 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
                 kind == 2 ? edge_r && i0 == 0 && jg < g.nth : act, F);
 #pragma unroll
         for (int f = 0; f < NG; ++f) {
-          if (kind == 0) s_ft[f][ti][tj + 1] = F[f];
-          else if (kind == 1) s_fr[f][ti + 1][tj] = F[f];
+          if (kind == 0) s_ft[f][tid] = F[f];
+          else if (kind == 1) s_fr[k & 1][f][ti + 1][tj] = F[f];
           else if (kind == 3) fzhi[f] = F[f];
-          else if (edge_r) s_fr[f][0][tid] = F[f];
-          else s_ft[f][tid - TJ][0] = F[f];
+          else if (edge_r) s_fr[k & 1][f][0][tid] = F[f];
+          else s_fe[k & 1][f][tid - TJ] = F[f];
         }
       }
     }
-    float dz[NG];
 #pragma unroll
     for (int f = 0; f < NG; ++f) {
-      dz[f] = (float)rt[RT_AZ] * (fzhi[f] - fzlo[f]);
+      dz[f] = (float)row[RW_AZ] * (fzhi[f] - fzlo[f]);
       fzlo[f] = fzhi[f];
-    }
-    // (the entries it replaces were last read before this plane's first barrier)
-    if (more) tab_store(k + 1, tab_next);
-    __syncthreads();
-    if (halo_t && more) halo_store(k + 1, hraw);
-    // boundary outflow ledger (the stationary flow has no mass flux through these faces)
-    if (a.second && act) {
-      if (ig == g.nr - 1) ledger += ar[igc + 1] * (double)s_fr[4][ti + 1][tj];
-      if (ig == 0) ledger -= ar[0] * (double)s_fr[4][0][tj];
-      if (!twod && k == g.nz - 1) ledger += rt[RT_AZ] * (double)fzlo[4];
-    }
-    // ---- divergence -sum_s A_s F.n_s (Sect. 2.2), sources (App. B), drag (Sect. 2.9): the
-    //      source change S(E) - S(E0), every term formed from the perturbations W' (the
-    //      stationary flow has no radial or vertical velocity)
-    float r0[NG];
-#pragma unroll
-    for (int f = 0; f < NG; ++f) r0[f] = s_pl[f][ti + 2][tj + 2];
-    const double* upd = &s_upd[k & 1][ti * 9];
-    const float rhop = r0[4], up = r0[0], vp = r0[1], wp = r0[2], pp = r0[3];
-    const float v0 = face_c[PF_V], rho = face_c[PF_RHO] + (rhop + face_c[PF_RLO]);
-    const float ir = (float)rt[RT_INVRC], fgr = (float)upd[5], fgz = (float)upd[6];
-    const float dmv2 = rhop * face_c[PF_VSQ] + rho * vp * (2.0f * v0 + vp);
-    float S[NG];
-    S[0] = (dmv2 + pp) * ir + rhop * fgr;
-    S[1] = -(rho * up * (v0 + vp)) * ir;
-    S[2] = rhop * fgz;
-    S[3] = rho * (up * fgr + wp * fgz);
-    S[4] = 0.0f;
-    if (drag) {
-      const double rg = upd[7] + (double)rhop;
-      const double u = (double)up, v = upd[8] + (double)vp, w2 = (double)wp;
-      const double pq = (EXT && g.drag_law) ? a.t.wc[((size_t)k * g.nr + igc) * WB_N + WB_P] + (double)pp : 0.0;
-      double dx = 0.0, dy = 0.0, dzz = 0.0;
-#pragma unroll
-      for (int s2 = 0; s2 < ND; ++s2) {
-        // the FP32 layout stores the dust velocities as deviations from the stationary
-        // flow's, as the gas W' is: the velocity difference is formed from the deviations
-        const double rd = rds[s2];
-        const bool full = rd > 0.0;
-        const double dud = full ? (double)vds[s2][0] - (double)up : -u;
-        const double dvd = full ? (double)vds[s2][1] - (double)vp : -v;
-        const double dwd = full ? (double)vds[s2][2] - (double)wp : -w2;
-        const double its = inv_tstop<EXT>(g, s2, rt[RT_OMK], rg, pq);
-        dx += rd * dud * its;
-        dy += rd * dvd * its;
-        dzz += rd * dwd * its;
-      }
-      S[0] += (float)dx;
-      S[1] += (float)dy;
-      S[2] += (float)dzz;
-      S[3] += (float)(u * dx + v * dy + w2 * dzz);
-    }
-    // indirect gravity (Sect. 2.10): minus the star's acceleration by the disc
-    if (EXT && g.indirect) {
-      const double A = a.t.indab[0], B = a.t.indab[1];
-      const double cs = a.t.trig[j0 + jl], sn = a.t.trig[g.nth + j0 + jl];
-      const double acr = -g.GM * (A * cs + B * sn), act_ = -g.GM * (B * cs - A * sn);
-      const double rg = upd[7] + (double)rhop;
-      S[0] += (float)(rg * acr);
-      S[1] += (float)(rg * act_);
-      S[3] += (float)(rg * (double)up * acr + rg * (upd[8] + (double)vp) * act_);
-    }
-    // boundary damping zones (Sect. 2.4): the gas deviation relaxes to the stationary flow
-    if (EXT && g.damp) {
-      const double kd = a.t.damp[(size_t)k * g.nr + igc];
-      Raw e;
-      col_fetch(vin, k, e);
-#pragma unroll
-      for (int f = 0; f < NG; ++f) S[f] -= (float)(kd * (double)e.e[f]);
-    }
-    float Gt[NG];
-#pragma unroll
-    for (int f = 0; f < NG; ++f) {
-      const float dr = (float)ar[igc + 1] * s_fr[f][ti + 1][tj] - (float)ar[igc] * s_fr[f][ti][tj];
-      const float dth = (float)rt[RT_ATH] * (s_ft[f][ti][tj + 1] - s_ft[f][ti][tj]);
-      Gt[f] = fma(S[f], (float)rt[RT_V], -((dr + dth) + dz[f]));
-    }
-    if (a.mode == MODE_OPER) {
-      if (act) {
-#pragma unroll
-        for (int f = 0; f < NG; ++f)
-          at_row((float*)a.out + (size_t)f * g.N + (size_t)k * plane + row0, jl) = Gt[f];
-      }
-    } else if (act) {
-      // all loads before any store (the second stage updates in place)
-      const float cdt = (float)(a.coef * dt * rt[RT_INVV]);
-      float nv[NG];
-      double qn[NG];
-#pragma unroll
-      for (int f = 0; f < NG; ++f) {
-        nv[f] = fma(cdt, Gt[f], base.e[f]);
-        qn[f] = upd[f] + (double)nv[f];
-        at_row((float*)a.out + (size_t)f * g.N + (size_t)k * plane + row0, jl) = nv[f];
-      }
-      // positivity of the new gas state; CFL of the new state (second stage)
-      const double in2 = 1.0 / qn[4];
-      const double un = qn[0] * in2, vn = qn[1] * in2, wn = qn[2] * in2;
-      const double pn = (g.gamma - 1.0) * (qn[3] - 0.5 * (qn[0] * un + qn[1] * vn + qn[2] * wn));
-      if (!(qn[4] > 0.0 && pn > 0.0)) {
-        atomicOr(&a.c.ctrl->status, FL_NEG);
-        atomicMin(&a.c.ctrl->first_bad, (unsigned long long)((size_t)k * plane + (size_t)ig * g.nth + jg));
-        atomicCAS(&a.c.ctrl->bad_step, -1, a.step);
-      } else if (a.second) {
-        const double spd = sqrt(un * un + vn * vn + wn * wn) + sqrt(g.gamma * pn * in2);
-        smax = fmax(smax, spd);
-        if (EXT && g.drag_law) {
-#pragma unroll
-          for (int s2 = 0; s2 < ND; ++s2)
-            tsmin = fmin(tsmin, 1.0 / inv_tstop<EXT>(g, s2, rt[RT_OMK], qn[4], pn));
-        }
-      }
-    }
-    // ---- shift the column
-    if (more) {
-#pragma unroll
-      for (int f = 0; f < NG; ++f) {
-        s_rm[f][tid] = r0[f];
-        if (centre) s_pl[f][ti + 2][tj + 2] = rp[f];
-        rp[f] = rn[f];
-      }
+      if (more && centre) s_pl[(k + 1) & 1][f][ti + 2][tj + 2] = rp[f];
+      rp[f] = rn[f];
     }
   }
 
@@ -1498,11 +1540,8 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
   __syncthreads();
   const int wv = tid / 64, ln = tid & 63;
   const int mi = wave_imax(maxit);
-#pragma unroll
-  for (int b = 0; b < 8; ++b) {
-    const int hb = wave_isum((int)((s_nh[b >> 1][tid] >> (16 * (b & 1))) & 0xffffu));
-    if (ln == 0 && hb) atomicAdd(&a.c.ctrl->newton_hist[b], (unsigned long long)hb);
-  }
+  if (ln < 8 && s_nh[wv][ln])
+    atomicAdd(&a.c.ctrl->newton_hist[ln], (unsigned long long)s_nh[wv][ln]);
   if (ln == 0 && mi) atomicMax(&a.c.ctrl->maxit, mi);
   if (tid == 0) {
     if (s_cnt.fall) atomicAdd(&a.c.ctrl->nfall, (unsigned long long)s_cnt.fall);
