@@ -27,52 +27,42 @@ namespace rb {
 // ------------------------------------------------------------------------------------
 // reverse of the building blocks
 
-// which argument minmod3 returned: 0 the first, 1 the second, 2 the third, 3 none (zero)
-__device__ __forceinline__ int minmod3_arg(double x, double y, double z) {
-  if (x > 0.0 && y > 0.0 && z > 0.0) return x <= fmin(y, z) ? 0 : (y <= z ? 1 : 2);
-  if (x < 0.0 && y < 0.0 && z < 0.0) return x >= fmax(y, z) ? 0 : (y >= z ? 1 : 2);
-  return 3;
+// Derivative (cm, cp) of a limited increment with respect to the backward and forward
+// differences of its cell, on the branch the limiter took: in the signed variables of
+// face_pair (any: the arguments are positive) the parabola's x where it is the least, else
+// the backward difference's y or the forward one's z.
+__device__ __forceinline__ void dlim(bool any, double x, double y, double z, double wm, double wp,
+                                     double lm, double lp, double& cm, double& cp) {
+  const bool par = any && x <= fmin(y, z), bwd = any && !par && y <= z, fwd = any && !par && !bwd;
+  cm = par ? wm : bwd ? lm : 0.0;
+  cp = par ? wp : fwd ? lp : 0.0;
 }
 
-// Derivative (cm, cp) of a limited face increment with respect to the backward and
-// forward differences dm = e0 - em, dp = ep - e0, on the branch the limiter took (the
-// arguments are the forward increments' own expressions).
-__device__ __forceinline__ void dinc_up_u(double em, double e0, double ep, double& cm, double& cp) {
-  const double dm = e0 - em, dp = ep - e0;
-  switch (minmod3_arg(fma(3.0, dp, dm) * 0.125, dm, dp)) {
-    case 0: cm = 0.125; cp = 0.375; break;
-    case 1: cm = 1.0; cp = 0.0; break;
-    case 2: cm = 0.0; cp = 1.0; break;
-    default: cm = 0.0; cp = 0.0;
+// The reverse of one field of face_pair: cotangents qL, qR of the limited states -> the
+// stencil cells' values; a state that fell back (fbL, fbR) is its cell's own.
+// ADD: added to oA .. oD, else stored.
+template <int DIR, bool ADD>
+__device__ __forceinline__ void pair_rev(double A, double B, double C, double D, const double* coB,
+                                         const double* coC, bool fbL, bool fbR, double qL,
+                                         double qR, double& oA, double& oB, double& oC, double& oD) {
+  const double d2 = C - B, s = copysign(1.0, d2), a = fabs(d2);
+  const double b1 = s * (B - A), b3 = s * (D - C);
+  double um, up, lm, lp;
+  if constexpr (DIR == 0) {
+    dlim(!fbL && a > 0.0 && b1 > 0.0, fma(coB[RC_WPP], a, coB[RC_WPM] * b1), coB[RC_LPM] * b1,
+         coB[RC_LPP] * a, coB[RC_WPM], coB[RC_WPP], coB[RC_LPM], coB[RC_LPP], um, up);
+    dlim(!fbR && a > 0.0 && b3 > 0.0, fma(-coC[RC_WMP], b3, -coC[RC_WMM] * a), -coC[RC_LMM] * a,
+         -coC[RC_LMP] * b3, coC[RC_WMM], coC[RC_WMP], coC[RC_LMM], coC[RC_LMP], lm, lp);
+  } else {
+    dlim(!fbL && a > 0.0 && b1 > 0.0, fma(3.0, a, b1) * 0.125, b1, a, 0.125, 0.375, 1.0, 1.0, um, up);
+    dlim(!fbR && a > 0.0 && b3 > 0.0, fma(3.0, a, b3) * 0.125, a, b3, -0.375, -0.125, -1.0, -1.0, lm, lp);
   }
-}
-__device__ __forceinline__ void dinc_lo_u(double em, double e0, double ep, double& cm, double& cp) {
-  const double dm = e0 - em, dp = ep - e0;
-  switch (minmod3_arg(-(fma(3.0, dm, dp) * 0.125), -dm, -dp)) {
-    case 0: cm = -0.375; cp = -0.125; break;
-    case 1: cm = -1.0; cp = 0.0; break;
-    case 2: cm = 0.0; cp = -1.0; break;
-    default: cm = 0.0; cp = 0.0;
-  }
-}
-__device__ __forceinline__ void dinc_up_c(double em, double e0, double ep, const double* co,
-                                          double& cm, double& cp) {
-  const double dm = e0 - em, dp = ep - e0;
-  switch (minmod3_arg(fma(co[RC_WPP], dp, co[RC_WPM] * dm), co[RC_LPM] * dm, co[RC_LPP] * dp)) {
-    case 0: cm = co[RC_WPM]; cp = co[RC_WPP]; break;
-    case 1: cm = co[RC_LPM]; cp = 0.0; break;
-    case 2: cm = 0.0; cp = co[RC_LPP]; break;
-    default: cm = 0.0; cp = 0.0;
-  }
-}
-__device__ __forceinline__ void dinc_lo_c(double em, double e0, double ep, const double* co,
-                                          double& cm, double& cp) {
-  const double dm = e0 - em, dp = ep - e0;
-  switch (minmod3_arg(fma(co[RC_WMP], dp, co[RC_WMM] * dm), co[RC_LMM] * dm, co[RC_LMP] * dp)) {
-    case 0: cm = co[RC_WMM]; cp = co[RC_WMP]; break;
-    case 1: cm = co[RC_LMM]; cp = 0.0; break;
-    case 2: cm = 0.0; cp = co[RC_LMP]; break;
-    default: cm = 0.0; cp = 0.0;
+  const double vA = -um * qL, vB = fma(1.0 + um - up, qL, -lm * qR);
+  const double vC = fma(up, qL, (1.0 + lm - lp) * qR), vD = lp * qR;
+  if constexpr (ADD) {
+    oA += vA; oB += vB; oC += vC; oD += vD;
+  } else {
+    oA = vA; oB = vB; oC = vC; oD = vD;
   }
 }
 
@@ -245,127 +235,155 @@ __device__ __forceinline__ void dust_cot_to_cons(const double* w, const double* 
   }
 }
 
-// limited face states of the gas (stationary flow at the face + W' + increment), rebuilt
-// for the reverse sweep rather than kept across the solve (registers)
+// Reverse of a gas face by the short form (gamma = 7/5; states, cotangents in field slots):
+// the star state and the pressure functions by gas_face64's polynomials, their slopes by the
+// same polynomials' derivatives, and the partial derivatives of f = sqrt(p_K / rho_K) h(p/p_K)
+// from f and f' alone: df/drho_K = -f / (2 rho_K), df/dp_K = f / (2 p_K) - (p / p_K) f'.
+// Returns false, the cotangents unset, where the short form does not apply.
 template <int DIR>
-__device__ __forceinline__ void gas_face_states(const double* wA, const double* wB,
-                                                const double* wC, const double* wD,
-                                                const double* coB, const double* coC,
-                                                const double* bf, double qL[5], double qR[5]) {
-#pragma unroll
-  for (int f = 0; f < 5; ++f) {
-    double iB, iC;
-    if (DIR == 0) {
-      iB = inc_up_c<double, true>(wA[f], wB[f], wC[f], coB);
-      iC = inc_lo_c<double, true>(wB[f], wC[f], wD[f], coC);
-    } else {
-      iB = inc_up_u<double, true>(wA[f], wB[f], wC[f]);
-      iC = inc_lo_u<double, true>(wB[f], wC[f], wD[f]);
-    }
-    qL[f] = bf[f] + (wB[f] + iB);
-    qR[f] = bf[f] + (wC[f] + iC);
+__device__ __forceinline__ bool gas_weak_rev(const GasC& c, const double* qL, const double* qR,
+                                             const double* Fb, double* qLb, double* qRb) {
+  constexpr int N = Dirs<DIR>::n, T1 = Dirs<DIR>::t1, T2 = Dirs<DIR>::t2;
+  const double rL = qL[4], rR = qR[4], pL = qL[3], pR = qR[3], uL = qL[N], uR = qR[N];
+  const double irL = frcp(rL), irR = frcp(rR);
+  const double c2L = c.g * pL * irL, c2R = c.g * pR * irR;
+  const bool weak = rL > 0.0 && pL > 0.0 && rR > 0.0 && pR > 0.0 && uL * uL < 0.81 * c2L &&
+                    uR * uR < 0.81 * c2R;
+  const double rsL = frsq(c2L), rsR = frsq(c2R);
+  const double cL = c2L * rsL, cR = c2R * rsR, du = uR - uL;
+  const double ipL = frcp(pL), ipR = frcp(pR);
+  const double gL = (5.0 / 7.0) * cL, gR = (5.0 / 7.0) * cR;
+  const WeakStar w = weak_star(c, pL, pR, ipL, ipR, gL, gR, irL * rsL, irR * rsR, du,
+                               0.5 * (pL + pR) - 0.125 * du * (rL + rR) * (cL + cR), weak);
+  const double ps = w.ps, xL = (ps - pL) * ipL, xR = (ps - pR) * ipR;
+  const bool narrow = wave_none(w.xm > 1.0 / 512.0);
+  double GL, GR, dGL, dGR;
+  if (narrow) {
+    const ctab t = weak_table(WK_G);
+    GL = weak_poly_d<4>(t, xL, 1.0, dGL);
+    GR = weak_poly_d<4>(t, xR, 1.0, dGR);
+  } else {
+    const ctab t = weak_table(WKW_G);
+    GL = weak_poly_d<8>(t, xL, 1.0, dGL);
+    GR = weak_poly_d<8>(t, xR, 1.0, dGR);
   }
+  const double fL = gL * xL * GL, fR = gR * xR * GR;
+  const double dfL = gL * ipL * fma(xL, dGL, GL), dfR = gR * ipR * fma(xR, dGR, GR);
+  const double us = 0.5 * (uL + uR) + 0.5 * (fR - fL);
+  if (!(weak && w.conv && us * us < 0.81 * fmin(c2L, c2R))) return false;
+  const bool left = us >= 0.0;
+  const double rK = left ? rL : rR, ipK = left ? ipL : ipR, x = left ? xL : xR;
+  double dR;
+  const double R = narrow ? weak_poly_d<4>(weak_table(WK_R), x, 5.0 / 7.0, dR)
+                          : weak_poly_d<8>(weak_table(WKW_R), x, 5.0 / 7.0, dR);
+  const double ratio = fma(x, R, 1.0), drs = rK * fma(x, dR, R) * ipK;  // rho* / rho_K, drho*/dp*
+  GasRec rec;
+  rec.rho = fma(rK * x, R, rK);
+  rec.un = us;
+  rec.t1 = left ? qL[T1] : qR[T1];
+  rec.t2 = left ? qL[T2] : qR[T2];
+  rec.p = ps;
+  const double flb[5] = {Fb[4], Fb[N], Fb[T1], Fb[T2], Fb[3]};
+  double Wb[5];
+  flux_rev(c, rec, flb, Wb);
+  // (as riemann_rev: through rho*, u* and p*)
+  const double hub = 0.5 * Wb[1], rb = Wb[0] * ratio, pb = -Wb[0] * drs * (1.0 + x);
+  const double s = (Wb[4] + Wb[0] * drs + hub * (dfR - dfL)) * frcp(dfL + dfR);
+  const double aL = -(hub + s), aR = hub - s;  // cotangents of f_L, f_R at fixed p*
+  qLb[4] = aL * (-0.5 * fL * irL) + (left ? rb : 0.0);
+  qRb[4] = aR * (-0.5 * fR * irR) + (left ? 0.0 : rb);
+  qLb[3] = aL * (0.5 * fL * ipL - (1.0 + xL) * dfL) + (left ? pb : 0.0);
+  qRb[3] = aR * (0.5 * fR * ipR - (1.0 + xR) * dfR) + (left ? 0.0 : pb);
+  qLb[N] = hub + s;
+  qRb[N] = hub - s;
+  qLb[T1] = left ? Wb[2] : 0.0;
+  qLb[T2] = left ? Wb[3] : 0.0;
+  qRb[T1] = left ? 0.0 : Wb[2];
+  qRb[T2] = left ? 0.0 : Wb[3];
+  return true;
 }
 
 // Reverse of one gas face: Fb (field order) is the cotangent of the face flux; the
 // contributions to the reconstructed variables W' of the stencil cells A, B | C, D are
-// added to cA..cD.
-template <int DIR, bool G75>
-__device__ void gas_face_vjp(const GasC& c, const double* wA, const double* wB, const double* wC,
-                             const double* wD, const double* coB, const double* coC,
-                             const double* bf, const double* bB, const double* bC,
-                             const double* Fb, double* cA, double* cB, double* cC, double* cD) {
+// stored in cA .. cD, or (ADD) added to them.  cell(c, f): W' of a cell, after again() read anew (held across
+// the solve the cells would cost 40 registers); bf(f): the stationary flow at the face;
+// bB(f), bC(f): at the centres of B and C.
+template <int DIR, bool ADD, bool G75, class Cell, class Bf, class Bc>
+__device__ __forceinline__ void gas_face_vjp(const GasC& c, const RecC& rc, Cell cell, const double* coB,
+                                             const double* coC, Bf bf, Bc bB, Bc bC,
+                                             const double* Fb, double* cA,
+                                             double* cB, double* cC, double* cD) {
   constexpr int N = Dirs<DIR>::n, T1 = Dirs<DIR>::t1, T2 = Dirs<DIR>::t2;
   double qL[5], qR[5];
-  gas_face_states<DIR>(wA, wB, wC, wD, coB, coC, bf, qL, qR);
-  const bool fbL = !(qL[4] > 0.0 && qL[3] > 0.0);
-  const bool fbR = !(qR[4] > 0.0 && qR[3] > 0.0);
-  if (fbL) {
-#pragma unroll
-    for (int f = 0; f < 5; ++f) qL[f] = bB[f] + wB[f];
-  }
-  if (fbR) {
-#pragma unroll
-    for (int f = 0; f < 5; ++f) qR[f] = bC[f] + wC[f];
-  }
-  double WLb[5], WRb[5];
-  {
-    double fl[5];
-    TStat st = {0, 0, 0, 0, 0, 0, 0};
-    GasRec rec;
-    gas_riemann<G75, true>(c, qL[4], frcp(qL[4]), qL[N], qL[T1], qL[T2], qL[3], qR[4], frcp(qR[4]),
-                           qR[N], qR[T1], qR[T2], qR[3], fl, st, &rec);
-    const double flb[5] = {Fb[4], Fb[N], Fb[T1], Fb[T2], Fb[3]};
-    double Wb[5];
-    flux_rev(c, rec, flb, Wb);
-    const double WL[5] = {qL[4], qL[N], qL[T1], qL[T2], qL[3]};
-    const double WR[5] = {qR[4], qR[N], qR[T1], qR[T2], qR[3]};
-    riemann_rev<G75>(c, WL, WR, rec, Wb, WLb, WRb);
-  }
-  // face-frame cotangents (rho, un, t1, t2, p) -> field slots (u, v, w, P, rho)
-  double qLb[5], qRb[5];
-  qLb[4] = WLb[0]; qLb[N] = WLb[1]; qLb[T1] = WLb[2]; qLb[T2] = WLb[3]; qLb[3] = WLb[4];
-  qRb[4] = WRb[0]; qRb[N] = WRb[1]; qRb[T1] = WRb[2]; qRb[T2] = WRb[3]; qRb[3] = WRb[4];
-  // left face state -> cells A, B, C (or B alone after a fallback); right -> B, C, D
 #pragma unroll
   for (int f = 0; f < 5; ++f) {
+    face_pair<DIR>(rc, cell(0, f), cell(1, f), cell(2, f), cell(3, f), coB, coC, qL[f], qR[f]);
+    const double w0 = bf(f);
+    qL[f] = w0 + qL[f];
+    qR[f] = w0 + qR[f];
+  }
+  double qLb[5], qRb[5];
+  bool fbL = false, fbR = false, done = false;
+  if constexpr (G75) done = gas_weak_rev<DIR>(c, qL, qR, Fb, qLb, qRb);
+  if (!done) {
+    fbL = !(qL[4] > 0.0 && qL[3] > 0.0);
+    fbR = !(qR[4] > 0.0 && qR[3] > 0.0);
     if (fbL) {
-      cB[f] += qLb[f];
-    } else {
-      double cm, cp;
-      if (DIR == 0) dinc_up_c(wA[f], wB[f], wC[f], coB, cm, cp);
-      else dinc_up_u(wA[f], wB[f], wC[f], cm, cp);
-      cA[f] -= cm * qLb[f];
-      cB[f] += (1.0 + cm - cp) * qLb[f];
-      cC[f] += cp * qLb[f];
+#pragma unroll
+      for (int f = 0; f < 5; ++f) qL[f] = bB(f) + cell(1, f);
     }
     if (fbR) {
-      cC[f] += qRb[f];
-    } else {
-      double cm, cp;
-      if (DIR == 0) dinc_lo_c(wB[f], wC[f], wD[f], coC, cm, cp);
-      else dinc_lo_u(wB[f], wC[f], wD[f], cm, cp);
-      cB[f] -= cm * qRb[f];
-      cC[f] += (1.0 + cm - cp) * qRb[f];
-      cD[f] += cp * qRb[f];
+#pragma unroll
+      for (int f = 0; f < 5; ++f) qR[f] = bC(f) + cell(2, f);
     }
+    double WLb[5], WRb[5];
+    {
+      double fl[5];
+      TStat st = {0, 0, 0, 0, 0, 0, 0};
+      GasRec rec;
+      gas_riemann<G75, true>(c, qL[4], frcp(qL[4]), qL[N], qL[T1], qL[T2], qL[3], qR[4], frcp(qR[4]),
+                             qR[N], qR[T1], qR[T2], qR[3], fl, st, &rec);
+      const double flb[5] = {Fb[4], Fb[N], Fb[T1], Fb[T2], Fb[3]};
+      double Wb[5];
+      flux_rev(c, rec, flb, Wb);
+      const double WL[5] = {qL[4], qL[N], qL[T1], qL[T2], qL[3]};
+      const double WR[5] = {qR[4], qR[N], qR[T1], qR[T2], qR[3]};
+      riemann_rev<G75>(c, WL, WR, rec, Wb, WLb, WRb);
+    }
+    // face-frame cotangents (rho, un, t1, t2, p) -> field slots (u, v, w, P, rho)
+    qLb[4] = WLb[0]; qLb[N] = WLb[1]; qLb[T1] = WLb[2]; qLb[T2] = WLb[3]; qLb[3] = WLb[4];
+    qRb[4] = WRb[0]; qRb[N] = WRb[1]; qRb[T1] = WRb[2]; qRb[T2] = WRb[3]; qRb[3] = WRb[4];
+  }
+  // left face state -> cells A, B, C (or B alone after a fallback); right -> B, C, D
+  cell.again();
+#pragma unroll
+  for (int f = 0; f < 5; ++f) {
+    pair_rev<DIR, ADD>(cell(0, f), cell(1, f), cell(2, f), cell(3, f), coB, coC, fbL, fbR, qLb[f],
+                       qRb[f], cA[f], cB[f], cC[f], cD[f]);
   }
 }
 
 // Reverse of one dust face (velocity and density reconstructed whole; a negative face
 // density falls back to the cell value).  Contributions to the cells' reconstructed
 // variables.
-template <int DIR>
-__device__ void dust_face_vjp(const double* wA, const double* wB, const double* wC,
-                              const double* wD, const double* coB, const double* coC,
-                              const double* Fb, double* cA, double* cB, double* cC, double* cD) {
+template <int DIR, bool ADD, class Cell>
+__device__ __forceinline__ void dust_face_vjp(const RecC& rc, Cell cell, const double* coB, const double* coC,
+                                              const double* Fb, double* cA,
+                                             double* cB, double* cC, double* cD) {
   constexpr int N = Dirs<DIR>::n, T1 = Dirs<DIR>::t1, T2 = Dirs<DIR>::t2;
-  double qL[4], qR[4], cmB[4], cpB[4], cmC[4], cpC[4];
+  double qL[4], qR[4];
 #pragma unroll
   for (int f = 0; f < 4; ++f) {
-    double iB, iC;
-    if (DIR == 0) {
-      iB = inc_up_c<double, true>(wA[f], wB[f], wC[f], coB);
-      iC = inc_lo_c<double, true>(wB[f], wC[f], wD[f], coC);
-      dinc_up_c(wA[f], wB[f], wC[f], coB, cmB[f], cpB[f]);
-      dinc_lo_c(wB[f], wC[f], wD[f], coC, cmC[f], cpC[f]);
-    } else {
-      iB = inc_up_u<double, true>(wA[f], wB[f], wC[f]);
-      iC = inc_lo_u<double, true>(wB[f], wC[f], wD[f]);
-      dinc_up_u(wA[f], wB[f], wC[f], cmB[f], cpB[f]);
-      dinc_lo_u(wB[f], wC[f], wD[f], cmC[f], cpC[f]);
-    }
-    qL[f] = wB[f] + iB;
-    qR[f] = wC[f] + iC;
+    face_pair<DIR>(rc, cell(0, f), cell(1, f), cell(2, f), cell(3, f), coB, coC, qL[f], qR[f]);
   }
   const bool fbL = qL[3] < 0.0, fbR = qR[3] < 0.0;
   if (fbL) {
 #pragma unroll
-    for (int f = 0; f < 4; ++f) qL[f] = wB[f];
+    for (int f = 0; f < 4; ++f) qL[f] = cell(1, f);
   }
   if (fbR) {
 #pragma unroll
-    for (int f = 0; f < 4; ++f) qR[f] = wC[f];
+    for (int f = 0; f < 4; ++f) qR[f] = cell(2, f);
   }
   double fl[4];
   int side;
@@ -389,22 +407,11 @@ __device__ void dust_face_vjp(const double* wA, const double* wB, const double* 
     side_rev(qL, 0.5, qLb);
     side_rev(qR, 0.5, qRb);
   }
+  cell.again();
 #pragma unroll
   for (int f = 0; f < 4; ++f) {
-    if (fbL) {
-      cB[f] += qLb[f];
-    } else {
-      cA[f] -= cmB[f] * qLb[f];
-      cB[f] += (1.0 + cmB[f] - cpB[f]) * qLb[f];
-      cC[f] += cpB[f] * qLb[f];
-    }
-    if (fbR) {
-      cC[f] += qRb[f];
-    } else {
-      cB[f] -= cmC[f] * qRb[f];
-      cC[f] += (1.0 + cmC[f] - cpC[f]) * qRb[f];
-      cD[f] += cpC[f] * qRb[f];
-    }
+    pair_rev<DIR, ADD>(cell(0, f), cell(1, f), cell(2, f), cell(3, f), coB, coC, fbL, fbR, qLb[f],
+                       qRb[f], cA[f], cB[f], cC[f], cD[f]);
   }
 }
 
@@ -428,12 +435,6 @@ struct AdjCtx {
   __device__ int jwrap(int j) const {
     j %= g.nth;
     return j < 0 ? j + g.nth : j;
-  }
-  // w = cw V^-1 lambda of an interior cell (zero outside the grid)
-  __device__ double wc(int f, int k, int i, int j) const {
-    if (k < 0 || k >= g.nz || i < 0 || i >= g.nr) return 0.0;
-    return A.cw * a.t.rt[(size_t)i * RT_N + RT_INVV] *
-           A.cot[(size_t)(F0 + f) * g.N + ((size_t)k * g.nr + i) * g.nth + j];
   }
   // w of every field of a cell (zero outside the grid), all loads requested together
   __device__ void wc_all(int k, int i, int j, double* out) const {
@@ -468,16 +469,13 @@ struct AdjCtx {
   }
 };
 
-template <int D, bool GAS, bool G75>
-__device__ __forceinline__ void face_vjp(const GasC& gc, const double* wA, const double* wB,
-                                         const double* wC, const double* wD, const double* coB,
-                                         const double* coC, const double* bf, const double* bB,
-                                         const double* bC, const double* Fb, double* oA,
-                                         double* oB, double* oC, double* oD) {
-  if constexpr (GAS)
-    gas_face_vjp<D, G75>(gc, wA, wB, wC, wD, coB, coC, bf, bB, bC, Fb, oA, oB, oC, oD);
-  else
-    dust_face_vjp<D>(wA, wB, wC, wD, coB, coC, Fb, oA, oB, oC, oD);
+template <int D, bool ADD, bool GAS, bool G75, class Cell, class Bf, class Bc>
+__device__ __forceinline__ void face_vjp(const GasC& gc, const RecC& rc, Cell cell, const double* coB,
+                                         const double* coC, Bf bf, Bc bB, Bc bC,
+                                         const double* Fb, double* cA,
+                                             double* cB, double* cC, double* cD) {
+  if constexpr (GAS) gas_face_vjp<D, ADD, G75>(gc, rc, cell, coB, coC, bf, bB, bC, Fb, cA, cB, cC, cD);
+  else dust_face_vjp<D, ADD>(rc, cell, coB, coC, Fb, cA, cB, cC, cD);
 }
 
 // cotangent of a cell's reconstructed variables w (stationary flow b) -> conservative
@@ -488,17 +486,32 @@ __device__ __forceinline__ void cot_to_cons(const double* w, const double* b, do
   else dust_cot_to_cons(w, wb, eb);
 }
 
+// In-plane faces and sources.  Bound by instruction issue (4000 -> 3000 lane-instructions per
+// cell of the gas) and, for a quarter of the time, by the loads of a plane and its halo.  The
+// general reverse of a face runs the recording solver, twenty divisions and every branch of
+// the wave pattern; a face of weak waves takes gas_weak_rev.  One copy of the face serves the
+// theta faces, the r faces and the tile's edge: four copies spilled 72 registers.  128 x 256 x
+// 32 cells, one dust species: gas 300 -> 186 us per launch, dust 158 -> 120.  Tiles of four rows
+// with two workgroups on a CU, which overlap the loads of one with the faces of the other,
+// gave 201 and 120: the halo and the edge faces weigh more.
 template <bool GAS, int ND, bool G75>
-__global__ void __launch_bounds__(NT) k_adj_plane(AdjArgs A, int species) {
+__global__ void __launch_bounds__(NT, 2) k_adj_plane(AdjArgs A, int species) {
   using C = AdjCtx<GAS>;
   constexpr int NG = C::NG;
   constexpr int H = 3;
-  __shared__ double s_e[NG][TI + 2 * H][TJ + 2 * H];
+  constexpr int W = TJ + 2 * H, PL = (TI + 2 * H) * W, PT = TI * TJ;
+  __shared__ double s_e[NG * PL];
   // w = cw V^-1 lambda of the staged cells (zero outside the grid), staged with the plane
   // so that the faces read no global memory
-  __shared__ double s_w[NG][TI + 2 * H][TJ + 2 * H];
-  __shared__ double s_at[NG][TI][TJ];
-  __shared__ double s_ar[NG][TI][TJ];
+  __shared__ double s_w[NG * PL];
+  // the cells' totals from the theta and the r faces
+  __shared__ double s_acc[2 * NG * PT];
+  // faces by slot: theta faces of row r in slot r, r faces above tile row rb in TI + 2 + rb:
+  // the face area and, per plane, the stationary flow there
+  constexpr int NS = 2 * TI + 3;
+  __shared__ double s_fa[NS], s_bf[GAS ? NS : 1][5];
+  // parabola weights of the cells of tile rows -2 .. TI + 1, and of a theta stencil
+  __shared__ double s_co[TI + 5][RC_N];
   __shared__ double s_red[NT / 64];
 
   const C X(A, species);
@@ -526,134 +539,128 @@ __global__ void __launch_bounds__(NT) k_adj_plane(AdjArgs A, int species) {
   const double cw = A.cw;
   const double* rt = a.t.rt + (size_t)igc * RT_N;
   const double invrc = rt[RT_INVRC], omk = rt[RT_OMK];
-  using DR = std::integral_constant<int, 0>;
-  using DT = std::integral_constant<int, 1>;
+  static_assert((TI + 5) * RC_N + NS <= NT && 5 * NS <= NT && 3 * (TI + TJ) <= NT,
+                "one table entry, one edge face per thread");
+  if (tid < (TI + 4) * RC_N) {
+    s_co[tid / RC_N][tid % RC_N] = rco_ptr(a, min(i0 + tid / RC_N - 2, g.nr))[tid % RC_N];
+  } else if (tid < (TI + 5) * RC_N) {
+    // (RC_WPM .. RC_LMP on equal spacing)
+    const int e = tid % RC_N;
+    s_co[TI + 4][e] = e == RC_WPM   ? 0.125
+                      : e == RC_WPP ? 0.375
+                      : e == RC_WMM ? -0.375
+                      : e == RC_WMP ? -0.125
+                      : e < RC_WMM  ? 1.0
+                                    : -1.0;
+  } else if (tid < (TI + 5) * RC_N + NS) {
+    const int q = tid - (TI + 5) * RC_N;
+    s_fa[q] = q < TI ? a.t.rt[(size_t)min(i0 + q, g.nr - 1) * RT_N + RT_ATH]
+                     : a.t.ar[min(max(i0 + q - TI - 1, 0), g.nr)];
+  }
 
-  // theta face between tile columns cb and cb + 1 (s_e column cb + H) of tile row r:
-  // contributions to columns cb - 1 .. cb + 2
-  auto theta_face = [&](int k, int r, int cb, double* oA, double* oB, double* oC, double* oD) {
-    double eA[NG], eB[NG], eC[NG], eD[NG], Fb[NG];
-    const int i = i0 + r;
-    const double ath = a.t.rt[(size_t)i * RT_N + RT_ATH];
-#pragma unroll
-    for (int f = 0; f < NG; ++f) Fb[f] = ath * (s_w[f][r + H][cb + 1 + H] - s_w[f][r + H][cb + H]);
-#pragma unroll
-    for (int f = 0; f < NG; ++f) {
-      eA[f] = s_e[f][r + H][cb + H - 1]; eB[f] = s_e[f][r + H][cb + H];
-      eC[f] = s_e[f][r + H][cb + H + 1]; eD[f] = s_e[f][r + H][cb + H + 2];
-      oA[f] = 0.0; oB[f] = 0.0; oC[f] = 0.0; oD[f] = 0.0;
-    }
-    const double* bf = a.t.wc + ((size_t)k * g.nr + i) * WB_N;
-    face_vjp<DT::value, GAS, G75>(X.gc, eA, eB, eC, eD, nullptr, nullptr, bf, bf, bf, Fb, oA, oB,
-                                  oC, oD);
-  };
-  // r face between tile rows rb and rb + 1 (s_e row rb + H) of tile column cl
-  auto r_face = [&](int k, int rb, int cl, double* oA, double* oB, double* oC, double* oD) {
-    double eA[NG], eB[NG], eC[NG], eD[NG], Fb[NG];
-    const int ib = i0 + rb;
-    const double ar = a.t.ar[ib + 1];
-#pragma unroll
-    for (int f = 0; f < NG; ++f) Fb[f] = ar * (s_w[f][rb + 1 + H][cl + H] - s_w[f][rb + H][cl + H]);
-#pragma unroll
-    for (int f = 0; f < NG; ++f) {
-      eA[f] = s_e[f][rb + H - 1][cl + H]; eB[f] = s_e[f][rb + H][cl + H];
-      eC[f] = s_e[f][rb + H + 1][cl + H]; eD[f] = s_e[f][rb + H + 2][cl + H];
-      oA[f] = 0.0; oB[f] = 0.0; oC[f] = 0.0; oD[f] = 0.0;
-    }
-    const double* bf = a.t.wr + ((size_t)k * (g.nr + 1) + (ib + 1)) * WB_N;
-    face_vjp<DR::value, GAS, G75>(X.gc, eA, eB, eC, eD, rco_ptr(a, ib), rco_ptr(a, ib + 1), bf,
-                                  bg_ptr(a, k, ib), bg_ptr(a, k, ib + 1), Fb, oA, oB, oC, oD);
-  };
-
+  const RecC recc;
   double stb = 0.0;  // Stokes-number partial (dust)
   for (int k = k0; k < k1; ++k) {
+    // (the last plane's cells have been read)
+    if (k > k0) __syncthreads();
     // ---- stage the plane with a three-cell halo; clear the tile accumulators
     {
-      // at most two cells per thread; both cells' loads issued before the stores
-      constexpr int W = TJ + 2 * H, NC = (TI + 2 * H) * W;
-      static_assert(NC <= 2 * NT, "two staged cells per thread");
-      const int h0 = tid, h1 = tid + NT;
-      const int ia = i0 + h0 / W - H, ja = X.jwrap(j0 + h0 % W - H);
-      const int ib = i0 + h1 / W - H, jb = X.jwrap(j0 + h1 % W - H);
-      double v0[NG], v1[NG], c0[NG], c1[NG];
-      X.wc_all(k, ia, ja, c0);
-      if (h1 < NC) X.wc_all(k, ib, jb, c1);
-      load_recon<false, false, NG>(a, E, F0, k, ia, ja, v0);
-      if (h1 < NC) load_recon<false, false, NG>(a, E, F0, k, ib, jb, v1);
+      // all cells' loads issued before the stores
+      constexpr int PER = (PL + NT - 1) / NT;
+      double v[PER][NG], c[PER][NG];
 #pragma unroll
-      for (int f = 0; f < NG; ++f) {
-        s_e[f][h0 / W][h0 % W] = v0[f];
-        s_w[f][h0 / W][h0 % W] = c0[f];
+      for (int q = 0; q < PER; ++q) {
+        const int h = min(tid + q * NT, PL - 1);
+        X.wc_all(k, i0 + h / W - H, X.jwrap(j0 + h % W - H), c[q]);
       }
-      if (h1 < NC) {
 #pragma unroll
-        for (int f = 0; f < NG; ++f) {
-          s_e[f][h1 / W][h1 % W] = v1[f];
-          s_w[f][h1 / W][h1 % W] = c1[f];
+      for (int q = 0; q < PER; ++q) {
+        const int h = min(tid + q * NT, PL - 1);
+        load_recon<false, false, NG>(a, E, F0, k, i0 + h / W - H, X.jwrap(j0 + h % W - H), v[q]);
+      }
+#pragma unroll
+      for (int q = 0; q < PER; ++q) {
+        const int h = tid + q * NT;
+        if (h < PL) {
+#pragma unroll
+          for (int f = 0; f < NG; ++f) {
+            s_e[f * PL + h] = v[q][f];
+            s_w[f * PL + h] = c[q][f];
+          }
         }
       }
+      if (GAS && tid >= NT - NS * 5) {
+        const int q = (tid - (NT - NS * 5)) / 5, f = (tid - (NT - NS * 5)) % 5;
+        const double* b = q < TI ? a.t.wc + ((size_t)k * g.nr + min(i0 + q, g.nr - 1)) * WB_N
+                                 : a.t.wr + ((size_t)k * (g.nr + 1) + min(max(i0 + q - TI - 1, 0), g.nr)) * WB_N;
+        s_bf[q][f] = b[f];
+      }
     }
 #pragma unroll
-    for (int f = 0; f < NG; ++f) { s_at[f][ti][tj] = 0.0; s_ar[f][ti][tj] = 0.0; }
+    for (int f = 0; f < 2 * NG; ++f) s_acc[f * PT + tid] = 0.0;
     __syncthreads();
 
-    double oA[NG], oB[NG], oC[NG], oD[NG];
-    // ---- theta faces j+1/2 of the thread's own cell; four ordered scatter phases
-    const bool tok = ig < g.nr;
-    if (tok) theta_face(k, ti, tj, oA, oB, oC, oD);
-#pragma unroll
-    for (int ph = 0; ph < 4; ++ph) {
-      const int col = tj - 1 + ph;
-      if (tok && col >= 0 && col < TJ) {
-        const double* o = ph == 0 ? oA : ph == 1 ? oB : ph == 2 ? oC : oD;
-#pragma unroll
-        for (int f = 0; f < NG; ++f) s_at[f][ti][col] += o[f];
+    // ---- the faces within 3/2 cells of the tile, one copy of the face for all: the thread's
+    //      own theta face j+1/2; its own r face i+1/2; the others (theta faces at tile columns
+    //      -3/2, -1/2, 64+1/2 of each row by the first 3 TI threads, r faces at tile rows -3/2,
+    //      -1/2, TI+1/2 of each column by the next 3 TJ).  A face in its own frame is a DIR = 0
+    //      face: the velocity along theta swaps slots with the radial one, and the equal
+    //      spacing's weights stand for the table's.  Four ordered scatter phases each
+#pragma nounroll
+    for (int pass = 0; pass < 3; ++pass) {
+      bool theta = pass == 0, ok = pass < 2 && ig < g.nr && (theta || colok);
+      int line = theta ? ti : tj, pos = theta ? tj : ti;  // tile row / column; lower cell
+      if (pass == 2) {
+        const int e = tid - 3 * TI, q = e < 0 ? tid % 3 : e / TJ;
+        theta = e < 0;
+        line = theta ? tid / 3 : e % TJ;
+        pos = q == 0 ? -2 : q == 1 ? -1 : theta ? TJ : TI;
+        ok = theta ? i0 + line < g.nr
+                   : e < 3 * TJ && i0 + pos + 1 >= 0 && i0 + pos < g.nr && j0 + line < g.nth;
       }
-      __syncthreads();
-    }
-    // ---- r faces i+1/2 of the thread's own cell
-    const bool rok = ig < g.nr && colok;
-    if (rok) r_face(k, ti, tj, oA, oB, oC, oD);
+      double o[4][NG];
+      const int s0 = theta ? 1 : 0, s1 = theta ? 0 : 1;  // slots of the normal and first tangent
+      if (ok) {
+        const int st = theta ? 1 : W, at = theta ? (line + H) * W + pos + H : (pos + H) * W + line + H;
+        const int slot = theta ? line : TI + 2 + pos;
+        auto off = [&](int f) { return at + (f == 0 ? s0 * PL : f == 1 ? s1 * PL : f * PL); };
+        // (the base index of the second reads is one the optimiser cannot see through)
+        struct Cells {
+          const double* e;
+          int at, o0, o1, st;
+          __device__ double operator()(int c, int f) const {
+            return e[at + (f == 0 ? o0 : f == 1 ? o1 : f * PL) + (c - 1) * st];
+          }
+          __device__ void again() { asm volatile("" : "+v"(at)); }
+        };
+        const Cells cell = {s_e, at, s0 * PL, s1 * PL, st};
+        double Fb[NG];
 #pragma unroll
-    for (int ph = 0; ph < 4; ++ph) {
-      const int row = ti - 1 + ph;
-      if (rok && row >= 0 && row < TI) {
-        const double* o = ph == 0 ? oA : ph == 1 ? oB : ph == 2 ? oC : oD;
-#pragma unroll
-        for (int f = 0; f < NG; ++f) s_ar[f][row][tj] += o[f];
+        for (int f = 0; f < NG; ++f) Fb[f] = s_fa[slot] * (s_w[off(f) + st] - s_w[off(f)]);
+        auto bf = [&](int f) { return s_bf[GAS ? slot : 0][f == 0 ? s0 : f == 1 ? s1 : f]; };
+        struct Centre {
+          const double* b;
+          int s0, s1;
+          __device__ double operator()(int f) const { return b[f == 0 ? s0 : f == 1 ? s1 : f]; }
+        };
+        const int ib = theta ? i0 + line : i0 + pos;
+        const Centre bB = {theta ? a.t.wc + ((size_t)k * g.nr + ib) * WB_N : bg_ptr(a, k, ib), s0, s1};
+        const Centre bC = {theta ? bB.b : bg_ptr(a, k, ib + 1), s0, s1};
+        const int co = theta ? TI + 4 : pos + 2;
+        face_vjp<0, false, GAS, G75>(X.gc, recc, cell, s_co[co], s_co[theta ? co : co + 1], bf, bB, bC, Fb,
+                              o[0], o[1], o[2], o[3]);
       }
-      __syncthreads();
-    }
-    // ---- the remaining faces within 3/2 cells of the tile: theta faces at tile columns
-    //      -3/2, -1/2, 64+1/2 of each row (threads 0..23), r faces at tile rows -3/2,
-    //      -1/2, 8+1/2 of each column (threads 24..215)
-    int ekind = 0, eline = 0, epos = 0;  // 1 theta, 2 r; tile row/column; face lower cell
-    if (tid < 3 * TI) {
-      const int q = tid % 3;
-      ekind = 1; eline = tid / 3; epos = q == 0 ? -2 : (q == 1 ? -1 : TJ);
-      if (i0 + eline >= g.nr) ekind = 0;
-    } else if (tid < 3 * TI + 3 * TJ) {
-      const int e = tid - 3 * TI;
-      const int q = e / TJ;
-      ekind = 2; eline = e % TJ; epos = q == 0 ? -2 : (q == 1 ? -1 : TI);
-      const int ib = i0 + epos;
-      if (ib + 1 < 0 || ib >= g.nr || j0 + eline >= g.nth) ekind = 0;
-    }
-    if (ekind == 1) theta_face(k, eline, epos, oA, oB, oC, oD);
-    else if (ekind == 2) r_face(k, epos, eline, oA, oB, oC, oD);
+      double* acc = s_acc + (theta ? 0 : NG * PT);
 #pragma unroll
-    for (int ph = 0; ph < 4; ++ph) {
-      const int t = epos - 1 + ph;  // target cell along the face normal
-      if (ekind == 1 && t >= 0 && t < TJ) {
-        const double* o = ph == 0 ? oA : ph == 1 ? oB : ph == 2 ? oC : oD;
+      for (int ph = 0; ph < 4; ++ph) {
+        const int t = pos - 1 + ph;  // target cell along the face normal
+        if (ok && t >= 0 && t < (theta ? TJ : TI)) {
+          const int at = theta ? line * TJ + t : t * TJ + line;
 #pragma unroll
-        for (int f = 0; f < NG; ++f) s_at[f][eline][t] += o[f];
-      } else if (ekind == 2 && t >= 0 && t < TI) {
-        const double* o = ph == 0 ? oA : ph == 1 ? oB : ph == 2 ? oC : oD;
-#pragma unroll
-        for (int f = 0; f < NG; ++f) s_ar[f][t][eline] += o[f];
+          for (int f = 0; f < NG; ++f) acc[(f == 0 ? s0 : f == 1 ? s1 : f) * PT + at] += o[ph][f];
+        }
+        __syncthreads();
       }
-      __syncthreads();
     }
     // ---- in-plane total of the thread's cell, the reverse of its sources, the bases
     if (!act) continue;
@@ -663,8 +670,8 @@ __global__ void __launch_bounds__(NT) k_adj_plane(AdjArgs A, int species) {
       double wb[NG], w[NG];
 #pragma unroll
       for (int f = 0; f < NG; ++f) {
-        wb[f] = s_at[f][ti][tj] + s_ar[f][ti][tj];
-        w[f] = s_e[f][ti + H][tj + H];
+        wb[f] = s_acc[f * PT + tid] + s_acc[(NG + f) * PT + tid];
+        w[f] = s_e[f * PL + (ti + H) * W + tj + H];
       }
       cot_to_cons<GAS>(w, a.t.wc + ((size_t)k * g.nr + ig) * WB_N, X.gc.gm1, wb, cur);
     }
@@ -795,7 +802,8 @@ __global__ void __launch_bounds__(NT) k_adj_plane(AdjArgs A, int species) {
 
 // z faces: one thread per column and chunk of planes, marching up; adds the four stencil
 // contributions of every z face to the output written by k_adj_plane (each cell
-// completed in order: its faces k-3/2 .. k+3/2, lower first).
+// completed in order: its faces k-3/2 .. k+3/2, lower first).  One copy of the face, with
+// k_adj_plane's short form: gas 134 -> 80 us per launch on 128 x 256 x 32, dust 44 -> 34.
 template <bool GAS, int ND, bool G75>
 __global__ void __launch_bounds__(256, 2) k_adj_z(AdjArgs A, int species, int tkz) {
   using C = AdjCtx<GAS>;
@@ -815,15 +823,27 @@ __global__ void __launch_bounds__(256, 2) k_adj_z(AdjArgs A, int species, int tk
   const double* E = (const double*)a.in;
   const double Az = a.t.rt[(size_t)ig * RT_N + RT_AZ];
 
+  const RecC recc;
   double ra[NG], rb[NG], rc[NG], rd[NG];  // cells kf-1 .. kf+2 of the face kf+1/2
   auto load = [&](double* dst, int k) { load_recon<false, false, NG>(a, E, F0, k, ig, jg, dst); };
+  struct ZCells {
+    const double *a, *b, *c, *d;
+    __device__ double operator()(int q, int f) const { return q == 0 ? a[f] : q == 1 ? b[f] : q == 2 ? c[f] : d[f]; }
+    __device__ void again() {}
+  };
+  const ZCells zcell = {ra, rb, rc, rd};
+  struct At {
+    const double* b;
+    __device__ double operator()(int f) const { return b[f]; }
+  };
   // adds the face's contributions into oA..oD
   auto zface = [&](int kf, double* oA, double* oB, double* oC, double* oD) {
     double Fb[NG];
     X.wc_diff(kf + 1, ig, jg, kf, ig, jg, Az, Fb);
     const double* bf = a.t.wz + ((size_t)(kf + 1) * g.nr + ig) * WB_N;
-    face_vjp<2, GAS, G75>(X.gc, ra, rb, rc, rd, nullptr, nullptr, bf, bg_ptr(a, kf, ig),
-                          bg_ptr(a, kf + 1, ig), Fb, oA, oB, oC, oD);
+    const double *bB = bg_ptr(a, kf, ig), *bC = bg_ptr(a, kf + 1, ig);
+    face_vjp<2, true, GAS, G75>(X.gc, recc, zcell, nullptr, nullptr, [&](int f) { return bf[f]; },
+                          At{bB}, At{bC}, Fb, oA, oB, oC, oD);
   };
   auto real = [&](int kf) { return kf >= -1 && kf <= g.nz - 1; };
   // adds the z faces' cotangent v of cell k's reconstructed variables (w: the cell's W')
@@ -839,30 +859,16 @@ __global__ void __launch_bounds__(256, 2) k_adj_z(AdjArgs A, int species, int tk
     for (int f = 0; f < NG; ++f) A.out[(size_t)(F0 + f) * g.N + cell] = o[f];
   };
 
-  // contributions of the faces below cell k to cells k (zb) and k+1 (zc); za = cell k-1
-  // za, zb, zc, zd: cells k-1, k, k+1, k+2 of the face k+1/2 being processed; the
-  // contributions to cells below k0 (faces k0-3/2, k0-1/2) land in scratch accumulators
+  // za, zb, zc, zd: totals of the cells k-1, k, k+1, k+2 of the face k+1/2 being processed; the
+  // first two faces (k0-3/2, k0-1/2) reach into the chunk from below, and what they and the
+  // next give to cells below k0 is dropped
   double za[NG], zb[NG], zc[NG], zd[NG];
 #pragma unroll
   for (int f = 0; f < NG; ++f) { za[f] = 0.0; zb[f] = 0.0; zc[f] = 0.0; zd[f] = 0.0; }
-  load(ra, k0 - 3); load(rb, k0 - 2); load(rc, k0 - 1); load(rd, k0);
-  // face k0-3/2: cells k0-3 .. k0 -> (za, za, za, zb); only its last one is kept
-  if (real(k0 - 2)) {
-    zface(k0 - 2, zd, zd, zc, zb);
-#pragma unroll
-    for (int f = 0; f < NG; ++f) { zc[f] = 0.0; zd[f] = 0.0; }
-  }
-#pragma unroll
-  for (int f = 0; f < NG; ++f) { ra[f] = rb[f]; rb[f] = rc[f]; rc[f] = rd[f]; }
-  load(rd, k0 + 1);
-  // face k0-1/2: cells k0-2 .. k0+1 -> (-, -, zb, zc)
-  if (real(k0 - 1)) {
-    zface(k0 - 1, zd, za, zb, zc);
-#pragma unroll
-    for (int f = 0; f < NG; ++f) { za[f] = 0.0; zd[f] = 0.0; }
-  }
+  const int kf0 = k0 - 2;
+  load(rb, kf0 - 1); load(rc, kf0); load(rd, kf0 + 1);
   if constexpr (GAS) {
-    for (int k = k0; k <= k1; ++k) {
+    for (int k = kf0; k <= k1; ++k) {
 #pragma unroll
       for (int f = 0; f < NG; ++f) { ra[f] = rb[f]; rb[f] = rc[f]; rc[f] = rd[f]; }
       load(rd, k + 2);
@@ -893,15 +899,15 @@ __global__ void __launch_bounds__(256, 2) k_adj_z(AdjArgs A, int species, int tk
     double wlo[NG], xr[NG], orw[NG];
     {
       double x[NG];
-      col_fetch(A.cot, k0, x);
-      wcell(k0, x, wlo);
+      col_fetch(A.cot, kf0, x);
+      wcell(kf0, x, wlo);
     }
-    col_fetch(A.cot, k0 + 1, xr);
+    col_fetch(A.cot, kf0 + 1, xr);
     DustRaw<false> nraw;
-    dust_fetch<false, false>(a, E, F0, k0 + 2, ig, jg, nraw);
+    dust_fetch<false, false>(a, E, F0, kf0 + 2, ig, jg, nraw);
 #pragma unroll
     for (int f = 0; f < NG; ++f) orw[f] = 0.0;
-    for (int k = k0; k <= k1; ++k) {
+    for (int k = kf0; k <= k1; ++k) {
 #pragma unroll
       for (int f = 0; f < NG; ++f) { ra[f] = rb[f]; rb[f] = rc[f]; rc[f] = rd[f]; }
       dust_finish<false>(nraw, rd);  // cell k+2
@@ -912,14 +918,14 @@ __global__ void __launch_bounds__(256, 2) k_adj_z(AdjArgs A, int species, int tk
       if (k + 1 <= k1) {
         dust_fetch<false, false>(a, E, F0, k + 3, ig, jg, nraw);
         col_fetch(A.cot, k + 2, xr);
-        col_fetch(A.out, k, orw);
+        col_fetch(A.out, max(k, k0), orw);
       }
       // face k+1/2 (cells k-1, k, k+1, k+2)
       if (real(k)) {
         double Fb[NG];
 #pragma unroll
         for (int f = 0; f < NG; ++f) Fb[f] = Az * (whi[f] - wlo[f]);
-        face_vjp<2, GAS, G75>(X.gc, ra, rb, rc, rd, nullptr, nullptr, nullptr, nullptr, nullptr,
+        face_vjp<2, true, GAS, G75>(X.gc, recc, zcell, nullptr, nullptr, At{nullptr}, At{nullptr}, At{nullptr},
                               Fb, za, zb, zc, zd);
       }
       if (k - 1 >= k0) {

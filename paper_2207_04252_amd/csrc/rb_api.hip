@@ -121,15 +121,15 @@ bool validate(const rb_config* c, std::string* why) {
   return true;
 }
 
-// z planes per block of a stage kernel of which `per_cu` workgroups fill a CU (the FP64 gas
-// one: at most 256 VGPRs per lane, two waves per SIMD; the others: 128, four).  A launch runs in
+// z planes per block of a stage kernel of which `per_cu` workgroups fill a CU (the gas ones:
+// at most 256 VGPRs per lane, two waves per SIMD; the dust one: 128, four).  A launch runs in
 // ceil(blocks / (256 per_cu)) rounds on the 256 CUs of an MI355X; a block marches tk planes
 // plus about 1.5 planes of set-up (initial column, first z face).  Takes the chunk length
 // with the fewest plane-times.
 int stage_chunk(const Layout& L, size_t nz, size_t per_cu) {
   if (nz == 1) return 1;
   const char* env = std::getenv("RB_TK");
-  if (env && std::atoi(env) > 0)  // at most 4096: the Newton histogram's 16-bit bins
+  if (env && std::atoi(env) > 0)
     return (int)std::min<size_t>(std::min(std::atoi(env), 4096), nz);
   const size_t tiles = (size_t)L.ntj * L.ntm, conc = 256 * per_cu;
   size_t tk = 2;

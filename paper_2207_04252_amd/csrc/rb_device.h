@@ -554,6 +554,68 @@ __device__ __forceinline__ double weak_poly(ctab t, double x, double c0) {
   return fma(x > 0.0 ? s : r, x, c0);
 }
 
+// the same with its derivative
+template <int DEG>
+__device__ __forceinline__ double weak_poly_d(ctab t, double x, double c0, double& dx) {
+  double r = t[0], s = t[1], dr = r, ds = s;
+#pragma unroll
+  for (int n = 1; n < DEG; ++n) {
+    r = fma(r, x, t[2 * n]);
+    s = fma(s, x, t[2 * n + 1]);
+    dr = fma(dr, x, r);
+    ds = fma(ds, x, s);
+  }
+  dx = x > 0.0 ? ds : dr;
+  return fma(x > 0.0 ? s : r, x, c0);
+}
+
+// The Newton iteration of the short form for the star pressure from the guess ps, where going:
+// the pressure functions f and slopes d (times rho c) of both sides at the last but one
+// iterate, the last step dp, the largest |x| met; conv: converged with |x| within 1/16.
+struct WeakStar {
+  double ps, fL, fR, dL, dR, dp, xm;
+  int it;
+  bool conv;
+};
+__device__ __forceinline__ WeakStar weak_star(const GasC& c, double pL, double pR, double ipL,
+                                              double ipR, double gL, double gR, double zL,
+                                              double zR, double du, double ps, bool going) {
+  WeakStar w;
+  double xm = 0.0;
+  bool conv = false;
+  w.dp = 0.0;
+  w.it = 0;
+  while (going && w.it < c.max_iter) {
+    ++w.it;
+    const double xL = (ps - pL) * ipL, xR = (ps - pR) * ipR;
+    xm = fmax(xm, fmax(fabs(xL), fabs(xR)));
+    if (wave_none(xm > 1.0 / 512.0)) {
+      const ctab t = weak_table(WK_G);
+      w.fL = gL * xL * weak_poly<4>(t, xL, 1.0);
+      w.fR = gR * xR * weak_poly<4>(t, xR, 1.0);
+      w.dL = zL * fma(fma(t[WK_D], xL, t[WK_D + 1]), xL, 1.0);
+      w.dR = zR * fma(fma(t[WK_D], xR, t[WK_D + 1]), xR, 1.0);
+    } else {
+      const ctab t = weak_table(WKW_G);
+      w.fL = gL * xL * weak_poly<8>(t, xL, 1.0);
+      w.fR = gR * xR * weak_poly<8>(t, xR, 1.0);
+      const ctab d = weak_table(WKW_D);
+      w.dL = zL * weak_poly<5>(d, xL, 1.0);
+      w.dR = zR * weak_poly<5>(d, xR, 1.0);
+    }
+    const double pn = ps - (w.fL + w.fR + du) * frcp(w.dL + w.dR);
+    w.dp = pn - ps;
+    // relative change 2|dp|/(p_new + p_old) <= 1e-12, written without a division
+    conv = 2.0 * fabs(w.dp) <= 1e-12 * (pn + ps);
+    ps = pn;
+    going = !conv && xm <= 0.0625;
+  }
+  w.ps = ps;
+  w.xm = xm;
+  w.conv = conv && xm <= 0.0625;
+  return w;
+}
+
 template <int DIR>
 __device__ __forceinline__ bool gas_face64(const GasC& c, const double* qL, const double* qR,
                                            double* F, int& last) {
@@ -581,47 +643,21 @@ __device__ __forceinline__ bool gas_face64(const GasC& c, const double* qL, cons
     const double ipL = frcp(pL), ipR = frcp(pR);
     const double gL = (5.0 / 7.0) * cL, gR = (5.0 / 7.0) * cR;
     double ps = 0.5 * (pL + pR) - 0.125 * du * (rL + rR) * (cL + cR);
-    double fL, fR, dL, dR, dp = 0.0, xm = 0.0;
-    int it = 0;
-    bool going = weak && ok && !sup, conv = false;
-    while (going && it < c.max_iter) {
-      ++it;
-      const double xL = (ps - pL) * ipL, xR = (ps - pR) * ipR;
-      xm = fmax(xm, fmax(fabs(xL), fabs(xR)));
-      if (wave_none(xm > 1.0 / 512.0)) {
-        const ctab t = weak_table(WK_G);
-        fL = gL * xL * weak_poly<4>(t, xL, 1.0);
-        fR = gR * xR * weak_poly<4>(t, xR, 1.0);
-        dL = zL * fma(fma(t[WK_D], xL, t[WK_D + 1]), xL, 1.0);
-        dR = zR * fma(fma(t[WK_D], xR, t[WK_D + 1]), xR, 1.0);
-      } else {
-        const ctab t = weak_table(WKW_G);
-        fL = gL * xL * weak_poly<8>(t, xL, 1.0);
-        fR = gR * xR * weak_poly<8>(t, xR, 1.0);
-        const ctab d = weak_table(WKW_D);
-        dL = zL * weak_poly<5>(d, xL, 1.0);
-        dR = zR * weak_poly<5>(d, xR, 1.0);
-      }
-      const double pn = ps - (fL + fR + du) * frcp(dL + dR);
-      dp = pn - ps;
-      // relative change 2|dp|/(p_new + p_old) <= 1e-12, written without a division
-      conv = 2.0 * fabs(dp) <= 1e-12 * (pn + ps);
-      ps = pn;
-      going = !conv && xm <= 0.0625;
-    }
-    weak = weak && conv && xm <= 0.0625;
+    const WeakStar w = weak_star(c, pL, pR, ipL, ipR, gL, gR, zL, zR, du, ps, weak && ok && !sup);
+    ps = w.ps;
+    weak = weak && w.conv;
     // star velocity at the converged p* (as gas_riemann)
-    const double us = 0.5 * (uL + uR) + 0.5 * ((fR + dR * dp) - (fL + dL * dp));
+    const double us = 0.5 * (uL + uR) + 0.5 * ((w.fR + w.dR * w.dp) - (w.fL + w.dL * w.dp));
     weak = weak && us * us < 0.81 * fmin(c2L, c2R);
     const bool left = us >= 0.0;
     const double pK = left ? pL : pR, ipK = left ? ipL : ipR, rK = left ? rL : rR;
     const double x = (ps - pK) * ipK;
-    const double R = wave_none(xm > 1.0 / 512.0) ? weak_poly<4>(weak_table(WK_R), x, 5.0 / 7.0)
-                                                 : weak_poly<8>(weak_table(WKW_R), x, 5.0 / 7.0);
+    const double R = wave_none(w.xm > 1.0 / 512.0) ? weak_poly<4>(weak_table(WK_R), x, 5.0 / 7.0)
+                                                   : weak_poly<8>(weak_table(WKW_R), x, 5.0 / 7.0);
     const double rs = fma(rK * x, R, rK);
     if (!sup) {
       ok = ok && weak;
-      last = it;
+      last = w.it;
       rho = rs; un = us; p = ps;
       t1 = left ? qL[T1] : qR[T1];
       t2 = left ? qL[T2] : qR[T2];

@@ -10,9 +10,8 @@
 
 namespace rb {
 
-// Tiles: 64 cells along theta (one wavefront per radial row) x 8 rows in r, marching
-// through a chunk of z planes; TM rows for the stage kernels, TI for the in-plane adjoint
-// kernel.
+// Tiles: 64 cells along theta (one wavefront per radial row) x TM rows in r for the stage
+// kernels, TI for the in-plane adjoint kernel, marching through a chunk of z planes.
 constexpr int TJ = 64;
 constexpr int TI = 8;
 constexpr int NT = TJ * TI;
