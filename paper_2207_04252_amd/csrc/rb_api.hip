@@ -159,7 +159,9 @@ Layout make_layout(const rb_config& c) {
   L.ncfl = (int)std::min<size_t>((N + 255) / 256, 2048);
   size_t o = 0;
   auto take = [&](size_t n) { size_t at = o; o += up32(n); return at; };
+  // (next to each other: rb_step reads both back in one copy)
   L.ctrl = take((sizeof(Ctrl) + 7) / 8);
+  L.dtlog = take(DTLOG + 2);
   L.rt = take(nr * RT_N);
   L.ar = take(nr + 1);
   L.rco = take((nr + 2) * RC_N);
@@ -190,7 +192,6 @@ Layout make_layout(const rb_config& c) {
   L.indp = take((size_t)L.nind * 2);
   L.damp = take(nz * nr);
   L.ozr = take(4 * nr);
-  L.dtlog = take(DTLOG + 2);
   const size_t nparts = std::max(L.nblocks, L.nblocks_dust);
   L.cflp = take(std::max(nparts * 5, (size_t)L.ncfl));
   L.outp = take(nparts * 5);
@@ -467,6 +468,7 @@ rb_status rb_step(rb_ctx* x, int n, const rb_dt_policy* policy, double* dt_out) 
   StageArgs a = base_args(x);
   double* dtlog = x->work + x->L.dtlog;
   std::vector<double> hd;
+  bool vacuum = false;
   int done = 0;
   while (done < n || (n == 0 && done == 0)) {
     const int m = std::min(n - done, DTLOG);
@@ -518,13 +520,18 @@ rb_status rb_step(rb_ctx* x, int n, const rb_dt_policy* policy, double* dt_out) 
         HIPCHK(x, launch_reduce(a, x->L.nblocks, x->L.nblocks_dust, q + 1, cfl ? 1 : 0, 1, x->stream), "reduce");
       }
     }
-    std::vector<double> got(m + 1);
-    HIPCHK(x, hipMemcpyAsync(got.data(), dtlog, (m + 1) * sizeof(double), hipMemcpyDeviceToHost,
-                             x->stream), "read dt");
-    Ctrl c;
-    HIPCHK(x, hipMemcpyAsync(&c, x->work + x->L.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, x->stream),
-           "read control");
+    // the control block and the steps' dt in one copy, which a step of a small grid (some
+    // 30 us of kernels) would otherwise wait for twice, and a third time for the flags of
+    // the vacuum check below
+    const size_t at = x->L.dtlog - x->L.ctrl;
+    std::vector<double> got_all(at + m + 1);
+    HIPCHK(x, hipMemcpyAsync(got_all.data(), x->work + x->L.ctrl, got_all.size() * sizeof(double),
+                             hipMemcpyDeviceToHost, x->stream), "read control and dt");
     HIPCHK(x, hipStreamSynchronize(x->stream), "sync");
+    Ctrl c;
+    std::memcpy(&c, got_all.data(), sizeof(Ctrl));
+    const double* got = got_all.data() + at;
+    vacuum = (c.status & FL_VAC) != 0;
     prof_collect(x);
     int completed = m;
     if (c.status & FL_HARD) {
@@ -546,9 +553,7 @@ rb_status rb_step(rb_ctx* x, int n, const rb_dt_policy* policy, double* dt_out) 
     }
     if (n == 0) break;
   }
-  Ctrl c;
-  HIPCHK(x, hipMemcpy(&c, x->work + x->L.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost), "read control");
-  if (c.status & FL_VAC) return fail(x, RB_EVACUUM, "vacuum generated in a Riemann problem");
+  if (vacuum) return fail(x, RB_EVACUUM, "vacuum generated in a Riemann problem");
   return RB_OK;
 }
 
