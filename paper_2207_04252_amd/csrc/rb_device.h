@@ -22,58 +22,34 @@ __device__ __forceinline__ ctab to_ctab(const double* p) { return (ctab)(uintptr
 using ctabf = const __attribute__((address_space(4))) float*;
 __device__ __forceinline__ ctabf to_ctabf(const float* p) { return (ctabf)(uintptr_t)p; }
 
-// minmod of three: when all three share a sign, the one of smallest magnitude, else zero.
-// Three branch-free forms giving the same value (only the sign of a zero result can
-// differ):
-//  * FP32: minmod(a, b) is the median of a, b and 0, and minmod of three is
-//    minmod(x, minmod(y, z)): two hardware medians, each returning one of its arguments;
-//  * FP64: all positive, the smallest (first term); all negative, the largest (second
-//    term); otherwise both terms are zero, and one term always is, so the sum is exact;
-//  * FP64 with SEL: the sign test on the sign bits and the magnitude from two minima
-//    (fewer live registers: the adjoint's face kernels take it).
-__device__ __forceinline__ double minmod3_sel(double x, double y, double z) {
-  const unsigned bx = (unsigned)(__double_as_longlong(x) >> 32);
-  const unsigned by = (unsigned)(__double_as_longlong(y) >> 32);
-  const unsigned bz = (unsigned)(__double_as_longlong(z) >> 32);
-  const double m = fmin(fabs(x), fmin(fabs(y), fabs(z)));
-  return (int)((bx ^ by) | (bx ^ bz)) >= 0 ? copysign(m, x) : 0.0;
-}
-template <class T, bool SEL = false>
-__device__ __forceinline__ T minmod3(T x, T y, T z) {
-  if constexpr (std::is_same<T, float>::value)
-    return __builtin_amdgcn_fmed3f(x, __builtin_amdgcn_fmed3f(y, z, 0.0f), 0.0f);
-  else if constexpr (SEL)
-    return minmod3_sel(x, y, z);
-  else
-    return fmax(fmin(x, fmin(y, z)), T(0)) + fmin(fmax(x, fmax(y, z)), T(0));
+// Minmod of three in FP32: minmod(a, b) is the median of a, b and 0, and minmod of three is
+// minmod(x, minmod(y, z)): two hardware medians, each returning one of its arguments.
+__device__ __forceinline__ float minmod3(float x, float y, float z) {
+  return __builtin_amdgcn_fmed3f(x, __builtin_amdgcn_fmed3f(y, z, 0.0f), 0.0f);
 }
 
 // Uniform direction (index coordinates): the three-point parabola gives the upper-face
 // increment (dm + 3 dp)/8 and the lower-face increment -(3 dm + dp)/8, limited by the
 // one-sided differences (Sect. 2.7).  Written so that mirrored data give exactly
 // opposite increments.
-template <class T, bool SEL = false>
-__device__ __forceinline__ T inc_up_u(T em, T e0, T ep) {
-  T dm = e0 - em, dp = ep - e0;
-  return minmod3<T, SEL>(fma(T(3), dp, dm) * T(0.125), dm, dp);
+__device__ __forceinline__ float inc_up_u(float em, float e0, float ep) {
+  const float dm = e0 - em, dp = ep - e0;
+  return minmod3(fma(3.0f, dp, dm) * 0.125f, dm, dp);
 }
-template <class T, bool SEL = false>
-__device__ __forceinline__ T inc_lo_u(T em, T e0, T ep) {
-  T dm = e0 - em, dp = ep - e0;
-  return minmod3<T, SEL>(-(fma(T(3), dm, dp) * T(0.125)), -dm, -dp);
+__device__ __forceinline__ float inc_lo_u(float em, float e0, float ep) {
+  const float dm = e0 - em, dp = ep - e0;
+  return minmod3(-(fma(3.0f, dm, dp) * 0.125f), -dm, -dp);
 }
 // Non-uniform r: precomputed parabola weights and limiter bounds of the cell.
-template <class T, bool SEL = false, class Co = const double*>
-__device__ __forceinline__ T inc_up_c(T em, T e0, T ep, Co co) {
-  T dm = e0 - em, dp = ep - e0;
-  return minmod3<T, SEL>(fma(T(co[RC_WPP]), dp, T(co[RC_WPM]) * dm), T(co[RC_LPM]) * dm,
-                         T(co[RC_LPP]) * dp);
+template <class Co>
+__device__ __forceinline__ float inc_up_c(float em, float e0, float ep, Co co) {
+  const float dm = e0 - em, dp = ep - e0;
+  return minmod3(fma(co[RC_WPP], dp, co[RC_WPM] * dm), co[RC_LPM] * dm, co[RC_LPP] * dp);
 }
-template <class T, bool SEL = false, class Co = const double*>
-__device__ __forceinline__ T inc_lo_c(T em, T e0, T ep, Co co) {
-  T dm = e0 - em, dp = ep - e0;
-  return minmod3<T, SEL>(fma(T(co[RC_WMP]), dp, T(co[RC_WMM]) * dm), T(co[RC_LMM]) * dm,
-                         T(co[RC_LMP]) * dp);
+template <class Co>
+__device__ __forceinline__ float inc_lo_c(float em, float e0, float ep, Co co) {
+  const float dm = e0 - em, dp = ep - e0;
+  return minmod3(fma(co[RC_WMP], dp, co[RC_WMM] * dm), co[RC_LMM] * dm, co[RC_LMP] * dp);
 }
 
 // Constants of the pair reconstruction, in scalar registers: written as literals they cost a
@@ -736,11 +712,11 @@ __device__ __forceinline__ void recon32(Cell cell, Co coB, Co coC, float qL[5], 
   for (int f = 0; f < 5; ++f) {
     const float A = cell(0, f), B = cell(1, f), C = cell(2, f), D = cell(3, f);
     if constexpr (DIR == 0) {
-      qL[f] = B + inc_up_c<float>(A, B, C, coB);
-      qR[f] = C + inc_lo_c<float>(B, C, D, coC);
+      qL[f] = B + inc_up_c(A, B, C, coB);
+      qR[f] = C + inc_lo_c(B, C, D, coC);
     } else {
-      qL[f] = B + inc_up_u<float>(A, B, C);
-      qR[f] = C + inc_lo_u<float>(B, C, D);
+      qL[f] = B + inc_up_u(A, B, C);
+      qR[f] = C + inc_lo_u(B, C, D);
     }
   }
 }
@@ -831,28 +807,6 @@ __device__ __forceinline__ void st_cell(const StageArgs& a, void* st, int f, int
   } else {
     ((double*)st)[(size_t)f * g.N + cell] = v;
   }
-}
-
-// All NG conservative fields of a group at an interior cell: the gas deviation E', the
-// dust momenta and density.
-template <bool P32, int NG>
-__device__ __forceinline__ void load_cons(const StageArgs& a, const void* st, int F0, int k, int i,
-                                          int j, double* out) {
-  const Geo& g = a.g;
-  const size_t cell = ((size_t)k * g.nr + i) * g.nth + j;
-  if constexpr (P32 && NG == 4) {
-    const int sp = (F0 - 5) >> 2;
-    const double rd = ((const double*)st)[p32_f64_base(g) + (size_t)sp * g.N + cell];
-    const float* vel = (const float*)st + (size_t)(5 + 3 * sp) * g.N + cell;
-    const double v0 = a.t.wc[((size_t)k * g.nr + i) * WB_N + WB_V];
-    out[0] = rd * (double)vel[0];
-    out[1] = rd * (v0 + (double)vel[g.N]);
-    out[2] = rd * (double)vel[2 * g.N];
-    out[3] = rd;
-    return;
-  }
-#pragma unroll
-  for (int f = 0; f < NG; ++f) out[f] = ld_cell<P32>(a, st, F0 + f, k, i, cell);
 }
 
 // Gas deviation W' = W(E0 + E') - W(E0) of a cell from its conservative deviation e and

@@ -1025,7 +1025,7 @@ __global__ void __launch_bounds__(NTM, 4) k_dust(StageArgs a, int species) {
 // take are marked and solved together, by one inlined copy of the general form per plane.
 // Lane-instructions per cell 1506 -> 1050 and transcendentals 73 -> 30: three-dust disc
 // 512 x 1024 x 128, 4.97 -> 3.3 ms per launch; gas disc 128 x 256 x 64, 182 -> 142 us, and
-// with one barrier per plane and batched reads (as k_gas) 113 us.  Two waves per SIMD: at three (12-row tiles, 168 VGPRs, the general form called) the largest
+// with one barrier per plane and batched reads (as k_gas) 3.08 ms and 113 us.  Two waves per SIMD: at three (12-row tiles, 168 VGPRs, the general form called) the largest
 // disc gains 4% and the others lose more, at four (128) the general form's registers spill
 // into the faces (7.2 ms).
 template <int ND, bool EXT>
