@@ -604,8 +604,9 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
 // where it can: the cell below (s_rm) and the current cell (the staged plane itself) of the
 // thread's column; registers keep only the cell above, the flux of the z face below and the
 // raw loads in flight, all requested before the faces that hide them.  Three-dust disc
-// 512 x 1024 x 128, FP32-perturbation form: 1.92 -> 1.74 ms per launch (4.7 GB, 2.7 TB/s);
-// one-dust disc 256 x 512 x 64, FP64: 0.30 -> 0.27 ms (1.0 GB, 3.7 TB/s).
+// 512 x 1024 x 128, FP32-perturbation form: 1.92 -> 1.74 ms per launch, 1.63 (4.7 GB, 2.9
+// TB/s) once its loads no longer counted as LDS accesses; one-dust disc 256 x 512 x 64, FP64:
+// 0.30 -> 0.25 ms (1.0 GB, 4.0 TB/s).
 template <bool P32, bool EXT>
 __global__ void __launch_bounds__(NTM, 4) k_dust(StageArgs a, int species) {
   __shared__ int s_stop;
