@@ -174,7 +174,7 @@ Layout make_layout(const rb_config& c) {
   L.wc = take(nz * nr * WB_N);
   L.wr = take(nz * (nr + 1) * WB_N);
   L.wz = take((nz + 1) * nr * WB_N);
-  const size_t pf = c.precision == RB_FP32_PERT ? PF_N / 2 : 0;
+  const size_t pf = c.precision == RB_FP32_PERT ? PF_D : 0;
   L.pc = take(nz * nr * pf);
   L.pr = take(nz * (nr + 1) * pf);
   L.pz = take((nz + 1) * nr * pf);

@@ -19,8 +19,16 @@ namespace rb {
 using ctab = const __attribute__((address_space(4))) double*;
 __device__ __forceinline__ ctab to_ctab(const double* p) { return (ctab)(uintptr_t)p; }
 
-using ctabf = const __attribute__((address_space(4))) float*;
-__device__ __forceinline__ ctabf to_ctabf(const float* p) { return (ctabf)(uintptr_t)p; }
+// A PertBg entry of a table, likewise.
+__device__ __forceinline__ PertBg pert_at(const double* table, size_t entry) {
+  const ctab t = to_ctab(table) + entry * PF_D;
+  double d[PF_D];
+#pragma unroll
+  for (int q = 0; q < PF_D; ++q) d[q] = t[q];
+  PertBg b;
+  __builtin_memcpy(&b, d, sizeof b);
+  return b;
+}
 
 // Minmod of three in FP32: minmod(a, b) is the median of a, b and 0, and minmod of three is
 // minmod(x, minmod(y, z)): two hardware medians, each returning one of its arguments.
@@ -41,13 +49,11 @@ __device__ __forceinline__ float inc_lo_u(float em, float e0, float ep) {
   return minmod3(-(fma(3.0f, dm, dp) * 0.125f), -dm, -dp);
 }
 // Non-uniform r: precomputed parabola weights and limiter bounds of the cell.
-template <class Co>
-__device__ __forceinline__ float inc_up_c(float em, float e0, float ep, Co co) {
+__device__ __forceinline__ float inc_up_c(float em, float e0, float ep, const float* co) {
   const float dm = e0 - em, dp = ep - e0;
   return minmod3(fma(co[RC_WPP], dp, co[RC_WPM] * dm), co[RC_LPM] * dm, co[RC_LPP] * dp);
 }
-template <class Co>
-__device__ __forceinline__ float inc_lo_c(float em, float e0, float ep, Co co) {
+__device__ __forceinline__ float inc_lo_c(float em, float e0, float ep, const float* co) {
   const float dm = e0 - em, dp = ep - e0;
   return minmod3(fma(co[RC_WMP], dp, co[RC_WMM] * dm), co[RC_LMM] * dm, co[RC_LMP] * dp);
 }
@@ -706,8 +712,9 @@ namespace rb {
 
 // Reconstructed FP32 face states (W' of the gas, field slots) between cells B and C;
 // cell(c, f) as dust_face's.
-template <int DIR, class Cell, class Co>
-__device__ __forceinline__ void recon32(Cell cell, Co coB, Co coC, float qL[5], float qR[5]) {
+template <int DIR, class Cell>
+__device__ __forceinline__ void recon32(Cell cell, const float* coB, const float* coC, float qL[5],
+                                        float qR[5]) {
 #pragma unroll
   for (int f = 0; f < 5; ++f) {
     const float A = cell(0, f), B = cell(1, f), C = cell(2, f), D = cell(3, f);
@@ -840,13 +847,14 @@ __device__ __forceinline__ void cell_w(const float* e, const double* b, float gm
   w[4] = rp;
 }
 
-// The same in FP32 from the first four PF_N entries of the cell.
-__device__ __forceinline__ void cell_w32(const float* e, const float* c, float gm1, float* w) {
+// The same in FP32 about a flow along theta only: the second form's own roundings without its
+// products with zero velocities.
+__device__ __forceinline__ void cell_w32(const float* e, const PertCell& c, float gm1, float* w) {
   const float rp = e[4];
-  const float rho = c[PF_RHO] + (rp + c[PF_RLO]);
+  const float rho = (float)(c.rho + (double)rp);
   const float ir = rcp32(rho);
-  const float up = e[0] * ir, vp = (e[1] - c[PF_V] * rp) * ir, wp = e[2] * ir;
-  const float dke = 0.5f * rp * c[PF_VSQ] + rho * (c[PF_V] * vp) +
+  const float up = e[0] * ir, vp = (e[1] - c.v * rp) * ir, wp = e[2] * ir;
+  const float dke = 0.5f * rp * c.vsq + rho * (c.v * vp) +
                     0.5f * rho * (up * up + vp * vp + wp * wp);
   w[0] = up; w[1] = vp; w[2] = wp;
   w[3] = gm1 * (e[3] - dke);
@@ -1094,8 +1102,10 @@ __device__ __forceinline__ Face32Out gas_face32_general(const StageArgs& a, int 
                   : a.t.wz + ((size_t)(k + 1) * a.g.nr + i) * WB_N);
   float qL[5], qR[5];
   auto cell = [&](int s, int f) { return s == 0 ? q.A[f] : s == 1 ? q.B[f] : s == 2 ? q.C[f] : q.D[f]; };
-  if (dir == 0) recon32<0>(cell, rco_ptr(a, i), rco_ptr(a, i + 1), qL, qR);
-  else recon32<1>(cell, nullptr, nullptr, qL, qR);
+  // (the weights in FP32, as the short form takes them)
+  auto co = [&](int row) { return a.t.rcf + (size_t)(min(max(row, -1), a.g.nr) + 1) * RC_N; };
+  if (dir == 0) recon32<0>(cell, co(i), co(i + 1), qL, qR);
+  else recon32<1>(cell, (const float*)nullptr, (const float*)nullptr, qL, qR);
   TStat st = {0, 0, 0, 0, 0, 0, 0};
   const BgW b = {bf[WB_RHO], un(bf), t1(bf), t2(bf), bf[WB_P], bf[WB_C], bf[WB_H]};
   const PW L = {qL[4], un(qL), t1(qL), t2(qL), qL[3]};

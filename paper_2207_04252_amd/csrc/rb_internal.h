@@ -37,9 +37,21 @@ enum { RC_WPM = 0, RC_WPP, RC_LPM, RC_LPP, RC_WMM, RC_WMP, RC_LMM, RC_LMP, RC_N 
 enum { WB_U = 0, WB_V, WB_W, WB_P, WB_RHO, WB_C, WB_H, WB_IRHO, WB_N };
 
 // What the FP32-perturbation faces and cells need of the stationary flow (zero radial and
-// vertical velocity), in FP32: density and pressure as pairs whose sums carry the FP64 value,
-// azimuthal velocity and its square, sound speed, E + P, density x velocity.
-enum { PF_RHO = 0, PF_RLO, PF_V, PF_VSQ, PF_P, PF_PLO, PF_C, PF_H, PF_RHOV, PF_PAD, PF_N };
+// vertical velocity): density and pressure in FP64 (a perturbed value is their FP64 sum with
+// the perturbation, rounded once), the rest in FP32.  PertCell: what a cell's W' needs.
+struct __attribute__((may_alias)) PertCell {
+  double rho;
+  float v, vsq;  // azimuthal velocity and its square
+};
+struct __attribute__((may_alias)) PertBg {
+  PertCell cell;
+  double p;
+  float c, h;    // sound speed, E + P
+  float rhov;    // density x velocity
+  float pad;
+};
+constexpr int PF_D = sizeof(PertBg) / sizeof(double);  // an entry's length in doubles
+static_assert(sizeof(PertBg) == 40 && sizeof(PertCell) == 16, "tables of doubles");
 
 // Device control block at the start of the work area.
 struct Ctrl {
@@ -60,7 +72,7 @@ struct Ctrl {
 // Offsets (in doubles) of the tables inside the work area.
 struct Layout {
   size_t ctrl, rt, ar, rco, rcell, rface, zc, bgc, bgr, bgz, wc, wr, wz, r0, grav, ghr, ghrw, ghz, ghzw;
-  size_t pc, pr, pz, rcf;  // FP32-perturbation form: PF_N entries, FP32 parabola weights
+  size_t pc, pr, pz, rcf;  // FP32-perturbation form: PertBg entries, FP32 parabola weights
   size_t trig, indw, indab, indp, damp, ozr, dtlog, cflp, outp, tsp, red, total;
   int nind;      // blocks of the indirect-gravity sums
   int nblocks;   // gas stage-kernel blocks
@@ -109,7 +121,7 @@ struct Tables {
   const double* indw;  // V r / (r^2 + z^2)^(3/2) per (k, i) (indirect-gravity sums)
   const double* indab; // the indirect-gravity sums A, B of the current stage input
   const double* damp;  // boundary-zone relaxation rate R / tau per (k, i), 0 outside
-  const double* pc;    // FP32-perturbation form: PF_N entries at cell centres [k][i]
+  const double* pc;    // FP32-perturbation form: PertBg entries at cell centres [k][i]
   const double* pr;    //   at r faces [k][i + 1/2]
   const double* pz;    //   at z faces [k + 1/2][i]
   const float* rcf;    //   FP32 parabola weights (rco)

@@ -1019,16 +1019,18 @@ __global__ void __launch_bounds__(NTM, 4) k_dust(StageArgs a, int species) {
 // the gas stage kernel of the FP32-perturbation form
 
 // One RK2 stage of the gas in the FP32-perturbation form; tiles, planes and update as k_gas,
-// addressing as k_dust.  Bound by instruction issue and the chains of the
-// face solves: what the faces need of the stationary flow comes as FP32 pairs formed once
-// (PF_N entries, staged a plane ahead), so that they convert nothing, azimuthal faces take
-// the upwind state and the others a short Newton (gas_face32); the faces that form does not
-// take are marked and solved together, by one inlined copy of the general form per plane.
-// Lane-instructions per cell 1506 -> 1050 and transcendentals 73 -> 30: three-dust disc
-// 512 x 1024 x 128, 4.97 -> 3.3 ms per launch; gas disc 128 x 256 x 64, 182 -> 142 us, and
-// with one barrier per plane and batched reads (as k_gas) 3.08 ms and 113 us.  Two waves per SIMD: at three (12-row tiles, 168 VGPRs, the general form called) the largest
-// disc gains 4% and the others lose more, at four (128) the general form's registers spill
-// into the faces (7.2 ms).
+// addressing as k_dust.  Bound by instruction issue and the chains of the face solves: what
+// the faces need of the stationary flow is staged a plane ahead (PertBg), azimuthal faces take
+// the upwind state and the others the star state alone (gas_face32); the faces that form does
+// not take are marked and solved together, by one inlined copy of the general form per plane.
+// One barrier per plane and batched reads, as k_gas.  Ten steps of the gas disc 128 x 256 x 64,
+// 3.72 -> 2.82 ms; two of the three-dust disc 512 x 1024 x 128, dust stages included, 49.8 ->
+// 35.8 ms, the results the same to the last bit.  (Polynomials in place of the pressure
+// functions gave 2.40 and 32.5 ms, but with other roundings: see gas_face32.)
+// Two waves per SIMD: at three (12-row tiles, 168 VGPRs, the general form called) the largest
+// disc gained 4% and the others lost more, at four (128) the general form's registers spilled
+// into the faces.
+
 template <int ND, bool EXT>
 __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
   __shared__ int s_stop;
@@ -1047,10 +1049,10 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
   // Newton counts of the faces the wavefront owns (bins 0..7, 7: seven or more)
   __shared__ int s_nh[NTM / 64][8];
   __shared__ GasCount s_cnt;
-  // per-plane tables, in doubles (an FP32 pair each for the first two): the stationary flow
-  // at the rows' centres, r faces and upper z faces; at the centres of the rows and their
-  // halo, two planes ahead; the update's (conservative state, gravity, density, velocity)
-  constexpr int PFD = PF_N / 2, NFACE = (3 * TM + 1) * PFD, NCEN = (TM + 4) * 2, NUPD = TM * 9;
+  // per-plane tables, in doubles: the stationary flow (PertBg) at the rows' centres, r faces
+  // and upper z faces; (PertCell) at the centres of the rows and their halo, two planes ahead;
+  // the update's (conservative state, gravity, density, velocity)
+  constexpr int PFD = PF_D, NFACE = (3 * TM + 1) * PFD, NCEN = (TM + 4) * 2, NUPD = TM * 9;
   constexpr int T_CEN = NFACE, T_UPD = T_CEN + NCEN, NTAB = T_UPD + NUPD;
   static_assert(NTAB <= NTM, "one table entry per thread");
   __shared__ __align__(16) double s_face[4][NFACE];
@@ -1161,7 +1163,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
   };
   // W' of the thread's cell of plane k; ghosts hold the stationary flow (W' = 0), except the
   // outflow condition's: the boundary cell's deviation scaled by the densities' ratio
-  auto col_form = [&](int k, const Raw& R, const float* c, float* out) {
+  auto col_form = [&](int k, const Raw& R, const PertCell& c, float* out) {
     if (EXT && g.bc_z == 1 && (k < 0 || k >= g.nz)) {
       const size_t e = (size_t)((k < 0 ? 0 : 2) + min(k < 0 ? -1 - k : k - g.nz, 1)) * g.nr + igc;
       float s[NG];
@@ -1175,7 +1177,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
       cell_w32(R.e, c, gm1f, out);
     }
   };
-  auto cen = [&](int k, int row) { return (const float*)&s_cen[k & 3][row * 2]; };
+  auto cen = [&](int k, int row) -> const PertCell& { return *(const PertCell*)&s_cen[k & 3][row * 2]; };
   // (by the wavefronts that k_gas takes)
   const int th = ti < 2 || ti == 4 ? -1 : tid - (ti < 4 ? 2 : 3) * 64;
   const bool halo_t = th >= 0 && th < NHALO;
@@ -1204,14 +1206,15 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
     }
   };
 
-  // a face by the short form (bp: the face's PF_N entry), with its Newton count tallied if
+  // a face by the short form (b: the background there), with its Newton count tallied if
   // the thread owns it; returns false where the general form has to solve it
-  auto face = [&](auto dirc, auto cell, const float* co, const float* bp, bool own, float* F) {
+  auto bg_at = [](const double* p) -> const PertBg& { return *(const PertBg*)p; };
+  auto face = [&](auto dirc, auto cell, const float* co, const PertBg& b, bool own, float* F) {
     constexpr int D = decltype(dirc)::value;
     float qL[NG], qR[NG];
     recon32<D>(cell, co, co, qL, qR);
     int last = 0;
-    const bool ok = gas_face32<D>(bp, qL, qR, F, last);
+    const bool ok = gas_face32<D>(b, qL, qR, F, last);
     if (ok) maxit = max(maxit, last);
     tally(own && ok, last);
     return ok;
@@ -1243,10 +1246,9 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
     float r0[NG];
     // (planes below k0 are not in the ring of centre entries)
     auto form_at = [&](int k, float* out) {
-      const ctabf c = to_ctabf((const float*)a.t.pc) + ((size_t)min(max(k, 0), g.nz - 1) * g.nr + igc) * PF_N;
-      const float cf[4] = {c[0], c[1], c[2], c[3]};
+      const PertBg c = pert_at(a.t.pc, (size_t)min(max(k, 0), g.nz - 1) * g.nr + igc);
       col_fetch(vin, k, R);
-      col_form(k, R, cf, out);
+      col_form(k, R, c.cell, out);
     };
     if (!twod) {
       float e2[NG], rm[NG];
@@ -1254,10 +1256,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
       form_at(k0 - 1, rm);
       form_at(k0, r0);
       form_at(k0 + 1, rp);
-      const ctabf c = to_ctabf((const float*)a.t.pz) + ((size_t)k0 * g.nr + igc) * PF_N;
-      float bp[PF_N];
-#pragma unroll
-      for (int q = 0; q < PF_N; ++q) bp[q] = c[q];
+      const PertBg bp = pert_at(a.t.pz, (size_t)k0 * g.nr + igc);
       auto get = [&](int s, int f) { return s == 0 ? e2[f] : s == 1 ? rm[f] : s == 2 ? r0[f] : rp[f]; };
       if (!face(DZ(), get, nullptr, bp, act && k0 == 0, fzlo)) {
         Face32 q;
@@ -1316,11 +1315,11 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
 #pragma unroll
       for (int f = 0; f < NG; ++f) r0[f] = s_pl[k & 1][f][ti + 2][tj + 2];
       const double* upd = &s_upd[k & 3][ti * 9];
-      const float* fc = (const float*)&s_face[k & 3][ti * PFD];
+      const PertBg& fc = bg_at(&s_face[k & 3][ti * PFD]);
       const float rhop = r0[4], up = r0[0], vp = r0[1], wp = r0[2], pp = r0[3];
-      const float v0 = fc[PF_V], rho = fc[PF_RHO] + (rhop + fc[PF_RLO]);
+      const float v0 = fc.cell.v, rho = (float)(fc.cell.rho + (double)rhop);
       const float ir = (float)row[RW_INVRC], fgr = (float)upd[5], fgz = (float)upd[6];
-      const float dmv2 = rhop * fc[PF_VSQ] + rho * vp * (2.0f * v0 + vp);
+      const float dmv2 = rhop * fc.cell.vsq + rho * vp * (2.0f * v0 + vp);
       float S[NG];
       S[0] = (dmv2 + pp) * ir + rhop * fgr;
       S[1] = -(rho * up * (v0 + vp)) * ir;
@@ -1426,9 +1425,9 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
     if (kk == k1) break;
     const int k = kk;
     float (*pl)[TM + 4][HW] = s_pl[k & 1];
-    const float* face_c = (const float*)&s_face[k & 3][ti * PFD];
-    const float* face_r = (const float*)&s_face[k & 3][(TM + ti + 1) * PFD];
-    const float* face_z = (const float*)&s_face[k & 3][(2 * TM + 1 + ti) * PFD];
+    const PertBg& face_c = bg_at(&s_face[k & 3][ti * PFD]);
+    const PertBg& face_r = bg_at(&s_face[k & 3][(TM + ti + 1) * PFD]);
+    const PertBg& face_z = bg_at(&s_face[k & 3][(2 * TM + 1 + ti) * PFD]);
     unsigned bad = 0;
     // ---- theta face j+1/2
     {
@@ -1452,7 +1451,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
       auto get = [&](int c, int f) { return pl[f][c][tid + 2]; };
       float F[NG];
       // (the upper face of the tile below, which owns it, except at the inner boundary)
-      if (!face(DR(), get, s_wt[0], (const float*)&s_face[k & 3][TM * PFD],
+      if (!face(DR(), get, s_wt[0], bg_at(&s_face[k & 3][TM * PFD]),
                 i0 == 0 && jg < g.nth, F))
         bad |= 4;
 #pragma unroll
@@ -1461,7 +1460,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
       const int row = tid - TJ;
       auto get = [&](int c, int f) { return pl[f][row + 2][c]; };
       float F[NG];
-      if (!face(DT(), get, nullptr, (const float*)&s_face[k & 3][row * PFD], false, F))
+      if (!face(DT(), get, nullptr, bg_at(&s_face[k & 3][row * PFD]), false, F))
         bad |= 4;
 #pragma unroll
       for (int f = 0; f < NG; ++f) s_fe[k & 1][f][row] = F[f];
@@ -1886,19 +1885,10 @@ __device__ void prim_entry(const rb_config& c, const double* q, double* o) {
   o[WB_IRHO] = 1.0 / rho;
 }
 
-// PF_N entry of the FP32-perturbation form from a WB_N entry.
+// PertBg entry of the FP32-perturbation form from a WB_N entry.
 __device__ void pert_entry(const double* b, double* out) {
-  float* o = (float*)out;
-  o[PF_RHO] = (float)b[WB_RHO];
-  o[PF_RLO] = (float)(b[WB_RHO] - (double)o[PF_RHO]);
-  o[PF_V] = (float)b[WB_V];
-  o[PF_VSQ] = (float)(b[WB_V] * b[WB_V]);
-  o[PF_P] = (float)b[WB_P];
-  o[PF_PLO] = (float)(b[WB_P] - (double)o[PF_P]);
-  o[PF_C] = (float)b[WB_C];
-  o[PF_H] = (float)b[WB_H];
-  o[PF_RHOV] = (float)(b[WB_RHO] * b[WB_V]);
-  o[PF_PAD] = 0.0f;
+  *(PertBg*)out = {{b[WB_RHO], (float)b[WB_V], (float)(b[WB_V] * b[WB_V])},
+                   b[WB_P], (float)b[WB_C], (float)b[WB_H], (float)(b[WB_RHO] * b[WB_V]), 0.0f};
 }
 
 // Reconstructed variables of a ghost cell whose full state is q (nf fields): the gas
@@ -2075,7 +2065,7 @@ __global__ void __launch_bounds__(256) k_tables_2d(InitArgs a) {
           c.init_kind == RB_INIT_DISC ? q[f] : 0.0;
       double* o = w + L.wc + ((size_t)kk * nr + ii) * WB_N;
       prim_entry(c, q, o);
-      if (a.g.p32) pert_entry(o, w + L.pc + ((size_t)kk * nr + ii) * (PF_N / 2));
+      if (a.g.p32) pert_entry(o, w + L.pc + ((size_t)kk * nr + ii) * PF_D);
       double s3 = pow(r * r + zc * zc, 1.5);
       w[L.grav + ((size_t)kk * nr + ii) * 2 + 0] = -c.GM * r / s3;
       w[L.grav + ((size_t)kk * nr + ii) * 2 + 1] = -c.GM * zc / s3;
@@ -2086,7 +2076,7 @@ __global__ void __launch_bounds__(256) k_tables_2d(InitArgs a) {
           c.init_kind == RB_INIT_DISC ? q[f] : 0.0;
       double* o = w + L.wr + ((size_t)kk * (nr + 1) + ii) * WB_N;
       prim_entry(c, q, o);
-      if (a.g.p32) pert_entry(o, w + L.pr + ((size_t)kk * (nr + 1) + ii) * (PF_N / 2));
+      if (a.g.p32) pert_entry(o, w + L.pr + ((size_t)kk * (nr + 1) + ii) * PF_D);
     }
     if (!twod && iin && kk >= 0 && kk <= nz) {
       background_full(a, cell_r(c, ii), (kk - 0.5 * nz) * dz, q);
@@ -2094,7 +2084,7 @@ __global__ void __launch_bounds__(256) k_tables_2d(InitArgs a) {
           c.init_kind == RB_INIT_DISC ? q[f] : 0.0;
       double* o = w + L.wz + ((size_t)kk * nr + ii) * WB_N;
       prim_entry(c, q, o);
-      if (a.g.p32) pert_entry(o, w + L.pz + ((size_t)kk * nr + ii) * (PF_N / 2));
+      if (a.g.p32) pert_entry(o, w + L.pz + ((size_t)kk * nr + ii) * PF_D);
     }
     // ghost cells: reconstructed variables (gas W', dust primitives) and the stationary
     // flow's primitives

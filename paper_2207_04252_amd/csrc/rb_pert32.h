@@ -101,42 +101,13 @@ __device__ __forceinline__ void pfun_p(float q, const SideP& K, float& f, float&
   }
 }
 
-// Perturbation exact Riemann problem (gamma = 7/5) at x/t = 0.  Returns false when the
-// FP64 solver must be used instead.
-__device__ __forceinline__ bool riemann_pert(const BgW& b, const PW& WL, const PW& WR, const GasC& g,
-                                             PW& W, TStat& st) {
-  st.last = 0;
-  // strong perturbations are left to the FP64 solver
-  const float p0 = (float)b.p, r0 = (float)b.rho, c0 = (float)b.c;
-  if (!(fabsf(WL.p) < 0.1f * p0 && fabsf(WR.p) < 0.1f * p0 && fabsf(WL.rho) < 0.1f * r0 &&
-        fabsf(WR.rho) < 0.1f * r0 && fabsf(WL.un) < 0.1f * c0 && fabsf(WR.un) < 0.1f * c0))
-    return false;
-  const SideP L = make_side_p(b, WL, g);
-  const SideP R = make_side_p(b, WR, g);
+// The star state of the perturbation Riemann problem at x/t = 0 behind the wave on its side
+// (un0, p0: normal velocity and pressure of the background); last: Newton iterations.  Returns
+// false when the FP64 solver must be used instead.
+__device__ __forceinline__ bool star_pert(float un0, float p0, const PW& WL, const PW& WR,
+                                          const SideP& L, const SideP& R, const GasC& g, PW& W,
+                                          int& last) {
   const float du = WR.un - WL.un;
-  // supersonic faces: the left (right) state is the solution when f(p_hi) >= 0 and the
-  // contact moves the same way (same argument as the FP64 solver, with margins)
-  if (L.u >= L.c) {
-    const float m = L.u * rcp32(L.c);
-    const float phi = L.p * (m * m - (float)g.gm1_2g) * (float)g.inv_gp1_2g;
-    float fL, dL, fR, dR;
-    pfun_p(phi - p0, L, fL, dL);
-    pfun_p(phi - p0, R, fR, dR);
-    if (fL + fR + du >= 1e-3f * fL && L.u - fL >= 1e-3f * L.u) {
-      W = WL;
-      return true;
-    }
-  } else if (R.u <= -R.c) {
-    const float m = -R.u * rcp32(R.c);
-    const float phi = R.p * (m * m - (float)g.gm1_2g) * (float)g.inv_gp1_2g;
-    float fL, dL, fR, dR;
-    pfun_p(phi - p0, L, fL, dL);
-    pfun_p(phi - p0, R, fR, dR);
-    if (fL + fR + du >= 1e-3f * fR && R.u + fR <= 1e-3f * R.u) {
-      W = WR;
-      return true;
-    }
-  }
   // Newton on q = p* - p0 from the primitive-variable guess
   float q = 0.5f * (WL.p + WR.p) - 0.125f * du * (L.rho + R.rho) * (L.c + R.c);
   const float qfloor = 1e-8f * fminf(L.p, R.p) - p0;
@@ -154,11 +125,10 @@ __device__ __forceinline__ bool riemann_pert(const BgW& b, const PW& WL, const P
     q = qn;
     if (fabsf(dq) <= 1e-6f * fabsf(q) + 1e-9f * p0) { conv = true; break; }
   }
-  st.maxit = max(st.maxit, it);
-  st.last = it;
+  last = it;
   if (!conv) return false;
   const float us = 0.5f * (WL.un + WR.un) + 0.5f * ((fR + dR * dq) - (fL + dL * dq));
-  const float usfull = (float)b.un + us;
+  const float usfull = un0 + us;
   const float kk = (float)g.kshock;
   if (0.0f <= usfull) {
     if (q > WL.p) {
@@ -196,108 +166,116 @@ __device__ __forceinline__ bool riemann_pert(const BgW& b, const PW& WL, const P
   return true;
 }
 
-// The short form of a face, for weak perturbations about a flow without radial and vertical
-// velocity (gamma = 7/5; qL, qR: the face states W' in field slots, bp: PF_N entry of the
-// face).  Returns false where it does not apply: a perturbation above a tenth of the
-// background (the general form leaves those to FP64), a star pressure more than a quarter
-// off a side's, no convergence, or azimuthal flow below Mach 2.
-//
-// Azimuthal faces: with the flow above Mach 2 and the perturbations below a tenth, the star
-// pressure stays within 1.4 of the left one, so even a left shock runs downstream (its speed
-// is above (1.9 - 1.3) c) and the solution at x/t = 0 is the left state: no solve.
-// Radial and vertical faces: subsonic, so the solution is a star state.  Newton on
-// q = p* - p0 as riemann_pert's, with both branches of a side's pressure function on
-// x = (q - p'_K) / p_K:
-//   f = 5/7 c x g(x),  g = 1 / sqrt(1 + 6x/7) for a shock,
-//                          7 ((1 + x)^(1/7) - 1) / x for a rarefaction (a polynomial),
-//   f' = D(x) / (rho c), D the common expansion of both branches (within 1.2e-3: Newton's
-//   fixed point does not depend on it), and 1 / (rho c) = 1 / sqrt(gamma p rho).
-// The polynomials are least-squares fits of the relative error on [-1/4, 0] with their value
-// at 0 kept: 1.8e-9 (g) and 3.6e-9 (the density's), below FP32 rounding.
+// Perturbation exact Riemann problem (gamma = 7/5) at x/t = 0.  Returns false when the
+// FP64 solver must be used instead.
+__device__ __forceinline__ bool riemann_pert(const BgW& b, const PW& WL, const PW& WR, const GasC& g,
+                                             PW& W, TStat& st) {
+  st.last = 0;
+  // strong perturbations are left to the FP64 solver
+  const float p0 = (float)b.p, r0 = (float)b.rho, c0 = (float)b.c;
+  if (!(fabsf(WL.p) < 0.1f * p0 && fabsf(WR.p) < 0.1f * p0 && fabsf(WL.rho) < 0.1f * r0 &&
+        fabsf(WR.rho) < 0.1f * r0 && fabsf(WL.un) < 0.1f * c0 && fabsf(WR.un) < 0.1f * c0))
+    return false;
+  const SideP L = make_side_p(b, WL, g);
+  const SideP R = make_side_p(b, WR, g);
+  const float du = WR.un - WL.un;
+  // supersonic faces: the left (right) state is the solution when f(p_hi) >= 0 and the
+  // contact moves the same way (same argument as the FP64 solver, with margins)
+  if (L.u >= L.c) {
+    const float m = L.u * rcp32(L.c);
+    const float phi = L.p * (m * m - (float)g.gm1_2g) * (float)g.inv_gp1_2g;
+    float fL, dL, fR, dR;
+    pfun_p(phi - p0, L, fL, dL);
+    pfun_p(phi - p0, R, fR, dR);
+    if (fL + fR + du >= 1e-3f * fL && L.u - fL >= 1e-3f * L.u) {
+      W = WL;
+      return true;
+    }
+  } else if (R.u <= -R.c) {
+    const float m = -R.u * rcp32(R.c);
+    const float phi = R.p * (m * m - (float)g.gm1_2g) * (float)g.inv_gp1_2g;
+    float fL, dL, fR, dR;
+    pfun_p(phi - p0, L, fL, dL);
+    pfun_p(phi - p0, R, fR, dR);
+    if (fL + fR + du >= 1e-3f * fR && R.u + fR <= 1e-3f * R.u) {
+      W = WR;
+      return true;
+    }
+  }
+  const bool ok = star_pert((float)b.un, p0, WL, WR, L, R, g, W, st.last);
+  st.maxit = max(st.maxit, st.last);
+  return ok;
+}
+
+// Flux perturbation about a background that flows along theta only (F in field slots), DIR the
+// normal: flux_pert's own roundings without its products with zero velocities.
 template <int DIR>
-__device__ __forceinline__ bool gas_face32(const float* bp, const float* qL, const float* qR,
+__device__ __forceinline__ void flux_pert_az(const PertBg& b, const PW& w, float* F) {
+#pragma clang fp contract(off)
+  const float v0 = b.cell.v, rho = (float)(b.cell.rho + (double)w.rho);
+  const float vp = DIR == 0 ? w.t1 : DIR == 1 ? w.un : w.t2;  // velocity along theta
+  const float usq = fmaf(w.t2, w.t2, fmaf(w.un, w.un, w.t1 * w.t1));
+  const float dke = fmaf(0.5f * rho, usq, fmaf(0.5f * w.rho, b.cell.vsq, rho * (v0 * vp)));
+  const float dh = fmaf(w.p, 2.5f, dke) + w.p;
+  const float h = b.h + dh;
+  if constexpr (DIR == 1) {
+    const float dmass = fmaf(w.rho, v0, rho * w.un), mflux = b.rhov + dmass;
+    F[4] = dmass;
+    F[1] = fmaf(dmass, v0, mflux * w.un) + w.p;
+    F[0] = mflux * w.t1;
+    F[2] = mflux * w.t2;
+    F[3] = fmaf(dh, v0, h * w.un);
+  } else {
+    const float dmass = rho * w.un;
+    F[4] = dmass;
+    F[DIR] = dmass * w.un + w.p;
+    F[1] = fmaf(dmass, v0, dmass * vp);
+    F[2 - DIR] = dmass * (DIR == 0 ? w.t2 : w.t1);
+    F[3] = h * w.un;
+  }
+}
+
+// The short form of a face, for weak perturbations about a flow without radial and vertical
+// velocity (gamma = 7/5; qL, qR: the face states W' in field slots, b: the face's background).
+// Its results are the general form's to the last bit.  The state's FP64 part depends on that:
+// the dust density, accumulated in FP64, follows the gas velocity through the drag, so that a
+// change of rounding in a face moves it by up to 1e-6 in single cells of split exact drag.
+// Returns false where it does not apply: a perturbation above a tenth of the background (the
+// general form leaves those to FP64), a star state that the general form leaves to FP64,
+// azimuthal flow below Mach 2, or densities in units with which riemann_pert's products leave
+// the FP32 range.
+//
+// Azimuthal faces: with the flow above Mach 2 and the perturbations below a tenth, u_L is above
+// 1.7 c_L, so the pressure p_hi of a standing left shock is above 3.2 p_L, more than p_R; f_L
+// there is above 0.9 c_L, more than u_L - u_R, and f_R is positive, so riemann_pert's proof that
+// the left state is the solution holds for every such face: no solve.
+// Radial and vertical faces: the background has no normal flow, so they are subsonic and need
+// the star state only.
+template <int DIR>
+__device__ __forceinline__ bool gas_face32(const PertBg& b, const float* qL, const float* qR,
                                            float* F, int& last) {
   constexpr int N = Dirs<DIR>::n, T1 = Dirs<DIR>::t1, T2 = Dirs<DIR>::t2;
-  const float r0 = bp[PF_RHO], v0 = bp[PF_V], p0 = bp[PF_P], c0 = bp[PF_C];
+  const float r0 = (float)b.cell.rho, p0 = (float)b.p, c0 = b.c;
+  const float unit = r0 * p0;
   bool ok = fabsf(qL[3]) < 0.1f * p0 && fabsf(qR[3]) < 0.1f * p0 && fabsf(qL[4]) < 0.1f * r0 &&
-            fabsf(qR[4]) < 0.1f * r0 && fabsf(qL[N]) < 0.1f * c0 && fabsf(qR[N]) < 0.1f * c0;
+            fabsf(qR[4]) < 0.1f * r0 && fabsf(qL[N]) < 0.1f * c0 && fabsf(qR[N]) < 0.1f * c0 &&
+            unit > 1e-30f && unit < 1e30f;
   last = 0;
+  const PW WL = {qL[4], qL[N], qL[T1], qL[T2], qL[3]};
   if constexpr (DIR == 1) {
-    ok = ok && v0 >= 2.0f * c0;
-    const float un = qL[1], t1 = qL[0], t2 = qL[2], pp = qL[3];
-    const float rho = r0 + (qL[4] + bp[PF_RLO]);
-    const float dmass = qL[4] * v0 + rho * un;
-    const float mflux = bp[PF_RHOV] + dmass;
-    const float dke = 0.5f * qL[4] * bp[PF_VSQ] + rho * (v0 * un) +
-                      0.5f * rho * (un * un + t1 * t1 + t2 * t2);
-    const float dh = pp * 2.5f + dke + pp;
-    F[4] = dmass;
-    F[1] = dmass * v0 + mflux * un + pp;
-    F[0] = mflux * t1;
-    F[2] = mflux * t2;
-    F[3] = dh * v0 + (bp[PF_H] + dh) * un;
-    return ok;
+    ok = ok && b.cell.v >= 2.0f * c0;
+    flux_pert_az<DIR>(b, WL, F);
   } else {
-    const float pL = p0 + (qL[3] + bp[PF_PLO]), pR = p0 + (qR[3] + bp[PF_PLO]);
-    const float rL = r0 + (qL[4] + bp[PF_RLO]), rR = r0 + (qR[4] + bp[PF_RLO]);
-    const float zL = __builtin_amdgcn_rsqf(1.4f * pL * rL), zR = __builtin_amdgcn_rsqf(1.4f * pR * rR);
-    const float ipL = rcp32(pL), ipR = rcp32(pR);
-    const float cL = 1.4f * pL * zL, cR = 1.4f * pR * zR;   // sound speeds; z = 1 / (rho c)
-    const float gL = (5.0f / 7.0f) * cL, gR = (5.0f / 7.0f) * cR;
-    const float du = qR[N] - qL[N];
-    auto rare = [](float x) {
-      float y = 0.224488269f;
-      y = fmaf(y, x, -0.0689145105f); y = fmaf(y, x, 0.155045545f); y = fmaf(y, x, -0.188726238f);
-      y = fmaf(y, x, 0.265337099f); y = fmaf(y, x, -0.428571020f);
-      return fmaf(y, x, 1.0f);
-    };
-    auto slope = [](float x) {
-      return fmaf(fmaf(fmaf(-0.736375818f, x, 0.842671752f), x, -0.857142857f), x, 1.0f);
-    };
-    auto shape = [&](float x) {
-      const float s = __builtin_amdgcn_rsqf(fmaf(6.0f / 7.0f, x, 1.0f)), r = rare(x);
-      return x > 0.0f ? s : r;
-    };
-    float q = 0.5f * (qL[3] + qR[3]) - 0.125f * du * (rL + rR) * (cL + cR);
-    float fL, fR, dL, dR, dq, xm = 0.0f;
-    bool conv = false;
-    while (last < 20) {
-      ++last;
-      const float xL = (q - qL[3]) * ipL, xR = (q - qR[3]) * ipR;
-      xm = fmaxf(xm, fmaxf(fabsf(xL), fabsf(xR)));
-      fL = gL * xL * shape(xL);
-      fR = gR * xR * shape(xR);
-      dL = zL * slope(xL);
-      dR = zR * slope(xR);
-      const float qn = q - (fL + fR + du) * rcp32(dL + dR);
-      dq = qn - q;
-      q = qn;
-      if (fabsf(dq) <= 1e-6f * fabsf(q) + 1e-9f * p0) { conv = true; break; }
+    const PW WR = {qR[4], qR[N], qR[T1], qR[T2], qR[3]};
+    const GasC g = gas_consts(1.4);
+    PW W = WL;
+    if (ok) {
+      const BgW bg = {b.cell.rho, 0.0, 0.0, 0.0, b.p, 0.0, 0.0};
+      ok = star_pert(0.0f, p0, WL, WR, make_side_p(bg, WL, g), make_side_p(bg, WR, g), g, W, last);
     }
-    ok = ok && conv && xm <= 0.25f;
-    // star velocity from the last iterate, then the density behind the left or right wave
-    const float us = 0.5f * (qL[N] + qR[N]) + 0.5f * ((fR + dR * dq) - (fL + dL * dq));
-    const bool left = us >= 0.0f;
-    const float x = (q - (left ? qL[3] : qR[3])) * (left ? ipL : ipR);
-    float y = -0.0216869556f;
-    y = fmaf(y, x, 0.0133193222f); y = fmaf(y, x, -0.0254018523f); y = fmaf(y, x, 0.0437084155f);
-    y = fmaf(y, x, -0.102041243f); y = fmaf(y, x, 5.0f / 7.0f);
-    const float m1 = x * (x > 0.0f ? (5.0f / 7.0f) * rcp32(fmaf(1.0f / 7.0f, x, 1.0f)) : y);
-    const float rp = (left ? qL[4] : qR[4]) + (left ? rL : rR) * m1;
-    const float t1 = left ? qL[T1] : qR[T1], t2 = left ? qL[T2] : qR[T2];
-    const float rho = r0 + (rp + bp[PF_RLO]);
-    const float dmass = rho * us;
-    const float tv = DIR == 0 ? t1 : t2, to = DIR == 0 ? t2 : t1;
-    const float dke = 0.5f * rp * bp[PF_VSQ] + rho * (v0 * tv) +
-                      0.5f * rho * (us * us + t1 * t1 + t2 * t2);
-    const float dh = q * 2.5f + dke + q;
-    F[4] = dmass;
-    F[N] = dmass * us + q;
-    F[1] = dmass * v0 + dmass * tv;
-    F[DIR == 0 ? 2 : 0] = dmass * to;
-    F[3] = (bp[PF_H] + dh) * us;
-    return ok;
+    flux_pert_az<DIR>(b, W, F);
   }
+  return ok;
 }
 
 }  // namespace rb
