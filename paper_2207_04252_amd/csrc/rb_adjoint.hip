@@ -256,7 +256,7 @@ __device__ __forceinline__ bool gas_weak_rev(const GasC& c, const double* qL, co
   const WeakStar w = weak_star(c, pL, pR, ipL, ipR, gL, gR, irL * rsL, irR * rsR, du,
                                0.5 * (pL + pR) - 0.125 * du * (rL + rR) * (cL + cR), weak);
   const double ps = w.ps, xL = (ps - pL) * ipL, xR = (ps - pR) * ipR;
-  const bool narrow = wave_none(w.xm > 1.0 / 512.0);
+  const bool narrow = w.xm <= 1.0 / 512.0;
   double GL, GR, dGL, dGR;
   if (narrow) {
     const ctab t = weak_table(WK_G);
@@ -273,9 +273,9 @@ __device__ __forceinline__ bool gas_weak_rev(const GasC& c, const double* qL, co
   if (!(weak && w.conv && us * us < 0.81 * fmin(c2L, c2R))) return false;
   const bool left = us >= 0.0;
   const double rK = left ? rL : rR, ipK = left ? ipL : ipR, x = left ? xL : xR;
-  double dR;
-  const double R = narrow ? weak_poly_d<4>(weak_table(WK_R), x, 5.0 / 7.0, dR)
-                          : weak_poly_d<8>(weak_table(WKW_R), x, 5.0 / 7.0, dR);
+  double R, dR;
+  if (narrow) R = weak_poly_d<4>(weak_table(WK_R), x, 5.0 / 7.0, dR);
+  else R = weak_poly_d<8>(weak_table(WKW_R), x, 5.0 / 7.0, dR);
   const double ratio = fma(x, R, 1.0), drs = rK * fma(x, dR, R) * ipK;  // rho* / rho_K, drho*/dp*
   GasRec rec;
   rec.rho = fma(rK * x, R, rK);

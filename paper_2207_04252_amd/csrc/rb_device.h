@@ -497,6 +497,8 @@ template <int DIR> struct Dirs {
 // error is then 1e-16 f, where the general form's difference of a root from 1 leaves 1e-16 c.
 // A Newton step costs some 50 instructions (x below 1/512) instead of 150: the general form
 // runs both branches of both sides wherever a wavefront's lanes differ.
+// Each lane takes the polynomials of its own range: the two ranges' values differ in the last
+// bit, and a face that two workgroups solve, beside other faces in each, has one flux.
 // Their coefficients, highest degree first, rarefaction and shock in turn (D of the narrow
 // range: one for both): g, D, R for X = 1/512, then for X = 1/16; the constant terms are 1, 1
 // and 5/7.  Read by scalar loads where they are used: as literals they would be kept in
@@ -571,7 +573,7 @@ __device__ __forceinline__ WeakStar weak_star(const GasC& c, double pL, double p
     ++w.it;
     const double xL = (ps - pL) * ipL, xR = (ps - pR) * ipR;
     xm = fmax(xm, fmax(fabs(xL), fabs(xR)));
-    if (wave_none(xm > 1.0 / 512.0)) {
+    if (xm <= 1.0 / 512.0) {
       const ctab t = weak_table(WK_G);
       w.fL = gL * xL * weak_poly<4>(t, xL, 1.0);
       w.fR = gR * xR * weak_poly<4>(t, xR, 1.0);
@@ -634,8 +636,9 @@ __device__ __forceinline__ bool gas_face64(const GasC& c, const double* qL, cons
     const bool left = us >= 0.0;
     const double pK = left ? pL : pR, ipK = left ? ipL : ipR, rK = left ? rL : rR;
     const double x = (ps - pK) * ipK;
-    const double R = wave_none(w.xm > 1.0 / 512.0) ? weak_poly<4>(weak_table(WK_R), x, 5.0 / 7.0)
-                                                   : weak_poly<8>(weak_table(WKW_R), x, 5.0 / 7.0);
+    double R;
+    if (w.xm <= 1.0 / 512.0) R = weak_poly<4>(weak_table(WK_R), x, 5.0 / 7.0);
+    else R = weak_poly<8>(weak_table(WKW_R), x, 5.0 / 7.0);
     const double rs = fma(rK * x, R, rK);
     if (!sup) {
       ok = ok && weak;

@@ -1,0 +1,89 @@
+"""The step is a function of the mesh alone: a cell's new state does not depend on where the
+cell lies in a tile, which faces share its wavefront, or how the planes are cut into chunks.
+The tiles cut the theta direction, the scheme has no preferred angle and the stationary flow
+none either, so a rotated state steps to the rotated result bit for bit; likewise any chunk
+length.  Every face is solved by both of its cells' workgroups where tiles meet, so anything
+else also breaks the conservation of mass across the tile's edges.  The states mix wave
+strengths from cell to cell: both ranges of the faces' short form and the general form."""
+import numpy as np
+import pytest
+
+from paper_2207_04252_amd import synth
+from tests.parity import sound_speed
+
+pytestmark = pytest.mark.gpu
+
+BASE = synth.C3_BIFLUID.with_(vortex_amp=0.0, noise_amp=0.0, z_half=0.1, hd_over_h=(1.0,))
+
+
+@pytest.fixture(scope="module")
+def rb():
+    import torch
+    assert torch.cuda.is_available(), "GPU test on a machine without a GPU"
+    from paper_2207_04252_amd import rossbi
+    rossbi.load()
+    return rossbi
+
+
+def stirred(cfg, E, strongest):
+    """The state with perturbations of random strengths 1e-5 .. 1e-3 in its columns, and some
+    strong columns, few enough that a wavefront may hold one or none."""
+    rng = np.random.default_rng(11)
+    cs, p = sound_speed(E, cfg.gamma)
+    amp = 10.0 ** rng.uniform(-5.0, -3.0, (1, cfg.nr, cfg.nth))
+    strong = 10.0 ** rng.uniform(-2.0, np.log10(strongest), amp.shape)
+    amp = np.where(rng.random(amp.shape) < 0.005, strong, amp)
+    d = amp * rng.uniform(-1.0, 1.0, E.shape)
+    rho = E[4] * (1.0 + d[4])
+    v = [E[f] / E[4] + d[f] * cs for f in range(3)]
+    p = p * (1.0 + d[3])
+    out = [rho * v[0], rho * v[1], rho * v[2],
+           p / (cfg.gamma - 1.0) + 0.5 * rho * (v[0] ** 2 + v[1] ** 2 + v[2] ** 2), rho]
+    for o in range(5, 5 + 4 * cfg.n_dust, 4):
+        rd = E[o + 3] * (1.0 + d[o + 3])
+        out += [rd * (E[o + f] / E[o + 3] + d[o + f] * cs) for f in range(3)] + [rd]
+    return np.stack(out)
+
+
+def after(rb, cfg, E, form, steps=3):
+    sim = rb.Sim(cfg, precision=rb.RB_FP32_PERT if form == "fp32p" else rb.RB_FP64)
+    if E is None:
+        E = stirred(cfg, sim.fields(), 0.12)
+    sim.set_fields(E)
+    st, dts = sim.step(steps)
+    assert st == rb.RB_OK, sim.error()
+    out = sim.fields()
+    d = sim.diagnostics()
+    sim.close()
+    return E, out, dts, (list(d.newton_hist), d.max_newton)
+
+
+def compare(a, b, shift):
+    (_, x, dx, cx), (_, y, dy, cy) = a, b
+    off = np.roll(x, shift, axis=-1) != y
+    print(f"[invariance] {off.sum()} of {off.size} values differ, counts {cx} {cy}", flush=True)
+    assert np.array_equal(dx, dy)
+    assert not off.any()
+    assert cx == cy
+
+
+@pytest.mark.parametrize("form", ["fp64", "fp32p"])
+@pytest.mark.parametrize("nz", [8, 1])
+@pytest.mark.parametrize("shift", [1, 37])
+def test_rotated_state(rb, form, nz, shift):
+    cfg = BASE.scaled(20, 128, nz)
+    print(f"[invariance] rotated by {shift}: 20x128x{nz} {form}", flush=True)
+    a = after(rb, cfg, None, form)
+    b = after(rb, cfg, np.roll(a[0], shift, axis=-1), form)
+    compare(a, b, shift)
+
+
+@pytest.mark.parametrize("form", ["fp64", "fp32p"])
+@pytest.mark.parametrize("tk", [1, 3, 7, 16])
+def test_chunk_length(rb, form, tk, monkeypatch):
+    cfg = BASE.scaled(20, 128, 16)
+    print(f"[invariance] chunks of {tk}: 20x128x16 {form}", flush=True)
+    monkeypatch.setenv("RB_TK", "4")
+    a = after(rb, cfg, None, form)
+    monkeypatch.setenv("RB_TK", str(tk))
+    compare(a, after(rb, cfg, a[0], form), 0)
