@@ -78,11 +78,8 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
   const size_t plane = (size_t)g.nr * g.nth;
   const GasC gc = gas_consts(g.gamma, g.newton_max);
   const RecC recc;
-  // columns past the grid and their slots: as k_dust
-  const int wcols = min(TJ, g.nth - j0);
-  const unsigned jl = min(tj, wcols - 1);
-  const bool centre = (unsigned)(tj - wcols) >= 2u;
-  const size_t row0 = (size_t)igc * g.nth + j0;
+  const unsigned jl = (unsigned)(jg % g.nth);  // (past the grid: as k_dust)
+  const size_t row0 = (size_t)igc * g.nth;
   const ctab rt = to_ctab(a.t.rt) + (size_t)igc * RT_N, ar = to_ctab(a.t.ar);
   if (tid < (TM + 1) * 8) {
     const int r = tid / 8, e = tid % 8, i = min(i0 + r - 1 + (e < 4 ? 0 : 1), g.nr);
@@ -200,9 +197,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
   if (!halo_t) {}
   else if (th < 2 * HW) { h_rr = th / HW; h_cc = th % HW; }
   else if (th < 4 * HW) { h_rr = TM + 2 + (th - 2 * HW) / HW; h_cc = (th - 2 * HW) % HW; }
-  else if (halo_t) { const int e = th - 4 * HW; h_rr = 2 + e / 4; h_cc = (e & 3) < 2 ? (e & 3) : wcols + (e & 3); }
-  int h_pad = 0;
-  if (th >= 4 * HW && wcols < TJ && h_cc > 1 && TJ + (th & 3) > wcols + 3) h_pad = TJ + (th & 3);
+  else if (halo_t) { const int e = th - 4 * HW; h_rr = 2 + e / 4; h_cc = (e & 3) < 2 ? (e & 3) : TJ + (e & 3); }
   const int h_ii = i0 + h_rr - 2;
   const size_t h_off = (size_t)min(max(h_ii, 0), g.nr - 1) * g.nth + (j0 + h_cc - 2 + g.nth) % g.nth;
   auto halo_fetch = [&](int k, Raw& R) {
@@ -221,10 +216,6 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
     }
 #pragma unroll
     for (int f = 0; f < NG; ++f) s_pl[k & 1][f][h_rr][h_cc] = w[f];
-    if (h_pad) {
-#pragma unroll
-      for (int f = 0; f < NG; ++f) s_pl[k & 1][f][h_rr][h_pad] = w[f];
-    }
   };
 
   // a face by the short form (bp: the stationary velocity, pressure and density there), with
@@ -302,10 +293,8 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
 #pragma unroll
       for (int f = 0; f < NG; ++f) { rp[f] = 0.0; fzlo[f] = 0.0; }
     }
-    if (centre) {
 #pragma unroll
-      for (int f = 0; f < NG; ++f) s_pl[k0 & 1][f][ti + 2][tj + 2] = r0[f];
-    }
+    for (int f = 0; f < NG; ++f) s_pl[k0 & 1][f][ti + 2][tj + 2] = r0[f];
     if (halo_t) {
       halo_fetch(k0, R);
       halo_store(k0, R);
@@ -377,7 +366,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
       // indirect gravity (Sect. 2.10): minus the star's acceleration by the disc
       if (EXT && g.indirect && a.mode != MODE_RESID) {
         const double A = a.t.indab[0], B = a.t.indab[1];
-        const double cs = a.t.trig[j0 + jl], sn = a.t.trig[g.nth + j0 + jl];
+        const double cs = a.t.trig[jl], sn = a.t.trig[g.nth + jl];
         const double acr = -g.GM * (A * cs + B * sn), act_ = -g.GM * (B * cs - A * sn);
         S[0] += rho * acr;
         S[1] += rho * act_;
@@ -556,7 +545,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
     for (int f = 0; f < NG; ++f) {
       dz[f] = row[RW_AZ] * (fzhi[f] - fzlo[f]);
       fzlo[f] = fzhi[f];
-      if (more && centre) s_pl[(k + 1) & 1][f][ti + 2][tj + 2] = rp[f];
+      if (more) s_pl[(k + 1) & 1][f][ti + 2][tj + 2] = rp[f];
       rp[f] = rn[f];
     }
   }
@@ -644,12 +633,11 @@ __global__ void __launch_bounds__(NTM, 4) k_dust(StageArgs a, int species) {
   const bool twod = g.twod != 0;
   const size_t plane = (size_t)g.nr * g.nth;
   TStat st = {0, 0, 0, 0, 0, 0, 0};
-  // the tile's columns inside the grid; the threads past them repeat the last one, except
-  // that the first two slots past it belong to the halo (the wrapped cells)
-  const int wcols = min(TJ, g.nth - j0);
-  const unsigned jl = min(tj, wcols - 1);
-  const bool centre = (unsigned)(tj - wcols) >= 2u;
-  const size_t row0 = (size_t)igc * g.nth + j0;  // (a wavefront has one row: scalar)
+  // the thread's column; the threads past the last one go on round the circle, so that every
+  // face solved is one of the mesh (their flags and counts are the mesh's) and no slot of the
+  // staged plane has two writers
+  const unsigned jl = (unsigned)(jg % g.nth);
+  const size_t row0 = (size_t)igc * g.nth;  // (a wavefront has one row: scalar)
   // tables of the wavefront's row, by scalar loads
   const ctab rt = to_ctab(a.t.rt) + (size_t)igc * RT_N, ar = to_ctab(a.t.ar), rco = to_ctab(a.t.rco);
   // thread t stages table entry t: tab_p + plane * tab_stride
@@ -729,11 +717,7 @@ __global__ void __launch_bounds__(NTM, 4) k_dust(StageArgs a, int species) {
   int h_rr = 0, h_cc = 0;
   if (tid < 2 * HW) { h_rr = tid / HW; h_cc = tid % HW; }
   else if (tid < 4 * HW) { h_rr = TM + 2 + (tid - 2 * HW) / HW; h_cc = (tid - 2 * HW) % HW; }
-  else if (halo_t) { const int e = tid - 4 * HW; h_rr = 2 + e / 4; h_cc = (e & 3) < 2 ? (e & 3) : wcols + (e & 3); }
-  // (a tile that ends inside the wavefront: the last two slots of its rows repeat the halo,
-  // so that the threads past the grid solve defined faces)
-  int h_pad = 0;
-  if (tid >= 4 * HW && wcols < TJ && h_cc > 1 && TJ + (tid & 3) > wcols + 3) h_pad = TJ + (tid & 3);
+  else if (halo_t) { const int e = tid - 4 * HW; h_rr = 2 + e / 4; h_cc = (e & 3) < 2 ? (e & 3) : TJ + (e & 3); }
   const int h_ii = i0 + h_rr - 2;
   const bool h_gh = h_ii < 0 || h_ii >= g.nr;
   const size_t h_off = (size_t)min(max(h_ii, 0), g.nr - 1) * g.nth + (j0 + h_cc - 2 + g.nth) % g.nth;
@@ -754,10 +738,6 @@ __global__ void __launch_bounds__(NTM, 4) k_dust(StageArgs a, int species) {
     }
 #pragma unroll
     for (int f = 0; f < NG; ++f) s_pl[f][h_rr][h_cc] = w[f];
-    if (h_pad) {
-#pragma unroll
-      for (int f = 0; f < NG; ++f) s_pl[f][h_rr][h_pad] = w[f];
-    }
   };
 
   using DR = std::integral_constant<int, 0>;
@@ -792,10 +772,8 @@ __global__ void __launch_bounds__(NTM, 4) k_dust(StageArgs a, int species) {
 #pragma unroll
       for (int f = 0; f < NG; ++f) { rp[f] = 0.0; fzlo[f] = 0.0; }
     }
-    if (centre) {
 #pragma unroll
-      for (int f = 0; f < NG; ++f) s_pl[f][ti + 2][tj + 2] = r0[f];
-    }
+    for (int f = 0; f < NG; ++f) s_pl[f][ti + 2][tj + 2] = r0[f];
     if (P32) __syncthreads();  // the velocity tables, with which the halo is formed
     if (halo_t) {
       halo_fetch(k0, R);
@@ -917,7 +895,7 @@ __global__ void __launch_bounds__(NTM, 4) k_dust(StageArgs a, int species) {
     // indirect gravity (Sect. 2.10): minus the star's acceleration by the disc
     if (EXT && g.indirect) {
       const double A = a.t.indab[0], B = a.t.indab[1];
-      const double cs = a.t.trig[j0 + jl], sn = a.t.trig[g.nth + j0 + jl];
+      const double cs = a.t.trig[jl], sn = a.t.trig[g.nth + jl];
       S[0] += rd * (-g.GM * (A * cs + B * sn));
       S[1] += rd * (-g.GM * (B * cs - A * sn));
     }
@@ -983,7 +961,7 @@ __global__ void __launch_bounds__(NTM, 4) k_dust(StageArgs a, int species) {
 #pragma unroll
       for (int f = 0; f < NG; ++f) {
         s_rm[f][tid] = r0[f];
-        if (centre) s_pl[f][ti + 2][tj + 2] = rp[f];
+        s_pl[f][ti + 2][tj + 2] = rp[f];
         rp[f] = rn[f];
       }
     }
@@ -1078,11 +1056,8 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
   const bool twod = g.twod != 0;
   const size_t plane = (size_t)g.nr * g.nth;
   const float gm1f = (float)(g.gamma - 1.0);
-  // columns past the grid and their slots: as k_dust
-  const int wcols = min(TJ, g.nth - j0);
-  const unsigned jl = min(tj, wcols - 1);
-  const bool centre = (unsigned)(tj - wcols) >= 2u;
-  const size_t row0 = (size_t)igc * g.nth + j0;
+  const unsigned jl = (unsigned)(jg % g.nth);  // (past the grid: as k_dust)
+  const size_t row0 = (size_t)igc * g.nth;
   const ctab rt = to_ctab(a.t.rt) + (size_t)igc * RT_N, ar = to_ctab(a.t.ar);
   if (tid < (TM + 1) * 8) {
     const int r = tid / 8, e = tid % 8, i = min(i0 + r - 1 + (e < 4 ? 0 : 1), g.nr);
@@ -1185,9 +1160,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
   if (!halo_t) {}
   else if (th < 2 * HW) { h_rr = th / HW; h_cc = th % HW; }
   else if (th < 4 * HW) { h_rr = TM + 2 + (th - 2 * HW) / HW; h_cc = (th - 2 * HW) % HW; }
-  else if (halo_t) { const int e = th - 4 * HW; h_rr = 2 + e / 4; h_cc = (e & 3) < 2 ? (e & 3) : wcols + (e & 3); }
-  int h_pad = 0;
-  if (th >= 4 * HW && wcols < TJ && h_cc > 1 && TJ + (th & 3) > wcols + 3) h_pad = TJ + (th & 3);
+  else if (halo_t) { const int e = th - 4 * HW; h_rr = 2 + e / 4; h_cc = (e & 3) < 2 ? (e & 3) : TJ + (e & 3); }
   const int h_ii = i0 + h_rr - 2;
   const size_t h_off = (size_t)min(max(h_ii, 0), g.nr - 1) * g.nth + (j0 + h_cc - 2 + g.nth) % g.nth;
   auto halo_fetch = [&](int k, Raw& R) {
@@ -1200,10 +1173,6 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
     const bool ghost = h_ii < 0 || h_ii >= g.nr;
 #pragma unroll
     for (int f = 0; f < NG; ++f) s_pl[k & 1][f][h_rr][h_cc] = ghost ? 0.0f : w[f];
-    if (h_pad) {
-#pragma unroll
-      for (int f = 0; f < NG; ++f) s_pl[k & 1][f][h_rr][h_pad] = ghost ? 0.0f : w[f];
-    }
   };
 
   // a face by the short form (b: the background there), with its Newton count tallied if
@@ -1272,10 +1241,8 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
 #pragma unroll
       for (int f = 0; f < NG; ++f) { rp[f] = 0.0f; fzlo[f] = 0.0f; }
     }
-    if (centre) {
 #pragma unroll
-      for (int f = 0; f < NG; ++f) s_pl[k0 & 1][f][ti + 2][tj + 2] = r0[f];
-    }
+    for (int f = 0; f < NG; ++f) s_pl[k0 & 1][f][ti + 2][tj + 2] = r0[f];
     if (halo_t) {
       halo_fetch(k0, R);
       halo_store(k0, R);
@@ -1353,7 +1320,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
       // indirect gravity (Sect. 2.10): minus the star's acceleration by the disc
       if (EXT && g.indirect) {
         const double A = a.t.indab[0], B = a.t.indab[1];
-        const double cs = a.t.trig[j0 + jl], sn = a.t.trig[g.nth + j0 + jl];
+        const double cs = a.t.trig[jl], sn = a.t.trig[g.nth + jl];
         const double acr = -g.GM * (A * cs + B * sn), act_ = -g.GM * (B * cs - A * sn);
         const double rg = upd[7] + (double)rhop;
         S[0] += (float)(rg * acr);
@@ -1531,7 +1498,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
     for (int f = 0; f < NG; ++f) {
       dz[f] = (float)row[RW_AZ] * (fzhi[f] - fzlo[f]);
       fzlo[f] = fzhi[f];
-      if (more && centre) s_pl[(k + 1) & 1][f][ti + 2][tj + 2] = rp[f];
+      if (more) s_pl[(k + 1) & 1][f][ti + 2][tj + 2] = rp[f];
       rp[f] = rn[f];
     }
   }

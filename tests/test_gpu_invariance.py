@@ -87,3 +87,56 @@ def test_chunk_length(rb, form, tk, monkeypatch):
     a = after(rb, cfg, None, form)
     monkeypatch.setenv("RB_TK", str(tk))
     compare(a, after(rb, cfg, a[0], form), 0)
+
+
+def sheared(cfg, E):
+    """The stirred state with strong azimuthal and vertical shear across theta = 0: wave
+    strengths up to the short forms' bounds in the first columns against none in the last,
+    of another sign in every layer."""
+    rng = np.random.default_rng(5)
+    cs, p = sound_speed(E, cfg.gamma)
+    ramp = np.linspace(0.08, 1e-4, cfg.nth)
+    side = (-1.0) ** np.arange(cfg.nz)[:, None, None]
+    u, w = side * ramp * cs, side * ramp[::-1] * cs * rng.uniform(0.5, 1.0, cs.shape)
+    rho, v, p = E[4] * (1.0 + ramp), E[1] / E[4] + ramp * cs, p * (1.0 + side * ramp)
+    out = [rho * u, rho * v, rho * w, p / (cfg.gamma - 1.0) + 0.5 * rho * (u ** 2 + v ** 2 + w ** 2), rho]
+    for o in range(5, 5 + 4 * cfg.n_dust, 4):
+        rd = E[o + 3] * (1.0 + 2.0 * ramp)
+        out += [rd * u, rd * E[o + 1] / E[o + 3], rd * w, rd]
+    return np.stack(out)
+
+
+@pytest.mark.parametrize("form", ["fp64", "fp32p"])
+@pytest.mark.parametrize("nth", [69, 65, 127, 70])
+@pytest.mark.parametrize("state", [stirred, sheared])
+def test_last_tile_of_a_ragged_grid(rb, form, nth, state):
+    """The threads past the last column take no part: the same result run after run (also with
+    other states in between, which leave other values behind) and in every rotation."""
+    cfg = BASE.scaled(20, nth, 8)
+    print(f"[invariance] {state.__name__} 20x{nth}x8 {form}", flush=True)
+    sim = rb.Sim(cfg)
+    E = stirred(cfg, sim.fields(), 0.12) if state is stirred else sheared(cfg, sim.fields())
+    sim.close()
+    first = after(rb, cfg, E, form)
+    for shift in (3, 40, 0):
+        compare(first, after(rb, cfg, np.roll(E, shift, axis=-1), form), shift)
+
+
+def test_faces_past_the_last_column(rb):
+    """Azimuthal velocity rising round the circle by twelve sound speeds and falling back in a
+    shock at theta = 0: no face of the mesh opens a vacuum or falls back, though the second
+    column beside the last one would (ten sound speeds)."""
+    cfg = BASE.scaled(20, 69, 8)
+    print("[invariance] azimuthal ramp 20x69x8", flush=True)
+    sim = rb.Sim(cfg)
+    E = sim.fields()
+    cs, p = sound_speed(E, cfg.gamma)
+    v = E[1] / E[4] + cs * np.linspace(-6.0, 6.0, cfg.nth)
+    E[1] = E[4] * v
+    E[3] = p / (cfg.gamma - 1.0) + 0.5 * E[4] * v * v
+    sim.set_fields(E)
+    sim.operator()
+    d = sim.diagnostics()
+    sim.close()
+    print(f"[invariance] vacuum {d.vacuum_faces} fallbacks {d.fallbacks} flags {d.flags}", flush=True)
+    assert d.vacuum_faces == 0 and d.fallbacks == 0 and d.flags == 0
