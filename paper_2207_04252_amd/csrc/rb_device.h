@@ -98,6 +98,14 @@ __device__ __forceinline__ void face_pair(const RecC& rc, double A, double B, do
 // true when the condition holds in no active lane of the wavefront (a scalar test)
 __device__ __forceinline__ bool wave_none(bool c) { return __builtin_amdgcn_ballot_w64(c) == 0; }
 
+// Orders what the lanes of a wavefront read of each other's LDS entries before against what
+// they write after.  The hardware keeps one wavefront's LDS accesses in order; this keeps the
+// compiler, which reasons about one lane, from moving them (no instruction).
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // x^(-1/7) for x > 0: FP32 hardware log2/exp2 seed (relative error ~1e-7 for x in the
 // clamped range), then Newton on z^-7 = x written as z <- z + (z/7)(1 - x z^7), whose error
 // goes e -> 4 e^2: two steps reach FP64 rounding (4 (4e-14)^2 ~ 1e-26); x = 1 is a fixed

@@ -40,6 +40,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
   __shared__ double s_pl[2][NG][TM + 4][HW];
   __shared__ double s_fr[2][NG][TM + 1][TJ];
   __shared__ double s_fe[2][NG][TM];
+  // (s_ft in one copy: its readers are its writer's wavefront, ordered by wave_order)
   __shared__ double s_ft[NG][NTM];
   __shared__ double s_rm[NG][NTM];
   __shared__ double s_red[NTM / 64][3];
@@ -442,6 +443,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
       }
     }
     if (kk == k1) break;
+    wave_order();
     const int k = kk;
     double (*pl)[TM + 4][HW] = s_pl[k & 1];
     const double* face_c = &s_face[k & 3][ti * NF];
@@ -1021,7 +1023,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
   __shared__ float s_pl[2][NG][TM + 4][HW];
   __shared__ float s_fr[2][NG][TM + 1][TJ];
   __shared__ float s_fe[2][NG][TM];
-  __shared__ float s_ft[NG][NTM];
+  __shared__ float s_ft[NG][NTM];  // (one copy: as k_gas)
   __shared__ float s_rm[NG][NTM];
   __shared__ double s_red[NTM / 64][3];
   // Newton counts of the faces the wavefront owns (bins 0..7, 7: seven or more)
@@ -1390,6 +1392,7 @@ __global__ void __launch_bounds__(NTM, 2) k_gas32(StageArgs a) {
       }
     }
     if (kk == k1) break;
+    wave_order();
     const int k = kk;
     float (*pl)[TM + 4][HW] = s_pl[k & 1];
     const PertBg& face_c = bg_at(&s_face[k & 3][ti * PFD]);
