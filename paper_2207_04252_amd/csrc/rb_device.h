@@ -572,11 +572,10 @@ struct WeakStar {
 __device__ __forceinline__ WeakStar weak_star(const GasC& c, double pL, double pR, double ipL,
                                               double ipR, double gL, double gR, double zL,
                                               double zR, double du, double ps, bool going) {
-  WeakStar w;
+  // (the caller computes on from here in every lane, and drops what did not converge)
+  WeakStar w = {ps, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0, false};
   double xm = 0.0;
   bool conv = false;
-  w.dp = 0.0;
-  w.it = 0;
   while (going && w.it < c.max_iter) {
     ++w.it;
     const double xL = (ps - pL) * ipL, xR = (ps - pR) * ipR;
