@@ -8,8 +8,9 @@
 // (Sect. 2.7), the positivity fallback on the side it was taken -- scattered back to the
 // four cells of each face stencil, plus the cell-local reverse of the geometric and
 // gravity sources and of the gas-dust drag (Sect. 2.9, App. B).  The primal face
-// solves are recomputed with the forward solver itself (recording variant), so every
-// branch decision is the forward run's.
+// solves are recomputed with the forward solver itself (its short form where that applies,
+// else its recording variant), so the branch decisions are the forward run's, but for ties:
+// a theta face's states, formed with r's weights, may differ from its in the last bit.
 //
 // k_adj_plane follows the forward stage kernel's tiles: a workgroup owns a 64 (theta) x
 // 8 (r) tile and a chunk of z planes.  Each plane is staged in LDS with a three-cell halo
@@ -576,7 +577,7 @@ __global__ void __launch_bounds__(NT, 2) k_adj_plane(AdjArgs A, int species) {
 #pragma unroll
       for (int q = 0; q < PER; ++q) {
         const int h = min(tid + q * NT, PL - 1);
-        load_recon<false, false, NG>(a, E, F0, k, i0 + h / W - H, X.jwrap(j0 + h % W - H), v[q]);
+        load_recon<NG>(a, E, F0, k, i0 + h / W - H, X.jwrap(j0 + h % W - H), v[q]);
       }
 #pragma unroll
       for (int q = 0; q < PER; ++q) {
@@ -825,7 +826,7 @@ __global__ void __launch_bounds__(256, 2) k_adj_z(AdjArgs A, int species, int tk
 
   const RecC recc;
   double ra[NG], rb[NG], rc[NG], rd[NG];  // cells kf-1 .. kf+2 of the face kf+1/2
-  auto load = [&](double* dst, int k) { load_recon<false, false, NG>(a, E, F0, k, ig, jg, dst); };
+  auto load = [&](double* dst, int k) { load_recon<NG>(a, E, F0, k, ig, jg, dst); };
   struct ZCells {
     const double *a, *b, *c, *d;
     __device__ double operator()(int q, int f) const { return q == 0 ? a[f] : q == 1 ? b[f] : q == 2 ? c[f] : d[f]; }
@@ -903,20 +904,20 @@ __global__ void __launch_bounds__(256, 2) k_adj_z(AdjArgs A, int species, int tk
       wcell(kf0, x, wlo);
     }
     col_fetch(A.cot, kf0 + 1, xr);
-    DustRaw<false> nraw;
-    dust_fetch<false, false>(a, E, F0, kf0 + 2, ig, jg, nraw);
+    DustRaw nraw;
+    dust_fetch(a, E, F0, kf0 + 2, ig, jg, nraw);
 #pragma unroll
     for (int f = 0; f < NG; ++f) orw[f] = 0.0;
     for (int k = kf0; k <= k1; ++k) {
 #pragma unroll
       for (int f = 0; f < NG; ++f) { ra[f] = rb[f]; rb[f] = rc[f]; rc[f] = rd[f]; }
-      dust_finish<false>(nraw, rd);  // cell k+2
+      dust_finish(nraw, rd);  // cell k+2
       double whi[NG], ocur[NG];
       wcell(k + 1, xr, whi);
 #pragma unroll
       for (int f = 0; f < NG; ++f) ocur[f] = orw[f];  // the output of cell k-1
       if (k + 1 <= k1) {
-        dust_fetch<false, false>(a, E, F0, k + 3, ig, jg, nraw);
+        dust_fetch(a, E, F0, k + 3, ig, jg, nraw);
         col_fetch(A.cot, k + 2, xr);
         col_fetch(A.out, max(k, k0), orw);
       }

@@ -501,7 +501,7 @@ template <int DIR> struct Dirs {
 // (rho* = rho_K (1 + x R(x))); with x and the velocities so bounded the state at x/t = 0 is
 // the star state.  The polynomials interpolate at the Chebyshev nodes of [-X, 0] or [0, X]:
 // relative error below 2.5e-17 with degree 4 for X = 1/512 and degree 8 for X = 1/16 (D:
-// 5e-8 with degree 2 and 3e-11 with degree 5, enough that Newton takes the same steps).  f's
+// 5e-8 with degree 2 and 5e-11 with degree 5, enough that Newton takes the same steps).  f's
 // error is then 1e-16 f, where the general form's difference of a root from 1 leaves 1e-16 c.
 // A Newton step costs some 50 instructions (x below 1/512) instead of 150: the general form
 // runs both branches of both sides wherever a wavefront's lanes differ.
@@ -871,103 +871,57 @@ __device__ __forceinline__ void cell_w32(const float* e, const PertCell& c, floa
   w[4] = rp;
 }
 
-// Reconstructed variables of a group at any cell, interior or ghost: the gas W', or the
-// dust velocity (zero where the density is not positive) and density.  EXT: the optional
-// boundary options may be active (outflow z ghosts carry the boundary cell's gas
-// deviation E' scaled by the ratio of the stationary densities, and its dust variables);
-// the base instantiation compiles them out.
-template <bool P32, bool EXT, int NG, class T>
+// Reconstructed variables of a group at any cell, interior or ghost, for FP64 storage and
+// stationary ghosts (what the adjoint takes): the gas W', or the dust velocity (zero where the
+// density is not positive) and density.  Each kind of ghost is read through a pointer of its
+// own: with one pointer picked from the two tables, ROCm 7.2's compiler merged the tails and
+// read the upper z ghosts of k_adj_z<gas> through the r table's base.
+template <int NG>
 __device__ __forceinline__ void load_recon(const StageArgs& a, const void* st, int F0, int k,
-                                           int i, int j, T* out) {
+                                           int i, int j, double* out) {
   const Geo& g = a.g;
-  constexpr bool GAS = NG == 5;
-  int kc = k;             // interior cell whose data are read
-  double scale = 1.0;     // outflow: gas deviation scale
-  const double* bw = nullptr;
   if (k < 0 || k >= g.nz) {
     const int ii = min(max(i, 0), g.nr - 1);
     const int side = k < 0 ? 0 : 1;
     const int layer = min(k < 0 ? -1 - k : k - g.nz, 1);
-    if (!(EXT && g.bc_z == 1)) {
-      const double* gt = a.t.ghz + ((size_t)(side * 2 + layer) * g.nr + ii) * g.nf + F0;
+    const double* gt = a.t.ghz + ((size_t)(side * 2 + layer) * g.nr + ii) * g.nf + F0;
 #pragma unroll
-      for (int f = 0; f < NG; ++f) out[f] = (T)gt[f];
-      return;
-    }
-    kc = k < 0 ? 0 : g.nz - 1;
-    i = ii;
-    scale = a.t.ozr[(size_t)(side * 2 + layer) * g.nr + ii];
-    bw = a.t.ghzw + ((size_t)(side * 2 + layer) * g.nr + ii) * WB_N;
+    for (int f = 0; f < NG; ++f) out[f] = gt[f];
+    return;
   } else if (i < 0 || i >= g.nr) {
     const int side = i < 0 ? 0 : 1;
     const int layer = min(i < 0 ? -1 - i : i - g.nr, 1);
     const double* gt = a.t.ghr + ((size_t)(side * 2 + layer) * g.nz + k) * g.nf + F0;
 #pragma unroll
-    for (int f = 0; f < NG; ++f) out[f] = (T)gt[f];
+    for (int f = 0; f < NG; ++f) out[f] = gt[f];
     return;
   }
-  const size_t cell = ((size_t)kc * g.nr + i) * g.nth + j;
-  if constexpr (GAS) {
-    if (!bw) bw = a.t.wc + ((size_t)kc * g.nr + i) * WB_N;
-    if constexpr (std::is_same<T, float>::value && P32) {
-      float e[5];
+  const double* d = (const double*)st + (size_t)F0 * g.N + ((size_t)k * g.nr + i) * g.nth + j;
+  if constexpr (NG == 5) {
+    double e[5];
 #pragma unroll
-      for (int f = 0; f < 5; ++f) e[f] = ((const float*)st)[(size_t)f * g.N + cell];
-      if (EXT && scale != 1.0) {
-#pragma unroll
-        for (int f = 0; f < 5; ++f) e[f] = (float)((double)e[f] * scale);
-      }
-      cell_w(e, bw, (float)(g.gamma - 1.0), out);
-    } else {
-      double e[5], w[5];
-#pragma unroll
-      for (int f = 0; f < 5; ++f) e[f] = ld_cell<P32>(a, st, f, kc, i, cell) * scale;
-      cell_w(e, bw, g.gamma - 1.0, w);
-#pragma unroll
-      for (int f = 0; f < 5; ++f) out[f] = (T)w[f];
-    }
+    for (int f = 0; f < 5; ++f) e[f] = d[(size_t)f * g.N];
+    cell_w(e, a.t.wc + ((size_t)k * g.nr + i) * WB_N, g.gamma - 1.0, out);
   } else {
-    const int sp = (F0 - 5) >> 2;
-    if constexpr (P32) {
-      // the FP32 layout stores the dust velocity deviations from the stationary flow
-      // (all requested before the density decides: a load made conditional on it would wait)
-      const float* vel = (const float*)st + (size_t)(5 + 3 * sp) * g.N + cell;
-      const double v0 = a.t.wc[((size_t)kc * g.nr + i) * WB_N + WB_V];
-      const double rd = ((const double*)st)[p32_f64_base(g) + (size_t)sp * g.N + cell];
-      const float v[3] = {vel[0], vel[g.N], vel[2 * g.N]};
-      const bool full = rd > 0.0;
-      out[0] = full ? (T)v[0] : T(0);
-      out[1] = full ? (T)(v0 + (double)v[1]) : T(0);
-      out[2] = full ? (T)v[2] : T(0);
-      out[3] = (T)rd;
-    } else {
-      const double* d = (const double*)st + (size_t)F0 * g.N + cell;
-      const double rd = d[3 * g.N];
-      const double id = rd > 0.0 ? 1.0 / rd : 0.0;
-      out[0] = (T)(d[0] * id);
-      out[1] = (T)(d[g.N] * id);
-      out[2] = (T)(d[2 * g.N] * id);
-      out[3] = (T)rd;
-    }
+    const double rd = d[3 * g.N];
+    const double id = rd > 0.0 ? 1.0 / rd : 0.0;
+    out[0] = d[0] * id;
+    out[1] = d[g.N] * id;
+    out[2] = d[2 * g.N] * id;
+    out[3] = rd;
   }
 }
 
-// A dust cell's reconstructed variables in two steps: dust_fetch issues the loads and does
-// no arithmetic on what they return, dust_finish forms the variables (the same values as
-// load_recon).  A wavefront waits for a load where its result is first used, so a fetch
-// made a phase or a plane ahead of its finish keeps that wait off the critical path.
-// Ghost cells carry their table values in d; interior cells carry the stored fields (FP64
-// layout: momenta and density in d) or (FP32 layout) the density in d[3], the stationary
-// azimuthal velocity in d[1] and the stored velocity deviations in v.
-template <bool P32>
+// A dust cell's in two steps: dust_fetch issues the loads and does no arithmetic on what they
+// return, dust_finish forms the variables (the same values as load_recon).  A wavefront waits
+// for a load where its result is first used, so a fetch made a phase or a plane ahead of its
+// finish keeps that wait off the critical path.  Ghost cells carry their table values in d.
 struct DustRaw {
   double d[4];
-  float v[P32 ? 3 : 1];
   bool ghost;
 };
-template <bool P32, bool EXT>
 __device__ __forceinline__ void dust_fetch(const StageArgs& a, const void* st, int F0, int k, int i,
-                                           int j, DustRaw<P32>& R) {
+                                           int j, DustRaw& R) {
   // the same loads on every path, from addresses chosen by selects (loads on separate
   // branches land in separate registers, and the copy that merges them waits for them)
   const Geo& g = a.g;
@@ -975,12 +929,10 @@ __device__ __forceinline__ void dust_fetch(const StageArgs& a, const void* st, i
   int kc = k;
   if (k < 0 || k >= g.nz) {
     const int ii = min(max(i, 0), g.nr - 1);
-    if (!(EXT && g.bc_z == 1)) {
-      const int side = k < 0 ? 0 : 1;
-      const int layer = min(k < 0 ? -1 - k : k - g.nz, 1);
-      gt = a.t.ghz + ((size_t)(side * 2 + layer) * g.nr + ii) * g.nf + F0;
-    }
-    kc = k < 0 ? 0 : g.nz - 1;  // outflow: the boundary cell's dust variables
+    const int side = k < 0 ? 0 : 1;
+    const int layer = min(k < 0 ? -1 - k : k - g.nz, 1);
+    gt = a.t.ghz + ((size_t)(side * 2 + layer) * g.nr + ii) * g.nf + F0;
+    kc = k < 0 ? 0 : g.nz - 1;
   } else if (i < 0 || i >= g.nr) {
     const int side = i < 0 ? 0 : 1;
     const int layer = min(i < 0 ? -1 - i : i - g.nr, 1);
@@ -989,45 +941,18 @@ __device__ __forceinline__ void dust_fetch(const StageArgs& a, const void* st, i
   const int ic = min(max(i, 0), g.nr - 1);  // a valid cell for the loads a ghost ignores
   const bool gh = gt != nullptr;
   R.ghost = gh;
-  const size_t cell = ((size_t)kc * g.nr + ic) * g.nth + j;
-  if constexpr (P32) {
-    const int sp = (F0 - 5) >> 2;
-    const float* vel = (const float*)st + (size_t)(5 + 3 * sp) * g.N + cell;
-    const double* v0 = a.t.wc + ((size_t)kc * g.nr + ic) * WB_N + WB_V;
-    const double* rd = (const double*)st + p32_f64_base(g) + (size_t)sp * g.N + cell;
-    const double* p0 = gh ? gt : v0;
-    const double* p1 = gh ? gt + 1 : v0;
-    const double* p2 = gh ? gt + 2 : v0;
-    const double* p3 = gh ? gt + 3 : rd;
-    R.d[0] = *p0;
-    R.d[1] = *p1;
-    R.d[2] = *p2;
-    R.d[3] = *p3;
-    R.v[0] = vel[0];
-    R.v[1] = vel[g.N];
-    R.v[2] = vel[2 * (size_t)g.N];
-  } else {
-    const double* d = (const double*)st + (size_t)F0 * g.N + cell;
+  const double* d = (const double*)st + (size_t)F0 * g.N + ((size_t)kc * g.nr + ic) * g.nth + j;
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {
-      const double* p = gh ? gt + f : d + (size_t)f * g.N;
-      R.d[f] = *p;
-    }
+  for (int f = 0; f < 4; ++f) {
+    const double* p = gh ? gt + f : d + (size_t)f * g.N;
+    R.d[f] = *p;
   }
 }
-template <bool P32>
-__device__ __forceinline__ void dust_finish(const DustRaw<P32>& R, double* out) {
+__device__ __forceinline__ void dust_finish(const DustRaw& R, double* out) {
   const double rd = R.d[3];
-  const bool full = rd > 0.0;
-  if constexpr (P32) {
-    out[0] = R.ghost ? R.d[0] : (full ? (double)R.v[0] : 0.0);
-    out[1] = R.ghost ? R.d[1] : (full ? R.d[1] + (double)R.v[1] : 0.0);
-    out[2] = R.ghost ? R.d[2] : (full ? (double)R.v[2] : 0.0);
-  } else {
-    const double id = full ? 1.0 / rd : 0.0;
+  const double id = rd > 0.0 ? 1.0 / rd : 0.0;
 #pragma unroll
-    for (int f = 0; f < 3; ++f) out[f] = R.ghost ? R.d[f] : R.d[f] * id;
-  }
+  for (int f = 0; f < 3; ++f) out[f] = R.ghost ? R.d[f] : R.d[f] * id;
   out[3] = rd;
 }
 
