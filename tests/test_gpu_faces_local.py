@@ -1,0 +1,119 @@
+"""The stage operator of both storage forms against the FP64 oracle, every cell on its own
+scale: the largest face term |E| A (|v| + c) of the cell and its neighbours, not of the disc,
+whose density falls by many orders of magnitude to its thin top layers, where perturbations
+cross the bounds of the faces' short forms first.  Bounds, per cell: FP64, a star pressure
+found to 1e-12 relative in each of six faces, 6e-12, taken as 1e-11; FP32-perturbation form,
+some fifty FP32 roundings of the perturbation flux, 50 x 2^-24 = 3e-6, taken as 1e-5 of the
+perturbations' amplitude (of the dust's whole flux: its operator is returned in FP32)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2207_04252_amd import synth
+from tests.parity import sound_speed
+
+pytestmark = pytest.mark.gpu
+
+BASE = synth.C3_BIFLUID.with_(vortex_amp=0.0, noise_amp=0.0, hd_over_h=(1.0,))
+
+
+@pytest.fixture(scope="module")
+def rb():
+    import torch
+    assert torch.cuda.is_available(), "GPU test on a machine without a GPU"
+    from paper_2207_04252_amd import rossbi
+    rossbi.load()
+    return rossbi
+
+
+def perturbed(cfg, E, amp, one_way):
+    """Perturbations up to amp (velocities in sound speeds) in every cell.  one_way: dust
+    streams that cross every face outward, upward and forward (a dust face between opposed
+    streams jumps with the last bit of the FP32 velocities)."""
+    rng = np.random.default_rng(3)
+    cs, p = sound_speed(E, cfg.gamma)
+    d = rng.uniform(-amp, amp, E.shape)
+    rho = E[4] * (1.0 + d[4])
+    v = [E[f] / E[4] + d[f] * cs for f in range(3)]
+    p = p * (1.0 + d[3])
+    out = [rho * v[0], rho * v[1], rho * v[2],
+           p / (cfg.gamma - 1.0) + 0.5 * rho * (v[0] ** 2 + v[1] ** 2 + v[2] ** 2), rho]
+    for o in range(5, 5 + 4 * cfg.n_dust, 4):
+        rd = E[o + 3] * (1.0 + d[o + 3])
+        dv = [amp + 0.5 * d[o + f] if one_way else d[o + f] for f in range(3)]
+        out += [rd * (E[o + f] / E[o + 3] + dv[f] * cs) for f in range(3)] + [rd]
+    return np.stack(out)
+
+
+def face_terms(cfg, E, g):
+    """The largest face term of each cell and its neighbours, per field."""
+    cs, _ = sound_speed(E, cfg.gamma)
+    amax = max(g["Ar"].max(), g["Ath"].max(), g["Az"].max() if cfg.nz > 1 else 0.0)
+    mag = np.abs(E).copy()
+    for f in range(3):
+        mag[f] = np.maximum(mag[f], E[4] * cs)
+    for o in range(5, 5 + 4 * cfg.n_dust, 4):
+        for f in range(3):
+            mag[o + f] = np.maximum(mag[o + f], E[o + 3] * cs)
+    mag *= np.sqrt(E[0] ** 2 + E[1] ** 2 + E[2] ** 2) / E[4] + cs
+    out = np.maximum(mag, np.maximum(np.roll(mag, 1, -1), np.roll(mag, -1, -1)))
+    for ax in (1, 2):
+        pad = np.pad(out, [(1, 1) if a == ax else (0, 0) for a in range(4)], mode="edge")
+        n = out.shape[ax]
+        out = np.maximum(out, np.maximum(np.take(pad, range(n), ax), np.take(pad, range(2, n + 2), ax)))
+    return out * amax
+
+
+def check(rb, cfg, amp, form):
+    o = oracle.Oracle(cfg)
+    E = perturbed(cfg, o.state(), amp, form == "fp32p")
+    o.set_state(E)
+    sim = rb.Sim(cfg, precision=rb.RB_FP32_PERT if form == "fp32p" else rb.RB_FP64)
+    sim.set_fields(E)
+    G, Go = sim.operator(), o.eval_G(with_dust=True, subtract_R0=True)
+    d = sim.diagnostics()
+    sim.close()
+    err = np.abs(G - Go) / face_terms(cfg, E, o.geometry())
+    worst = [float(err[f].max()) for f in range(cfg.n_fields)]
+    print("[faces local] " + " ".join(f"{e:.1e}" for e in worst), flush=True)
+    for f, e in enumerate(worst):
+        assert e <= (1e-11 if form == "fp64" else 1e-5 * amp if f < 5 else 1e-5), (f, e)
+    return d
+
+
+@pytest.mark.parametrize("amp", [1e-5, 2e-3, 0.03, 0.09, 0.11, 0.2])
+@pytest.mark.parametrize("form", ["fp64", "fp32p"])
+@pytest.mark.parametrize("nz", [24, 1])
+def test_thin_layers(rb, form, amp, nz):
+    cfg = BASE.scaled(20, 72, nz)
+    print(f"[faces local] 20x72x{nz} {form} amplitude {amp}", flush=True)
+    check(rb, cfg, amp, form)
+
+
+@pytest.mark.parametrize("tk", [7, 16])
+@pytest.mark.parametrize("amp", [1e-3, 0.15])
+@pytest.mark.parametrize("form,gamma", [("fp64", 1.4), ("fp64", 5.0 / 3.0), ("fp32p", 1.4)])
+def test_long_chunks_of_a_ragged_grid(rb, form, amp, tk, gamma, monkeypatch):
+    """Chunks longer than the tables' rings of four planes, on tiles filled in no direction."""
+    cfg = BASE.scaled(21, 69, 16).with_(gamma=gamma)
+    print(f"[faces local] 21x69x16 {form} amplitude {amp} chunks of {tk} gamma {gamma:.3f}", flush=True)
+    monkeypatch.setenv("RB_TK", str(tk))
+    check(rb, cfg, amp, form)
+
+
+@pytest.mark.parametrize("amp,low,high", [(1e-6, 0.0, 0.0), (1e-3, 0.0, 0.0),
+                                          (0.11, 0.05, 1.0), (0.2, 0.3, 2.0)])
+def test_resolved_in_fp64(rb, amp, low, high):
+    """How many faces the FP32-perturbation form leaves to FP64, as a share of the mesh's, in a
+    disc of two scale heights: its layers differ by less than a factor of 3, so perturbations
+    of 1e-3 stay far below a tenth of a face's background and none is left.  (At 0.03 none
+    crosses the bound either, but 0.2% of the faces are left because their FP32 Newton does
+    not settle.)  The bound is crossed by a tenth of the cells' values at 0.11 and by half of
+    them at 0.2; a face is left where any of six values crosses it (faces at tile and chunk
+    edges are solved and counted twice)."""
+    cfg = BASE.scaled(20, 128, 8).with_(z_half=0.05)
+    print(f"[faces local] resolves at amplitude {amp}", flush=True)
+    d = check(rb, cfg, amp, "fp32p")
+    share = d.fp64_resolves / (3 * cfg.n_cells)
+    print(f"[faces local] share of faces resolved in FP64: {share:.3f}", flush=True)
+    assert low <= share <= high and (low > 0 or d.fp64_resolves == 0)
