@@ -117,3 +117,13 @@ def test_resolved_in_fp64(rb, amp, low, high):
     share = d.fp64_resolves / (3 * cfg.n_cells)
     print(f"[faces local] share of faces resolved in FP64: {share:.3f}", flush=True)
     assert low <= share <= high and (low > 0 or d.fp64_resolves == 0)
+
+
+@pytest.mark.parametrize("rho_mid0", [1e-10, 1e-14])
+@pytest.mark.parametrize("amp", [1e-3, 0.03])
+def test_small_density_units(rb, rho_mid0, amp):
+    """The FP32-perturbation form does not depend on the density unit: products of a density
+    and a pressure leave the FP32 range six scale heights above a midplane density of 1e-10."""
+    cfg = BASE.scaled(20, 64, 24).with_(rho_mid0=rho_mid0)
+    print(f"[faces local] 20x64x24 fp32p midplane density {rho_mid0} amplitude {amp}", flush=True)
+    check(rb, cfg, amp, "fp32p")
