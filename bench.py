@@ -122,7 +122,7 @@ def kernel_roofline(cfg, fp32p, r):
     bytes_launch = per_cell * cfg.n_cells
     achieved = bytes_launch / (ms * 1e-3) / 1e9
     form = "fp32p" if fp32p else "fp64"
-    kname = f"k_{group}<{form}>"
+    kname = "k_gas32" if group == "gas" and fp32p else f"k_{group}<{form}>"
     cs = counter_summary(f"counters_{group}_stage_{form}_{cfg.name}")
     traffic = cs["bytes_per_launch"] if cs else None
     out = {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBPS, "unit": "GB/s",

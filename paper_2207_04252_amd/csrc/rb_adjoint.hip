@@ -487,12 +487,12 @@ __device__ __forceinline__ void cot_to_cons(const double* w, const double* b, do
   else dust_cot_to_cons(w, wb, eb);
 }
 
-// In-plane faces and sources.  Bound by instruction issue (4000 -> 3000 lane-instructions per
+// In-plane faces and sources.  Bound by instruction issue (4000 -> 2700 lane-instructions per
 // cell of the gas) and, for a quarter of the time, by the loads of a plane and its halo.  The
 // general reverse of a face runs the recording solver, twenty divisions and every branch of
 // the wave pattern; a face of weak waves takes gas_weak_rev.  One copy of the face serves the
 // theta faces, the r faces and the tile's edge: four copies spilled 72 registers.  128 x 256 x
-// 32 cells, one dust species: gas 300 -> 186 us per launch, dust 158 -> 120.  Tiles of four rows
+// 32 cells, one dust species: gas 300 -> 183 us per launch, dust 158 -> 120.  Tiles of four rows
 // with two workgroups on a CU, which overlap the loads of one with the faces of the other,
 // gave 201 and 120: the halo and the edge faces weigh more.
 template <bool GAS, int ND, bool G75>

@@ -23,9 +23,9 @@ namespace rb {
 // the update, and what the update needs per row is read there in batches (as scalar loads
 // each value waited for its own).  The older wave of a SIMD is served first, so the younger
 // ones end a plane: the first two wavefronts, which solve the tile's edge faces, and the
-// first one's partner take no halo cells.  Gas disc 128 x 256 x 64: 235 -> 150 us per
-// launch (two barriers and scalar loads 194, one barrier 160); bi-fluid disc 256 x 512 x 64,
-// 800 -> 595; 50 steps of the 2D disc 3.32 -> 2.23 ms.
+// first one's partner take no halo cells.  Gas disc 128 x 256 x 64: 235 -> 157 us per
+// launch (two barriers and scalar loads 194); bi-fluid disc 256 x 512 x 64, 800 -> 600; 50
+// steps of the 2D disc 3.32 -> 2.18 ms.
 
 template <int ND, bool G75, bool EXT>
 __global__ void __launch_bounds__(NTM, 2) k_gas(StageArgs a) {
@@ -1003,10 +1003,10 @@ __global__ void __launch_bounds__(NTM, 4) k_dust(StageArgs a, int species) {
 // the faces need of the stationary flow is staged a plane ahead (PertBg), azimuthal faces take
 // the upwind state and the others the star state alone (gas_face32); the faces that form does
 // not take are marked and solved together, by one inlined copy of the general form per plane.
-// One barrier per plane and batched reads, as k_gas.  Ten steps of the gas disc 128 x 256 x 64,
-// 3.72 -> 2.82 ms; two of the three-dust disc 512 x 1024 x 128, dust stages included, 49.8 ->
-// 35.8 ms, the results the same to the last bit.  (Polynomials in place of the pressure
-// functions gave 2.40 and 32.5 ms, but with other roundings: see gas_face32.)
+// One barrier per plane and batched reads, as k_gas.  Lane-instructions per cell 1506 -> 1200:
+// three-dust disc 512 x 1024 x 128, 4.97 -> 3.9 ms per launch; gas disc 128 x 256 x 64, 182 ->
+// 136 us; the results the same to the last bit.  (Polynomials in place of the pressure
+// functions took 990 instructions, 3.0 ms and 113 us, with other roundings: see gas_face32.)
 // Two waves per SIMD: at three (12-row tiles, 168 VGPRs, the general form called) the largest
 // disc gained 4% and the others lost more, at four (128) the general form's registers spilled
 // into the faces.
