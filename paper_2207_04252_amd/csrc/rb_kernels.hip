@@ -1003,10 +1003,10 @@ __global__ void __launch_bounds__(NTM, 4) k_dust(StageArgs a, int species) {
 // the faces need of the stationary flow is staged a plane ahead (PertBg), azimuthal faces take
 // the upwind state and the others the star state alone (gas_face32); the faces that form does
 // not take are marked and solved together, by one inlined copy of the general form per plane.
-// One barrier per plane and batched reads, as k_gas.  Lane-instructions per cell 1506 -> 1200:
+// One barrier per plane and batched reads, as k_gas.  Lane-instructions per cell 1506 -> 1270:
 // three-dust disc 512 x 1024 x 128, 4.97 -> 3.9 ms per launch; gas disc 128 x 256 x 64, 182 ->
 // 136 us; the results the same to the last bit.  (Polynomials in place of the pressure
-// functions took 990 instructions, 3.0 ms and 113 us, with other roundings: see gas_face32.)
+// functions took 990 instructions, 3.1 ms and 113 us, with other roundings: see gas_face32.)
 // Two waves per SIMD: at three (12-row tiles, 168 VGPRs, the general form called) the largest
 // disc gained 4% and the others lost more, at four (128) the general form's registers spilled
 // into the faces.
